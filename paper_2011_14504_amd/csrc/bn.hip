@@ -10,21 +10,20 @@
 //     written as one partial per block and channel (no global atomics, so no
 //     same-address serialization across blocks);
 //   * finalize steps that reduce the partials and do the exact rational
-//     arithmetic in __int128 once per channel or per table entry.  The
-//     per-channel step runs in the tail of a streaming pass, in the last
-//     block of each channel slice to finish (an arrival counter picks it, no
-//     block waits), and grid-wide maxima in the last slice to finish; the
-//     per-(channel, code) tables take one block per channel.
+//     arithmetic once per channel or per table entry, in kernels of their own
+//     (rounding E2: in the tails of the streaming passes, in the last block of
+//     each channel slice to finish; an arrival counter picks it, no block
+//     waits).
 // sgn(x - mu_q) and the ReLU mask are monotone in the input code, so the
 // streaming passes get them from two thresholds per channel instead of a
 // table.
 //
 // Forward:  stats1 (block partials of sum q, min q, max q) -> stats2 (each
 //           block first forms n_mu and the occupied code range of its slice
-//           from them; sum |x - mu_q| | tails: n_sigma, den, the slice's
-//           bound on b) -> fin2 (b; xhat codes, y, thresholds, max|y|, y
-//           staged at each channel's own Q_A shift) -> apply (Q_A's shift from
-//           the channels' maxima; A codes; table gather).
+//           from them; the sums that give sum |x - mu_q|) -> fin2 (n_sigma,
+//           den, b; xhat codes, y, thresholds, max|y|, y staged at each
+//           channel's own Q_A shift) -> apply (Q_A's shift from the channels'
+//           maxima; A codes; table gather).
 // Backward: exact E2 (k_E2 >= 15): stats (block partials of sum delta, sum
 //           delta*xhat, sum sgn and the per-class extremes of delta) ->
 //           per-channel kernel (dgamma, dbeta, the channel's bound on E1's
@@ -43,6 +42,7 @@ namespace {
 
 constexpr int kSentinelLo = -(1 << 30);
 typedef short short2v __attribute__((ext_vector_type(2)));
+typedef short short4v __attribute__((ext_vector_type(4)));
 
 // launch geometry of the streaming passes (compile-time tuning knobs)
 #ifndef ISEG_BN_NT
@@ -50,9 +50,6 @@ typedef short short2v __attribute__((ext_vector_type(2)));
 #endif
 #ifndef ISEG_BN_BLOCKS
 #define ISEG_BN_BLOCKS 256       // streaming blocks per call, all channel slices
-#endif
-#ifndef ISEG_BNF_STATS_CPL
-#define ISEG_BNF_STATS_CPL 4     // channels per lane of the forward statistics
 #endif
 #ifndef ISEG_BNB_ROWS
 #define ISEG_BNB_ROWS 2          // row groups per lane that size the backward statistics grid
@@ -421,37 +418,77 @@ __device__ __forceinline__ T block_max_nt(T v, T* sh)
 }
 
 // ---------------------------------------------------------------------------
+// forward statistics geometry: a block covers one slice of CS = CPL * G
+// channels (the last slice of a C that CS does not divide leaves lanes idle)
+// and walks row tiles of 4 * kNT / G rows, four rows of CPL channels per lane
+// in flight.  Slices are 64 channels wide (16 or 32 for narrower tensors):
+// each block of the second pass reads the first one's partials of its whole
+// slice, gx * CS of them, and gx shrinks with the number of slices, so that
+// read is a quarter of what 128-channel slices need (C = 256: 32 KB instead
+// of 131 KB per block).
+// ---------------------------------------------------------------------------
+struct FStat {
+    int64_t M;
+    int32_t C, nsl, gx, ntiles;
+    int32_t pad;                     // row slots past M in the tiles
+};
+
+template <int CPL, int G>
+FStat make_fstat(int64_t M, int64_t C)
+{
+    constexpr int CS = CPL * G, TR = 4 * kNT / G;
+    FStat f;
+    f.M = M; f.C = (int32_t)C;
+    f.nsl = (int32_t)ceil_div64(C, CS);
+    f.ntiles = (int32_t)ceil_div64(M, TR);
+    f.pad = (int32_t)((int64_t)f.ntiles * TR - M);
+    int64_t gx = kMaxBlocks / f.nsl;
+    if (gx > f.ntiles) gx = f.ntiles;
+    if (gx < 1) gx = 1;
+    f.gx = (int32_t)gx;
+    return f;
+}
+
+// lanes per row of the 16-channel-lane variant
+int fstat_g16(int64_t C) { return C <= 16 ? 1 : (C <= 32 ? 2 : 4); }
+
+// ---------------------------------------------------------------------------
 // forward workspace.  It starts, like the backward's, with ctr_bytes(C)
-// bytes of arrival counters that each call leaves at zero.
+// bytes of arrival counters, which the forward leaves alone.
 // ---------------------------------------------------------------------------
 struct FwdWs {
-    uint32_t* ctr;                   // arrival counters
     int32_t* b_glob;                 // exponent of Q_xhat's scale (fin2, block 0)
-    int32_t *p_s1, *p_mm;            // [slice][gx][CS] partials: sum q; (min q + 128) | (max q + 128) << 16
-    long long* p_abs;                // [gx][C]
-    int32_t* sbmax;                  // [slices] largest channel bound on b of each slice (stats2's tails)
+    int2* part;                      // [slice][gx][CS] sum q; (min q + 128) | (max q + 128) << 16
+    unsigned long long* acc;         // [C] sum |q - T| (low half) and sum |q - T - 1| (high half)
+    int32_t* sumq;                   // [C] sum q
     unsigned long long* maxYc;       // [C] max |ReLU(y)| of channel c over its occupied codes (fin2)
 };
 
-size_t fwd_ws_bytes(const Stream& st)
+// partial entries of either variant: at most max(kMaxBlocks, slices) blocks of
+// CS <= 64 channels
+size_t fwd_part_entries(int64_t C)
 {
-    size_t pc = (size_t)st.gx * st.C;
-    return ctr_bytes(st.C) + 256 + 2 * align256(pc * 4) + align256(pc * 8) + align256((size_t)st.C) +
-           align256((size_t)st.C * 8);
+    const int64_t n64 = ceil_div64(C, 64);
+    return (size_t)(n64 > kMaxBlocks ? n64 : kMaxBlocks) * 64;
 }
 
-FwdWs fwd_ws_map(void* base, const Stream& st)
+size_t fwd_ws_bytes(int64_t C)
+{
+    const size_t c = (size_t)C;
+    return ctr_bytes(C) + 256 + align256(fwd_part_entries(C) * 8) + align256(c * 8) + align256(c * 4) +
+           align256(c * 8);
+}
+
+FwdWs fwd_ws_map(void* base, int64_t C)
 {
     char* p = (char*)base;
-    size_t pc = (size_t)st.gx * st.C;
+    const size_t c = (size_t)C;
     FwdWs w;
-    w.ctr = (uint32_t*)p; p += ctr_bytes(st.C);
-    w.b_glob = (int32_t*)p;
-    p += 256;
-    w.p_s1 = (int32_t*)p; p += align256(pc * 4);
-    w.p_mm = (int32_t*)p; p += align256(pc * 4);
-    w.p_abs = (long long*)p; p += align256(pc * 8);
-    w.sbmax = (int32_t*)p; p += align256((size_t)st.C);       // slices <= C / 4
+    p += ctr_bytes(C);
+    w.b_glob = (int32_t*)p; p += 256;
+    w.part = (int2*)p; p += align256(fwd_part_entries(C) * 8);
+    w.acc = (unsigned long long*)p; p += align256(c * 8);
+    w.sumq = (int32_t*)p; p += align256(c * 4);
     w.maxYc = (unsigned long long*)p;
     return w;
 }
@@ -461,98 +498,196 @@ FwdWs fwd_ws_map(void* base, const Stream& st)
 //
 // stats1 | block partials of sum q, min q, max q
 // stats2 | prologue: n_mu and the occupied code range of the slice's channels
-//          from stats1's partials | tails: n_sigma, the denominator and each
-//          channel's bound on max|xhat|; the slice's largest bound
-// fin2   (one block per channel, one thread per code): b (Q_xhat's scale) from
-//          the slices' bounds; xhat codes, y, sgn / ReLU thresholds, the
-//          backward's entries, the channel's max|ReLU(y)| and ReLU(y) staged
-//          at the channel's own Q_A shift
+//          from stats1's partials | the channel sums of |q - T| and |q - T - 1|
+//          added to the channel's accumulator
+// fin2   (four channels per block, one thread per code): every block forms
+//          all channels' sigma, denominator and bound on b (Q_xhat's scale);
+//          xhat codes, y, sgn / ReLU thresholds, the backward's entries, the
+//          channel's max|ReLU(y)| and ReLU(y) staged at the channel's own Q_A
+//          shift
 // apply  Q_A's shift r from the channels' maxima; the saved A codes; the
 //          gather table from the staged values; table gather
+//
+// No pass ends in a tail: a kernel boundary costs less than the arrival,
+// the reload and the serial arithmetic of a last block.
 // ---------------------------------------------------------------------------
+constexpr uint32_t kSign4 = 0x80808080u;
 
-// Partial rows of a slice tail in flight per thread: the thread of channel
-// t % CS in row group t / CS reduces partial rows t / CS + k ng (ng = kNT /
-// CS), kTailU of them per batch, all loads of a batch issued before the first
-// is used (an index past the last row re-reads the group's first row, whose
-// value the reduction ignores).
-constexpr int kTailU = 8;
-
-template <int CPL>
-__global__ __launch_bounds__(1024) void k_bnf_stats1(const int8_t* __restrict__ x, Stream st, FwdWs w)
+// lanes l and l ^ 32 (l ^ 16) exchange: bit clear lanes get op(a, a of the
+// partner), bit set lanes op(b of the partner, b)
+template <int O, typename T, typename Op>
+__device__ __forceinline__ T swap_fold(T a, T b, Op op)
 {
-    __shared__ int32_t sS[128], sMin[128], sMax[128];
-    __shared__ int32_t wst[3 * kWaves * 128];      // wave totals [quantity][wave][channel]
-    const bool fold = (st.G & (st.G - 1)) == 0 && st.G <= 64;
-    if (!fold && (int)threadIdx.x < st.CS) { sS[threadIdx.x] = 0; sMin[threadIdx.x] = 1000; sMax[threadIdx.x] = -1000; }
-    __syncthreads();
-    int g, rsub;
-    const bool active = stream_lane(st, g, rsub);
-    int s[CPL], mn[CPL], mx[CPL];
-#pragma unroll
-    for (int i = 0; i < CPL; i++) { s[i] = 0; mn[i] = 1000; mx[i] = -1000; }
-    if (active) {
-        int c0 = blockIdx.y * st.CS + g * CPL;
-        stream_rows<CPL, 4>(st, x, c0, rsub, [&](int64_t, const Vec<CPL>& v) {
-#pragma unroll
-            for (int i = 0; i < CPL; i++) {
-                int q = sbyte(v.w[i >> 2], i & 3);
-                s[i] += q;
-                mn[i] = q < mn[i] ? q : mn[i];
-                mx[i] = q > mx[i] ? q : mx[i];
-            }
-        });
+    if constexpr (O == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a),
+                                                        __builtin_bit_cast(uint32_t, b), false, false);
+        const uint32_t u = r[0], v = r[1];
+        return op(__builtin_bit_cast(T, u), __builtin_bit_cast(T, v));
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a),
+                                                        __builtin_bit_cast(uint32_t, b), false, false);
+        const uint32_t u = r[0], v = r[1];
+        return op(__builtin_bit_cast(T, u), __builtin_bit_cast(T, v));
     }
-    with_g(st.G, [&](auto gc) {
-        constexpr int GG = decltype(gc)::value;
+}
+
+// v folded over the lanes of a 16-lane row that are multiples of G apart
+// (rotations by DPP: every lane gets the total)
+template <int G, typename T, typename Op>
+__device__ __forceinline__ T row_fold(T v, Op op)
+{
+    auto ror = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        const int u = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, false);
+        v = op(v, __builtin_bit_cast(T, u));
+    };
+    if constexpr (G <= 8) ror(std::integral_constant<int, 8>());
+    if constexpr (G <= 4) ror(std::integral_constant<int, 4>());
+    if constexpr (G <= 2) ror(std::integral_constant<int, 2>());
+    if constexpr (G <= 1) ror(std::integral_constant<int, 1>());
+    return v;
+}
+
+// Fold N = CPL values (channel i of the lane) over the wave's rows.  CPL = 16
+// (G <= 4): the lane ends with channels fold_ch(l) + 0..3 in v[0..3]; CPL = 4
+// (G = 16): with channel fold_ch(l) in v[0].  Two reduce-scatter steps halve
+// the channels a lane holds, so 16 channels cost 12 swaps instead of 32.
+template <int CPL, int G, typename T, typename Op>
+__device__ __forceinline__ void wave_fold(T (&v)[CPL], Op op)
+{
 #pragma unroll
-        for (int i = 0; i < CPL; i++) {
-            s[i] = fold_g<GG>(s[i], OpAdd());
-            mn[i] = fold_g<GG>(mn[i], OpMin());
-            mx[i] = fold_g<GG>(mx[i], OpMax());
+    for (int i = 0; i < CPL / 2; i++) v[i] = swap_fold<32>(v[i], v[i + CPL / 2], op);
+#pragma unroll
+    for (int i = 0; i < CPL / 4; i++) v[i] = swap_fold<16>(v[i], v[i + CPL / 4], op);
+    if constexpr (CPL == 16) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = row_fold<G>(v[i], op);
+    }
+}
+
+// first channel (of the lane's CPL) that a lane holds after wave_fold
+template <int CPL>
+__device__ __forceinline__ int fold_ch(int lane)
+{
+    return ((lane >> 5) & 1) * (CPL / 2) + ((lane >> 4) & 1) * (CPL / 4);
+}
+
+// four dwords of four channels (rows a, b, c, d) -> four dwords of four rows
+__device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&o)[4])
+{
+    const uint32_t ab0 = __builtin_amdgcn_perm(b, a, 0x05010400u);    // a0 b0 a1 b1
+    const uint32_t ab1 = __builtin_amdgcn_perm(b, a, 0x07030602u);    // a2 b2 a3 b3
+    const uint32_t cd0 = __builtin_amdgcn_perm(d, c, 0x05010400u);
+    const uint32_t cd1 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+    o[0] = __builtin_amdgcn_perm(cd0, ab0, 0x05040100u);
+    o[1] = __builtin_amdgcn_perm(cd0, ab0, 0x07060302u);
+    o[2] = __builtin_amdgcn_perm(cd1, ab1, 0x05040100u);
+    o[3] = __builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
+}
+
+// Walk the block's row tiles: f(rows[4], valid[4]) with the lane's four rows of
+// CPL channels; rows past M repeat the last one and are not valid.  The next
+// tile's loads are issued before f runs on the current one.
+template <int CPL, int G, typename F>
+__device__ __forceinline__ void fstat_rows(const FStat& st, const int8_t* __restrict__ x, int c0, F f)
+{
+    constexpr int RPI = kNT / G;
+    const int64_t rsub = threadIdx.x / G, last = st.M - 1;
+    const int8_t* base = x + c0;
+    Vec<CPL> cur[4], nxt[4];
+    auto load = [&](int tile, Vec<CPL>* v) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int64_t r = (int64_t)tile * (4 * RPI) + u * RPI + rsub;
+            v[u] = vload<CPL>(base + (r < last ? r : last) * st.C);
         }
+    };
+    int tile = blockIdx.x;
+    if (tile < st.ntiles) load(tile, cur);
+    while (tile < st.ntiles) {
+        const int tn = tile + st.gx;
+        if (tn < st.ntiles) load(tn, nxt);
+        bool ok[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) ok[u] = (int64_t)tile * (4 * RPI) + u * RPI + rsub <= last;
+        f(cur, ok);
+#pragma unroll
+        for (int u = 0; u < 4; u++) cur[u] = nxt[u];
+        tile = tn;
+    }
+}
+
+// Bound by memory on the large tensors and by latency on the small ones; a
+// lane's 16-byte loads keep 64 KB per CU in flight (131072 x 256 codes: 10.2 ->
+// 8.5 us).  Sums by v_dot4 against a
+// selector byte, minima and maxima as packed 16-bit operations on the bytes in
+// the high halves (the low byte below them cannot change which high byte wins).
+template <int CPL, int G>
+__global__ __launch_bounds__(1024) void k_bnf_stats1(const int8_t* __restrict__ x, FStat st, FwdWs w)
+{
+    constexpr int CS = CPL * G, DW = CPL / 4;
+    __shared__ int32_t sS[kWaves * CS];
+    __shared__ int32_t sMm[kWaves * CS];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, g = t % G;
+    const int c0 = blockIdx.y * CS + g * CPL;
+    int s[CPL];
+    short2v mnh[DW], mnl[DW], mxh[DW], mxl[DW];
+#pragma unroll
+    for (int i = 0; i < CPL; i++) s[i] = 0;
+#pragma unroll
+    for (int j = 0; j < DW; j++) { mnh[j] = mnl[j] = (short)0x7fff; mxh[j] = mxl[j] = (short)-0x8000; }
+    fstat_rows<CPL, G>(st, x, c0 < st.C ? c0 : 0, [&](const Vec<CPL>* v, const bool* ok) {
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+#pragma unroll
+            for (int j = 0; j < DW; j++) {
+                const uint32_t q = v[u].w[j], qs = ok[u] ? q : 0u;
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    s[4 * j + i] = __builtin_amdgcn_sdot4((int)qs, 1 << (8 * i), s[4 * j + i], false);
+                const short2v h = __builtin_bit_cast(short2v, q), l = __builtin_bit_cast(short2v, q << 8);
+                mnh[j] = __builtin_elementwise_min(mnh[j], h);
+                mxh[j] = __builtin_elementwise_max(mxh[j], h);
+                mnl[j] = __builtin_elementwise_min(mnl[j], l);
+                mxl[j] = __builtin_elementwise_max(mxl[j], l);
+            }
     });
-    // block totals: the 16 wave totals of each channel staged in LDS and summed
-    // by one thread per channel (see k_bnb_stats); other widths: LDS atomics
-    if (fold) {
-        const int wv = threadIdx.x >> 6;
-        if ((int)(threadIdx.x & 63) < st.G) {
+    // (min + 128) | (max + 128) << 16 by channel; the halves' high bytes
+    int mn[CPL], mx[CPL];
 #pragma unroll
-            for (int i = 0; i < CPL; i++) {
-                const int c = g * CPL + i;
-                wst[wv * 128 + c] = s[i];
-                wst[(kWaves + wv) * 128 + c] = mn[i];
-                wst[(2 * kWaves + wv) * 128 + c] = mx[i];
-            }
-        }
-        __syncthreads();
-        if ((int)threadIdx.x < st.CS) {
-            const int c = threadIdx.x;
-            int bs = 0, bmn = 1000, bmx = -1000;
-#pragma unroll 4
-            for (int v = 0; v < kWaves; v++) {
-                bs += wst[v * 128 + c];
-                bmn = min(bmn, wst[(kWaves + v) * 128 + c]);
-                bmx = max(bmx, wst[(2 * kWaves + v) * 128 + c]);
-            }
-            sS[c] = bs; sMin[c] = bmn; sMax[c] = bmx;
-        }
-    } else if (active && group_leader(st.G)) {
+    for (int j = 0; j < DW; j++) {
+        mn[4 * j] = mnl[j].x >> 8; mn[4 * j + 1] = mnh[j].x >> 8;
+        mn[4 * j + 2] = mnl[j].y >> 8; mn[4 * j + 3] = mnh[j].y >> 8;
+        mx[4 * j] = mxl[j].x >> 8; mx[4 * j + 1] = mxh[j].x >> 8;
+        mx[4 * j + 2] = mxl[j].y >> 8; mx[4 * j + 3] = mxh[j].y >> 8;
+    }
+    wave_fold<CPL, G>(s, OpAdd());
+    wave_fold<CPL, G>(mn, OpMin());
+    wave_fold<CPL, G>(mx, OpMax());
+    if ((lane & 15) < G) {
+        constexpr int NV = CPL == 16 ? 4 : 1;
+        const int cl = g * CPL + fold_ch<CPL>(lane);
 #pragma unroll
-        for (int i = 0; i < CPL; i++) {
-            atomicAdd(&sS[g * CPL + i], s[i]);
-            atomicMin(&sMin[g * CPL + i], mn[i]);
-            atomicMax(&sMax[g * CPL + i], mx[i]);
+        for (int i = 0; i < NV; i++) {
+            sS[wv * CS + cl + i] = s[i];
+            sMm[wv * CS + cl + i] = (mn[i] + 128) | ((mx[i] + 128) << 16);
         }
     }
     __syncthreads();
-    // every block holds at least one row of the slice, so its extremes are
-    // codes; one contiguous row of partials per block, reduced by every block
-    // of the next pass for its slice
-    if ((int)threadIdx.x < st.CS) {
-        const int64_t o = ((int64_t)blockIdx.y * st.gx + blockIdx.x) * st.CS + threadIdx.x;
-        w.p_s1[o] = sS[threadIdx.x];
-        w.p_mm[o] = (sMin[threadIdx.x] + 128) | ((sMax[threadIdx.x] + 128) << 16);
+    const int c = blockIdx.y * CS + t;
+    if (t < CS) {
+        int bs = 0, lo = 255, hi = 0;
+#pragma unroll
+        for (int v = 0; v < kWaves; v++) {
+            const int m = sMm[v * CS + t];
+            bs += sS[v * CS + t];
+            lo = min(lo, m & 0xffff);
+            hi = max(hi, m >> 16);
+        }
+        // one contiguous row of partials per block, reduced by every block of
+        // the next pass for its slice; the next pass's accumulators start at zero
+        w.part[((int64_t)blockIdx.y * st.gx + blockIdx.x) * CS + t] = make_int2(bs, lo | (hi << 16));
+        if (blockIdx.x == 0 && c < st.C) w.acc[c] = 0;
     }
 }
 
@@ -583,198 +718,161 @@ __device__ __forceinline__ i128 fwd_y(i128 nx, int gq, int bq, const FwdExps& e)
     return (i128)gq * nx * pow2_128(e.e_g + e.e_xh - e.e_y) + (i128)bq * pow2_128(e.e_b - e.e_y);
 }
 
-template <int CPL>
-__global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ x, const int32_t* x_exp,
-                                                    Stream st, FwdWs w, Saved sv, BnCfg cf, int32_t* dev_status)
+// The channel's offset off = n_mu 2^(e_mu - g) on the grid of its centred values
+// D = q 2^(s_x - g) - off (g = min(s_x, e_mu)) and T = floor(off / 2^(s_x - g)),
+// the largest code whose D is not positive.
+__device__ __forceinline__ int64_t bn_off(int32_t s_x, int32_t n_mu, int e_mu)
 {
-    __shared__ int32_t sSg[128], sNg[128];         // block sums of q and counts above each channel's T
-    __shared__ long long tA[kNT];
-    __shared__ int32_t rb[kNT / 64];
-    __shared__ int32_t wst[2 * kWaves * 128];      // wave totals [quantity][wave][channel]
-    const bool fold = (st.G & (st.G - 1)) == 0 && st.G <= 64;
-    int32_t s_x = *x_exp;
-    if (!sx_ok(s_x)) {
-        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) set_status(dev_status, ISEG_DEV_RANGE);
-        s_x = -14;     // keep shifts defined; outputs are unspecified
-    }
-    if (!fold && (int)threadIdx.x < st.CS) { sSg[threadIdx.x] = 0; sNg[threadIdx.x] = 0; }
-    // prologue: n_mu (Eq. 12) and the occupied code range of the slice's
-    // channels from stats1's partial rows (every block of the slice forms them;
-    // the slice's last block stores them)
-    __shared__ int32_t sNmu[128], sLo[128], sHi[128];
-    __shared__ long long sSum[128];
+    const int g = s_x < e_mu ? s_x : e_mu;
+    return (int64_t)n_mu * ((int64_t)1 << (e_mu - g));
+}
+__device__ __forceinline__ int bn_T(int64_t off, int32_t s_x, int e_mu)
+{
+    const int g = s_x < e_mu ? s_x : e_mu;
+    const int64_t t = off >> (s_x - g);
+    return (int)(t < -129 ? -129 : (t > 127 ? 127 : t));
+}
+// reference byte (code + 128) of the first sum of absolute differences
+__device__ __forceinline__ int bn_ref(int T) { return min(max(T + 128, 0), 254); }
+
+// |D| is linear in q on either side of T .. T + 1, so sum |D| follows exactly
+// from the two sums of absolute differences A0 = sum |q - T| and A1 = sum
+// |q - T - 1| (see bnf_sigma).  Both come from v_sad_u8 on dwords of four rows
+// of one channel (a 4x4 byte transpose per 16 elements): one VALU operation
+// per element where a compare, select and two adds per element took five
+// (the pass on 131072 x 256 codes: 23.8 -> 8.5 us, 3.9 TB/s; on 1024 x 16: 12.8 ->
+// 4.5 us, with the slice tail gone; what is left there is the launch and the
+// two round trips of the prologue and the rows).
+template <int CPL, int G>
+__global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ x, const int32_t* x_exp,
+                                                    FStat st, FwdWs w, Saved sv, BnCfg cf, int32_t* dev_status)
+{
+    constexpr int CS = CPL * G, DW = CPL / 4, NG = kNT / CS;
+    __shared__ int32_t sS[kNT], sMm[kNT];          // prologue sums; then the wave totals of A0 and A1
+    __shared__ int32_t sRef[CS];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, g = t % G;
+    const int32_t s_in = *x_exp;
+    const int32_t s_x = sx_ok(s_in) ? s_in : -14;     // keeps shifts defined; outputs are unspecified
+    const int e_mu = 2 - cf.k_mu;
     {
-        const int CS = st.CS, ng = kNT / CS, t = threadIdx.x, ch = t % CS, grp = t / CS;
-        const int32_t* ps = w.p_s1 + (int64_t)blockIdx.y * st.gx * CS;
-        const int32_t* pm = w.p_mm + (int64_t)blockIdx.y * st.gx * CS;
-        long long sum = 0;
-        int lo = 255, hi = 0;
-        if (grp < ng)
-            for (int b0 = grp; b0 < st.gx; b0 += kTailU * ng) {
-                int32_t vs[kTailU], vm[kTailU];
+        // n_mu (Eq. 12) and the occupied code range of the slice's channels from
+        // stats1's partial rows: every block of the slice forms them, its first
+        // block stores them.  All loads of a thread go out together; a row past
+        // the last repeats the thread's first one, whose extremes change nothing.
+        const int ch = t % CS, grp = t / CS;
+        const int2* ps = w.part + (int64_t)blockIdx.y * st.gx * CS;
+        int sum = 0, lo = 255, hi = 0;
+        for (int b0 = grp; b0 < st.gx; b0 += 4 * NG) {
+            int2 v[4];
 #pragma unroll
-                for (int u = 0; u < kTailU; u++) {
-                    const int b = b0 + u * ng;
-                    const int64_t q = (int64_t)(b < st.gx ? b : b0) * CS + ch;
-                    vs[u] = ps[q];
-                    vm[u] = pm[q];
-                }
-#pragma unroll
-                for (int u = 0; u < kTailU; u++) {
-                    if (b0 + u * ng < st.gx) sum += vs[u];
-                    lo = min(lo, vm[u] & 0xffff);       // a repeated row changes no extreme
-                    hi = max(hi, vm[u] >> 16);
-                }
+            for (int u = 0; u < 4; u++) {
+                const int b = b0 + u * NG;
+                v[u] = ps[(int64_t)(b < st.gx ? b : b0) * CS + ch];
             }
-        tA[t] = sum;
-        __shared__ int32_t tMm[kNT];
-        tMm[t] = lo | (hi << 16);
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (b0 + u * NG < st.gx) sum += v[u].x;      // |sum q| <= 2^29
+                lo = min(lo, v[u].y & 0xffff);
+                hi = max(hi, v[u].y >> 16);
+            }
+        }
+        sS[t] = sum;
+        sMm[t] = lo | (hi << 16);
         __syncthreads();
         if (t < CS) {
+            const int ng = st.gx < NG ? st.gx : NG;
             for (int g2 = 1; g2 < ng; g2++) {
-                const int i = g2 * CS + t;
-                sum += tA[i];
-                lo = min(lo, tMm[i] & 0xffff);
-                hi = max(hi, tMm[i] >> 16);
+                const int m = sMm[g2 * CS + t];
+                sum += sS[g2 * CS + t];
+                lo = min(lo, m & 0xffff);
+                hi = max(hi, m >> 16);
             }
-            // mu/2 = S1 2^(s_x - 1) / M, code floor(mu/2 2^(k_mu-1) + 1/2)
-            sNmu[t] = (int32_t)clamp_k128(rhu128((i128)sum, s_x - 1 + (cf.k_mu - 1), (i128)st.M), cf.k_mu);
-            sSum[t] = sum;
-            sLo[t] = lo - 128;
-            sHi[t] = hi - 128;
-        }
-    }
-    __syncthreads();
-    // Sum |D| over the channel's elements, D = q 2^(s_x - g) - n_mu 2^(e_mu - g)
-    // (g = min(s_x, e_mu)), from int32 sums: with T the largest code whose D is
-    // not positive, sum |D| = 2^(s_x - g) (2 S_gt - S) + n_mu 2^(e_mu - g) (M - 2 N_gt),
-    // S_gt and N_gt the sum and count of the codes above T (the tail forms it)
-    const int e_mu = 2 - cf.k_mu;
-    const int gg = s_x < e_mu ? s_x : e_mu;
-    int g, rsub;
-    const bool active = stream_lane(st, g, rsub);
-    int32_t sg[CPL], ng[CPL];
-#pragma unroll
-    for (int i = 0; i < CPL; i++) { sg[i] = 0; ng[i] = 0; }
-    if (active) {
-        int c0 = blockIdx.y * st.CS + g * CPL;
-        int32_t T[CPL];
-#pragma unroll
-        for (int i = 0; i < CPL; i++) {
-            const int64_t off = (int64_t)sNmu[g * CPL + i] * ((int64_t)1 << (e_mu - gg));
-            const int64_t t = off >> (s_x - gg);          // floor(off / 2^(s_x - g))
-            T[i] = (int32_t)(t < -129 ? -129 : (t > 127 ? 127 : t));
-        }
-        stream_rows<CPL, 4>(st, x, c0, rsub, [&](int64_t, const Vec<CPL>& v) {
-#pragma unroll
-            for (int i = 0; i < CPL; i++) {
-                const int q = sbyte(v.w[i >> 2], i & 3);
-                const bool up = q > T[i];
-                sg[i] += up ? q : 0;
-                ng[i] += up ? 1 : 0;
+            // mu/2 = S1 2^(s_x - 1) / M, code floor(mu/2 2^(k_mu-1) + 1/2); the mean
+            // code is at most 128, so shifts below -24 give 0 like -24 does
+            const int32_t nm = (int32_t)clamp_k(rhu64(sum, max(s_x - 1 + (cf.k_mu - 1), -24), st.M), cf.k_mu);
+            sRef[t] = bn_ref(bn_T(bn_off(s_x, nm, e_mu), s_x, e_mu));
+            const int c = blockIdx.y * CS + t;
+            if (blockIdx.x == 0 && c < st.C) {
+                sv.n_mu[c] = nm;
+                sv.qmin[c] = lo - 128;
+                sv.qmax[c] = hi - 128;
+                w.sumq[c] = sum;
             }
-        });
+        }
+        __syncthreads();
     }
-    with_g(st.G, [&](auto gc) {
-        constexpr int GG = decltype(gc)::value;
+    const int c0 = blockIdx.y * CS + g * CPL;
+    uint32_t a0[CPL], a1[CPL], r0[CPL];
 #pragma unroll
-        for (int i = 0; i < CPL; i++) {
-            sg[i] = fold_g<GG>(sg[i], OpAdd());
-            ng[i] = fold_g<GG>(ng[i], OpAdd());
+    for (int i = 0; i < CPL; i++) {
+        a0[i] = a1[i] = 0;
+        r0[i] = (uint32_t)sRef[g * CPL + i] * 0x01010101u;
+    }
+    fstat_rows<CPL, G>(st, x, c0 < st.C ? c0 : 0, [&](const Vec<CPL>* v, const bool* ok) {
+#pragma unroll
+        for (int j = 0; j < DW; j++) {
+            uint32_t u[4], o[4];
+            // rows past M count as byte 0; their known share is taken out in bnf_sigma
+#pragma unroll
+            for (int k = 0; k < 4; k++) u[k] = ok[k] ? v[k].w[j] ^ kSign4 : 0u;
+            transpose4(u[0], u[1], u[2], u[3], o);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                a0[4 * j + i] = __builtin_amdgcn_sad_u8(o[i], r0[4 * j + i], a0[4 * j + i]);
+                a1[4 * j + i] = __builtin_amdgcn_sad_u8(o[i], r0[4 * j + i] + 0x01010101u, a1[4 * j + i]);
+            }
         }
     });
-    if (fold) {
-        const int wv = threadIdx.x >> 6;
-        if ((int)(threadIdx.x & 63) < st.G) {
+    wave_fold<CPL, G>(a0, OpAdd());
+    wave_fold<CPL, G>(a1, OpAdd());
+    if ((lane & 15) < G) {
+        constexpr int NV = CPL == 16 ? 4 : 1;
+        const int cl = g * CPL + fold_ch<CPL>(lane);
 #pragma unroll
-            for (int i = 0; i < CPL; i++) {
-                wst[wv * 128 + g * CPL + i] = sg[i];
-                wst[(kWaves + wv) * 128 + g * CPL + i] = ng[i];
-            }
-        }
-        __syncthreads();
-        if ((int)threadIdx.x < st.CS) {
-            int32_t bs = 0, bn = 0;
-#pragma unroll 4
-            for (int v = 0; v < kWaves; v++) {
-                bs += wst[v * 128 + threadIdx.x];
-                bn += wst[(kWaves + v) * 128 + threadIdx.x];
-            }
-            sSg[threadIdx.x] = bs;
-            sNg[threadIdx.x] = bn;
-        }
-    } else if (active && group_leader(st.G)) {
-#pragma unroll
-        for (int i = 0; i < CPL; i++) {
-            atomicAdd(&sSg[g * CPL + i], sg[i]);
-            atomicAdd(&sNg[g * CPL + i], ng[i]);
+        for (int i = 0; i < NV; i++) {
+            sS[wv * CS + cl + i] = (int32_t)a0[i];
+            sMm[wv * CS + cl + i] = (int32_t)a1[i];
         }
     }
     __syncthreads();
-    // one 8-byte partial per channel: the sum (low half) and the count (high half)
-    if ((int)threadIdx.x < st.CS)
-        st_x(&w.p_abs[(int64_t)blockIdx.x * st.C + blockIdx.y * st.CS + threadIdx.x],
-             (long long)(((uint64_t)(uint32_t)sNg[threadIdx.x] << 32) | (uint32_t)sSg[threadIdx.x]));
-    if (!arrive_last(w.ctr + 1 + blockIdx.y, gridDim.x)) return;
-    // slice tail: sigma (Eq. 13-14), the denominator and this channel's bound on max|xhat|
-    const int CS = st.CS, ngr = kNT / CS, t = threadIdx.x, ch = t % CS, grp = t / CS;
-    const int64_t cb = (int64_t)blockIdx.y * CS;
-    const int e_sig = 2 - cf.k_sigma;
-    {
-        long long acc_s = 0, acc_n = 0;
-        if (grp < ngr)
-            for (int b0 = grp; b0 < st.gx; b0 += kTailU * ngr) {
-                long long va[kTailU];
+    const int c = blockIdx.y * CS + t;
+    if (!sx_ok(s_in) && blockIdx.x == 0 && blockIdx.y == 0 && t == 0) set_status(dev_status, ISEG_DEV_RANGE);
+    if (t < CS && c < st.C) {
+        uint32_t b0 = 0, b1 = 0;
 #pragma unroll
-                for (int u = 0; u < kTailU; u++) {
-                    const int b = b0 + u * ngr;
-                    va[u] = ld_x(&w.p_abs[(int64_t)(b < st.gx ? b : b0) * st.C + cb + ch]);
-                }
-#pragma unroll
-                for (int u = 0; u < kTailU; u++)
-                    if (b0 + u * ngr < st.gx) {
-                        acc_s += (int32_t)(uint32_t)((uint64_t)va[u] & 0xffffffffu);
-                        acc_n += (int32_t)(uint32_t)((uint64_t)va[u] >> 32);
-                    }
-            }
-        tA[t] = acc_s;
-        __syncthreads();
-        if (t < CS)
-            for (int g2 = 1; g2 < ngr; g2++) acc_s += tA[g2 * CS + t];
-        __syncthreads();
-        tA[t] = acc_n;
-        __syncthreads();
-        if (t < CS) {
-            for (int g2 = 1; g2 < ngr; g2++) acc_n += tA[g2 * CS + t];
-            const int64_t c = cb + t;
-            const i128 mulq = pow2_128(s_x - gg), off = (i128)sNmu[t] * pow2_128(e_mu - gg);
-            const i128 acc = mulq * (2 * (i128)acc_s - (i128)sSum[t]) + off * ((i128)st.M - 2 * (i128)acc_n);
-            // sigma/2 = sumabs 2^(g-1) / M ; n_sigma = floor(sigma/2 2^(k_sigma-1) + 1/2)
-            int32_t ns = (int32_t)clamp_k128(rhu128(acc, gg - 1 + (cf.k_sigma - 1), (i128)st.M), cf.k_sigma);
-            int32_t den = ns + cf.eps_code;
-            if (den < 1) den = 1;
-            sv.n_sigma[c] = ns;
-            sv.den[c] = den;
-            const int32_t nm = sNmu[t];
-            sv.n_mu[c] = nm;
-            sv.qmin[c] = sLo[t];
-            sv.qmax[c] = sHi[t];
-            int best = kSentinelLo;
-            const int qs[2] = {sLo[t], sHi[t]};
-            for (int k = 0; k < 2; k++) {          // xhat is linear in q: extremes at qmin / qmax
-                const int64_t D = bn_D(qs[k], s_x, nm, e_mu);
-                if (D == 0) continue;
-                const int e = ceil_pow2_exp128(abs128((i128)D), (i128)den) + gg - e_sig;
-                best = e > best ? e : best;
-            }
-            tA[t] = best;                          // slot t is read by thread t only above
+        for (int v = 0; v < kWaves; v++) {
+            b0 += (uint32_t)sS[v * CS + t];
+            b1 += (uint32_t)sMm[v * CS + t];
         }
+        // each total stays below 255 (2^22 + 4096) < 2^31, so the halves of the
+        // 64-bit addition never carry into each other
+        atomicAdd(&w.acc[c], (unsigned long long)b0 | ((unsigned long long)b1 << 32));
     }
-    __syncthreads();
-    int bmax = kSentinelLo;
-    for (int i = t; i < CS; i += kNT) bmax = max(bmax, (int)tA[i]);
-    bmax = block_max_nt(bmax, rb);
-    if (t == 0) w.sbmax[blockIdx.y] = bmax;
+}
+
+// n_sigma (Eq. 13-14) from the channel's sums.  With diff = A1 - A0 = M - 2
+// N(q > T): sum |D| = 2^(s_x - g) (A0 - T diff) + off diff for T in [-128, 126];
+// beyond, every D has one sign.  Magnitudes: either s_x <= e_mu and the power
+// is 1 with |off| <= 255, or |off| < 2^15 and the power is at most 2^30: below 2^61.
+__device__ __forceinline__ int32_t bnf_sigma(unsigned long long acc, int32_t sumq, const FStat& st, int32_t s_x,
+                                             int32_t n_mu, int e_mu, const BnCfg& cf)
+{
+    const int g = s_x < e_mu ? s_x : e_mu;
+    const int64_t off = bn_off(s_x, n_mu, e_mu), mul = (int64_t)1 << (s_x - g);
+    const int T = bn_T(off, s_x, e_mu);
+    int64_t sabs;
+    if (T > 126) sabs = off * st.M - mul * sumq;
+    else if (T < -128) sabs = mul * sumq - off * st.M;
+    else {
+        const int64_t ref = bn_ref(T);
+        const int64_t A0 = (int64_t)(uint32_t)acc - (int64_t)st.pad * ref;
+        const int64_t A1 = (int64_t)(uint32_t)(acc >> 32) - (int64_t)st.pad * (ref + 1);
+        const int64_t diff = A1 - A0;
+        sabs = mul * (A0 - T * diff) + off * diff;
+    }
+    // sigma/2 = sumabs 2^(g-1) / M ; n_sigma = floor(sigma/2 2^(k_sigma-1) + 1/2).
+    // A shift below -24 needs g = s_x < e_mu, hence sumabs / M <= 512: 0 as with -24
+    return (int32_t)clamp_k(rhu64(sabs, max(g - 1 + (cf.k_sigma - 1), -24), st.M), cf.k_sigma);
 }
 
 // max of n per-slice values, by every thread of the block (kSentinelLo if n = 0)
@@ -799,65 +897,132 @@ __device__ __forceinline__ int ystg_shift(uint64_t maxy, int kA)
     return rc > 1 ? rc - 1 : 0;
 }
 
-// per (channel, code): xhat code, y, flags and the backward's entry; per
+// x-hat code of D and its y: 64-bit arithmetic where the operands fit (always
+// for the occupied codes of ordinary layers), 128-bit otherwise
+__device__ __forceinline__ int32_t fwd_xcode_any(int64_t D, int32_t den, int b, const FwdExps& e)
+{
+    const int sh = e.gg - e.e_sig + (e.kx - 1) - b;
+    const uint64_t aD = (uint64_t)(D < 0 ? -D : D);
+    const int lb = bitlen_u64(aD) + (sh > 0 ? sh : 0), ld = bitlen_u64((uint64_t)den) + (sh < 0 ? -sh : 0);
+    if (lb <= 60 && ld <= 60 && lb - ld < 46) return (int32_t)clamp_k(rhu64(D, sh, den), e.kx);
+    return (int32_t)fwd_xcode(D, den, b, e);
+}
+
+// Per (channel, code): xhat code, y, flags and the backward's entry; per
 // channel: the sgn and ReLU thresholds and max |ReLU(y)| over the occupied
-// codes (y is monotone in q, so over qmin and qmax)
-__global__ __launch_bounds__(256) void k_bnf_fin2(const int32_t* x_exp, int nslices, FwdWs w, Saved sv, BnCfg cf,
+// codes (y is monotone in q, so over qmin and qmax).  Every block forms all
+// channels' denominators and bounds on b itself (a few values per thread; C
+// is at most a few thousand): the arrival, reload and arithmetic of a tail in
+// the statistics pass took longer.  Bound by latency: the loads, two exact
+// divisions and three barriers.
+constexpr int kFinCh = kNT / 256;              // channels per block
+__global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat st, FwdWs w, Saved sv, BnCfg cf,
                                                   const int8_t* gamma_q, const int8_t* beta_q)
 {
-    __shared__ int32_t rsh[4];
-    const int c = blockIdx.x;
-    const int q = (int)threadIdx.x - 128;
-    int32_t s_x = *x_exp;
-    if (!sx_ok(s_x)) return;
-    int b = slices_max(w.sbmax, nslices, rsh);
+    __shared__ int32_t rsh[kWaves], sNs[kFinCh], sDen[kFinCh];
+    __shared__ uint64_t sBal[kWaves][3], sAy[kFinCh][2];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lc = t >> 8;
+    const int c = blockIdx.x * kFinCh + lc;
+    const int q = (t & 255) - 128;
+    const bool own = c < st.C;
+    // every load of the first round goes out before the first wait (no branch on
+    // a loaded value in between)
+    const int32_t s_in = *x_exp;
+    const int cs = own ? c : 0, k0 = t < st.C ? t : 0;
+    const int32_t nmu = sv.n_mu[cs], qlo = sv.qmin[cs], qhi = sv.qmax[cs];
+    const int gq = gamma_q[cs], bq = beta_q[cs];
+    int32_t nm = sv.n_mu[k0], lo = sv.qmin[k0], hi = sv.qmax[k0], sumq = w.sumq[k0];
+    unsigned long long acc = w.acc[k0];
+    const int e_mu = 2 - cf.k_mu, e_sig = 2 - cf.k_sigma;
+    const int32_t s_x = sx_ok(s_in) ? s_in : -14;     // outputs unspecified, shifts defined
+    int best = kSentinelLo;
+    for (int k = t; k < st.C; k += kNT) {
+        if (k != t) { nm = sv.n_mu[k]; lo = sv.qmin[k]; hi = sv.qmax[k]; sumq = w.sumq[k]; acc = w.acc[k]; }
+        const int32_t ns = bnf_sigma(acc, sumq, st, s_x, nm, e_mu, cf);
+        const int32_t den = max(ns + cf.eps_code, 1);
+        if (k / kFinCh == (int)blockIdx.x) { sNs[k % kFinCh] = ns; sDen[k % kFinCh] = den; }
+        // xhat is linear in q: its largest magnitude is at qmin or qmax
+        const int64_t D0 = bn_D(lo, s_x, nm, e_mu), D1 = bn_D(hi, s_x, nm, e_mu);
+        const uint64_t m0 = (uint64_t)(D0 < 0 ? -D0 : D0), m1 = (uint64_t)(D1 < 0 ? -D1 : D1);
+        const uint64_t m = m0 > m1 ? m0 : m1;
+        if (m) best = max(best, ceil_pow2_exp64(m, (uint64_t)den) + min(s_x, e_mu) - e_sig);
+    }
+    for (int o = 32; o > 0; o >>= 1) best = max(best, __shfl_xor(best, o, 64));
+    if (lane == 0) rsh[wv] = best;
+    __syncthreads();
+    int b = rsh[0];
+#pragma unroll
+    for (int k = 1; k < kWaves; k++) b = max(b, rsh[k]);
     if (b == kSentinelLo) b = 0;
-    if (c == 0 && threadIdx.x == 0) *w.b_glob = b;
+    const int32_t den = sDen[lc];
+    if (blockIdx.x == 0 && t == 0) *w.b_glob = b;
     const FwdExps e = fwd_exps(s_x, b, cf);
-    const int64_t D = bn_D(q, s_x, sv.n_mu[c], e.e_mu);
-    const i128 nx = fwd_xcode(D, sv.den[c], b, e);
-    const i128 Y = fwd_y(nx, gamma_q[c], beta_q[c], e);
-    const int idx = c * 256 + threadIdx.x;
-    sv.xcode[idx] = (int16_t)nx;
+    const int64_t D = bn_D(q, s_x, nmu, e.e_mu);
+    const int32_t nx = own ? fwd_xcode_any(D, den, b, e) : 0;
+    // y on its grid: one of the two shifts is zero; |y| < 2^62 for gaps up to 48
+    const int gx = e.e_g + e.e_xh - e.e_y, gb = e.e_b - e.e_y;
+    const bool wide = gx > 38 || gb > 48;          // uniform over the grid
+    int64_t Yr = 0;
+    bool pos;
+    i128 Yw = 0;
+    if (wide) {
+        Yw = fwd_y(nx, gq, bq, e);
+        pos = Yw > 0;
+        if (cf.relu && Yw < 0) Yw = 0;
+    } else {
+        Yr = (int64_t)(gq * nx) * ((int64_t)1 << gx) + (int64_t)bq * ((int64_t)1 << gb);
+        pos = Yr > 0;
+        if (cf.relu && Yr < 0) Yr = 0;
+    }
+    const int idx = c * 256 + (t & 255);
     const int sg = (D > 0) - (D < 0);
-    sv.flags[idx] = (uint8_t)((Y > 0 ? 1 : 0) | ((sg + 1) << 1));
-    sv.btab[c * 256 + (q & 255)] = ((uint32_t)(uint16_t)(int16_t)nx << 16) | ((uint32_t)(sg & 3) << 8) |
-                                   ((uint32_t)(sg != 0) << 10) | (Y > 0 ? 1u : 0u);
-    // thresholds (least code with D >= 0, least with D > 0, code range with y > 0)
-    // and the channel's max |ReLU(y)| over its occupied code extremes, by block
-    // reductions: same-address atomics would serialize 256 updates per channel
-    int v0 = D >= 0 ? q : 128, v1 = D > 0 ? q : 128, v2 = Y > 0 ? q : 128, v3 = Y > 0 ? q : -129;
-    const i128 Yr = cf.relu && Y < 0 ? 0 : Y;
-    uint64_t ay = (q == sv.qmin[c] || q == sv.qmax[c]) ? (uint64_t)abs128(Yr) : 0;
-    for (int o = 32; o > 0; o >>= 1) {
-        v0 = min(v0, __shfl_xor(v0, o)); v1 = min(v1, __shfl_xor(v1, o));
-        v2 = min(v2, __shfl_xor(v2, o)); v3 = max(v3, __shfl_xor(v3, o));
-        const uint64_t t = __shfl_xor(ay, o);
-        ay = t > ay ? t : ay;
+    if (own) {
+        sv.xcode[idx] = (int16_t)nx;
+        sv.flags[idx] = (uint8_t)((pos ? 1 : 0) | ((sg + 1) << 1));
+        sv.btab[c * 256 + (q & 255)] = ((uint32_t)(uint16_t)(int16_t)nx << 16) | ((uint32_t)(sg & 3) << 8) |
+                                       ((uint32_t)(sg != 0) << 10) | (pos ? 1u : 0u);
     }
-    __shared__ int32_t red[4][4];
-    __shared__ uint64_t ry[4];
-    const int wv = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { red[wv][0] = v0; red[wv][1] = v1; red[wv][2] = v2; red[wv][3] = v3; ry[wv] = ay; }
+    // thresholds (least code with D >= 0, least with D > 0, code range with y >
+    // 0) from the waves' ballots
+    const uint64_t m0 = __ballot(D >= 0), m1 = __ballot(D > 0), m2 = __ballot(pos);
+    if (lane == 0) { sBal[wv][0] = m0; sBal[wv][1] = m1; sBal[wv][2] = m2; }
+    const uint64_t ay = wide ? (uint64_t)abs128(Yw) : (uint64_t)(Yr < 0 ? -Yr : Yr);
+    if (q == qlo) sAy[lc][0] = ay;
+    if (q == qhi) sAy[lc][1] = ay;
     __syncthreads();
-    __shared__ uint64_t s_ay;
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < 4; k++) {
-            v0 = min(v0, red[k][0]); v1 = min(v1, red[k][1]); v2 = min(v2, red[k][2]); v3 = max(v3, red[k][3]);
-            ay = ry[k] > ay ? ry[k] : ay;
+    const uint64_t mx = sAy[lc][0] > sAy[lc][1] ? sAy[lc][0] : sAy[lc][1];
+    if (own && (t & 255) == 0) {
+        int v[4] = {128, 128, 128, -129};
+#pragma unroll
+        for (int k = 3; k >= 0; k--)
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const uint64_t bm = sBal[wv + k][j];
+                if (bm) v[j] = -128 + 64 * k + __builtin_ctzll(bm);
+            }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const uint64_t bm = sBal[wv + k][2];
+            if (bm) v[3] = -128 + 64 * k + 63 - __builtin_clzll(bm);
         }
-        sv.t0[c] = v0; sv.p0[c] = v1; sv.mlo[c] = v2; sv.mhi[c] = v3;
-        w.maxYc[c] = ay;
-        s_ay = ay;
+        sv.t0[c] = v[0]; sv.p0[c] = v[1]; sv.mlo[c] = v[2]; sv.mhi[c] = v[3];
+        sv.n_sigma[c] = sNs[lc];
+        sv.den[c] = den;
+        w.maxYc[c] = mx;
     }
-    __syncthreads();
     // ReLU(y) floored by 2^t_c, t_c = max(0, r_c - 1) with r_c the Q_A shift
     // this channel's own maximum would give: below 2^k_A in magnitude for the
     // occupied codes (clamped elsewhere, where the output pass never looks)
-    const int tc = ystg_shift(s_ay, cf.k_A);
-    i128 z = tc ? (Yr >> tc) : Yr;
-    z = z > 32767 ? 32767 : (z < -32767 ? -32767 : z);
-    sv.ystg[idx] = (int16_t)z;
+    const int tc = ystg_shift(mx, cf.k_A);
+    int64_t z;
+    if (wide) {
+        const i128 zw = tc ? (Yw >> tc) : Yw;
+        z = zw > 32767 ? 32767 : (zw < -32767 ? -32767 : (int64_t)zw);
+    } else {
+        z = Yr >> tc;
+        z = z > 32767 ? 32767 : (z < -32767 ? -32767 : z);
+    }
+    if (own) sv.ystg[idx] = (int16_t)z;
 }
 
 // Output pass.  Every block first takes Q_A's shift r from the channels'
@@ -868,90 +1033,148 @@ __global__ __launch_bounds__(256) void k_bnf_fin2(const int32_t* x_exp, int nsli
 //     code = ((z >> (r - 1 - t_c)) + 1) >> 1, the half-up rounding of
 //     ReLU(y) by 2^r (half-up rounding of floor(v / 2^t) by 2^(r - t) equals
 //     that of v for t < r), two codes per packed 16-bit operation.
-template <int CPL>
+// The loads of the maxima, the staged table, the share of xhat codes and the
+// first row tile all go out together, so the prologue costs one round trip
+// (131072 x 256 codes: 15.8 -> 14.0 us, 4.8 TB/s; 1024 x 16: 6.5 -> 4.5 us).
+// U rows per lane and tile: 4, or 1 where four would leave most CUs idle.
+template <int CPL, int G, int U>
+FStat make_fapply(int64_t M, int64_t C)
+{
+    FStat f = make_fstat<CPL, G>(M, C);
+    f.ntiles = (int32_t)ceil_div64(M, (int64_t)U * kNT / G);
+    int64_t gx = kMaxBlocks / f.nsl;
+    if (gx > f.ntiles) gx = f.ntiles;
+    f.gx = (int32_t)(gx < 1 ? 1 : gx);
+    return f;
+}
+
+template <int CPL, int G, int U>
 __global__ __launch_bounds__(1024) void k_bnf_apply(const int8_t* __restrict__ x, int8_t* __restrict__ y,
-                                                   Stream st, Saved sv, FwdWs w, BnCfg cf, const int32_t* x_exp,
+                                                   FStat st, Saved sv, FwdWs w, BnCfg cf, const int32_t* x_exp,
                                                    const int8_t* gamma_q, const int8_t* beta_q, int32_t* y_exp)
 {
-    __shared__ __attribute__((aligned(16))) int8_t lut[128 * kRowB];
-    __shared__ uint64_t rmax[kNT / 64];
-    uint64_t M = 0;
-    for (int k = threadIdx.x; k < st.C; k += kNT) M = w.maxYc[k] > M ? w.maxYc[k] : M;
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t t = __shfl_xor(M, o);
-        M = t > M ? t : M;
+    constexpr int CS = CPL * G, RPI = kNT / G, TV = (CS * 32 + kNT - 1) / kNT;
+    __shared__ __attribute__((aligned(16))) int8_t lut[CS * kRowB];
+    __shared__ uint64_t rmax[kWaves];
+    const int t = threadIdx.x, g = t % G, rsub = t / G;
+    const int c0 = blockIdx.y * CS + g * CPL, cb = blockIdx.y * CS;
+    const int64_t last = st.M - 1;
+    const int8_t* xb = x + (c0 < st.C ? c0 : 0);
+    Vec<CPL> cur[U], nxt[U];
+    auto load = [&](int tile, Vec<CPL>* v) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t r = (int64_t)tile * (U * RPI) + u * RPI + rsub;
+            v[u] = vload<CPL>(xb + (r < last ? r : last) * st.C);
+        }
+    };
+    uint64_t M = w.maxYc[t < st.C ? t : 0];
+    const int32_t s_in = *x_exp;
+    const int b = *w.b_glob;
+    int4 zq[TV];
+    uint64_t my[TV];
+#pragma unroll
+    for (int k = 0; k < TV; k++) {
+        const int v = t + k * kNT, row = v >> 5;
+        const int c = row < CS && cb + row < st.C ? cb + row : cb;
+        zq[k] = *(const int4*)(sv.ystg + (int64_t)c * 256 + (v & 31) * 8);
+        my[k] = w.maxYc[c];
     }
-    if ((threadIdx.x & 63) == 0) rmax[threadIdx.x >> 6] = M;
+    // share of the saved A codes, four codes of one channel per step
+    const int64_t nall = (int64_t)st.C * 64, nb = (int64_t)gridDim.x * gridDim.y;
+    const int64_t per = (nall + nb - 1) / nb;
+    const int64_t i0 = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * per;
+    const int64_t i1 = i0 + per < nall ? i0 + per : nall;
+    int64_t ia = i0 + t;
+    const int64_t il = ia < i1 ? ia : 0;
+    short4v xq = *(const short4v*)(sv.xcode + il * 4);
+    int gq = gamma_q[il >> 6], bq = beta_q[il >> 6];
+    int tile = blockIdx.x;
+    if (tile < st.ntiles) load(tile, cur);
+    for (int k = t + kNT; k < st.C; k += kNT) M = w.maxYc[k] > M ? w.maxYc[k] : M;
+    M = wave_max_u64(M);
+    if ((t & 63) == 0) rmax[t >> 6] = M;
     __syncthreads();
     M = rmax[0];
-    for (int k = 1; k < kNT / 64; k++) M = rmax[k] > M ? rmax[k] : M;
+#pragma unroll
+    for (int k = 1; k < kWaves; k++) M = rmax[k] > M ? rmax[k] : M;
     const int r = M ? bitlen_u64(M) - (cf.k_A - 1) : 0;
-    int32_t s_x = *x_exp;
-    const bool ok = sx_ok(s_x);
-    if (!ok) s_x = -14;          // outputs unspecified; keeps the shifts defined
-    const int b = *w.b_glob;
+    const bool ok = sx_ok(s_in);
+    const int32_t s_x = ok ? s_in : -14;          // outputs unspecified; keeps the shifts defined
     const FwdExps e = fwd_exps(s_x, b, cf);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && ok) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0 && ok) {
         *y_exp = e.e_y + r;
         sv.hdr[0] = b;
         sv.hdr[1] = e.e_y;
         sv.hdr[2] = e.e_y + r;
         sv.hdr[3] = s_x;
     }
-    if (ok) {
-        const int64_t nall = (int64_t)st.C * 256, nb = (int64_t)gridDim.x * gridDim.y;
-        const int64_t per = (nall + nb - 1) / nb;
-        const int64_t i0 = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * per;
-        for (int64_t i = i0 + threadIdx.x; i < i0 + per && i < nall; i += kNT) {
-            const int c = (int)(i >> 8);
-            i128 Yv = fwd_y((i128)sv.xcode[i], gamma_q[c], beta_q[c], e);
-            if (cf.relu && Yv < 0) Yv = 0;
-            sv.acode[i] = (int8_t)sq_code((long long)Yv, r, cf.k_A);
-        }
-    }
-    if (!ok) {
-        for (int i = threadIdx.x; i < st.CS * kRowB; i += kNT) lut[i] = 0;
-    } else {
-        const short lim = (short)((1 << (cf.k_A - 1)) - 1);
-        const int16_t* src = sv.ystg + (int64_t)blockIdx.y * st.CS * 256;
-        for (int v = threadIdx.x; v < st.CS * 32; v += kNT) {       // eight codes per step
-            const int i0 = v * 8, row = i0 >> 8, col = i0 & 255;
-            const int tc = ystg_shift(w.maxYc[blockIdx.y * st.CS + row], cf.k_A);
-            const int4 q = *(const int4*)(src + i0);
-            const int qw[4] = {q.x, q.y, q.z, q.w};
-            uint32_t ow[2] = {0, 0};
-            const short sh = (short)(r > 0 ? min(r - 1 - tc, 15) : 0), up = (short)(r < 0 ? -r : 0);
+    const short lim = (short)((1 << (cf.k_A - 1)) - 1);
+    const short up = (short)(r < 0 ? -r : 0);
 #pragma unroll
-            for (int h = 0; h < 4; h++) {
-                short2v zv = __builtin_bit_cast(short2v, qw[h]);
-                if (r > 0) zv = ((zv >> sh) + (short)1) >> (short)1;
-                else zv = zv << up;
-                zv = zv > lim ? lim : zv;
-                zv = zv < (short)-lim ? (short)-lim : zv;
-                const uint32_t bb = ((uint32_t)(uint16_t)zv.x & 0xffu) | (((uint32_t)(uint16_t)zv.y & 0xffu) << 8);
-                ow[h >> 1] |= bb << (16 * (h & 1));
+    for (int k = 0; k < TV; k++) {
+        const int v = t + k * kNT, row = v >> 5, col = (v & 31) * 8;
+        if (row >= CS) break;
+        const int tc = ystg_shift(my[k], cf.k_A);
+        const int qw[4] = {zq[k].x, zq[k].y, zq[k].z, zq[k].w};
+        uint32_t ow[2] = {0, 0};
+        const short sh = (short)(r > 0 ? min(max(r - 1 - tc, 0), 15) : 0);
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            short2v zv = __builtin_bit_cast(short2v, qw[h]);
+            if (r > 0) zv = ((zv >> sh) + (short)1) >> (short)1;
+            else zv = zv << up;
+            zv = zv > lim ? lim : zv;
+            zv = zv < (short)-lim ? (short)-lim : zv;
+            const uint32_t bb = ((uint32_t)(uint16_t)zv.x & 0xffu) | (((uint32_t)(uint16_t)zv.y & 0xffu) << 8);
+            ow[h >> 1] |= bb << (16 * (h & 1));
+        }
+        *(uint32_t*)(lut + row * kRowB + col) = ok ? ow[0] : 0u;
+        *(uint32_t*)(lut + row * kRowB + col + 4) = ok ? ow[1] : 0u;
+    }
+    if (ok) {
+        const int gx = e.e_g + e.e_xh - e.e_y, gb = e.e_b - e.e_y;
+        const bool wide = gx > 38 || gb > 48;      // uniform over the grid
+        for (; ia < i1; ia += kNT) {
+            if (ia != i0 + t) {
+                xq = *(const short4v*)(sv.xcode + ia * 4);
+                gq = gamma_q[ia >> 6];
+                bq = beta_q[ia >> 6];
             }
-            *(uint32_t*)(lut + row * kRowB + col) = ow[0];
-            *(uint32_t*)(lut + row * kRowB + col + 4) = ow[1];
+            uint32_t o = 0;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                int64_t Yv = wide ? (int64_t)fwd_y((i128)xq[k], gq, bq, e)
+                                  : (int64_t)(gq * xq[k]) * ((int64_t)1 << gx) + (int64_t)bq * ((int64_t)1 << gb);
+                if (cf.relu && Yv < 0) Yv = 0;
+                o |= (uint32_t)(uint8_t)sq_code(Yv, r, cf.k_A) << (8 * k);
+            }
+            *(uint32_t*)(sv.acode + ia * 4) = o;
         }
     }
     __syncthreads();
-    int g, rsub;
-    if (!stream_lane(st, g, rsub)) return;
-    const int c0 = blockIdx.y * st.CS + g * CPL;
     const int8_t* l = lut + g * CPL * kRowB + 128;
-    stream_rows<CPL, 4>(st, x, c0, rsub, [&](int64_t r, const Vec<CPL>& v) {
-        Vec<CPL> o;
+    while (tile < st.ntiles) {
+        const int tn = tile + st.gx;
+        if (tn < st.ntiles) load(tn, nxt);
 #pragma unroll
-        for (int j = 0; j < CPL / 4; j++) {
-            uint32_t ow = 0;
+        for (int u = 0; u < U; u++) {
+            const int64_t rr = (int64_t)tile * (U * RPI) + u * RPI + rsub;
+            Vec<CPL> o;
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-                ow |= (uint32_t)(uint8_t)l[(j * 4 + i) * kRowB + sbyte(v.w[j], i)] << (8 * i);
-            o.w[j] = ow;
+            for (int j = 0; j < CPL / 4; j++) {
+                uint32_t ow = 0;
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    ow |= (uint32_t)(uint8_t)l[(j * 4 + i) * kRowB + sbyte(cur[u].w[j], i)] << (8 * i);
+                o.w[j] = ow;
+            }
+            if (rr <= last && c0 < st.C) vstore<CPL>(y + rr * st.C + c0, o);
         }
-        vstore<CPL>(y + r * st.C + c0, o);
-    });
+#pragma unroll
+        for (int u = 0; u < U; u++) cur[u] = nxt[u];
+        tile = tn;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1816,13 +2039,6 @@ bool cfg_ok(const iseg_bn_cfg* c)
            in(c->k_E2, 2, 16) && in(c->eps_code, 0, 1 << 15) && (c->relu == 0 || c->relu == 1);
 }
 
-// forward statistics geometry; the 4-channel-lane variant has the most
-// blocks, so it sizes the workspace for both
-Stream fwd_stats_stream(int64_t M, int64_t C, int cs, bool v16)
-{
-    return make_stream(M, C, cs, v16 && ISEG_BNF_STATS_CPL == 16 ? 16 : 4, 4, kMaxBlocks);
-}
-
 bool shape_ok(int64_t M, int64_t C) { return M >= 1 && C >= 4 && M <= ((int64_t)1 << 22) && C <= (1 << 16); }
 
 }  // namespace
@@ -1834,9 +2050,8 @@ extern "C" size_t iseg_bn_saved_bytes(int64_t C) { return C > 0 ? saved_bytes(C)
 
 extern "C" size_t iseg_bn_fwd_ws(int64_t M, int64_t C)
 {
-    int cs = pick_cs(C, 128);
-    if (!shape_ok(M, C) || !cs) return 0;
-    return fwd_ws_bytes(fwd_stats_stream(M, C, cs, false));
+    if (!shape_ok(M, C) || C % 4) return 0;
+    return fwd_ws_bytes(C);
 }
 
 extern "C" size_t iseg_bn_bwd_ws(int64_t M, int64_t C)
@@ -1855,36 +2070,55 @@ static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t
     if (!shape_ok(M, C)) return ISEG_ERR_UNSUPPORTED;
     if (!x || !x_exp || !gamma_q || !beta_q || !y_out || !y_exp || !saved || !cfg_ok(cfg))
         return ISEG_ERR_ARG;
-    int cs = pick_cs(C, 128);
-    if (!cs || (((uintptr_t)x | (uintptr_t)y_out) & 3)) return ISEG_ERR_UNSUPPORTED;
-    const bool v16 = cs % 16 == 0 && (((uintptr_t)x | (uintptr_t)y_out) & 15) == 0;
-    const bool s16 = v16 && ISEG_BNF_STATS_CPL == 16;
-    Stream st = fwd_stats_stream(M, C, cs, v16);
-    if (!ws || ws_bytes < fwd_ws_bytes(fwd_stats_stream(M, C, cs, false))) return ISEG_ERR_WORKSPACE;
+    if (C % 4 || (((uintptr_t)x | (uintptr_t)y_out) & 3)) return ISEG_ERR_UNSUPPORTED;
+    const bool v16 = C % 16 == 0 && (((uintptr_t)x | (uintptr_t)y_out) & 15) == 0;
+    if (!ws || ws_bytes < fwd_ws_bytes(C)) return ISEG_ERR_WORKSPACE;
     BnCfg cf = to_cfg(cfg);
     Saved sv = saved_map(saved, C);
-    FwdWs w = fwd_ws_map(ws, st);
-    dim3 sg = stream_grid(st);
-    dim3 cb((unsigned)C);
-    if (s16)
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS1, stream, k_bnf_stats1<16>, sg, dim3(kNT), 0, stream, x, st, w);
-    else
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS1, stream, k_bnf_stats1<4>, sg, dim3(kNT), 0, stream, x, st, w);
-    if (s16)
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS2, stream, k_bnf_stats2<16>, sg, dim3(kNT), 0, stream, x, x_exp,
+    FwdWs w = fwd_ws_map(ws, C);
+    // 16 channels per lane wherever the rows allow 16-byte loads
+    auto stats = [&](auto cpl, auto gl) {
+        constexpr int CPL = decltype(cpl)::value, G = decltype(gl)::value;
+        const FStat st = make_fstat<CPL, G>(M, C);
+        const dim3 sg((unsigned)st.gx, (unsigned)st.nsl);
+        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS1, stream, (k_bnf_stats1<CPL, G>), sg, dim3(kNT), 0, stream, x, st, w);
+        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS2, stream, (k_bnf_stats2<CPL, G>), sg, dim3(kNT), 0, stream, x, x_exp,
                           st, w, sv, cf, dev_status);
-    else
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS2, stream, k_bnf_stats2<4>, sg, dim3(kNT), 0, stream, x, x_exp,
-                          st, w, sv, cf, dev_status);
-    hipLaunchKernelGGL(k_bnf_fin2, cb, dim3(256), 0, stream, x_exp, (int)sg.y, w, sv, cf, gamma_q, beta_q);
-    if (v16) {
-        Stream a16 = make_stream(M, C, cs, 16, 4, kMaxBlocks);
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, k_bnf_apply<16>, stream_grid(a16), dim3(kNT), 0,
-                          stream, x, y_out, a16, sv, w, cf, x_exp, gamma_q, beta_q, y_exp);
+        hipLaunchKernelGGL(k_bnf_fin2, dim3((unsigned)ceil_div64(C, kFinCh)), dim3(kNT), 0, stream, x_exp, st, w, sv,
+                           cf, gamma_q, beta_q);
+    };
+    const std::integral_constant<int, 16> v16c;
+    if (C % 16 == 0 && ((uintptr_t)x & 15) == 0) {
+        switch (fstat_g16(C)) {
+        case 1: stats(v16c, std::integral_constant<int, 1>()); break;
+        case 2: stats(v16c, std::integral_constant<int, 2>()); break;
+        default: stats(v16c, std::integral_constant<int, 4>()); break;
+        }
     } else {
-        Stream s4 = make_stream(M, C, cs, 4, 4, kMaxBlocks);
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, k_bnf_apply<4>, stream_grid(s4), dim3(kNT), 0, stream,
-                          x, y_out, s4, sv, w, cf, x_exp, gamma_q, beta_q, y_exp);
+        stats(std::integral_constant<int, 4>(), std::integral_constant<int, 16>());
+    }
+    auto apply = [&](auto cpl, auto gl) {
+        constexpr int CPL = decltype(cpl)::value, G = decltype(gl)::value;
+        // four rows per lane keep the most loads in flight; one where that
+        // would use less than half the CUs
+        const FStat s4 = make_fapply<CPL, G, 4>(M, C), s1 = make_fapply<CPL, G, 1>(M, C);
+        if (s4.gx * s4.nsl > kMaxBlocks / 2)
+            ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 4>),
+                              dim3((unsigned)s4.gx, (unsigned)s4.nsl), dim3(kNT), 0, stream, x, y_out, s4, sv, w, cf,
+                              x_exp, gamma_q, beta_q, y_exp);
+        else
+            ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 1>),
+                              dim3((unsigned)s1.gx, (unsigned)s1.nsl), dim3(kNT), 0, stream, x, y_out, s1, sv, w, cf,
+                              x_exp, gamma_q, beta_q, y_exp);
+    };
+    if (v16) {
+        switch (fstat_g16(C)) {
+        case 1: apply(v16c, std::integral_constant<int, 1>()); break;
+        case 2: apply(v16c, std::integral_constant<int, 2>()); break;
+        default: apply(v16c, std::integral_constant<int, 4>()); break;
+        }
+    } else {
+        apply(std::integral_constant<int, 4>(), std::integral_constant<int, 16>());
     }
     return launch_ok();
 }

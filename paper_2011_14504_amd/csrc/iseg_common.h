@@ -84,6 +84,31 @@ ISEG_HD int ceil_pow2_exp128(i128 A, i128 B)
     return e;
 }
 
+// The same three for operands that fit 64 bits: |a| and b below 2^62 and a
+// quotient below 2^48 (the double estimate is then within one of the floor).
+ISEG_HD int64_t floordiv64(int64_t a, int64_t b)
+{
+    int64_t q = (int64_t)floor((double)a / (double)b);
+    int64_t r = a - q * b;
+    for (int i = 0; i < 2 && r < 0; i++) { q -= 1; r += b; }
+    for (int i = 0; i < 2 && r >= b; i++) { q += 1; r -= b; }
+    return q;
+}
+
+ISEG_HD int64_t rhu64(int64_t num, int sh, int64_t den)
+{
+    if (sh >= 0) return floordiv64(2 * (num * ((int64_t)1 << sh)) + den, 2 * den);
+    return floordiv64(2 * num + (den << -sh), 2 * (den << -sh));
+}
+
+// smallest e with A < B * 2^e (0 < A, B < 2^62)
+ISEG_HD int ceil_pow2_exp64(uint64_t A, uint64_t B)
+{
+    const int e = bitlen_u64(A) - bitlen_u64(B);       // the bit lengths agree after this shift
+    const bool lt = e >= 0 ? A < (B << e) : (A << -e) < B;
+    return lt ? e : e + 1;
+}
+
 ISEG_HD int64_t clamp_k(int64_t v, int k)
 {
     int64_t lim = ((int64_t)1 << (k - 1)) - 1;
