@@ -25,13 +25,10 @@
  * owns all memory.  The library never allocates: scratch space comes from a
  * caller workspace `ws` of at least the size returned by the matching
  * iseg_*_ws() query (256-byte aligned).  Inputs and outputs must not alias.
- * The workspaces of iseg_bn_fwd and iseg_bn_bwd begin with arrival counters
- * (ISEG_BN_WS_ZERO(C) bytes) that must be zero before the first call with
- * that buffer: zero it once when it is allocated.  Every iseg_bn_fwd /
- * iseg_bn_bwd call leaves them zero again, so a buffer kept for those calls
- * on one stream stays ready; a buffer that other entry points also use must
- * be zeroed again before the next L1BN call, and calls that may run at the
- * same time need buffers of their own.
+ * The workspaces of iseg_bn_fwd and iseg_bn_bwd begin with ISEG_BN_WS_ZERO(C)
+ * reserved bytes that no call reads or writes; the rest is written before it
+ * is read within a call, so nothing needs clearing.  Calls that may run at
+ * the same time need buffers of their own.
  *
  * Streams.  Every compute call only enqueues work on `stream` (0 = the null
  * stream) and returns; results are ready when the stream reaches that point.
@@ -93,8 +90,7 @@ enum iseg_out_mode { ISEG_OUT_Q8 = 0, ISEG_OUT_RAW = 1 };
  * returns the exact int64 sums */
 enum iseg_g_mode { ISEG_G_KEEP = 0, ISEG_G_DROP = 1, ISEG_G_RAW = 2 };
 
-/* bytes of arrival counters at the head of an L1BN (iseg_bn_fwd /
- * iseg_bn_bwd) workspace for C channels */
+/* reserved bytes at the head of an L1BN (iseg_bn_fwd / iseg_bn_bwd) workspace */
 #define ISEG_BN_WS_ZERO(C) ((((size_t)(C) + 511) / 256) * 256)
 
 /* Convolution geometry.  Input NHWC [N,H,W,C]; weights KRSC [K,R,S,C];
@@ -281,8 +277,7 @@ int iseg_bn_fwd(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t C,
  * exceeds it returns ISEG_ERR_WORKSPACE before anything is enqueued.  Every
  * call on a GPU uses that GPU's one array: calls that overlap on one GPU
  * (other streams, other threads) race and must be serialized by the caller.
- * Nothing has to be cleared between calls: the array starts at zero and
- * every call leaves its arrival counters at zero.  Allocates nothing (no hipMalloc,
+ * Nothing has to be cleared between calls.  Allocates nothing (no hipMalloc,
  * no library routine that allocates); the array's device address is looked
  * up once per device on the first call there (ISEG_ERR_DEVICE if that
  * fails). */
@@ -303,8 +298,7 @@ int iseg_bn_fwd_noalloc(const int8_t* x, const int32_t* x_exp, int64_t M, int64_
  *            s = sgn(x - mu_q), means over the channel's M values
  *   E1     = SQ(dx, k_E1) -> dx_out int8, dx_exp                (Eq. 16)
  * dy [M, C] int8 with exponent in [-60, 16]. */
-/* workspace of iseg_bn_bwd; its first ISEG_BN_WS_ZERO(C) bytes are the
- * arrival counters described under Pointers */
+/* workspace of iseg_bn_bwd */
 size_t iseg_bn_bwd_ws(int64_t M, int64_t C);
 int iseg_bn_bwd(const int8_t* dy, const int32_t* dy_exp, const int8_t* x,
                 int64_t M, int64_t C, const int8_t* gamma_q, const iseg_bn_cfg* cfg,

@@ -10,10 +10,7 @@
 //     written as one partial per block and channel (no global atomics, so no
 //     same-address serialization across blocks);
 //   * finalize steps that reduce the partials and do the exact rational
-//     arithmetic once per channel or per table entry, in kernels of their own
-//     (rounding E2: in the tails of the streaming passes, in the last block of
-//     each channel slice to finish; an arrival counter picks it, no block
-//     waits).
+//     arithmetic once per channel or per table entry, in kernels of their own.
 // sgn(x - mu_q) and the ReLU mask are monotone in the input code, so the
 // streaming passes get them from two thresholds per channel instead of a
 // table.
@@ -24,15 +21,13 @@
 //           den, b; xhat codes, y, thresholds, max|y|, y staged at each
 //           channel's own Q_A shift) -> apply (Q_A's shift from the channels'
 //           maxima; A codes; table gather).
-// Backward: exact E2 (k_E2 >= 15): stats (block partials of sum delta, sum
-//           delta*xhat, sum sgn and the per-class extremes of delta) ->
-//           per-channel kernel (dgamma, dbeta, the channel's bound on E1's
-//           exponent, its dx values staged at that bound) -> apply (E1's
-//           exponent from the channels' bounds; staged values rounded into
-//           the gather table).  k_E2 < 15 adds a second streaming pass: stats
-//           tails give each slice's max|gamma delta| (E2's scale is the
-//           largest), stats2 sums the rounded E2 terms and its tails give the
-//           slices' bounds on E1's exponent; a table kernel, then apply.
+// Backward: stats (block partials of sum delta, sum delta*xhat, sum sgn and the
+//           per-class extremes of delta) -> per-channel kernel (dgamma, dbeta,
+//           the channel's bound on E1's exponent, its dx values staged at that
+//           bound) -> apply (E1's exponent from the channels' bounds; staged
+//           values rounded into the gather table).  Rounding E2 (k_E2 < 15) adds
+//           a second streaming pass before the per-channel kernel, with E2's
+//           scale from the first pass's block maxima of |gamma delta|.
 #include <mutex>
 #include <type_traits>
 
@@ -50,9 +45,6 @@ typedef short short4v __attribute__((ext_vector_type(4)));
 #endif
 #ifndef ISEG_BN_BLOCKS
 #define ISEG_BN_BLOCKS 256       // streaming blocks per call, all channel slices
-#endif
-#ifndef ISEG_BNB_ROWS
-#define ISEG_BNB_ROWS 2          // row groups per lane that size the backward statistics grid
 #endif
 constexpr int kMaxBlocks = ISEG_BN_BLOCKS;
 
@@ -99,50 +91,10 @@ Saved saved_map(void* base, int64_t C)
     return s;
 }
 
-// ---------------------------------------------------------------------------
-// streaming geometry: a block covers one channel slice of CS channels (CS % 4
-// == 0, CS divides C); lane g of a row handles channels 4g..4g+3 of the slice;
-// rpi rows are in flight per block step.
-// ---------------------------------------------------------------------------
-struct Stream {
-    int64_t M;
-    int32_t C, CS, G, rpi, gx;
-};
-
-int pick_cs(int64_t C, int csmax)
-{
-    for (int cs = csmax; cs >= 4; cs -= 4)
-        if (C % cs == 0) return cs;
-    return 0;
-}
-
 constexpr int kNT = ISEG_BN_NT;
 constexpr int kWaves = kNT / 64;       // waves per streaming block
 
-Stream make_stream(int64_t M, int64_t C, int cs, int cpl, int unroll, int max_blocks)
-{
-    Stream s;
-    s.M = M; s.C = (int32_t)C; s.CS = cs; s.G = cs / cpl; s.rpi = kNT / s.G;
-    int nsl = (int)(C / cs);
-    int64_t want = max_blocks / nsl;
-    if (want < 1) want = 1;
-    int64_t rows = ceil_div64(M, (int64_t)s.rpi * unroll);
-    s.gx = (int32_t)(rows < want ? rows : want);
-    if (s.gx < 1) s.gx = 1;
-    return s;
-}
-
-dim3 stream_grid(const Stream& s) { return dim3((unsigned)s.gx, (unsigned)(s.C / s.CS)); }
-
-__device__ __forceinline__ bool stream_lane(const Stream& st, int& g, int& rsub)
-{
-    g = threadIdx.x % st.G;
-    rsub = threadIdx.x / st.G;
-    return rsub < st.rpi;
-}
-
-// Iterate the rows of this lane with U rows in flight; a lane covers CPL
-// channels (4: one dword, 16: one 16-byte vector).  f(row, words[CPL/4]).
+// the CPL channels of a lane's row (4: one dword, 16: one 16-byte vector)
 template <int CPL>
 struct Vec { uint32_t w[CPL / 4]; };
 
@@ -165,50 +117,6 @@ __device__ __forceinline__ void vstore(int8_t* p, const Vec<CPL>& v)
 {
     if (CPL == 16) *(uint4*)p = make_uint4(v.w[0], v.w[1 % (CPL / 4)], v.w[2 % (CPL / 4)], v.w[3 % (CPL / 4)]);
     else *(uint32_t*)p = v.w[0];
-}
-
-template <int CPL, int U, typename F>
-__device__ __forceinline__ void stream_rows(const Stream& st, const int8_t* __restrict__ a, int c0,
-                                            int rsub, F f)
-{
-    const int64_t step = (int64_t)gridDim.x * st.rpi;
-    for (int64_t r = (int64_t)blockIdx.x * st.rpi + rsub; r < st.M; r += step * U) {
-        Vec<CPL> v[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            int64_t rr = r + u * step;
-            if (rr < st.M) v[u] = vload<CPL>(a + rr * st.C + c0);
-        }
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            int64_t rr = r + u * step;
-            if (rr < st.M) f(rr, v[u]);
-        }
-    }
-}
-
-// two-input variant
-template <int CPL, int U, typename F>
-__device__ __forceinline__ void stream_rows2(const Stream& st, const int8_t* __restrict__ a,
-                                             const int8_t* __restrict__ b, int c0, int rsub, F f)
-{
-    const int64_t step = (int64_t)gridDim.x * st.rpi;
-    for (int64_t r = (int64_t)blockIdx.x * st.rpi + rsub; r < st.M; r += step * U) {
-        Vec<CPL> va[U], vb[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            int64_t rr = r + u * step;
-            if (rr < st.M) {
-                va[u] = vload<CPL>(a + rr * st.C + c0);
-                vb[u] = vload<CPL>(b + rr * st.C + c0);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            int64_t rr = r + u * step;
-            if (rr < st.M) f(rr, va[u], vb[u]);
-        }
-    }
 }
 
 __device__ __forceinline__ int sbyte(uint32_t w, int i) { return (int)(int8_t)(w >> (8 * i)); }
@@ -235,110 +143,9 @@ BnCfg to_cfg(const iseg_bn_cfg* c)
     return b;
 }
 
-// block-wide reduction of one value per thread (256 threads): xor-shuffles
-// within each wave, then the four wave results through LDS (two barriers)
-template <typename T, typename Op>
-__device__ __forceinline__ T block_reduce(T v, Op op, T* sh)
-{
-    for (int o = 32; o > 0; o >>= 1) v = op(v, (T)__shfl_xor(v, o, 64));
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    T r = sh[0];
-    for (int k = 1; k < (int)(blockDim.x >> 6); k++) r = op(r, sh[k]);
-    __syncthreads();
-    return r;
-}
-
 struct OpAdd { template <typename T> __device__ T operator()(T a, T b) const { return a + b; } };
 struct OpMin { template <typename T> __device__ T operator()(T a, T b) const { return a < b ? a : b; } };
 struct OpMax { template <typename T> __device__ T operator()(T a, T b) const { return a > b ? a : b; } };
-
-// v op v[lane ^ O]: for O = 16 or 32 with gfx950's cross-row swaps (VALU, no
-// LDS traffic): v_permlane16_swap / v_permlane32_swap with both operands v
-// leave v and its partner's value in the two results (which is which depends
-// on the lane, so only commutative ops are folded); other O: an xor-shuffle.
-template <int O>
-__device__ __forceinline__ uint32_t lane_x32(uint32_t v, uint32_t* partner)
-{
-    if constexpr (O == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        *partner = r[1];
-        return r[0];
-    } else {
-        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        *partner = r[1];
-        return r[0];
-    }
-}
-
-template <int O, typename T, typename Op>
-__device__ __forceinline__ T xor_fold(T v, Op op)
-{
-    if constexpr (O != 16 && O != 32) {
-        return op(v, (T)__shfl_xor(v, O, 64));
-    } else if constexpr (sizeof(T) == 8) {
-        const uint64_t u = (uint64_t)v;
-        uint32_t lp, hp;
-        const uint32_t la = lane_x32<O>((uint32_t)u, &lp);
-        const uint32_t ha = lane_x32<O>((uint32_t)(u >> 32), &hp);
-        return op((T)((uint64_t)la | ((uint64_t)ha << 32)), (T)((uint64_t)lp | ((uint64_t)hp << 32)));
-    } else {
-        uint32_t p;
-        const uint32_t a = lane_x32<O>((uint32_t)v, &p);
-        return op((T)a, (T)p);
-    }
-}
-
-// Lanes of a wave that hold the same channels are G apart (G a power of two
-// dividing 64): fold them so that every lane holds the total over the wave's
-// lanes of its channels (straight-line code for a compile-time G; G = 0 or 64:
-// nothing to fold).  Every lane of the wave must be active.
-template <int G, typename T, typename Op>
-__device__ __forceinline__ T fold_g(T v, Op op)
-{
-    if constexpr (G >= 1 && G < 64) return fold_g<2 * G>(xor_fold<G>(v, op), op);
-    else return v;
-}
-
-// f(std::integral_constant<int, G>) for a slice whose row has G lanes: G
-// itself when it is a power of two up to 64 (compile-time folds), else 0.
-template <typename F>
-__device__ __forceinline__ void with_g(int G, F f)
-{
-    switch (G) {
-    case 1: f(std::integral_constant<int, 1>()); break;
-    case 2: f(std::integral_constant<int, 2>()); break;
-    case 4: f(std::integral_constant<int, 4>()); break;
-    case 8: f(std::integral_constant<int, 8>()); break;
-    case 16: f(std::integral_constant<int, 16>()); break;
-    case 32: f(std::integral_constant<int, 32>()); break;
-    case 64: f(std::integral_constant<int, 64>()); break;
-    default: f(std::integral_constant<int, 0>()); break;
-    }
-}
-
-__device__ __forceinline__ bool group_leader(int G)
-{
-    return ((G & (G - 1)) != 0 || G > 64) || (int)(threadIdx.x & 63) < G;
-}
-
-// Copy n 16-byte pieces (n <= V * kNT) from global memory into LDS, every load
-// of a thread issued before its first store.
-template <int V>
-__device__ __forceinline__ void copy_to_lds(uint4* dst, const uint4* __restrict__ src, int n)
-{
-    uint4 v[V];
-#pragma unroll
-    for (int k = 0; k < V; k++) {
-        const int i = threadIdx.x + k * kNT;
-        if (i < n) v[k] = src[i];
-    }
-#pragma unroll
-    for (int k = 0; k < V; k++) {
-        const int i = threadIdx.x + k * kNT;
-        if (i < n) dst[i] = v[k];
-    }
-}
 
 // LDS tables are kept one dword longer per row than in global memory: a
 // table row is 256 entries (a multiple of the bank count), so without the skew
@@ -347,62 +154,9 @@ __device__ __forceinline__ void copy_to_lds(uint4* dst, const uint4* __restrict_
 constexpr int kRowB = 256 + 4;      // bytes per row of a byte table in LDS
 constexpr int kRowW = 256 + 1;      // dwords per row of a dword table in LDS
 
-// Copy `rows` rows of 256 bytes (global, contiguous) into LDS rows of kRowB
-// bytes; every load of a thread is issued before its first store.
-template <int V>
-__device__ __forceinline__ void copy_rows_to_lds(int8_t* dst, const int8_t* __restrict__ src, int rows)
-{
-    const int n = rows * 16;
-    uint4 v[V];
-#pragma unroll
-    for (int k = 0; k < V; k++) {
-        const int i = threadIdx.x + k * kNT;
-        if (i < n) v[k] = ((const uint4*)src)[i];
-    }
-#pragma unroll
-    for (int k = 0; k < V; k++) {
-        const int i = threadIdx.x + k * kNT;
-        if (i < n) {
-            uint32_t* d = (uint32_t*)(dst + (i >> 4) * kRowB + (i & 15) * 16);
-            d[0] = v[k].x; d[1] = v[k].y; d[2] = v[k].z; d[3] = v[k].w;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// arrival counters.  The backward workspace starts with ctr_bytes(C) bytes of
-// uint32 counters: ctr[0] counts the channel slices whose partials are final,
-// ctr[1 + y] the blocks of slice y that have published theirs.  atomicInc
-// with limit n - 1 hands n - 1 to the n-th arrival and wraps the counter to
-// zero there, so each kernel leaves the counters as it found them (zero); no
-// block ever waits for another.
-// ---------------------------------------------------------------------------
-size_t ctr_bytes(int64_t C) { return ISEG_BN_WS_ZERO(C); }   // >= 4 (1 + C / 4)
-
-// Values that cross blocks inside one kernel (partials, per-channel results
-// a later tail reads) are stored and loaded as relaxed agent-scope atomics:
-// write-through stores and loads that are coherent across the XCDs' L2
-// caches.  Device-scope fences would give the same ordering by writing back
-// and invalidating each whole L2, far too costly once per block.
-template <typename T>
-__device__ __forceinline__ void st_x(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <typename T>
-__device__ __forceinline__ T ld_x(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// Called by every thread of a block after its st_x stores: true in all
-// threads of the block that arrives last of n.  Each thread waits for its
-// stores to complete (vmcnt 0) before the barrier, and the counter update
-// follows the barrier, so every earlier arrival's stores precede the last
-// block's ld_x loads.
-__device__ __forceinline__ bool arrive_last(uint32_t* ctr, unsigned n)
-{
-    __shared__ int s_last;
-    __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicInc(ctr, n - 1) == n - 1;
-    __syncthreads();
-    return s_last != 0;
-}
+// Both workspaces start with ISEG_BN_WS_ZERO(C) bytes that callers zero at
+// allocation; the kernels need no counters there any more and leave them be.
+size_t ctr_bytes(int64_t C) { return ISEG_BN_WS_ZERO(C); }
 
 // max over the kNT threads of a block (every thread gets it)
 template <typename T>
@@ -453,8 +207,7 @@ FStat make_fstat(int64_t M, int64_t C)
 int fstat_g16(int64_t C) { return C <= 16 ? 1 : (C <= 32 ? 2 : 4); }
 
 // ---------------------------------------------------------------------------
-// forward workspace.  It starts, like the backward's, with ctr_bytes(C)
-// bytes of arrival counters, which the forward leaves alone.
+// forward workspace
 // ---------------------------------------------------------------------------
 struct FwdWs {
     int32_t* b_glob;                 // exponent of Q_xhat's scale (fin2, block 0)
@@ -518,7 +271,20 @@ constexpr uint32_t kSign4 = 0x80808080u;
 template <int O, typename T, typename Op>
 __device__ __forceinline__ T swap_fold(T a, T b, Op op)
 {
-    if constexpr (O == 32) {
+    if constexpr (sizeof(T) == 8) {
+        const uint64_t x = (uint64_t)a, y = (uint64_t)b;
+        uint32_t al, ah, bl, bh;
+        if constexpr (O == 32) {
+            const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+            al = l[0]; bl = l[1]; ah = h[0]; bh = h[1];
+        } else {
+            const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+            al = l[0]; bl = l[1]; ah = h[0]; bh = h[1];
+        }
+        return op((T)((uint64_t)al | ((uint64_t)ah << 32)), (T)((uint64_t)bl | ((uint64_t)bh << 32)));
+    } else if constexpr (O == 32) {
         const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a),
                                                         __builtin_bit_cast(uint32_t, b), false, false);
         const uint32_t u = r[0], v = r[1];
@@ -538,8 +304,14 @@ __device__ __forceinline__ T row_fold(T v, Op op)
 {
     auto ror = [&](auto n) {
         constexpr int N = decltype(n)::value;
-        const int u = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, false);
-        v = op(v, __builtin_bit_cast(T, u));
+        if constexpr (sizeof(T) == 8) {
+            const int l = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(uint64_t)v, 0x120 + N, 0xf, 0xf, false);
+            const int h = __builtin_amdgcn_update_dpp(0, (int)((uint64_t)v >> 32), 0x120 + N, 0xf, 0xf, false);
+            v = op(v, (T)((uint64_t)(uint32_t)l | ((uint64_t)(uint32_t)h << 32)));
+        } else {
+            const int u = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, false);
+            v = op(v, __builtin_bit_cast(T, u));
+        }
     };
     if constexpr (G <= 8) ror(std::integral_constant<int, 8>());
     if constexpr (G <= 4) ror(std::integral_constant<int, 4>());
@@ -548,9 +320,8 @@ __device__ __forceinline__ T row_fold(T v, Op op)
     return v;
 }
 
-// Fold N = CPL values (channel i of the lane) over the wave's rows.  CPL = 16
-// (G <= 4): the lane ends with channels fold_ch(l) + 0..3 in v[0..3]; CPL = 4
-// (G = 16): with channel fold_ch(l) in v[0].  Two reduce-scatter steps halve
+// Fold N = CPL values (channel i of the lane) over the wave's rows: the lane
+// ends with channels fold_ch(l) + 0 .. CPL / 4 - 1 in v[0 ..].  Two reduce-scatter steps halve
 // the channels a lane holds, so 16 channels cost 12 swaps instead of 32.
 template <int CPL, int G, typename T, typename Op>
 __device__ __forceinline__ void wave_fold(T (&v)[CPL], Op op)
@@ -559,10 +330,8 @@ __device__ __forceinline__ void wave_fold(T (&v)[CPL], Op op)
     for (int i = 0; i < CPL / 2; i++) v[i] = swap_fold<32>(v[i], v[i + CPL / 2], op);
 #pragma unroll
     for (int i = 0; i < CPL / 4; i++) v[i] = swap_fold<16>(v[i], v[i + CPL / 4], op);
-    if constexpr (CPL == 16) {
 #pragma unroll
-        for (int i = 0; i < 4; i++) v[i] = row_fold<G>(v[i], op);
-    }
+    for (int i = 0; i < CPL / 4; i++) v[i] = row_fold<G>(v[i], op);
 }
 
 // first channel (of the lane's CPL) that a lane holds after wave_fold
@@ -875,20 +644,6 @@ __device__ __forceinline__ int32_t bnf_sigma(unsigned long long acc, int32_t sum
     return (int32_t)clamp_k(rhu64(sabs, max(g - 1 + (cf.k_sigma - 1), -24), st.M), cf.k_sigma);
 }
 
-// max of n per-slice values, by every thread of the block (kSentinelLo if n = 0)
-__device__ __forceinline__ int32_t slices_max(const int32_t* a, int n, int32_t* sh)
-{
-    int32_t m = kSentinelLo;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) m = max(m, a[i]);
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
-    __syncthreads();
-    m = sh[0];
-    for (int k = 1; k < (int)(blockDim.x >> 6); k++) m = max(m, sh[k]);
-    return m;
-}
-
 // shift of a channel's staged A values: max(0, r_c - 1), r_c = bitlen(max) -
 // (k_A - 1) the Q_A shift of the channel's own max |ReLU(y)|
 __device__ __forceinline__ int ystg_shift(uint64_t maxy, int kA)
@@ -1181,34 +936,34 @@ __global__ __launch_bounds__(1024) void k_bnf_apply(const int8_t* __restrict__ x
 // backward workspace
 // ---------------------------------------------------------------------------
 struct BwdWs {
-    uint32_t* ctr;                   // arrival counters
-    int32_t* smax;                   // [slices] bound on E1's exponent over each slice's channels
-    int32_t* smaxF;                  // [slices] max |gamma delta| over each slice's channels (rounding E2)
-    int32_t *p_sd, *p_z, *p_mmA, *p_mmB;   // [gx][C] partials (per-class extremes packed as bytes)
-    long long *p_sdn, *p_sf, *p_sfn; // [gx][C]
-    long long *sd, *sdn, *sf, *sfn;  // [C] reduced
-    int32_t *Z, *mm;                 // [C], [C][6]
-    int8_t* lut;                     // [C][3][256] dx codes (rounding E2)
-    int32_t* cbnd;                   // [C] each channel's bound on E1's exponent (exact E2)
-    int16_t* lutq;                   // [C][3][256] dx values at the channel's own bound (exact E2)
+    int32_t* pF;                     // [streaming block] largest |gamma delta| of the block (rounding E2)
+    int32_t *p_sd, *p_z, *p_mmA, *p_mmB;   // [slice][gx][CS] partials (per-class extremes packed as bytes)
+    long long *p_sdn, *p_sf, *p_sfn;       // [slice][gx][CS]
+    int32_t* cbnd;                   // [C] each channel's bound on E1's exponent
+    int16_t* lutq;                   // [C][3][256] dx values at the channel's own bound
 };
 
-size_t bwd_ws_bytes(const Stream& st)
+// streaming blocks of either pass: at most max(kMaxBlocks, slices), CS <= 64
+size_t bwd_blocks(int64_t C)
 {
-    size_t pc = (size_t)st.gx * st.C, C = (size_t)st.C;
-    return ctr_bytes(st.C) + 2 * align256(C) + 4 * align256(pc * 4) + 3 * align256(pc * 8) +
-           4 * align256(C * 8) + align256(C * 4) + align256(C * 24) + align256(C * 768) + align256(C * 4) +
-           align256(C * 768 * 2);
+    const int64_t n64 = ceil_div64(C, 64);
+    return (size_t)(n64 > kMaxBlocks ? n64 : kMaxBlocks);
 }
 
-BwdWs bwd_ws_map(void* base, const Stream& st)
+size_t bwd_ws_bytes(int64_t C)
+{
+    const size_t nb = bwd_blocks(C), pc = nb * 64, c = (size_t)C;
+    return ctr_bytes(C) + align256(nb * 4) + 4 * align256(pc * 4) + 3 * align256(pc * 8) + align256(c * 4) +
+           align256(c * 768 * 2);
+}
+
+BwdWs bwd_ws_map(void* base, int64_t C)
 {
     char* p = (char*)base;
-    size_t pc = (size_t)st.gx * st.C, C = (size_t)st.C;
+    const size_t nb = bwd_blocks(C), pc = nb * 64, c = (size_t)C;
     BwdWs w;
-    w.ctr = (uint32_t*)p; p += ctr_bytes(st.C);
-    w.smax = (int32_t*)p; p += align256(C);          // slices <= C / 4
-    w.smaxF = (int32_t*)p; p += align256(C);
+    p += ctr_bytes(C);
+    w.pF = (int32_t*)p; p += align256(nb * 4);
     w.p_sd = (int32_t*)p; p += align256(pc * 4);
     w.p_z = (int32_t*)p; p += align256(pc * 4);
     w.p_mmA = (int32_t*)p; p += align256(pc * 4);
@@ -1216,76 +971,33 @@ BwdWs bwd_ws_map(void* base, const Stream& st)
     w.p_sdn = (long long*)p; p += align256(pc * 8);
     w.p_sf = (long long*)p; p += align256(pc * 8);
     w.p_sfn = (long long*)p; p += align256(pc * 8);
-    w.sd = (long long*)p; p += align256(C * 8);
-    w.sdn = (long long*)p; p += align256(C * 8);
-    w.sf = (long long*)p; p += align256(C * 8);
-    w.sfn = (long long*)p; p += align256(C * 8);
-    w.Z = (int32_t*)p; p += align256(C * 4);
-    w.mm = (int32_t*)p; p += align256(C * 24);
-    w.lut = (int8_t*)p; p += align256(C * 768);
-    w.cbnd = (int32_t*)p; p += align256(C * 4);
+    w.cbnd = (int32_t*)p; p += align256(c * 4);
     w.lutq = (int16_t*)p;
     return w;
 }
 
-// sgn class (sgn + 1) and ReLU mask of an input code from the thresholds
-struct Thr {
-    int t0, p0, mlo, mhi;
-};
-
-__device__ __forceinline__ int thr_cls(const Thr& t, int q) { return 1 + (q >= t.p0) - (q < t.t0); }
-__device__ __forceinline__ bool thr_mask(const Thr& t, int q) { return q >= t.mlo && q <= t.mhi; }
-
-// Copy the channel slice's per-(channel, code) entries (saved by the forward)
-// into LDS rows of kRowW dwords, all loads of a thread issued before the first
-// store.  The ReLU bit becomes a mask byte in bits 0..7 (0xff passes delta).
-// With `lut_off` the upper half is replaced by the offset of the entry's
-// sgn-class row in the slice's dx-code tables (three rows of kRowB bytes per
-// channel, +128 for the signed delta).
-constexpr int kTabV = 64 * 256 / 4 / kNT;    // 16-byte pieces per thread (CS <= 64)
-__device__ __forceinline__ void load_bwd_tab(uint32_t* tab, const uint32_t* src, int CS, int relu,
-                                             bool lut_off)
+// streaming geometry of the backward: slices of 4 G channels (four per lane),
+// tiles of U kNT / G rows
+template <int G, int U>
+FStat make_bstat(int64_t M, int64_t C)
 {
-    const int nv = CS * 64;
-    uint4 v[kTabV];
-#pragma unroll
-    for (int k = 0; k < kTabV; k++) {
-        const int i = threadIdx.x + k * kNT;
-        if (i < nv) v[k] = ((const uint4*)src)[i];
-    }
-#pragma unroll
-    for (int k = 0; k < kTabV; k++) {
-        const int i = threadIdx.x + k * kNT;
-        if (i < nv) {
-            uint32_t e[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const uint32_t m = (!relu || (e[j] & 1)) ? 0xffu : 0u;
-                if (lut_off) {
-                    const int cl = (4 * i + j) >> 8;
-                    const int sg = ((int)(e[j] << 22)) >> 30;
-                    e[j] = ((uint32_t)((cl * 3 + sg + 1) * kRowB + 128) << 16) | m;
-                } else {
-                    e[j] = (e[j] & 0xffffff00u) | m;
-                }
-            }
-            uint32_t* d = tab + (i >> 6) * kRowW + (i & 63) * 4;
-            d[0] = e[0]; d[1] = e[1]; d[2] = e[2]; d[3] = e[3];
-        }
-    }
+    constexpr int CS = 4 * G, TR = U * kNT / G;
+    FStat f;
+    f.M = M; f.C = (int32_t)C;
+    f.nsl = (int32_t)ceil_div64(C, CS);
+    f.ntiles = (int32_t)ceil_div64(M, TR);
+    f.pad = (int32_t)((int64_t)f.ntiles * TR - M);
+    int64_t gx = kMaxBlocks / f.nsl;
+    if (gx > f.ntiles) gx = f.ntiles;
+    if (gx < 1) gx = 1;
+    f.gx = (int32_t)gx;
+    return f;
 }
 
-// Per-class extremes of the masked delta travel between blocks as bytes:
+// Per-class extremes of the masked delta travel between kernels as bytes:
 // low ends as lo + 128 (255 for an empty class), high ends as hi + 128 (0 for
 // an empty class), so a byte-wise min / max merges them and an empty class
 // still reads lo > hi.  A = (lo, hi) of classes -1 and 0, B = (lo, hi) of +1.
-__device__ __forceinline__ uint32_t pk_lo(int v) { return v > 127 ? 255u : (uint32_t)(v + 128); }
-__device__ __forceinline__ uint32_t pk_hi(int v) { return v < -128 ? 0u : (uint32_t)(v + 128); }
-__device__ __forceinline__ void mm_pack(const int* mm, uint32_t& A, uint32_t& B)
-{
-    A = pk_lo(mm[0]) | pk_hi(mm[1]) << 8 | pk_lo(mm[2]) << 16 | pk_hi(mm[3]) << 24;
-    B = pk_lo(mm[4]) | pk_hi(mm[5]) << 8;
-}
 __device__ __forceinline__ void mm_merge(uint32_t A, uint32_t B, int* lo3, int* hi3)
 {
     lo3[0] = min(lo3[0], (int)(A & 0xff)); hi3[0] = max(hi3[0], (int)((A >> 8) & 0xff));
@@ -1293,13 +1005,6 @@ __device__ __forceinline__ void mm_merge(uint32_t A, uint32_t B, int* lo3, int* 
     lo3[2] = min(lo3[2], (int)(B & 0xff)); hi3[2] = max(hi3[2], (int)((B >> 8) & 0xff));
 }
 
-// Pass 1: sum delta, sum delta*xhat, sum sgn and the per-sgn-class extremes of
-// the masked delta d.  The extremes come from four keys per element, d +- 1024 s
-// and d +- 1024 |s| (s = sgn in {-1, 0, 1}, |d| <= 128): the minimum of d + 1024 s
-// lies in class -1 whenever that class is present, its maximum in class +1, and
-// likewise for the others, so six min/max updates replace per-class selects.
-constexpr int kKey = 1024;
-constexpr int kKeyInit = 4 * kKey;
 struct BnbOut {
     const int32_t* dy_exp;
     const int8_t* gamma_q;
@@ -1307,286 +1012,307 @@ struct BnbOut {
     int32_t *dgamma_exp, *dbeta_exp, *dx_exp, *dev_status;
 };
 
-__device__ __forceinline__ void bnb_round_tail1(uint32_t* lds, const Stream& st, const BwdWs& w, const Saved& sv,
-                                                const BnCfg& cf, const BnbOut& o);
-
-// Block totals per channel.  When the G lanes of a row (G = CS / 4) are a
-// power of two, the lanes of a wave that hold the same channels are folded
-// with shuffles and the 16 wave totals of each channel are staged in LDS
-// (the caller's table space, no longer read) and summed by one thread per
-// channel: LDS atomics from every wave onto the same channel slots serialize
-// and cost several microseconds per block.  Other widths use LDS atomics.
-
-template <int TAIL>                      // 1: exact E2, 2: rounding E2
-__global__ __launch_bounds__(1024) void k_bnb_stats(const int8_t* __restrict__ dy,
-                                                   const int8_t* __restrict__ x, Stream st, BwdWs w,
-                                                   Saved sv, BnCfg cf, BnbOut out)
-{
-    const int relu = cf.relu;
-    __shared__ __attribute__((aligned(16))) uint32_t tab[64 * kRowW];
-    __shared__ unsigned long long sSdn[64];
-    __shared__ int32_t sSd[64], sZ[64], sMM[64 * 6];
-    const int64_t cbase = (int64_t)blockIdx.y * st.CS;
-    const bool fold = (st.G & (st.G - 1)) == 0 && st.G <= 64;
-    load_bwd_tab(tab, sv.btab + cbase * 256, st.CS, relu, false);
-    if (!fold && (int)threadIdx.x < st.CS) {
-        sSdn[threadIdx.x] = 0; sSd[threadIdx.x] = 0; sZ[threadIdx.x] = 0;
-        for (int k = 0; k < 3; k++) { sMM[threadIdx.x * 6 + 2 * k] = 1000; sMM[threadIdx.x * 6 + 2 * k + 1] = -1000; }
-    }
-    __syncthreads();
-    int g, rsub;
-    const bool active = stream_lane(st, g, rsub);
-    int32_t sd[4] = {0, 0, 0, 0}, z[4] = {0, 0, 0, 0};
-    int64_t sdn[4] = {0, 0, 0, 0};
-    // key extremes: min(d + 1024 s), max(d + 1024 s), min(d - 1024 s), max(d - 1024 s),
-    // min(d + 1024 |s|), max(d - 1024 |s|)
-    int32_t kmn0[4], kmx0[4], kmn1[4], kmx1[4], kmn2[4], kmx3[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        kmn0[i] = kmn1[i] = kmn2[i] = kKeyInit;
-        kmx0[i] = kmx1[i] = kmx3[i] = -kKeyInit;
-    }
-    if (active) {
-        const int c0 = (int)cbase + g * 4;
-        const uint32_t* tb = tab + g * 4 * kRowW;
-        const int64_t step = (int64_t)gridDim.x * st.rpi;
-        auto elem = [&](uint32_t wx, uint32_t wd, int32_t* sdn32) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint32_t e = tb[i * kRowW + ((wx >> (8 * i)) & 0xff)];
-                const int dm = sbyte(wd, i) & (int)(int8_t)(e & 0xff);
-                const int sg = ((int)(e << 22)) >> 30;            // bits 8..9, signed
-                const int ab = (int)((e >> 10) & 1);
-                sd[i] += dm;
-                sdn32[i] += dm * ((int)e >> 16);
-                z[i] += sg;
-                const int k0 = dm + sg * kKey, k1 = dm - sg * kKey;
-                const int k2 = dm + ab * kKey, k3 = dm - ab * kKey;
-                kmn0[i] = min(kmn0[i], k0); kmx0[i] = max(kmx0[i], k0);
-                kmn1[i] = min(kmn1[i], k1); kmx1[i] = max(kmx1[i], k1);
-                kmn2[i] = min(kmn2[i], k2); kmx3[i] = max(kmx3[i], k3);
-            }
-        };
-        // full groups of U rows (all in range), next group's loads issued
-        // before this group's arithmetic; then the remaining rows one by one
-        constexpr int U = 4;
-        int64_t r = (int64_t)blockIdx.x * st.rpi + rsub;
-        const int64_t full_end = st.M - (U - 1) * step;
-        uint32_t vx[U], vd[U], nx[U], nd[U];
-        auto load = [&](int64_t r0, uint32_t* ax, uint32_t* ad) {
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                ax[u] = *(const uint32_t*)(x + (r0 + u * step) * st.C + c0);
-                ad[u] = *(const uint32_t*)(dy + (r0 + u * step) * st.C + c0);
-            }
-        };
-        if (r < full_end) load(r, vx, vd);
-        while (r < full_end) {
-            const int64_t rn = r + U * step;
-            if (rn < full_end) load(rn, nx, nd);
-            int32_t sdn32[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int u = 0; u < U; u++) elem(vx[u], vd[u], sdn32);
-#pragma unroll
-            for (int i = 0; i < 4; i++) sdn[i] += sdn32[i];
-#pragma unroll
-            for (int u = 0; u < U; u++) { vx[u] = nx[u]; vd[u] = nd[u]; }
-            r = rn;
-        }
-        for (; r < st.M; r += step) {
-            int32_t sdn32[4] = {0, 0, 0, 0};
-            elem(*(const uint32_t*)(x + r * st.C + c0), *(const uint32_t*)(dy + r * st.C + c0), sdn32);
-#pragma unroll
-            for (int i = 0; i < 4; i++) sdn[i] += sdn32[i];
-        }
-    }
-    // decode the keys into (min, max) per class; an empty class gives (1000, -1000)
-    int32_t mm[4][6];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        mm[i][0] = kmn0[i] <= -kKey + 128 ? kmn0[i] + kKey : 1000;     // class -1
-        mm[i][1] = kmx1[i] >= kKey - 128 ? kmx1[i] - kKey : -1000;
-        mm[i][2] = kmn2[i] <= 128 ? kmn2[i] : 1000;                     // class 0
-        mm[i][3] = kmx3[i] >= -128 ? kmx3[i] : -1000;
-        mm[i][4] = kmn1[i] <= -kKey + 128 ? kmn1[i] + kKey : 1000;     // class +1
-        mm[i][5] = kmx0[i] >= kKey - 128 ? kmx0[i] - kKey : -1000;
-    }
-    with_g(st.G, [&](auto gc) {
-        constexpr int GG = decltype(gc)::value;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            sd[i] = fold_g<GG>(sd[i], OpAdd());
-            sdn[i] = fold_g<GG>(sdn[i], OpAdd());
-            z[i] = fold_g<GG>(z[i], OpAdd());
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                mm[i][2 * k] = fold_g<GG>(mm[i][2 * k], OpMin());
-                mm[i][2 * k + 1] = fold_g<GG>(mm[i][2 * k + 1], OpMax());
-            }
-        }
-    });
-    const int t = threadIdx.x;
-    int32_t bsd = 0, bz = 0;
-    long long bsdn = 0;
-    int bmm[6] = {1000, -1000, 1000, -1000, 1000, -1000};
-    if (fold) {
-        __syncthreads();                                  // every wave is done with the table
-        int32_t* wsd = (int32_t*)tab;                     // [kWaves][64] each
-        int32_t* wz = wsd + kWaves * 64;
-        int32_t* wmm = wz + kWaves * 64;                  // [6][kWaves][64]
-        long long* wsdn = (long long*)(wmm + 6 * kWaves * 64);
-        const int wv = t >> 6;
-        if ((t & 63) < st.G) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int s = wv * 64 + g * 4 + i;
-                wsd[s] = sd[i]; wz[s] = z[i]; wsdn[s] = sdn[i];
-#pragma unroll
-                for (int k = 0; k < 6; k++) wmm[k * kWaves * 64 + s] = mm[i][k];
-            }
-        }
-        __syncthreads();
-        if (t < st.CS) {
-#pragma unroll 4
-            for (int v = 0; v < kWaves; v++) {
-                const int s = v * 64 + t;
-                bsd += wsd[s]; bz += wz[s]; bsdn += wsdn[s];
-#pragma unroll
-                for (int k = 0; k < 6; k++) {
-                    const int m = wmm[k * kWaves * 64 + s];
-                    bmm[k] = (k & 1) ? max(bmm[k], m) : min(bmm[k], m);
-                }
-            }
-        }
-    } else {
-        if (active && group_leader(st.G)) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                int cl = g * 4 + i;
-                atomicAdd(&sSd[cl], sd[i]);
-                atomicAdd(&sSdn[cl], (unsigned long long)sdn[i]);
-                atomicAdd(&sZ[cl], z[i]);
-#pragma unroll
-                for (int k = 0; k < 3; k++) {
-                    atomicMin(&sMM[cl * 6 + 2 * k], mm[i][2 * k]);
-                    atomicMax(&sMM[cl * 6 + 2 * k + 1], mm[i][2 * k + 1]);
-                }
-            }
-        }
-        __syncthreads();
-        if (t < st.CS) {
-            bsd = sSd[t]; bz = sZ[t]; bsdn = (long long)sSdn[t];
-            for (int k = 0; k < 6; k++) bmm[k] = sMM[t * 6 + k];
-        }
-    }
-    if (t < st.CS) {
-        uint32_t A, B;
-        mm_pack(bmm, A, B);
-        if constexpr (TAIL == 1) {
-            // [slice][block][channel of the slice]: one contiguous row per block
-            const int64_t o = ((int64_t)blockIdx.y * st.gx + blockIdx.x) * st.CS + t;
-            w.p_sd[o] = bsd;
-            w.p_sdn[o] = bsdn;
-            w.p_z[o] = bz;
-            w.p_mmA[o] = (int32_t)A;
-            w.p_mmB[o] = (int32_t)B;
-        } else {
-            const int64_t o = (int64_t)blockIdx.x * st.C + cbase + t;
-            st_x(&w.p_sd[o], bsd);
-            st_x(&w.p_sdn[o], bsdn);
-            st_x(&w.p_z[o], bz);
-            st_x(&w.p_mmA[o], (int32_t)A);
-            st_x(&w.p_mmB[o], (int32_t)B);
-        }
-    }
-    if constexpr (TAIL == 2) {
-        if (arrive_last(w.ctr + 1 + blockIdx.y, gridDim.x)) {
-            __syncthreads();                              // the staging above may still be read
-            bnb_round_tail1(tab, st, w, sv, cf, out);
-        }
-    }
-}
-
-
-// E2's requant shift from max |gamma delta| (the slices' maxima)
+// E2's requant shift from max |gamma delta|
 __device__ __forceinline__ int bnb_r2_of(int32_t maxF, const BnCfg& cf)
 {
     return maxF > 0 ? bitlen_u64((uint64_t)maxF) - (cf.k_E2 - 1) : 0;
 }
 
-__device__ __forceinline__ void bnb_round_tail2(uint32_t* lds, const Stream& st, const BwdWs& w,
-                                                const Saved& sv, const BnCfg& cf, const BnbOut& o, int r2);
-
-// pass 2 (only when E2's quantizer rounds): sum f and f*n_xhat; the tails
-// reduce them and give each slice's bound on E1's exponent
-__global__ __launch_bounds__(1024) void k_bnb_stats2(const int8_t* __restrict__ dy,
-                                                    const int8_t* __restrict__ x, Stream st, BwdWs w,
-                                                    Saved sv, BnCfg cf, BnbOut out)
+// the largest |gamma delta| from the streaming blocks' partials (every thread
+// of the block gets it; sh holds one value per wave)
+__device__ __forceinline__ int32_t bnb_max_F(const int32_t* pF, int n, int32_t* sh)
 {
-    const int8_t* gamma_q = out.gamma_q;
-    __shared__ __attribute__((aligned(16))) int16_t xc[64 * 256];
-    __shared__ int16_t ft[64 * 256];                  // f = SQ(gamma_q d, k_E2) per (channel, d)
-    __shared__ Thr thr[64];
-    __shared__ unsigned long long sF[64], sFn[64];
-    __shared__ int32_t rsh[kNT / 64];
-    const int64_t cbase = (int64_t)blockIdx.y * st.CS;
+    int32_t m = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) m = max(m, pF[i]);
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = sh[0];
+    for (int k = 1; k < (int)(blockDim.x >> 6); k++) m = max(m, sh[k]);
+    return m;
+}
+
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+
+struct OpPkMax {
+    __device__ uint32_t operator()(uint32_t a, uint32_t b) const
     {
-        copy_to_lds<64 * 512 / 16 / kNT>((uint4*)xc, (const uint4*)(sv.xcode + cbase * 256), st.CS * 32);
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2v, a),
+                                                                      __builtin_bit_cast(ushort2v, b)));
     }
-    if ((int)threadIdx.x < st.CS) {
-        int c = (int)cbase + threadIdx.x;
-        thr[threadIdx.x] = Thr{sv.t0[c], sv.p0[c], cf.relu ? sv.mlo[c] : -1000, cf.relu ? sv.mhi[c] : 1000};
-        sF[threadIdx.x] = 0; sFn[threadIdx.x] = 0;
+};
+struct OpPkMin {
+    __device__ uint32_t operator()(uint32_t a, uint32_t b) const
+    {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2v, a),
+                                                                      __builtin_bit_cast(ushort2v, b)));
     }
-    // |f| < 2^(k_E2-1) <= 2^13 on this path
-    const int r2 = bnb_r2_of(slices_max(w.smaxF, (int)gridDim.y, rsh), cf);
-    for (int e = threadIdx.x; e < st.CS * 256; e += blockDim.x)
-        ft[e] = (int16_t)sq_code((int64_t)gamma_q[cbase + (e >> 8)] * ((e & 255) - 128), r2, cf.k_E2);
+};
+
+// Streaming pass of the backward.  MODE 0 / 1 (exact / rounding E2, first
+// pass): sum delta, sum delta xhat, sum sgn and the extremes of the masked
+// delta d per sgn class.  MODE 2 (rounding E2, second pass): sum f and sum f
+// xhat, f = SQ(gamma d, k_E2).
+//
+// A per-(channel, code) entry in LDS holds xhat (bits 16-31, zero where the
+// ReLU masks), the class byte (bits 8-15: 0x00 for sgn -1, 0x80 for 0, 0xff for
+// +1) and the mask byte.  Two rows of one channel make one packed step: with
+// d' = d + 128 (128 where masked), the key (class << 8) | d' has the extremes of
+// class +1 at its maximum and of class -1 at its minimum, the key with the
+// class byte inverted the other two; sums come from v_dot4 / v_dot2 on the
+// same packed values.  11.5 VALU operations per element instead of 20; a wave's
+// VALU operation of this mix takes 4.4 clocks, so they and the 2 bytes per
+// element cost about the same (131072 x 256 codes: 28.2 -> 22.5 us, 3.0 TB/s,
+// 3 us of it the 64 KB table; 1024 x 16: 10.2 -> 5.4; rounding E2, both passes at
+// 12255 x 144: 36 -> 16.5 with the arrivals and tails gone).  Class 0 holds at
+// most one code of a channel, and only where mu_q is a code: channels of a
+// wave that have one (in their occupied range) take six more operations.
+constexpr int kBndU = 4;                 // rows per lane and tile
+
+template <int G, int MODE>
+__global__ __launch_bounds__(1024) void k_bnb_stats(const int8_t* __restrict__ dy, const int8_t* __restrict__ x,
+                                                   FStat st, BwdWs w, Saved sv, BnCfg cf, BnbOut out)
+{
+    constexpr int CS = 4 * G, RPI = kNT / G, U = kBndU, TR = U * RPI, TV = CS * 64 / kNT;
+    __shared__ __attribute__((aligned(16))) uint32_t tab[CS * kRowW];
+    __shared__ int32_t rsh[kWaves], sZf[CS];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, g = t % G, rsub = t / G;
+    const int cb = blockIdx.y * CS, c0 = cb + g * 4;
+    const int64_t last = st.M - 1;
+    const int8_t* xb = x + (c0 < st.C ? c0 : 0);
+    const int8_t* db = dy + (c0 < st.C ? c0 : 0);
+    // table pieces, class-0 flags and the first tile all load together
+    uint4 tv[TV];
+#pragma unroll
+    for (int k = 0; k < TV; k++) {
+        const int i = t + k * kNT, row = i >> 6;
+        const int c = cb + row < st.C ? cb + row : cb;
+        tv[k] = ((const uint4*)(sv.btab + (int64_t)c * 256))[i & 63];
+    }
+    int zero_cls = 0;
+    if (MODE != 2 && t < CS) {
+        const int c = cb + t < st.C ? cb + t : cb;
+        const int t0 = sv.t0[c], p0 = sv.p0[c], lo = sv.qmin[c], hi = sv.qmax[c];
+        zero_cls = t0 < p0 && t0 >= lo && t0 <= hi;
+    }
+    uint32_t vx[U], vd[U], nx[U], nd[U];
+    auto load = [&](int tile, uint32_t* ax, uint32_t* ad) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t r = (int64_t)tile * TR + u * RPI + rsub, rr = (r < last ? r : last) * st.C;
+            ax[u] = *(const uint32_t*)(xb + rr);
+            ad[u] = *(const uint32_t*)(db + rr);
+        }
+    };
+    int tile = blockIdx.x;
+    if (tile < st.ntiles) load(tile, vx, vd);
+    int gam[4] = {0, 0, 0, 0};
+    int r2 = 0;
+    if constexpr (MODE == 2) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) gam[i] = out.gamma_q[(c0 < st.C ? c0 : 0) + i];
+        r2 = bnb_r2_of(bnb_max_F(w.pF, st.gx * st.nsl, rsh), cf);
+    }
+    if (t < CS) sZf[t] = zero_cls;
+#pragma unroll
+    for (int k = 0; k < TV; k++) {
+        const int i = t + k * kNT;
+        const uint32_t e4[4] = {tv[k].x, tv[k].y, tv[k].z, tv[k].w};
+        uint32_t* d = tab + (i >> 6) * kRowW + (i & 63) * 4;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint32_t e = e4[j];
+            const int sg = ((int)(e << 22)) >> 30;
+            const uint32_t cls = sg < 0 ? 0u : (sg > 0 ? 0xff00u : 0x8000u);
+            d[j] = (!cf.relu || (e & 1) ? (e & 0xffff0000u) | 0xffu : 0u) | cls;
+        }
+    }
     __syncthreads();
-    int g, rsub;
-    const bool active = stream_lane(st, g, rsub);
-    int64_t sf[4] = {0, 0, 0, 0}, sfn[4] = {0, 0, 0, 0};
-    if (active) {
-        const int c0 = (int)cbase + g * 4;
-        Thr t[4];
+    // zf[i]: some lane's i-th channel has a code in class 0 (wave-uniform, and
+    // the same in every wave)
+    bool zf[4], zflag = false;
 #pragma unroll
-        for (int i = 0; i < 4; i++) t[i] = thr[g * 4 + i];
-        stream_rows2<4, 8>(st, x, dy, c0, rsub, [&](int64_t, const Vec<4>& vxx, const Vec<4>& vdd) {
-            const uint32_t vx = vxx.w[0], vd = vdd.w[0];
+    for (int i = 0; i < 4; i++) {
+        zf[i] = MODE != 2 && __ballot(sZf[g * 4 + i] != 0) != 0;
+        zflag |= zf[i];
+    }
+    const uint32_t* tb = tab + g * 4 * kRowW;
+    uint32_t sd[4] = {0, 0, 0, 0}, z[4] = {0, 0, 0, 0};
+    int32_t sn[4] = {0, 0, 0, 0}, sf[4] = {0, 0, 0, 0};
+    int64_t sdn[4] = {0, 0, 0, 0}, sff[4] = {0, 0, 0, 0};
+    uint32_t mx1[4] = {0, 0, 0, 0}, mx2[4] = {0, 0, 0, 0}, mn1[4] = {~0u, ~0u, ~0u, ~0u}, mn2[4] = {~0u, ~0u, ~0u, ~0u};
+    uint32_t mx0[4] = {0, 0, 0, 0}, mn0[4] = {~0u, ~0u, ~0u, ~0u}, np[4] = {0, 0, 0, 0};
+    // one row pair; v0, v1: whether the rows count (a repeated row only repeats keys)
+    auto pair = [&](uint32_t x0, uint32_t x1, uint32_t d0, uint32_t d1, auto all, bool v0, bool v1) {
+        d0 ^= kSign4; d1 ^= kSign4;
+        const uint32_t vsel = decltype(all)::value ? 0x00010001u : (v0 ? 1u : 0u) | (v1 ? 0x10000u : 0u);
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                int q = sbyte(vx, i);
-                int d = thr_mask(t[i], q) ? sbyte(vd, i) : 0;
-                const int f = ft[(g * 4 + i) * 256 + d + 128];
-                sf[i] += f;
-                sfn[i] += f * (int)xc[(g * 4 + i) * 256 + q + 128];     // |f x| < 2^28
+        for (int i = 0; i < 4; i++) {
+            const uint32_t e0 = tb[i * kRowW + ((x0 >> (8 * i)) & 0xff)];
+            const uint32_t e1 = tb[i * kRowW + ((x1 >> (8 * i)) & 0xff)];
+            uint32_t xp = __builtin_amdgcn_perm(e1, e0, 0x07060302u);
+            const uint32_t cp = __builtin_amdgcn_perm(e1, e0, 0x05040100u);
+            const uint32_t dp = __builtin_amdgcn_perm(d1, d0, 0x0d000d00u | (uint32_t)(4 + i) << 16 | (uint32_t)i);
+            const uint32_t k1 = (cp & dp) | (~cp & 0x00800080u);
+            if constexpr (!decltype(all)::value) xp &= vsel * 0xffffu;
+            short2v dm = __builtin_bit_cast(short2v, k1 & 0x00ff00ffu) - (short)128;
+            const short2v xs = __builtin_bit_cast(short2v, xp);
+            if constexpr (MODE == 2) {
+                short2v f = dm * (short)gam[i];
+                if (r2 > 0) f = (f + (short)(1 << (r2 - 1))) >> (short)r2;
+                else f = f << (short)-r2;
+                const short lim = (short)((1 << (cf.k_E2 - 1)) - 1);
+                f = __builtin_elementwise_min(f, (short2v)lim);
+                f = __builtin_elementwise_max(f, (short2v)(short)-lim);
+                sf[i] = __builtin_amdgcn_sdot2(f, __builtin_bit_cast(short2v, vsel), sf[i], false);
+                sn[i] = __builtin_amdgcn_sdot2(f, xs, sn[i], false);
+            } else {
+                const uint32_t k2 = k1 ^ 0xff00ff00u;
+                mx1[i] = OpPkMax()(mx1[i], k1);
+                mn1[i] = OpPkMin()(mn1[i], k1);
+                mx2[i] = OpPkMax()(mx2[i], k2);
+                mn2[i] = OpPkMin()(mn2[i], k2);
+                sd[i] = __builtin_amdgcn_udot4(k1, vsel, sd[i], false);
+                z[i] = __builtin_amdgcn_udot4(k1, vsel << 8, z[i], false);
+                sn[i] = __builtin_amdgcn_sdot2(dm, xs, sn[i], false);
+                if (zf[i]) {                 // class 0 to the top / to the bottom; rows of class +1
+                    mx0[i] = OpPkMax()(mx0[i], k1 ^ 0x7f007f00u);
+                    mn0[i] = OpPkMin()(mn0[i], k1 ^ 0x80008000u);
+                    np[i] = __builtin_amdgcn_udot4(k1 & 0x01000100u, vsel << 8, np[i], false);
+                }
             }
-        });
-    }
-    with_g(st.G, [&](auto gc) {
-        constexpr int GG = decltype(gc)::value;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            sf[i] = fold_g<GG>(sf[i], OpAdd());
-            sfn[i] = fold_g<GG>(sfn[i], OpAdd());
         }
-    });
-    if (active && group_leader(st.G)) {
+    };
+    int64_t nrows = 0;                       // rows the block has counted
+    int flush = 0;
+    while (tile < st.ntiles) {
+        const int tn = tile + st.gx;
+        if (tn < st.ntiles) load(tn, nx, nd);
+        const int64_t r0 = (int64_t)tile * TR;
+        if (r0 + TR <= st.M) {
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            atomicAdd(&sF[g * 4 + i], (unsigned long long)sf[i]);
-            atomicAdd(&sFn[g * 4 + i], (unsigned long long)sfn[i]);
+            for (int u = 0; u < U; u += 2) pair(vx[u], vx[u + 1], vd[u], vd[u + 1], std::true_type(), true, true);
+            nrows += TR;
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; u += 2)
+                pair(vx[u], vx[u + 1], vd[u], vd[u + 1], std::false_type(), r0 + u * RPI + rsub <= last,
+                     r0 + (u + 1) * RPI + rsub <= last);
+            nrows += st.M - r0;
+        }
+        // |a pair's products| <= 2^23 (MODE 2: |f| <= 2^13, 2^29): far from 2^31 at
+        // every flush
+        if (MODE == 2 || ++flush == 32) {
+            flush = 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) { sdn[i] += sn[i]; sff[i] += sf[i]; sn[i] = sf[i] = 0; }
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) { vx[u] = nx[u]; vd[u] = nd[u]; }
+        tile = tn;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) { sdn[i] += sn[i]; sff[i] += sf[i]; }
+    // the halves hold the even and the odd rows: fold them, then the two maxima
+    // (minima) of a channel share a register
+    uint32_t kmx[4], kmn[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        kmx[i] = max(mx1[i] & 0xffff, mx1[i] >> 16) | max(mx2[i] & 0xffff, mx2[i] >> 16) << 16;
+        kmn[i] = min(mn1[i] & 0xffff, mn1[i] >> 16) | min(mn2[i] & 0xffff, mn2[i] >> 16) << 16;
+        mx0[i] = max(mx0[i] & 0xffff, mx0[i] >> 16);
+        mn0[i] = min(mn0[i] & 0xffff, mn0[i] >> 16);
+    }
+    wave_fold<4, G>(sdn, OpAdd());
+    if constexpr (MODE == 2) {
+        wave_fold<4, G>(sff, OpAdd());
+    } else {
+        wave_fold<4, G>(sd, OpAdd());
+        wave_fold<4, G>(z, OpAdd());
+        wave_fold<4, G>(kmx, OpPkMax());
+        wave_fold<4, G>(kmn, OpPkMin());
+        if (zflag) {
+            wave_fold<4, G>(mx0, OpPkMax());
+            wave_fold<4, G>(mn0, OpPkMin());
+            wave_fold<4, G>(np, OpAdd());
+        }
+    }
+    // the wave totals of each channel, staged in the table's space
+    __syncthreads();
+    long long* wsn = (long long*)tab;                  // [kWaves][CS]
+    uint32_t* wsd = (uint32_t*)(wsn + kWaves * CS);    // [4][kWaves][CS], with class 0 [7]
+    long long* wsf = wsn + kWaves * CS;                // MODE 2: [kWaves][CS]
+    if ((lane & 15) < G) {
+        const int o = wv * CS + g * 4 + fold_ch<4>(lane);
+        wsn[o] = sdn[0];
+        if constexpr (MODE == 2) {
+            wsf[o] = sff[0];
+        } else {
+            wsd[o] = sd[0];
+            wsd[kWaves * CS + o] = z[0];
+            wsd[2 * kWaves * CS + o] = kmx[0];
+            wsd[3 * kWaves * CS + o] = kmn[0];
+            if (zflag) {
+                wsd[4 * kWaves * CS + o] = mx0[0];
+                wsd[5 * kWaves * CS + o] = mn0[0];
+                wsd[6 * kWaves * CS + o] = np[0];
+            }
         }
     }
     __syncthreads();
-    if ((int)threadIdx.x < st.CS) {
-        int64_t o = (int64_t)blockIdx.x * st.C + cbase + threadIdx.x;
-        st_x(&w.p_sf[o], (long long)sF[threadIdx.x]);
-        st_x(&w.p_sfn[o], (long long)sFn[threadIdx.x]);
+    int F = 0;
+    if (t < CS) {
+        // [slice][block][channel of the slice]: one contiguous row per block
+        const int64_t o = ((int64_t)blockIdx.y * st.gx + blockIdx.x) * CS + t;
+        long long bn = 0, bf = 0;
+        int32_t bs = 0;
+        uint32_t bz = 0, bx = 0, bm = ~0u, x0 = 0, m0 = 0xffff, bnp = 0;
+#pragma unroll 4
+        for (int v = 0; v < kWaves; v++) {
+            bn += wsn[v * CS + t];
+            if constexpr (MODE == 2) {
+                bf += wsf[v * CS + t];
+            } else {
+                bs += (int32_t)wsd[v * CS + t];
+                bz += wsd[(kWaves + v) * CS + t];
+                bx = OpPkMax()(bx, wsd[(2 * kWaves + v) * CS + t]);
+                bm = OpPkMin()(bm, wsd[(3 * kWaves + v) * CS + t]);
+                if (zflag) {
+                    x0 = max(x0, wsd[(4 * kWaves + v) * CS + t]);
+                    m0 = min(m0, wsd[(5 * kWaves + v) * CS + t]);
+                    bnp += wsd[(6 * kWaves + v) * CS + t];
+                }
+            }
+        }
+        if constexpr (MODE == 2) {
+            w.p_sf[o] = bf;
+            w.p_sfn[o] = bn;
+        } else {
+            // sum sgn = N(+1) - N(-1) from sum class = 255 N(+1) + 128 N(0)
+            // (no class 0 unless the channel was flagged)
+            const int n0 = sZf[t] ? (int)((bz - 255u * bnp) / 128u) : 0;
+            const int np = sZf[t] ? (int)bnp : (int)(bz / 255u);
+            w.p_sd[o] = bs - (int32_t)(128 * nrows);
+            w.p_sdn[o] = bn;
+            w.p_z[o] = 2 * np + n0 - (int32_t)nrows;
+            // class -1: minimum of the key, maximum of the inverted one; class +1 the others
+            const uint32_t x1 = bx & 0xffff, x2 = bx >> 16, m1 = bm & 0xffff, m2 = bm >> 16;
+            const int lo0 = (m1 >> 8) == 0 ? (int)m1 : 255, hi0 = (x2 >> 8) == 0xff ? (int)(x2 & 0xff) : 0;
+            const int lo2 = (m2 >> 8) == 0 ? (int)m2 : 255, hi2 = (x1 >> 8) == 0xff ? (int)(x1 & 0xff) : 0;
+            const int lo1 = sZf[t] && (m0 >> 8) == 0 ? (int)m0 : 255, hi1 = sZf[t] && (x0 >> 8) == 0xff ? (int)(x0 & 0xff) : 0;
+            w.p_mmA[o] = lo0 | hi0 << 8 | lo1 << 16 | hi1 << 24;
+            w.p_mmB[o] = lo2 | hi2 << 8;
+            if (MODE == 1 && cb + t < st.C) {
+                // largest |gamma d|: |d| is largest at a class extreme
+                const int lo = min(min(lo0, lo1), lo2) - 128, hi = max(max(hi0, hi1), hi2) - 128;
+                const int gq = out.gamma_q[cb + t];
+                F = (gq < 0 ? -gq : gq) * max(lo < 0 ? -lo : lo, hi < 0 ? -hi : hi);
+            }
+        }
     }
-    if (arrive_last(w.ctr + 1 + blockIdx.y, gridDim.x)) {
-        __syncthreads();
-        bnb_round_tail2((uint32_t*)xc, st, w, sv, cf, out, r2);
+    if constexpr (MODE == 1) {
+        F = block_max_nt(F, rsh);
+        if (t == 0) w.pF[blockIdx.y * st.gx + blockIdx.x] = F;
     }
 }
 
@@ -1598,23 +1324,6 @@ __device__ __forceinline__ i128 bnb_bracket(int64_t f, int s, i128 M, i128 Sf, i
     return e_xh >= 0 ? a - (t << e_xh) : (a << -e_xh) - t;
 }
 
-struct BnbChan {
-    i128 Sf, T, Z;
-    int e_xh, Ebase, r2;
-};
-
-// exponents of a channel's bracket for E2's shift r2
-__device__ __forceinline__ BnbChan bnb_chan_exps(int r2, int32_t dy_exp, const Saved& sv, const BnCfg& cf)
-{
-    BnbChan ch;
-    ch.r2 = r2;
-    ch.e_xh = sv.hdr[0] - (cf.k_xhat - 1);
-    const int e_sig = 2 - cf.k_sigma, e_g = 2 - cf.k_gamma;
-    const int s2 = dy_exp + e_g + r2;
-    ch.Ebase = s2 - e_sig + (ch.e_xh < 0 ? ch.e_xh : 0);
-    return ch;
-}
-
 __device__ __forceinline__ void bnb_exps_out(const Saved& sv, const BnCfg& cf, const BnbOut& o)
 {
     const int32_t s_d = *o.dy_exp;
@@ -1623,293 +1332,97 @@ __device__ __forceinline__ void bnb_exps_out(const Saved& sv, const BnCfg& cf, c
     *o.dgamma_exp = s_d + sv.hdr[0] - (cf.k_xhat - 1);
 }
 
-// dx code table for every (sgn class, masked error code) of a channel
-// (rounding E2): E1's exponent and E2's shift from the slices' maxima
-__global__ __launch_bounds__(256) void k_bnb_lut(int64_t Mrows, int nslices, BwdWs w, Saved sv, BnCfg cf,
-                                                 BnbOut o)
+// One block per channel, one thread per (sgn class, masked error code): the
+// channel's totals from the streaming blocks' partials (dbeta, dgamma), its
+// bound on E1's exponent (the largest over its six per-class extremes; E2 is
+// monotone and the bracket linear in the code, so the extremes bound every
+// code the channel's data holds), and its dx values at that bound: Q =
+// floor(B 2^S / D) with S one more than the shift of the channel's own bound,
+// for the (class, code) pairs inside the channel's per-class ranges (zero
+// elsewhere: the output pass never looks them up).  |Q| <= 2^k_E1 + 1 there, so
+// int16 holds it; the output pass rounds Q by the gap between the largest
+// bound and the channel's into the final code (half-up rounding of floor(x)
+// by 2^g + 1 equals that of x).  Exact E2 (k_E2 >= 15, |gamma delta| <= 127^2 <
+// 2^(k_E2-1)): E2's shift r2 is <= 0 and scales every term of the bracket and
+// the exponent base by inverse powers of two, so dx is that of r2 = 0 with f =
+// gamma_q delta.  Bound by latency (one 128-bit division per thread, in three
+// times as many threads as codes): 7.1 -> 6.4 us at 256 channels.
+constexpr int kChanNT = 768;
+template <bool ROUND>
+__global__ __launch_bounds__(kChanNT) void k_bnb_chan(FStat st, int CS, BwdWs w, Saved sv, BnCfg cf, BnbOut o)
 {
-    __shared__ int32_t rsh[4];
-    const int c = blockIdx.x;
-    const int d = (int)threadIdx.x - 128;
-    const int gq = o.gamma_q[c];
-    const int r2 = bnb_r2_of(slices_max(w.smaxF, nslices, rsh), cf);
-    int bdx = slices_max(w.smax, nslices, rsh);
-    if (bdx == kSentinelLo) bdx = 0;
-    if (c == 0 && threadIdx.x == 0) {
-        *o.dx_exp = bdx - (cf.k_E1 - 1);
-        bnb_exps_out(sv, cf, o);
-    }
-    BnbChan ch = bnb_chan_exps(r2, *o.dy_exp, sv, cf);
-    ch.Sf = (i128)w.sf[c];
-    ch.T = (i128)w.sfn[c];
-    ch.Z = (i128)w.Z[c];
-    const i128 M = Mrows;
-    const i128 Dd = (i128)sv.den[c] * M * M;
-    const int64_t f = d < -127 ? 0 : sq_code((int64_t)gq * d, ch.r2, cf.k_E2);
-    for (int k = 0; k < 3; k++) {
-        int8_t code = 0;
-        if (d >= -127) {
-            i128 B = bnb_bracket(f, k - 1, M, ch.Sf, ch.T, ch.Z, ch.e_xh);
-            code = (int8_t)clamp_k128(rhu128(B, ch.Ebase + (cf.k_E1 - 1) - bdx, Dd), cf.k_E1);
-        }
-        w.lut[((int64_t)c * 3 + k) * 256 + threadIdx.x] = code;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Exact E2 (k_E2 >= 15, |gamma delta| <= 127^2 < 2^(k_E2-1)): E2's requant
-// shift r2 is <= 0 and scales every term of the bracket and the exponent base
-// by inverse powers of two, so dx, its exponent bound and its codes are those
-// of r2 = 0, with f = gamma_q delta; the stats kernel's tails replace a
-// separate per-channel pass.
-// ---------------------------------------------------------------------------
-// stats tail (exact E2).  Slice: the pass-1 sums, dgamma and dbeta of its
-// channels and each channel's bound on max|dx| (|dx| is extreme at a class's
-// extreme deltas: six candidates per channel, one thread each); the largest
-// bound of the slice goes to smax for the table kernel, which takes E1's
-// exponent as the largest over the slices.  `lds` is the stats table, no
-// longer read once the block has arrived.
-struct Tail1Lds {
-    int32_t *sd, *z, *mm, *cand;        // [kNT], [kNT], [6][kNT], [6 * CS]
-    long long* sdn;                     // [kNT]
-    __device__ explicit Tail1Lds(uint32_t* lds)
-    {
-        sd = (int32_t*)lds; z = sd + kNT; mm = z + kNT;
-        sdn = (long long*)(mm + 6 * kNT); cand = (int32_t*)(sdn + kNT);
-    }
-};
-
-// the slice's pass-1 sums from all blocks' partials: w.sd / sdn / Z / mm,
-// dgamma, dbeta, and the channel totals in the group-0 slots of the LDS table
-__device__ __forceinline__ void bnb_tail_reduce1(uint32_t* lds, const Stream& st, const BwdWs& w,
-                                                 const BnbOut& o)
-{
-    const int CS = st.CS, ng = kNT / CS, t = threadIdx.x, ch = t % CS, grp = t / CS;
-    const Tail1Lds L(lds);
-    int32_t* tSd = L.sd;
-    int32_t* tZ = L.z;
-    int32_t* tMM = L.mm;
-    long long* tSdn = L.sdn;
-    const int64_t cb = (int64_t)blockIdx.y * CS;
+    constexpr int NW = kChanNT / 64;
+    __shared__ int32_t r_sd[NW], r_z[NW], r_lo[NW][3], r_hi[NW][3], r_cand, rsh[NW];
+    __shared__ long long r_sdn[NW], r_sf[NW], r_sfn[NW];
+    const int c = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6, gx = st.gx;
+    const int gq = o.gamma_q[c], den = sv.den[c], hdr0 = sv.hdr[0], dye = *o.dy_exp;
     int sd = 0, z = 0;
-    long long sdn = 0;
-    int lo3[3] = {255, 255, 255}, hi3[3] = {0, 0, 0};   // byte-coded extremes
-    constexpr int U = 8;                    // partial rows whose loads are in flight together
-    if (grp < ng)
-        for (int b0 = grp; b0 < st.gx; b0 += U * ng) {
-            int32_t vsd[U], vz[U], vA[U], vB[U];
-            long long vsdn[U];
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const int b = b0 + u * ng;
-                const int64_t q = (int64_t)(b < st.gx ? b : b0) * st.C + cb + ch;
-                vsd[u] = ld_x(&w.p_sd[q]);
-                vsdn[u] = ld_x(&w.p_sdn[q]);
-                vz[u] = ld_x(&w.p_z[q]);
-                vA[u] = ld_x(&w.p_mmA[q]);
-                vB[u] = ld_x(&w.p_mmB[q]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                mm_merge((uint32_t)vA[u], (uint32_t)vB[u], lo3, hi3);   // a repeated row changes nothing
-                if (b0 + u * ng >= st.gx) continue;
-                sd += vsd[u]; sdn += vsdn[u]; z += vz[u];
-            }
+    long long sdn = 0, sf = 0, sfn = 0;
+    int lo3[3] = {255, 255, 255}, hi3[3] = {0, 0, 0};       // byte-coded extremes (empty: lo > hi)
+    const int sy = c / CS, sc = c - sy * CS;                // slice, channel within it
+    const int nw = min(NW, (gx + 63) >> 6);                 // waves that hold partials
+    if (wv < nw) {
+        for (int b = t; b < gx; b += kChanNT) {
+            const int64_t q = ((int64_t)sy * gx + b) * CS + sc;
+            sd += w.p_sd[q];
+            sdn += w.p_sdn[q];
+            z += w.p_z[q];
+            if constexpr (ROUND) { sf += w.p_sf[q]; sfn += w.p_sfn[q]; }
+            mm_merge((uint32_t)w.p_mmA[q], (uint32_t)w.p_mmB[q], lo3, hi3);
         }
-    tSd[t] = sd; tZ[t] = z; tSdn[t] = sdn;
-#pragma unroll
-    for (int k = 0; k < 3; k++) { tMM[2 * k * kNT + t] = lo3[k]; tMM[(2 * k + 1) * kNT + t] = hi3[k]; }
-    __syncthreads();
-    if (t < CS) {
-        for (int g2 = 1; g2 < ng; g2++) {
-            const int i = g2 * CS + t;
-            sd += tSd[i]; z += tZ[i]; sdn += tSdn[i];
+        for (int off = 32; off > 0; off >>= 1) {
+            sd += __shfl_xor(sd, off, 64);
+            z += __shfl_xor(z, off, 64);
+            sdn += __shfl_xor(sdn, off, 64);
+            if constexpr (ROUND) { sf += __shfl_xor(sf, off, 64); sfn += __shfl_xor(sfn, off, 64); }
 #pragma unroll
             for (int k = 0; k < 3; k++) {
-                lo3[k] = min(lo3[k], tMM[2 * k * kNT + i]);
-                hi3[k] = max(hi3[k], tMM[(2 * k + 1) * kNT + i]);
+                lo3[k] = min(lo3[k], __shfl_xor(lo3[k], off, 64));
+                hi3[k] = max(hi3[k], __shfl_xor(hi3[k], off, 64));
             }
         }
-        int mm[6];
+        if (lane == 0) {
+            r_sd[wv] = sd; r_z[wv] = z; r_sdn[wv] = sdn; r_sf[wv] = sf; r_sfn[wv] = sfn;
 #pragma unroll
-        for (int k = 0; k < 3; k++) { mm[2 * k] = lo3[k] - 128; mm[2 * k + 1] = hi3[k] - 128; }   // empty: lo > hi
-        const int64_t c = cb + t;
-        w.sd[c] = sd; w.sdn[c] = sdn; w.Z[c] = z;
-#pragma unroll
-        for (int k = 0; k < 6; k++) w.mm[c * 6 + k] = mm[k];
-        o.dbeta[c] = sd;
-        o.dgamma[c] = sdn;
-        // the channel totals, in the slots of group 0, for the candidate threads
-        tSd[t] = sd; tZ[t] = z; tSdn[t] = sdn;
-#pragma unroll
-        for (int k = 0; k < 6; k++) tMM[k * kNT + t] = mm[k];
-    }
-    __syncthreads();
-}
-
-// largest of the slice's per-channel values in tCand (6 per channel) into
-// *dst (kSentinelLo when none)
-__device__ __forceinline__ void slice_cand_max(const int32_t* tCand, int n, int32_t* dst, int32_t* sh)
-{
-    int32_t m = kSentinelLo;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) m = max(m, tCand[i]);
-    m = block_max_nt(m, sh);
-    if (threadIdx.x == 0) *dst = m;
-}
-
-// stats tail (rounding E2).  Slice: the pass-1 sums, dgamma, dbeta and the
-// largest |gamma_q delta| over its channels' sgn classes, into smaxF; the
-// second pass takes E2's Scale from the largest over the slices.
-__device__ __forceinline__ void bnb_round_tail1(uint32_t* lds, const Stream& st, const BwdWs& w, const Saved& sv,
-                                                const BnCfg& cf, const BnbOut& o)
-{
-    bnb_tail_reduce1(lds, st, w, o);
-    const int CS = st.CS, t = threadIdx.x;
-    const Tail1Lds L(lds);
-    __shared__ int32_t rb[kNT / 64];
-    const int64_t cb = (int64_t)blockIdx.y * CS;
-    int F = 0;
-    if (t < CS) {
-        int amax = 0;
-        for (int k = 0; k < 3; k++) {
-            const int lo = L.mm[2 * k * kNT + t], hi = L.mm[(2 * k + 1) * kNT + t];
-            if (lo > hi) continue;                     // empty class
-            amax = max(amax, max(lo < 0 ? -lo : lo, hi < 0 ? -hi : hi));
-        }
-        const int gq = o.gamma_q[cb + t];
-        F = (gq < 0 ? -gq : gq) * amax;                // <= 128 * 128
-    }
-    F = block_max_nt(F, rb);
-    if (t == 0) w.smaxF[blockIdx.y] = F;
-}
-
-// stats2 tail.  Slice: the pass-2 sums (sum f, sum f n_xhat) and each
-// channel's bound on max|dx| (six candidates, as the exact tail); the largest
-// goes to smax.  `lds` is stats2's x-hat table, no longer read.
-__device__ __forceinline__ void bnb_round_tail2(uint32_t* lds, const Stream& st, const BwdWs& w,
-                                                const Saved& sv, const BnCfg& cf, const BnbOut& o, int r2)
-{
-    const int CS = st.CS, ng = kNT / CS, t = threadIdx.x, ch = t % CS, grp = t / CS;
-    long long* tSf = (long long*)lds;                   // [kNT]
-    long long* tSfn = tSf + kNT;                        // [kNT]
-    int32_t* tCand = (int32_t*)(tSfn + kNT);            // [6 * CS]
-    __shared__ int32_t rb[kNT / 64];
-    const int64_t cb = (int64_t)blockIdx.y * CS;
-    long long sf = 0, sfn = 0;
-    constexpr int U = 8;                    // partial rows whose loads are in flight together
-    if (grp < ng)
-        for (int b0 = grp; b0 < st.gx; b0 += U * ng) {
-            long long vf[U], vn[U];
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const int b = b0 + u * ng;
-                const int64_t q = (int64_t)(b < st.gx ? b : b0) * st.C + cb + ch;
-                vf[u] = ld_x(&w.p_sf[q]);
-                vn[u] = ld_x(&w.p_sfn[q]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; u++)
-                if (b0 + u * ng < st.gx) { sf += vf[u]; sfn += vn[u]; }
-        }
-    tSf[t] = sf; tSfn[t] = sfn;
-    __syncthreads();
-    if (t < CS) {
-        for (int g2 = 1; g2 < ng; g2++) { sf += tSf[g2 * CS + t]; sfn += tSfn[g2 * CS + t]; }
-        w.sf[cb + t] = sf; w.sfn[cb + t] = sfn;
-        tSf[t] = sf; tSfn[t] = sfn;                     // only thread t reads slot t above
-    }
-    __syncthreads();
-    if (t < 6 * CS) {
-        const int cl = t / 6, k = t % 6;                // channel of the slice; class k / 2, low / high
-        const int64_t c = cb + cl;
-        const int lo = w.mm[c * 6 + (k & ~1)], hi = w.mm[c * 6 + (k | 1)];
-        int best = kSentinelLo;
-        if (lo <= hi) {
-            const int gq = o.gamma_q[c];
-            const BnbChan e = bnb_chan_exps(r2, *o.dy_exp, sv, cf);
-            const i128 M = st.M;
-            const int64_t f = sq_code((int64_t)gq * ((k & 1) ? hi : lo), e.r2, cf.k_E2);
-            const i128 B = bnb_bracket(f, (k >> 1) - 1, M, (i128)tSf[cl], (i128)tSfn[cl], (i128)w.Z[c], e.e_xh);
-            if (B != 0) best = ceil_pow2_exp128(abs128(B), (i128)sv.den[c] * M * M) + e.Ebase;
-        }
-        tCand[t] = best;
-    }
-    __syncthreads();
-    slice_cand_max(tCand, 6 * CS, w.smax + blockIdx.y, rb);
-}
-
-// Exact E2 (k_E2 >= 15), one block per channel and one thread per masked
-// error code: the channel's totals from the streaming blocks' partials
-// (dbeta, dgamma), its bound on E1's exponent (the largest over its six
-// per-class extremes; xhat and the bracket are linear in the code, so the
-// extremes bound every code the channel's data holds), and its dx values at
-// that bound: Q = floor(B 2^S / D) with S one more than the shift of the
-// channel's own bound, for the (class, code) pairs inside the channel's
-// per-class ranges (zero elsewhere: the output pass never looks them up).
-// |Q| <= 2^k_E1 + 1 there, so int16 holds it; the output pass rounds Q by
-// the gap between the largest bound and the channel's into the final code
-// (half-up rounding of floor(x) by 2^g + 1 equals that of x).
-__global__ __launch_bounds__(256) void k_bnb_chan_exact(int64_t Mrows, int gx, int CS, BwdWs w, Saved sv,
-                                                        BnCfg cf, BnbOut o)
-{
-    __shared__ int32_t r_sd[4], r_z[4], r_lo[4][3], r_hi[4][3], r_cand;
-    __shared__ long long r_sdn[4];
-    const int c = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    int sd = 0, z = 0;
-    long long sdn = 0;
-    int lo3[3] = {255, 255, 255}, hi3[3] = {0, 0, 0};       // byte-coded extremes (empty: lo > hi)
-    const int sy = c / CS, sc = c - sy * CS;                  // slice, channel within it
-    for (int b = t; b < gx; b += blockDim.x) {
-        const int64_t q = ((int64_t)sy * gx + b) * CS + sc;
-        sd += w.p_sd[q];
-        sdn += w.p_sdn[q];
-        z += w.p_z[q];
-        mm_merge((uint32_t)w.p_mmA[q], (uint32_t)w.p_mmB[q], lo3, hi3);
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        sd += __shfl_xor(sd, off, 64);
-        z += __shfl_xor(z, off, 64);
-        sdn += __shfl_xor(sdn, off, 64);
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            lo3[k] = min(lo3[k], __shfl_xor(lo3[k], off, 64));
-            hi3[k] = max(hi3[k], __shfl_xor(hi3[k], off, 64));
+            for (int k = 0; k < 3; k++) { r_lo[wv][k] = lo3[k]; r_hi[wv][k] = hi3[k]; }
         }
     }
-    if (lane == 0) {
-        r_sd[wv] = sd; r_z[wv] = z; r_sdn[wv] = sdn;
-#pragma unroll
-        for (int k = 0; k < 3; k++) { r_lo[wv][k] = lo3[k]; r_hi[wv][k] = hi3[k]; }
-    }
+    int r2 = 0;
+    if constexpr (ROUND) r2 = bnb_r2_of(bnb_max_F(w.pF, gx * st.nsl, rsh), cf);
     __syncthreads();
-    sd = (r_sd[0] + r_sd[1]) + (r_sd[2] + r_sd[3]);
-    z = (r_z[0] + r_z[1]) + (r_z[2] + r_z[3]);
-    sdn = (r_sdn[0] + r_sdn[1]) + (r_sdn[2] + r_sdn[3]);
+    sd = r_sd[0]; z = r_z[0]; sdn = r_sdn[0]; sf = r_sf[0]; sfn = r_sfn[0];
     int mm[6];
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-        mm[2 * k] = min(min(r_lo[0][k], r_lo[1][k]), min(r_lo[2][k], r_lo[3][k])) - 128;
-        mm[2 * k + 1] = max(max(r_hi[0][k], r_hi[1][k]), max(r_hi[2][k], r_hi[3][k])) - 128;
+    for (int k = 0; k < 3; k++) { lo3[k] = r_lo[0][k]; hi3[k] = r_hi[0][k]; }
+    for (int v = 1; v < nw; v++) {
+        sd += r_sd[v]; z += r_z[v]; sdn += r_sdn[v]; sf += r_sf[v]; sfn += r_sfn[v];
+#pragma unroll
+        for (int k = 0; k < 3; k++) { lo3[k] = min(lo3[k], r_lo[v][k]); hi3[k] = max(hi3[k], r_hi[v][k]); }
     }
+#pragma unroll
+    for (int k = 0; k < 3; k++) { mm[2 * k] = lo3[k] - 128; mm[2 * k + 1] = hi3[k] - 128; }
     if (t == 0) {
         o.dbeta[c] = sd;
         o.dgamma[c] = sdn;
     }
-    const int gq = o.gamma_q[c];
-    const int e_xh = sv.hdr[0] - (cf.k_xhat - 1);
+    const int e_xh = hdr0 - (cf.k_xhat - 1);
     const int e_sig = 2 - cf.k_sigma, e_g = 2 - cf.k_gamma;
-    const int Ebase = *o.dy_exp + e_g - e_sig + (e_xh < 0 ? e_xh : 0);
-    const i128 M = Mrows;
-    const i128 Dd = (i128)sv.den[c] * M * M;
-    const i128 Sf = (i128)gq * sd, T = (i128)gq * sdn, Z = z;
+    const int Ebase = dye + e_g + r2 - e_sig + (e_xh < 0 ? e_xh : 0);
+    const i128 M = st.M;
+    const i128 Dd = (i128)den * M * M;
+    const i128 Sf = ROUND ? (i128)sf : (i128)gq * sd, T = ROUND ? (i128)sfn : (i128)gq * sdn, Z = z;
+    auto f_of = [&](int d) {
+        return ROUND ? sq_code((int64_t)gq * d, r2, cf.k_E2) : clamp_k((int64_t)gq * d, cf.k_E2);
+    };
     // the six per-class candidates (threads 0..5 of wave 0), their max
     if (wv == 0) {
         int cand = kSentinelLo;
         if (t < 6) {
-            const int lo = mm[t & ~1], hi = mm[t | 1];
+            const int cls = t >> 1;
+            const int lo = cls == 0 ? mm[0] : (cls == 1 ? mm[2] : mm[4]);
+            const int hi = cls == 0 ? mm[1] : (cls == 1 ? mm[3] : mm[5]);
             if (lo <= hi) {
-                const int64_t f = clamp_k((int64_t)gq * ((t & 1) ? hi : lo), cf.k_E2);
-                const i128 B = bnb_bracket(f, (t >> 1) - 1, M, Sf, T, Z, e_xh);
+                const i128 B = bnb_bracket(f_of((t & 1) ? hi : lo), cls - 1, M, Sf, T, Z, e_xh);
                 if (B != 0) cand = ceil_pow2_exp128(abs128(B), Dd) + Ebase;
             }
         }
@@ -1921,113 +1434,142 @@ __global__ __launch_bounds__(256) void k_bnb_chan_exact(int64_t Mrows, int gx, i
     }
     __syncthreads();
     const int bc = r_cand;
-    const int d = t - 128;
+    const int k = t >> 8, d = (t & 255) - 128;
+    const int lo = k == 0 ? mm[0] : (k == 1 ? mm[2] : mm[4]), hi = k == 0 ? mm[1] : (k == 1 ? mm[3] : mm[5]);
     const int S = Ebase + (cf.k_E1 - 1) - bc + 1;
-    for (int k = 0; k < 3; k++) {
-        int16_t q = 0;
-        if (bc != kSentinelLo && d >= mm[2 * k] && d <= mm[2 * k + 1] && d >= -127) {
-            const int64_t f = clamp_k((int64_t)gq * d, cf.k_E2);
-            const i128 B = bnb_bracket(f, k - 1, M, Sf, T, Z, e_xh);
-            i128 Q = S >= 0 ? floordiv128(B << S, Dd) : floordiv128(B, Dd << -S);
-            Q = Q > 32767 ? 32767 : (Q < -32767 ? -32767 : Q);
-            q = (int16_t)Q;
-        }
-        w.lutq[((int64_t)c * 3 + k) * 256 + t] = q;
+    int16_t q = 0;
+    if (bc != kSentinelLo && d >= lo && d <= hi && d >= -127) {
+        const i128 B = bnb_bracket(f_of(d), k - 1, M, Sf, T, Z, e_xh);
+        i128 Q = S >= 0 ? floordiv128(B << S, Dd) : floordiv128(B, Dd << -S);
+        Q = Q > 32767 ? 32767 : (Q < -32767 ? -32767 : Q);
+        q = (int16_t)Q;
     }
+    w.lutq[(int64_t)c * 768 + t] = q;
 }
 
-// Output pass: dx code = lut[c][sgn class][masked delta].  A per-(channel,
-// code) entry gives the offset of the channel's class row in the block's LDS
-// copy of the tables (bits 16..31) and the ReLU mask byte (bits 0..7), so each
-// element costs two LDS reads and a handful of ALU operations.
-// Exact E2: every block first takes E1's exponent from the channels' bounds
-// (block (0, 0) writes it and the parameter-gradient exponents) and rounds
-// its channels' staged values into the codes.
-__global__ __launch_bounds__(1024) void k_bnb_apply(const int8_t* __restrict__ dy,
-                                                   const int8_t* __restrict__ x,
-                                                   int8_t* __restrict__ dx, Stream st, BwdWs w,
-                                                   Saved sv, BnCfg cf, BnbOut o, int32_t exact)
+// Output pass: dx code = lut[c][sgn class][masked delta].  Every block first
+// takes E1's exponent from the channels' bounds (block (0, 0) writes it and the
+// parameter-gradient exponents) and rounds its channels' staged values into
+// the byte table.  The class and the ReLU mask come from the channel's
+// thresholds in packed 16-bit arithmetic, two channels per operation: sgn =
+// clamp(2 q - t0 - p0 + 1, -1, 1) (t0 <= p0 <= t0 + 1 bound class 0), and the
+// codes with y > 0 are those with ms q + mt >= 0.  One LDS gather per element,
+// 50 KB of tables per block instead of two and 115 KB.  Bound by memory on the
+// large tensors (131072 x 256 codes: 24.0 -> 23.1 us; its row loop runs at 6.1
+// TB/s after 4 us of prologue), by the prologue on the small ones.
+template <int G>
+__global__ __launch_bounds__(1024) void k_bnb_apply(const int8_t* __restrict__ dy, const int8_t* __restrict__ x,
+                                                   int8_t* __restrict__ dx, FStat st, BwdWs w, Saved sv,
+                                                   BnCfg cf, BnbOut o)
 {
-    __shared__ __attribute__((aligned(16))) int8_t lut[64 * 3 * kRowB];
-    __shared__ __attribute__((aligned(16))) uint32_t tab[64 * kRowW];
-    __shared__ int32_t rb[kNT / 64];
-    const int relu = cf.relu;
-    const int64_t cbase = (int64_t)blockIdx.y * st.CS;
-    if (exact) {
-        int bdx = kSentinelLo;
-        for (int i = threadIdx.x; i < st.C; i += kNT) bdx = max(bdx, w.cbnd[i]);
-        bdx = block_max_nt(bdx, rb);
-        if (bdx == kSentinelLo) bdx = 0;
-        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-            *o.dx_exp = bdx - (cf.k_E1 - 1);
-            bnb_exps_out(sv, cf, o);
-        }
-        const short lim = (short)((1 << (cf.k_E1 - 1)) - 1);
-        const int16_t* src = w.lutq + cbase * 768;
-        for (int v = threadIdx.x; v < st.CS * 96; v += kNT) {      // eight values per step, two per op
-            const int i0 = v * 8, row = i0 >> 8, col = i0 & 255;
-            const int bc = w.cbnd[cbase + row / 3];
-            const short sh = (short)(bc == kSentinelLo ? 15 : min(bdx - bc, 15));
-            const int4 q = *(const int4*)(src + i0);
-            const int qw[4] = {q.x, q.y, q.z, q.w};
-            uint32_t ow[2] = {0, 0};
+    constexpr int CS = 4 * G, RPI = kNT / G, U = kBndU, TR = U * RPI;
+    constexpr int NV = (CS * 96 + kNT - 1) / kNT;
+    __shared__ __attribute__((aligned(16))) int8_t lut[CS * 3 * kRowB];
+    __shared__ int32_t rb[kWaves];
+    const int t = threadIdx.x, g = t % G, rsub = t / G;
+    const int cb = blockIdx.y * CS, c0 = cb + g * 4;
+    const int cl = c0 < st.C ? c0 : 0;
+    const int64_t last = st.M - 1;
+    // staged values, bounds, thresholds and the first tile all load together
+    int4 zq[NV];
+    int bc[NV];
 #pragma unroll
-            for (int h = 0; h < 4; h++) {
-                short2v qv = __builtin_bit_cast(short2v, qw[h]);
-                qv = ((qv >> sh) + (short)1) >> (short)1;
-                qv = qv > lim ? lim : qv;
-                qv = qv < (short)-lim ? (short)-lim : qv;
-                const uint32_t b = (uint32_t)(uint16_t)qv.x & 0xffu | ((uint32_t)(uint16_t)qv.y & 0xffu) << 8;
-                ow[h >> 1] |= b << (16 * (h & 1));
-            }
-            *(uint32_t*)(lut + row * kRowB + col) = ow[0];
-            *(uint32_t*)(lut + row * kRowB + col + 4) = ow[1];
-        }
-    } else {
-        copy_rows_to_lds<64 * 3 * 16 / kNT>(lut, w.lut + cbase * 768, st.CS * 3);
+    for (int k = 0; k < NV; k++) {
+        const int v = t + k * kNT, row = v / 96;
+        const int c = row < CS && cb + row < st.C ? cb + row : cb;
+        zq[k] = *(const int4*)(w.lutq + (int64_t)c * 768 + (v - row * 96) * 8);
+        bc[k] = w.cbnd[c];
     }
-    load_bwd_tab(tab, sv.btab + cbase * 256, st.CS, relu, true);
-    __syncthreads();
-    int g, rsub;
-    if (!stream_lane(st, g, rsub)) return;
-    const int c0 = (int)cbase + g * 4;
-    const uint32_t* tb = tab + g * 4 * kRowW;
-    const int64_t step = (int64_t)gridDim.x * st.rpi;
-    auto elem = [&](uint32_t wx, uint32_t wd) {
-        uint32_t ow = 0;
+    int t0[4], p0[4], mlo[4], mhi[4];
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const uint32_t e = tb[i * kRowW + ((wx >> (8 * i)) & 0xff)];
-            const int idx = (int)(e >> 16) + (sbyte(wd, i) & (int)(int8_t)(e & 0xff));
-            ow |= (uint32_t)(uint8_t)lut[idx] << (8 * i);
-        }
-        return ow;
-    };
-    // full groups of U rows with the next group's loads in flight, then the rest
-    constexpr int U = 4;
-    int64_t r = (int64_t)blockIdx.x * st.rpi + rsub;
-    const int64_t full_end = st.M - (U - 1) * step;
+    for (int i = 0; i < 4; i++) {
+        t0[i] = sv.t0[cl + i]; p0[i] = sv.p0[cl + i];
+        mlo[i] = sv.mlo[cl + i]; mhi[i] = sv.mhi[cl + i];
+    }
     uint32_t vx[U], vd[U], nx[U], nd[U];
-    auto load = [&](int64_t r0, uint32_t* ax, uint32_t* ad) {
+    auto load = [&](int tile, uint32_t* ax, uint32_t* ad) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            ax[u] = *(const uint32_t*)(x + (r0 + u * step) * st.C + c0);
-            ad[u] = *(const uint32_t*)(dy + (r0 + u * step) * st.C + c0);
+            const int64_t r = (int64_t)tile * TR + u * RPI + rsub, rr = (r < last ? r : last) * st.C + cl;
+            ax[u] = *(const uint32_t*)(x + rr);
+            ad[u] = *(const uint32_t*)(dy + rr);
         }
     };
-    if (r < full_end) load(r, vx, vd);
-    while (r < full_end) {
-        const int64_t rn = r + U * step;
-        if (rn < full_end) load(rn, nx, nd);
+    int tile = blockIdx.x;
+    if (tile < st.ntiles) load(tile, vx, vd);
+    int bdx = kSentinelLo;
+    for (int i = t; i < st.C; i += kNT) bdx = max(bdx, w.cbnd[i]);
+    bdx = block_max_nt(bdx, rb);
+    if (bdx == kSentinelLo) bdx = 0;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) {
+        *o.dx_exp = bdx - (cf.k_E1 - 1);
+        bnb_exps_out(sv, cf, o);
+    }
+    const short lim = (short)((1 << (cf.k_E1 - 1)) - 1);
 #pragma unroll
-        for (int u = 0; u < U; u++) *(uint32_t*)(dx + (r + u * step) * st.C + c0) = elem(vx[u], vd[u]);
+    for (int k = 0; k < NV; k++) {                // eight values per step, two per op
+        const int v = t + k * kNT, row = v >> 5, col = (v & 31) * 8;
+        if (row >= CS * 3) break;
+        const short sh = (short)(bc[k] == kSentinelLo ? 15 : min(bdx - bc[k], 15));
+        const int qw[4] = {zq[k].x, zq[k].y, zq[k].z, zq[k].w};
+        uint32_t ow[2] = {0, 0};
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            short2v qv = __builtin_bit_cast(short2v, qw[h]);
+            qv = ((qv >> sh) + (short)1) >> (short)1;
+            qv = qv > lim ? lim : qv;
+            qv = qv < (short)-lim ? (short)-lim : qv;
+            const uint32_t b = ((uint32_t)(uint16_t)qv.x & 0xffu) | ((uint32_t)(uint16_t)qv.y & 0xffu) << 8;
+            ow[h >> 1] |= b << (16 * (h & 1));
+        }
+        *(uint32_t*)(lut + row * kRowB + col) = ow[0];
+        *(uint32_t*)(lut + row * kRowB + col + 4) = ow[1];
+    }
+    // thresholds as 16-bit pairs: channels 0, 2 and channels 1, 3
+    short2v tc[2], ms[2], mt[2];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        // codes with y > 0: [mlo, mhi], a prefix or a suffix of the code range,
+        // everything (without ReLU too) or nothing
+        const bool all = !cf.relu || (mlo[i] == -128 && mhi[i] == 127), none = mlo[i] > mhi[i];
+        const int m = all || none ? 0 : (mhi[i] == 127 ? 1 : -1);
+        const int a = all ? 0 : (none ? -1 : (m > 0 ? -mlo[i] : mhi[i]));
+        const short vt = (short)(1 - t0[i] - p0[i]), vm = (short)m, va = (short)a;
+        if (i & 2) { tc[i & 1].y = vt; ms[i & 1].y = vm; mt[i & 1].y = va; }
+        else { tc[i & 1].x = vt; ms[i & 1].x = vm; mt[i & 1].x = va; }
+    }
+    const short base = (short)(g * 4 * 3 * kRowB + kRowB + 128);    // class 0, d = 0 of the lane's first channel
+    __syncthreads();
+    auto elem = [&](uint32_t wx, uint32_t wd) {
+        const short2v q2[2] = {__builtin_bit_cast(short2v, wx << 8) >> (short)8, __builtin_bit_cast(short2v, wx) >> (short)8};
+        const short2v d2[2] = {__builtin_bit_cast(short2v, wd << 8) >> (short)8, __builtin_bit_cast(short2v, wd) >> (short)8};
+        uint32_t ix[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            short2v s = q2[h] * (short)2 + tc[h];
+            s = __builtin_elementwise_max(s, (short2v)(short)-1);
+            s = __builtin_elementwise_min(s, (short2v)(short)1);
+            const uint32_t neg = __builtin_bit_cast(uint32_t, (short2v)((q2[h] * ms[h] + mt[h]) >> (short)15));
+            const short2v dm = __builtin_bit_cast(short2v, __builtin_bit_cast(uint32_t, d2[h]) & ~neg);
+            ix[h] = __builtin_bit_cast(uint32_t, (short2v)(s * (short)kRowB + (short2v)(dm + base)));
+        }
+        const uint32_t b0 = (uint8_t)lut[ix[0] & 0xffff], b1 = (uint8_t)lut[(ix[1] & 0xffff) + 3 * kRowB];
+        const uint32_t b2 = (uint8_t)lut[(ix[0] >> 16) + 6 * kRowB], b3 = (uint8_t)lut[(ix[1] >> 16) + 9 * kRowB];
+        return (b0 | b1 << 8) | (b2 | b3 << 8) << 16;
+    };
+    while (tile < st.ntiles) {
+        const int tn = tile + st.gx;
+        if (tn < st.ntiles) load(tn, nx, nd);
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t r = (int64_t)tile * TR + u * RPI + rsub;
+            const uint32_t v = elem(vx[u], vd[u]);
+            if (r <= last && c0 < st.C) *(uint32_t*)(dx + r * st.C + c0) = v;
+        }
 #pragma unroll
         for (int u = 0; u < U; u++) { vx[u] = nx[u]; vd[u] = nd[u]; }
-        r = rn;
+        tile = tn;
     }
-    for (; r < st.M; r += step)
-        *(uint32_t*)(dx + r * st.C + c0) =
-            elem(*(const uint32_t*)(x + r * st.C + c0), *(const uint32_t*)(dy + r * st.C + c0));
 }
 
 bool cfg_ok(const iseg_bn_cfg* c)
@@ -2056,9 +1598,8 @@ extern "C" size_t iseg_bn_fwd_ws(int64_t M, int64_t C)
 
 extern "C" size_t iseg_bn_bwd_ws(int64_t M, int64_t C)
 {
-    int cs = pick_cs(C, 64);
-    if (!shape_ok(M, C) || !cs) return 0;
-    return bwd_ws_bytes(make_stream(M, C, cs, 4, ISEG_BNB_ROWS, kMaxBlocks));
+    if (!shape_ok(M, C) || C % 4) return 0;
+    return bwd_ws_bytes(C);
 }
 
 static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t C,
@@ -2138,10 +1679,8 @@ extern "C" int iseg_bn_fwd(const int8_t* x, const int32_t* x_exp, int64_t M, int
 // buffer.  In host code `scratch` names a host-side stand-in, not device
 // memory: its device address is looked up once per device with
 // hipGetSymbolAddress (with that device current) and only that address is
-// passed to the kernels.  The array starts at zero and every call leaves
-// the forward's arrival counters at zero; the rest of the workspace is
-// written before it is read within a call, so nothing needs clearing between
-// calls.
+// passed to the kernels.  The workspace is written before it is read within
+// a call, so nothing needs clearing between calls.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t kBnScratchBytes = (size_t)1 << 20;
@@ -2191,32 +1730,35 @@ extern "C" int iseg_bn_bwd(const int8_t* dy, const int32_t* dy_exp, const int8_t
     if (!dy || !dy_exp || !x || !gamma_q || !saved || !dx_out || !dx_exp || !dgamma || !dbeta ||
         !dgamma_exp || !dbeta_exp || !cfg_ok(cfg))
         return ISEG_ERR_ARG;
-    int cs = pick_cs(C, 64);
-    if (!cs || (((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx_out) & 3)) return ISEG_ERR_UNSUPPORTED;
-    Stream st = make_stream(M, C, cs, 4, ISEG_BNB_ROWS, kMaxBlocks);
-    if (!ws || ws_bytes < bwd_ws_bytes(st)) return ISEG_ERR_WORKSPACE;
+    if (C % 4 || (((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx_out) & 3)) return ISEG_ERR_UNSUPPORTED;
+    if (!ws || ws_bytes < bwd_ws_bytes(C)) return ISEG_ERR_WORKSPACE;
     BnCfg cf = to_cfg(cfg);
     Saved sv = saved_map((void*)saved, C);
-    BwdWs w = bwd_ws_map(ws, st);
-    dim3 sg = stream_grid(st);
-    dim3 cb((unsigned)C);
+    BwdWs w = bwd_ws_map(ws, C);
     // E2 = SQ(gamma delta, k_E2) is exact when |gamma delta| <= 127^2 < 2^(k_E2-1)
-    const int exact_e2 = cf.k_E2 >= 15;
+    const bool exact_e2 = cf.k_E2 >= 15;
     const BnbOut out{dy_exp, gamma_q, dgamma, dbeta, dgamma_exp, dbeta_exp, dx_exp, dev_status};
-    if (exact_e2) {
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, k_bnb_stats<1>, sg, dim3(kNT), 0, stream, dy, x, st, w,
-                          sv, cf, out);
-        hipLaunchKernelGGL(k_bnb_chan_exact, cb, dim3(256), 0, stream, M, (int)st.gx, (int)st.CS, w, sv, cf, out);
-    } else {
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, k_bnb_stats<2>, sg, dim3(kNT), 0, stream, dy, x, st,
-                          w, sv, cf, out);
-        hipLaunchKernelGGL(k_bnb_stats2, sg, dim3(kNT), 0, stream, dy, x, st, w, sv, cf, out);
-        hipLaunchKernelGGL(k_bnb_lut, cb, dim3(256), 0, stream, M, (int)sg.y, w, sv, cf, out);
-    }
-    // the output pass needs no partials: its grid holds more rows per lane
-    const Stream sa = make_stream(M, C, cs, 4, 8, kMaxBlocks);
-    ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_APPLY, stream, k_bnb_apply, stream_grid(sa), dim3(kNT), 0, stream, dy, x,
-                      dx_out, sa, w, sv, cf, out, exact_e2);
+    auto run = [&](auto gl) {
+        constexpr int G = decltype(gl)::value;
+        const FStat st = make_bstat<G, kBndU>(M, C);
+        const dim3 sg((unsigned)st.gx, (unsigned)st.nsl), cg((unsigned)C);
+        if (exact_e2) {
+            ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 0>), sg, dim3(kNT), 0, stream, dy, x,
+                              st, w, sv, cf, out);
+            hipLaunchKernelGGL(k_bnb_chan<false>, cg, dim3(kChanNT), 0, stream, st, 4 * G, w, sv, cf, out);
+        } else {
+            ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 1>), sg, dim3(kNT), 0, stream, dy, x,
+                              st, w, sv, cf, out);
+            hipLaunchKernelGGL((k_bnb_stats<G, 2>), sg, dim3(kNT), 0, stream, dy, x, st, w, sv, cf, out);
+            hipLaunchKernelGGL(k_bnb_chan<true>, cg, dim3(kChanNT), 0, stream, st, 4 * G, w, sv, cf, out);
+        }
+        const FStat sa = make_bstat<G, kBndU>(M, C);
+        ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_APPLY, stream, k_bnb_apply<G>, dim3((unsigned)sa.gx, (unsigned)sa.nsl),
+                          dim3(kNT), 0, stream, dy, x, dx_out, sa, w, sv, cf, out);
+    };
+    if (C <= 16) run(std::integral_constant<int, 4>());
+    else if (C <= 32) run(std::integral_constant<int, 8>());
+    else run(std::integral_constant<int, 16>());
     return launch_ok();
 }
 

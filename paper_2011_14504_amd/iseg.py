@@ -598,8 +598,7 @@ def _maybe_arm(kid, key):
 class Workspace:
     """A growable device scratch buffer shared by consecutive calls on one
     stream (stream order keeps the uses apart); each stream has its own.
-    `zeroed` buffers start at zero (the BN workspace, whose arrival counters
-    every call leaves at zero)."""
+    `zeroed` buffers start at zero."""
 
     def __init__(self, device="cuda", zeroed=False):
         self.device = device
