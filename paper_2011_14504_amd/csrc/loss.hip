@@ -11,12 +11,12 @@
 // Float64 throughout, so that the integer codes decided at the end agree with
 // a float64 reference except where a value sits within ~1e-14 relative of a
 // rounding boundary.  Deterministic: every sum runs in a fixed order.
-//   k_ce_cells    one wave per bilinear cell (a run of output rows that read
-//                 the same two source rows x a run of columns): softmax of each
+//   k_ce_cells8   one block per bilinear cell (a run of output rows that read
+//   / k_ce_cells  the same two source rows x a run of columns): softmax of each
 //                 pixel with lanes over classes, the gradient folded into the
 //                 cell's four source corners, the cell's loss
-//   k_ce_combine  one block per low-res row: the corner sums of every cell
-//                 touching each low-res element, in cell order -> gradient
+//   k_ce_combine  one thread per low-res element: the corner sums of every cell
+//                 touching it, in a fixed order -> gradient
 //   k_ce_quant    SQ codes and exponent; block 0 also forms the mean loss
 #include <math.h>
 
@@ -91,8 +91,10 @@ struct CeCellArgs {
     int32_t nry, nrx;
     Run ry[kMaxRuns];
     Run rx[kMaxRuns];
-    int16_t ylo[64], yhi[64];  // per low-res row: first and last row run touching it
-    int16_t xlo[64], xhi[64];  // per low-res column: likewise for column runs
+    // per low-res row / column: the (run << 1 | corner) pairs that touch it, in run
+    // order, -1 past the last.  A run's corners are i0 and i1 = min(i0 + 1, n - 1),
+    // and only i0 = 0 has a second (clamped) run, so there are at most four
+    int16_t ey[64][4], ex[64][4];
     double* cell;        // [N][nry][nrx][4][K]: corner sums (i0,j0),(i0,j1),(i1,j0),(i1,j1)
     double* cell_loss;   // [N][nry][nrx]
     double* grad;        // [N][h][w][K]
@@ -205,7 +207,7 @@ __device__ __forceinline__ double swap_max_f64(double v)
     return fmax(v, __longlong_as_double((long long)(((uint64_t)h1 << 32) | l1)));
 }
 
-// group-wide (L = 16: one DPP row, L = 32: two) sum / max of a double, by
+// group-wide (L = 8: half a DPP row, L = 32: two) sum / max of a double, by
 // steps whose partner pairs are symmetric: every lane of the group ends with
 // the same bits
 template <int L>
@@ -214,8 +216,7 @@ __device__ __forceinline__ double group_sum_f64(double v)
     v += dpp_f64<0xB1>(v);
     v += dpp_f64<0x4E>(v);
     v += dpp_f64<0x141>(v);
-    v += dpp_f64<0x140>(v);
-    if constexpr (L == 32) v = swap_sum_f64<16>(v);
+    if constexpr (L == 32) v = swap_sum_f64<16>(v + dpp_f64<0x140>(v));
     return v;
 }
 
@@ -235,7 +236,7 @@ __device__ __forceinline__ double group_max_f64(double v)
 template <int L>
 __device__ __forceinline__ double groups_sum_f64(double v)
 {
-    if constexpr (L == 16) v = swap_sum_f64<16>(v);
+    static_assert(L == 32, "group width");
     return swap_sum_f64<32>(v);
 }
 
@@ -281,11 +282,273 @@ __device__ __forceinline__ void lds_add_f64(double* p, double v)
     (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// exp(x) for |x| below 2^20 (here |x| <= 256 unless the logit exponent is out of
+// range, where nothing is used): x = k ln 2 + r with ln 2 in two parts (Cody and
+// Waite), |r| <= ln 2 / 2, the Taylor polynomial of degree 13 (its remainder is
+// below 5e-18) by Horner's rule, scaled by 2^k.  Straight-line: a fifth of the
+// library call's instructions.
+__device__ __forceinline__ double exp_small(double x)
+{
+    const double k = rint(x * 1.44269504088896340736);
+    double r = fma(k, -0x1.62e42fefap-1, x);             // ln 2 to 36 bits: k times it is exact
+    r = fma(k, -(0.69314718055994530942 - 0x1.62e42fefap-1 + 2.3190468138462996e-17), r);
+    double p = 1.0 / 6227020800.0;
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)k);
+}
+
+// Up to 176 classes: groups of eight lanes, KT classes per lane, so a wave
+// takes eight rows of the cell at once and what a pixel costs besides its
+// four operations per class (the denominator's cross-lane sum, the division,
+// the label) is shared by eight pixels.  Two waves per block, 16 rows per
+// pass; four blocks fit a CU (40 KB of LDS at 150 classes).  One LDS region
+// [row][2][8 KT] serves a pass three times: the rows' starting exps and x-step
+// ratios (one thread per class multiplies them down the rows; zero past the
+// last row and class, so no later step has a condition), then the one-hot sums
+// (added to by the lane that owns a pixel's label, each row its own region),
+// then the rows' two column sums, which one thread per class folds into the
+// cell's four corners in row order.  The loss takes log(s) of a row as the log
+// of the product of the mantissas plus the exponents, and the label logits from
+// eight threads per row.  Bound by instruction issue, float64 at 4.5 clocks per
+// wave: 1.3 G lane operations of the four per class, 41 us of 132 at 8 x 512 x
+// 512 pixels and 150 classes; 313 us for rows of 32-lane groups.
+constexpr int kCell8Waves = 2, kCell8Rows = kCell8Waves * 8;
+
+template <int KT>
+__global__ __launch_bounds__(64 * kCell8Waves, 2) void k_ce_cells8(const CeCellArgs a, int maxlen)
+{
+    constexpr int NT = 64 * kCell8Waves, RW = kCell8Rows, KP = 8 * KT, KR = (KP + NT - 1) / NT;
+    constexpr bool TWO = KT <= 16;                     // two pixels in flight (registers)
+    extern __shared__ __align__(16) char smem[];
+    __shared__ double wl[kCell8Waves], wys[RW];
+    __shared__ int smax[kCell8Waves];
+    const int n = blockIdx.z, sy = blockIdx.y, sx = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lig = lane & 7, row = t >> 3;
+    const int K = a.K, wk = a.w * a.K;
+    const Run ry = a.ry[sy], rx = a.rx[sx];
+    const int j0 = rx.i0, j1 = rx.i1, len = rx.len;
+    double* reg = (double*)smem;                       // [RW][2][KP]
+    double* wxs = reg + RW * 2 * KP;                   // column weight lambda_x per pixel of the run
+    int8_t* C0 = (int8_t*)(wxs + maxlen);              // corner codes [4][KP]
+    uint8_t* labs = (uint8_t*)(C0 + 4 * KP);           // [RW][maxlen]
+    const uint8_t* lab_base = a.labels + ((int64_t)n * a.H + ry.start) * a.W + rx.start;
+    const int8_t* r0 = a.logits + ((int64_t)n * a.h + ry.i0) * wk;
+    const int8_t* r1 = a.logits + ((int64_t)n * a.h + ry.i1) * wk;
+    const int32_t le = *a.logit_exp;
+    // this thread's classes t, t + NT: corner codes to registers and LDS
+    int c4[KR][4], mxc = -128;
+#pragma unroll
+    for (int r = 0; r < KR; r++) {
+        const int k = t + r * NT, kk = k < K ? k : 0;
+        c4[r][0] = r0[j0 * K + kk]; c4[r][1] = r0[j1 * K + kk];
+        c4[r][2] = r1[j0 * K + kk]; c4[r][3] = r1[j1 * K + kk];
+    }
+    for (int c = t; c < len; c += NT) {
+        int e0, e1;
+        bool ecl;
+        double lx;
+        src_coord_hd(rx.start + c, a.w, a.W, e0, e1, lx, ecl);
+        wxs[c] = lx;
+    }
+#pragma unroll
+    for (int r = 0; r < KR; r++) {
+        const int k = t + r * NT;
+        mxc = max(mxc, max(max(c4[r][0], c4[r][1]), max(c4[r][2], c4[r][3])));
+        if (k < KP) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) C0[q * KP + k] = (int8_t)c4[r][q];
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) mxc = max(mxc, __shfl_xor(mxc, o, 64));
+    if (lane == 0) smax[wv] = mxc;
+    __syncthreads();
+    // outside the documented range the outputs are discarded (k_ce_quant)
+    const double scale = logit_exp_ok(le) ? ldexp(1.0, le) : 0.0;
+    const double invP = 1.0 / ((double)a.N * (double)a.H * (double)a.W);
+    int mi = smax[0];
+#pragma unroll
+    for (int v = 1; v < kCell8Waves; v++) mi = max(mi, smax[v]);
+    const double m = (double)mi * scale;               // the cell's max logit
+    // per class: the current row's exp at the first pixel and x-step ratio, and
+    // the factors that take them to the next row
+    double e0r[KR], x0r[KR], ys[KR], xs[KR], g4[KR][4];
+    {
+        int d0, d1;
+        bool dcl;
+        double ly0, ly1;
+        src_coord_hd(ry.start, a.h, a.H, d0, d1, ly0, dcl);
+        src_coord_hd(ry.start + (ry.len > 1 ? 1 : 0), a.h, a.H, d0, d1, ly1, dcl);
+        const double lx0 = wxs[0], lx1 = wxs[len > 1 ? 1 : 0];
+#pragma unroll
+        for (int r = 0; r < KR; r++) {
+            const double c00 = c4[r][0], c01 = c4[r][1], c10 = c4[r][2], c11 = c4[r][3];
+            const double l00 = interp(c00, c01, c10, c11, 1.0 - lx0, lx0, 1.0 - ly0, ly0, scale);
+            const double l10 = interp(c00, c01, c10, c11, 1.0 - lx1, lx1, 1.0 - ly0, ly0, scale);
+            const double l01 = interp(c00, c01, c10, c11, 1.0 - lx0, lx0, 1.0 - ly1, ly1, scale);
+            const double l11 = interp(c00, c01, c10, c11, 1.0 - lx1, lx1, 1.0 - ly1, ly1, scale);
+            e0r[r] = t + r * NT < K ? exp_small(l00 - m) : 0.0;
+            x0r[r] = exp_small(l10 - l00);
+            ys[r] = exp_small(l01 - l00);
+            xs[r] = exp_small((l11 - l01) - (l10 - l00));
+            g4[r][0] = g4[r][1] = g4[r][2] = g4[r][3] = 0.0;
+        }
+    }
+    double lsum = 0.0;
+    bool bad = false;
+    for (int base = 0; base < ry.len; base += RW) {
+        const int rows = min(RW, ry.len - base);
+        if (base) __syncthreads();                     // the last pass's column sums are read
+        const bool live = row < rows;
+        // labels and row weights (eight threads per row), the rows' starting values
+        for (int c = lig; c < len; c += 8)
+            labs[row * maxlen + c] = live ? lab_base[(int64_t)(base + row) * a.W + c] : (uint8_t)0;
+        double ly;
+        {
+            int q0, q1;
+            bool qcl;
+            src_coord_hd(ry.start + base + (live ? row : 0), a.h, a.H, q0, q1, ly, qcl);
+            if (lig == 0) wys[row] = ly;
+        }
+#pragma unroll
+        for (int r = 0; r < KR; r++) {
+            const int k = t + r * NT;
+            if (k < KP) {
+                double* d = reg + k;
+#pragma unroll 4
+                for (int q = 0; q < RW; q++, d += 2 * KP) {
+                    d[0] = q < rows ? e0r[r] : 0.0;
+                    d[KP] = x0r[r];
+                    if (q < rows) { e0r[r] *= ys[r]; x0r[r] *= xs[r]; }
+                }
+            }
+        }
+        __syncthreads();
+        // label logits
+        for (int c = lig; c < len; c += 8) {
+            const int lab = labs[row * maxlen + c], lc = lab < K ? lab : 0;
+            const double lx = wxs[c];
+            const double l = interp((double)C0[lc], (double)C0[KP + lc], (double)C0[2 * KP + lc],
+                                    (double)C0[3 * KP + lc], 1.0 - lx, lx, 1.0 - ly, ly, scale);
+            lsum -= live && lab < K ? l : 0.0;
+            bad |= lab >= K;
+        }
+        double* rg = reg + row * 2 * KP;
+        double E[KT], R[KT], alo[KT], ahi[KT];
+#pragma unroll
+        for (int q = 0; q < KT; q++) {                 // read and cleared by the same lane
+            E[q] = rg[lig + 8 * q];
+            R[q] = rg[KP + lig + 8 * q];
+            rg[lig + 8 * q] = 0.0;
+            rg[KP + lig + 8 * q] = 0.0;
+            alo[q] = ahi[q] = 0.0;
+        }
+        __builtin_amdgcn_wave_barrier();
+        double prod = 1.0;
+        int pexp = 0;
+        const uint8_t* lab_row = labs + row * maxlen;
+        // a row past the last has E = 0: its quotients are not finite and its
+        // sums are not used
+        auto pixel = [&](const double* Ev, double s, double lx, int lab) {
+            const double cp = div_pos(invP, s);
+            const double c1 = lx * cp, c0 = (1.0 - lx) * cp;
+#pragma unroll
+            for (int q = 0; q < KT; q++) {
+                alo[q] = fma(c0, Ev[q], alo[q]);
+                ahi[q] = fma(c1, Ev[q], ahi[q]);
+            }
+            if (lab < K && lig == (lab & 7)) {
+                lds_add_f64(&rg[lab], 1.0 - lx);
+                lds_add_f64(&rg[KP + lab], lx);
+            }
+            // mantissas in [1/2, 1): at most 256 factors stay above 2^-256
+            prod *= __builtin_amdgcn_frexp_mant(s);
+            pexp += __builtin_amdgcn_frexp_exp(s);
+        };
+        int c = 0;
+        if constexpr (TWO) {
+            for (; c + 1 < len; c += 2) {
+                double E1[KT];
+#pragma unroll
+                for (int q = 0; q < KT; q++) E1[q] = E[q] * R[q];
+                const double sa = group_sum_f64<8>(tree_sum<KT>(E)), sb = group_sum_f64<8>(tree_sum<KT>(E1));
+                pixel(E, sa, wxs[c], lab_row[c]);
+                pixel(E1, sb, wxs[c + 1], lab_row[c + 1]);
+#pragma unroll
+                for (int q = 0; q < KT; q++) E[q] = E1[q] * R[q];
+            }
+        }
+        for (; c < len; c++) {
+            const double sa = group_sum_f64<8>(tree_sum<KT>(E));
+            pixel(E, sa, wxs[c], lab_row[c]);
+#pragma unroll
+            for (int q = 0; q < KT; q++) E[q] *= R[q];
+        }
+        const double ls = log(prod) + (double)pexp * 0.69314718055994530942;
+        lsum += live && lig == 0 ? ls : 0.0;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < KT; q++) {
+            double* d = rg + lig + 8 * q;
+            d[0] = alo[q] - d[0] * invP;
+            d[KP] = ahi[q] - d[KP] * invP;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < KR; r++) {
+            const int k = t + r * NT;
+            if (k < K) {
+                const double* d = reg + k;
+#pragma unroll 4
+                for (int q = 0; q < rows; q++, d += 2 * KP) {
+                    const double wy = wys[q], glo = d[0], ghi = d[KP];
+                    g4[r][0] = fma(1.0 - wy, glo, g4[r][0]);
+                    g4[r][1] = fma(1.0 - wy, ghi, g4[r][1]);
+                    g4[r][2] = fma(wy, glo, g4[r][2]);
+                    g4[r][3] = fma(wy, ghi, g4[r][3]);
+                }
+            }
+        }
+    }
+    const int64_t cid = ((int64_t)n * a.nry + sy) * a.nrx + sx;
+    double* out = a.cell + cid * 4 * K;
+#pragma unroll
+    for (int r = 0; r < KR; r++) {
+        const int k = t + r * NT;
+        if (k < K) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) out[q * K + k] = g4[r][q];
+        }
+    }
+    lsum = wave_sum_f64(lsum);
+    if (lane == 0) wl[wv] = lsum;
+    if (__any(bad) && lane == 0) set_status(a.status, ISEG_DEV_RANGE);
+    __syncthreads();
+    if (t == 0) {
+        double ls = wl[0];
+#pragma unroll
+        for (int v = 1; v < kCell8Waves; v++) ls += wl[v];
+        a.cell_loss[cid] = ls + m * ((double)ry.len * (double)len);
+    }
+}
+
+// More classes: groups of 32 lanes.
 template <int L, int KT>
 __global__ __launch_bounds__(256, 3) void k_ce_cells(const CeCellArgs a)
 {
     constexpr int P = 64 / L;
-    static_assert(L == 16 || L == 32, "group width");
+    static_assert(L == 32, "group width");
     extern __shared__ __align__(16) char smem[];
     __shared__ double wxs[kMaxRunLen];                     // column weight lambda_x per pixel of the run
     __shared__ double wl[kCellWaves];
@@ -498,9 +761,11 @@ __global__ __launch_bounds__(256, 3) void k_ce_cells(const CeCellArgs a)
         a.cell_loss[cid] = (((wl[0] + wl[1]) + wl[2]) + wl[3]) + m * ((double)ry.len * (double)len);
 }
 
-// grad[n,i,j,k]: sum over the cells with a corner at (i, j), in cell order
-// (row runs, then column runs, then corners); one thread per element, a block
-// per 256 elements of one low-res row, the runs touching i and j from tables
+// grad[n,i,j,k]: sum over the cells with a corner at (i, j), in the order of
+// the row entries, then of the column entries; one thread per element, a block
+// per 256 elements of one low-res row.  The loads of the (usually 2 x 2) first
+// entries go out together (behind the branch of each cell they took a round
+// trip each: 20.6 -> 12.2 us at 8 x 32 x 32 x 150).
 __global__ __launch_bounds__(256) void k_ce_combine(const CeCellArgs a)
 {
     const int n = blockIdx.z, i = blockIdx.y;
@@ -509,17 +774,30 @@ __global__ __launch_bounds__(256) void k_ce_combine(const CeCellArgs a)
     uint64_t mx = 0;
     if (e < wk) {
         const int j = e / a.K, k = e - j * a.K;
+        const double* cell = a.cell + (int64_t)n * a.nry * a.nrx * 4 * a.K + k;
+        auto at = [&](int y, int x) {
+            const int64_t cid = (int64_t)(y >> 1) * a.nrx + (x >> 1);
+            return cell[(cid * 4 + 2 * (y & 1) + (x & 1)) * a.K];
+        };
+        int ey[4], ex[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) { ey[q] = a.ey[i][q]; ex[q] = a.ex[j][q]; }
+        // every low-res index is touched by at least one run
+        const int y1 = ey[1] >= 0 ? ey[1] : ey[0], x1 = ex[1] >= 0 ? ex[1] : ex[0];
+        const double v00 = at(ey[0], ex[0]), v01 = at(ey[0], x1), v10 = at(y1, ex[0]), v11 = at(y1, x1);
         double acc = 0.0;
-        for (int s = a.ylo[i]; s <= a.yhi[i]; s++) {
-            const Run ry = a.ry[s];
-            for (int g = a.xlo[j]; g <= a.xhi[j]; g++) {
-                const Run rx = a.rx[g];
-                const double* c = a.cell + (((int64_t)n * a.nry + s) * a.nrx + g) * 4 * a.K + k;
-                if (ry.i0 == i && rx.i0 == j) acc += c[0];
-                if (ry.i0 == i && rx.i1 == j) acc += c[a.K];
-                if (ry.i1 == i && rx.i0 == j) acc += c[2 * a.K];
-                if (ry.i1 == i && rx.i1 == j) acc += c[3 * a.K];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            if (ey[q] < 0) break;
+            if (q < 2) {
+                acc += q ? v10 : v00;
+                if (ex[1] >= 0) acc += q ? v11 : v01;
+            } else {
+                acc += at(ey[q], ex[0]);
+                if (ex[1] >= 0) acc += at(ey[q], ex[1]);
             }
+            if (ex[2] >= 0) acc += at(ey[q], ex[2]);
+            if (ex[3] >= 0) acc += at(ey[q], ex[3]);
         }
         a.grad[((int64_t)n * a.h + i) * wk + e] = acc;
         mx = (uint64_t)__double_as_longlong(acc) & 0x7fffffffffffffffull;
@@ -563,7 +841,17 @@ __global__ __launch_bounds__(256) void k_ce_quant(const CeCellArgs a, int64_t np
         __shared__ double red[256];
         double s = 0.0;
         const int64_t cells = (int64_t)a.N * a.nry * a.nrx;
-        for (int64_t r = threadIdx.x; r < cells; r += blockDim.x) s += a.cell_loss[r];
+        // eight loads in flight (one at a time they set the kernel's time: 17.8 -> 10.3 us)
+        for (int64_t r = threadIdx.x; r < cells; r += 8 * (int64_t)blockDim.x) {
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                const int64_t x = r + q * (int64_t)blockDim.x;
+                v[q] = a.cell_loss[x < cells ? x : r];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; q++) s += r + q * (int64_t)blockDim.x < cells ? v[q] : 0.0;
+        }
         red[threadIdx.x] = s;
         __syncthreads();
         for (int o = 128; o > 0; o >>= 1) {
@@ -594,18 +882,36 @@ int launch_cells(const CeCellArgs& a, hipStream_t s)
     return launch_ok();
 }
 
-// first and last run touching each low-res index (an empty range: lo > hi)
-void run_ranges(const Run* runs, int nr, int n_low, int16_t* lo, int16_t* hi)
+template <int KT>
+int launch_cells8(const CeCellArgs& a, hipStream_t s)
+{
+    int maxlen = 1;
+    for (int i = 0; i < a.nrx; i++) maxlen = a.rx[i].len > maxlen ? a.rx[i].len : maxlen;
+    maxlen = (maxlen + 3) & ~3;
+    const size_t lds = (size_t)kCell8Rows * 2 * 8 * KT * 8 + (size_t)maxlen * 8 + (size_t)4 * 8 * KT +
+                       (size_t)kCell8Rows * maxlen;
+    if (!lds_limit((const void*)k_ce_cells8<KT>, lds)) return ISEG_ERR_DEVICE;
+    hipLaunchKernelGGL(k_ce_cells8<KT>, dim3((unsigned)a.nrx, (unsigned)a.nry, (unsigned)a.N),
+                       dim3(64 * kCell8Waves), lds, s, a, maxlen);
+    return launch_ok();
+}
+
+// the (run << 1 | corner) entries touching each low-res index, in run order;
+// false if an index has more than four (it cannot) or none
+bool run_entries(const Run* runs, int nr, int n_low, int16_t (*ent)[4])
 {
     for (int i = 0; i < n_low; i++) {
-        lo[i] = (int16_t)nr;
-        hi[i] = -1;
+        int n = 0;
+        for (int q = 0; q < 4; q++) ent[i][q] = -1;
         for (int s = 0; s < nr; s++)
-            if (runs[s].i0 == i || runs[s].i1 == i) {
-                if (s < lo[i]) lo[i] = (int16_t)s;
-                hi[i] = (int16_t)s;
-            }
+            for (int c = 0; c < 2; c++)
+                if ((c ? runs[s].i1 : runs[s].i0) == i) {
+                    if (n == 4) return false;
+                    ent[i][n++] = (int16_t)(s << 1 | c);
+                }
+        if (!n) return false;
     }
+    return true;
 }
 
 // max |grad| partials: one per combine block
@@ -649,8 +955,8 @@ extern "C" int iseg_softmax_ce(const int8_t* logits, const int32_t* logit_exp, c
     a.nrx = make_runs((int)w, (int)W, a.rx);
     for (int i = 0; i < a.nrx; i++)
         if (a.rx[i].len > kMaxRunLen) return ISEG_ERR_UNSUPPORTED;
-    run_ranges(a.ry, a.nry, (int)h, a.ylo, a.yhi);
-    run_ranges(a.rx, a.nrx, (int)w, a.xlo, a.xhi);
+    if (!run_entries(a.ry, a.nry, (int)h, a.ey) || !run_entries(a.rx, a.nrx, (int)w, a.ex))
+        return ISEG_ERR_UNSUPPORTED;
     a.status = dev_status;
     char* p = (char*)ws;
     p += 256;
@@ -663,16 +969,18 @@ extern "C" int iseg_softmax_ce(const int8_t* logits, const int32_t* logit_exp, c
     a.part = (uint64_t*)p;
     a.grad = grad ? grad : gws;
     int rc;
-    // groups of 16 lanes up to 128 classes (KT rounded up to an instantiated
-    // width), else 32: more classes per lane cost occupancy
-    const int kt16 = (int)((K + 15) / 16), kt32 = (int)((K + 31) / 32);
-    rc = kt16 <= 1   ? launch_cells<16, 1>(a, stream)
-       : kt16 <= 2   ? launch_cells<16, 2>(a, stream)
-       : kt16 <= 4   ? launch_cells<16, 4>(a, stream)
-       : kt16 <= 6   ? launch_cells<16, 6>(a, stream)
-       : kt16 <= 8   ? launch_cells<16, 8>(a, stream)
-       : kt32 <= 5   ? launch_cells<32, 5>(a, stream)
-       : kt32 <= 6   ? launch_cells<32, 6>(a, stream)
+    // groups of 8 lanes up to 176 classes (KT rounded up to an instantiated
+    // width), else 32: 23 and more classes per lane no longer fit the registers
+    // of two waves per SIMD
+    const int kt8 = (int)((K + 7) / 8);
+    rc = kt8 <= 3    ? launch_cells8<3>(a, stream)
+       : kt8 <= 6    ? launch_cells8<6>(a, stream)
+       : kt8 <= 8    ? launch_cells8<8>(a, stream)
+       : kt8 <= 12   ? launch_cells8<12>(a, stream)
+       : kt8 <= 16   ? launch_cells8<16>(a, stream)
+       : kt8 <= 19   ? launch_cells8<19>(a, stream)
+       : kt8 <= 22   ? launch_cells8<22>(a, stream)
+       : K <= 192    ? launch_cells<32, 6>(a, stream)
                      : launch_cells<32, 8>(a, stream);
     if (rc) return rc;
     const unsigned cx = (unsigned)ceil_div64(w * K, 256);
