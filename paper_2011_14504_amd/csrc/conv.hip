@@ -3403,10 +3403,274 @@ __global__ __launch_bounds__(64 * RS) void k_conv_wgrad_taps(WgradArgs a, int32_
         }
 }
 
+// Backward-weight of a 3x3 stride-1 conv whose output has the input's size
+// (padding = dilation), C % 64 == 0, K % 64 == 0.  The all-taps kernel above
+// loads each x tile nine times and is bound by those loads (64 pixels x 64
+// channels of dy and nine of x for 2.4 M multiply-adds: 40 KB a step); here the
+// output pixels are enumerated over rows extended by `dil` zero columns
+// (E = W + dil, the padding between one row's end and the next row's start), so
+// the three taps of a filter row read one x row buffer at offsets -dil, 0, dil,
+// and dy is shared by all nine.  Per step of 64 extended pixels a block loads 64
+// x rows for each of the three filter rows (12 KB) and KB output channels of dy
+// (8 KB) for 4.7 M multiply-adds at KB = 128.  The x rows sit in rings of eight
+// 64-row chunks (a step reads its own and both neighbours, so dil <= 64), dy in
+// a ring of six tiles, both filled by direct-to-LDS loads four steps ahead; two
+// steps share a barrier, so the waves of a SIMD drift apart and one's reads run
+// under another's products.
+// Twelve waves, three per SIMD: wave = (filter row, quarter); a wave holds 64
+// output channels x 32 input channels x 3 taps (96 accumulators,
+// v_mfma_i32_32x32x32_i8: ten transposing reads per six).  KB = 64 (K not a
+// multiple of 128): the quarter's other bit takes one 32-pixel half of each
+// step and the halves are added in LDS at the end.  Rows are 64 bytes (dy at KB
+// = 128: 128) with swizzled 16-byte parts, so a transposing read touches every
+// bank about twice.  2048 -> 256 channels, 8 x 32 x 32, dil 12: 149 -> 53 us
+// (1.46 POP/s over all taps); 128 -> 128, 8 x 64 x 64: 25.8 -> 17.9 us.
+constexpr int kWrNX = 8, kWrND = 6;                 // x chunks, dy tiles
+constexpr int kWrXB = 64 * 64, kWrXR = kWrNX * kWrXB;
+
+template <int KB>
+constexpr size_t wgrad_rows_lds() { return (size_t)3 * kWrXR + (size_t)kWrND * 64 * KB; }
+
+// 16-byte part swizzle of a dy row of 128 bytes
+__device__ __forceinline__ int wr_dsw(int row) { return ((row >> 1) & 3) << 1; }
+
+template <int KB>
+__global__ __launch_bounds__(768) void k_conv_wgrad_rows(WgradArgs a, int32_t* __restrict__ part_out)
+{
+    typedef int v16i __attribute__((ext_vector_type(16)));
+    constexpr int DB = 64 * KB;                          // dy tile bytes
+    constexpr int MASK = kWrXR - 1;
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = wv >> 2, q4 = wv & 3, ch = q4 & 1, kh = q4 >> 1;   // kh: K half (KB 128) or pixel half (KB 64)
+    const int nch = a.C / 64;
+    const int c0 = (blockIdx.x % nch) * 64, k0 = (blockIdx.x / nch) * KB;
+    const int32_t E = a.W + a.dw, EH = E * a.H, N = (int32_t)(a.NPQ / ((int64_t)a.H * a.W));
+    const int32_t total = N * EH;                        // < 2^31 (wgrad_rows_ok)
+    const int32_t ebeg = (int32_t)(blockIdx.y * a.pix_per_split);
+    const int32_t eend = (int32_t)(ebeg + a.pix_per_split < total ? ebeg + a.pix_per_split : total);
+    const int nsteps = (eend - ebeg + 63) / 64;
+    uint64_t zbits = (uint64_t)(uintptr_t)g_conv_zero;
+    asm volatile("" : "+s"(zbits));
+    const int8_t* zp = (const int8_t*)(uintptr_t)zbits;
+
+    // x cursor: this lane's row of the chunk being issued (the first chunk lies
+    // before the split's start), its image row and extended column, and the byte
+    // offset of the tap row's pixel (wrapping: only used where it is valid)
+    const int rin = 16 * q4 + (lane >> 2), dr = (r - 1) * a.dh;
+    int32_t xe = ebeg - 64 + rin, xcol, xp;
+    uint32_t xoff;
+    {
+        const int32_t em = xe < 0 ? xe + (64 / EH + 1) * EH : xe, row = em / E;
+        xcol = em - row * E;
+        xp = row % a.H;
+        const int32_t grow = xe < 0 ? row - (64 / EH + 1) * a.H : row;
+        xoff = ((uint32_t)(grow + dr) * (uint32_t)a.W + (uint32_t)xcol) * (uint32_t)a.C +
+               (uint32_t)(c0 + (((lane & 3) ^ wg_sw(rin)) << 4));
+    }
+    const uint32_t xstep = 64u * (uint32_t)a.C, xwrap = (uint32_t)a.dw * (uint32_t)a.C;
+    int8_t* const xdst = smem + r * kWrXR + q4 * 1024;
+    int xslot = 0;
+    auto issue_x = [&]() {
+        const bool v = xe >= 0 && xe < total && xcol < a.W && (uint32_t)(xp + dr) < (uint32_t)a.H;
+        dma16(v ? a.x + xoff : zp, xdst + xslot);
+        xslot = (xslot + kWrXB) & MASK;
+        xe += 64;
+        xcol += 64;
+        xoff += xstep;
+        while (xcol >= E) {
+            xcol -= E;
+            xoff -= xwrap;
+            xp = xp + 1 == a.H ? 0 : xp + 1;
+        }
+    };
+    // dy cursor: KB 128: waves 0..7, eight rows of 128 bytes each; KB 64: waves
+    // 0..3, sixteen rows of 64 bytes
+    constexpr int DW = KB == 128 ? 8 : 4;
+    const bool dyw = wv < DW;
+    const int drow = KB == 128 ? 8 * (wv & 7) + (lane >> 3) : 16 * (wv & 3) + (lane >> 2);
+    const int dpart = KB == 128 ? (lane & 7) ^ wr_dsw(drow) : (lane & 3) ^ wg_sw(drow);
+    int32_t de = ebeg + drow, dcol = de % E;
+    uint32_t doff = ((uint32_t)(de / E) * (uint32_t)a.W + (uint32_t)dcol) * (uint32_t)a.K +
+                    (uint32_t)(k0 + dpart * 16);
+    const uint32_t dstep = 64u * (uint32_t)a.K, dwrap = (uint32_t)a.dw * (uint32_t)a.K;
+    int8_t* const ddst = smem + 3 * kWrXR + (wv & (DW - 1)) * 1024;
+    int dslot = 0;
+    auto issue_d = [&]() {
+        if (!dyw) return;
+        dma16(de < eend && dcol < a.W ? a.dy + doff : zp, ddst + dslot);
+        dslot = dslot + DB == kWrND * DB ? 0 : dslot + DB;
+        de += 64;
+        dcol += 64;
+        doff += dstep;
+        while (dcol >= E) { dcol -= E; doff -= dwrap; }
+    };
+
+    // read addresses: a 16-lane group g reads pixels 16 (g >> 1) + 0..15 of a
+    // 32-pixel half (two transposing reads of eight) of channels 16 (g & 1) + 0..15
+    const int g = lane >> 4, i8 = (lane & 15) >> 1, h8 = (lane & 1) * 8;
+    const uint32_t lds0 = lds_off(smem);
+    uint32_t xc[3][2][2], dc[2];                         // [tap][pixel half][rows 0-7 / 8-15], [channel block]
+#pragma unroll
+    for (int s = 0; s < 3; s++)
+#pragma unroll
+        for (int kk = 0; kk < 2; kk++)
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                const int row = 64 + 32 * kk + (s - 1) * a.dw + 16 * (g >> 1) + i8 + 8 * b;
+                xc[s][kk][b] = (uint32_t)(row * 64 + (((2 * ch + (g & 1)) ^ wg_sw(row & 63)) << 4) + h8);
+            }
+    const uint32_t xbase = lds0 + (uint32_t)(r * kWrXR);
+#pragma unroll
+    for (int f = 0; f < 2; f++) {
+        const int row = 16 * (g >> 1) + i8;
+        if constexpr (KB == 128)
+            dc[f] = lds0 + 3 * kWrXR +
+                    (uint32_t)(row * 128 + (((4 * kh + 2 * f + (g & 1)) ^ wr_dsw(row)) << 4) + h8);
+        else
+            dc[f] = (uint32_t)(2 * f + (g & 1));         // part; the row's swizzle is added per read
+    }
+
+    v16i acc[2][3];
+#pragma unroll
+    for (int f = 0; f < 2; f++)
+#pragma unroll
+        for (int s = 0; s < 3; s++) acc[f][s] = (v16i){};
+
+    auto half = [&](int st, int dt, int kk, int kc) {    // kc: kk as a constant where the registers need one
+        uint32_t xa[6], da[4];
+#pragma unroll
+        for (int s = 0; s < 3; s++)
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                const uint32_t c = kc ? xc[s][1][b] : xc[s][0][b];
+                xa[2 * s + b] = xbase + ((c + (uint32_t)st * kWrXB) & (uint32_t)MASK);
+            }
+        const uint32_t dst = (uint32_t)dt * DB;
+#pragma unroll
+        for (int f = 0; f < 2; f++)
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                if constexpr (KB == 128) {
+                    da[2 * f + b] = dc[f] + dst + (uint32_t)(kk * 32 * 128 + b * 8 * 128);
+                } else {
+                    const int row = 32 * kk + 16 * (g >> 1) + i8 + 8 * b;
+                    da[2 * f + b] = lds0 + 3 * kWrXR + dst + (uint32_t)(row * 64 + ((dc[f] ^ wg_sw(row)) << 4) + h8);
+                }
+            }
+        // two blocks of reads: the second one's latency hides behind the first tap's products
+        v2i_t v0, v1, v2, v3, v4, v5;
+        asm volatile("ds_read_b64_tr_b8 %0, %6\n\t"
+                     "ds_read_b64_tr_b8 %1, %7\n\t"
+                     "ds_read_b64_tr_b8 %2, %8\n\t"
+                     "ds_read_b64_tr_b8 %3, %9\n\t"
+                     "ds_read_b64_tr_b8 %4, %10\n\t"
+                     "ds_read_b64_tr_b8 %5, %11\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3), "=&v"(v4), "=&v"(v5)
+                     : "v"(da[0]), "v"(da[1]), "v"(da[2]), "v"(da[3]), "v"(xa[0]), "v"(xa[1])
+                     : "memory");
+        const v4i fa[2] = {(v4i){v0.x, v0.y, v1.x, v1.y}, (v4i){v2.x, v2.y, v3.x, v3.y}};
+        const v4i fb0 = (v4i){v4.x, v4.y, v5.x, v5.y};
+#pragma unroll
+        for (int f = 0; f < 2; f++)
+            acc[f][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[f], fb0, acc[f][0], 0, 0, 0);
+        v2i_t w0, w1, w2, w3;
+        asm volatile("ds_read_b64_tr_b8 %0, %4\n\t"
+                     "ds_read_b64_tr_b8 %1, %5\n\t"
+                     "ds_read_b64_tr_b8 %2, %6\n\t"
+                     "ds_read_b64_tr_b8 %3, %7\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(w0), "=&v"(w1), "=&v"(w2), "=&v"(w3)
+                     : "v"(xa[2]), "v"(xa[3]), "v"(xa[4]), "v"(xa[5])
+                     : "memory");
+        const v4i fb[2] = {(v4i){w0.x, w0.y, w1.x, w1.y}, (v4i){w2.x, w2.y, w3.x, w3.y}};
+#pragma unroll
+        for (int s = 0; s < 2; s++)
+#pragma unroll
+            for (int f = 0; f < 2; f++)
+                acc[f][1 + s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[f], fb[s], acc[f][1 + s], 0, 0, 0);
+    };
+
+    issue_x();                                           // chunks -1 and 0
+    issue_x();
+    // steps go in pairs: one wait and one barrier per 128 extended pixels
+    const int npairs = (nsteps + 1) / 2;
+    auto issue = [&]() { issue_x(); issue_d(); issue_x(); issue_d(); };
+    issue();
+    if (npairs > 1) issue();
+    int dtile = 0;
+    for (int pr = 0; pr < npairs; pr++) {
+        // this wave's loads of the pair have landed (the next pair's may be in
+        // flight) and its reads of the last pair are done; after the barrier
+        // every wave's are, so the oldest x chunks and dy tiles are free
+        if (pr + 1 >= npairs) wait_vm_lgkm0<0>();
+        else if (dyw) wait_vm_lgkm0<4>();
+        else wait_vm_lgkm0<2>();
+        __builtin_amdgcn_s_barrier();
+        if (pr + 2 < npairs) issue();
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            if constexpr (KB == 128) {
+                half(2 * pr + u, dtile, 0, 0);
+                half(2 * pr + u, dtile, 1, 1);
+            } else {
+                half(2 * pr + u, dtile, kh, kh);
+            }
+            dtile = dtile + 1 == kWrND ? 0 : dtile + 1;
+        }
+    }
+    wait_vm<0>();                                        // no load into LDS outlives the block
+
+    int32_t* outp = part_out + (int64_t)blockIdx.y * a.K * a.RSC;
+    const int kb = k0 + (KB == 128 ? 64 * kh : 0);
+    auto store = [&](int f) {
+#pragma unroll
+        for (int s = 0; s < 3; s++) {
+            const int64_t col = (int64_t)(3 * r + s) * a.C + c0 + 32 * ch + (lane & 31);
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const int k = kb + 32 * f + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                outp[(int64_t)k * a.RSC + col] = acc[f][s][e];
+            }
+        }
+    };
+    if constexpr (KB == 128) {
+        store(0);
+        store(1);
+    } else {
+        // add the second pixel half's sums, one channel block at a time
+        int32_t* red = (int32_t*)smem + (r * 2 + ch) * 48 * 64 + lane;
+#pragma unroll
+        for (int f = 0; f < 2; f++) {
+            __syncthreads();
+            if (kh) {
+#pragma unroll
+                for (int s = 0; s < 3; s++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++) red[(s * 16 + e) * 64] = acc[f][s][e];
+            }
+            __syncthreads();
+            if (!kh) {
+#pragma unroll
+                for (int s = 0; s < 3; s++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++) acc[f][s][e] += red[(s * 16 + e) * 64];
+                store(f);
+            }
+        }
+    }
+}
+
 // Sum the per-split int32 partials in int64 (and take their max |.| for the
 // quantizer).  A block owns 256 consecutive elements (one int4 per lane); its
-// 8 waves take every 8th split, four loads in flight each, then fold in LDS.
-constexpr int kRedWaves = 8;
+// 16 waves take every 16th split, eight loads in flight each, then fold in
+// LDS.  One launch also where the weight tensor gives few blocks (64 x 64: 16
+// blocks over 196 splits): a second level over chunks of the splits cost a
+// launch of 4-5 us and saved less (128 x 128 x 9 over 52 splits: 11.8 us for the
+// two, 8.0 here).
+constexpr int kRedWaves = 16, kRedU = 8;
 __global__ __launch_bounds__(64 * kRedWaves) void k_wgrad_reduce(const int32_t* __restrict__ part, int64_t n,
                                                                  int splits, long long* __restrict__ out,
                                                                  uint64_t* pmax)
@@ -3414,20 +3678,18 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_wgrad_reduce(const int32_t* 
     __shared__ long long red[kRedWaves][256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t e0 = (int64_t)blockIdx.x * 256 + lane * 4;
+    const int64_t el = e0 < n ? e0 : 0;   // n % 4 == 0: K is a multiple of 64
     long long s[4] = {0, 0, 0, 0};
-    if (e0 < n) {                         // n % 4 == 0: K is a multiple of 64
-        int k = wave;
-        for (; k + 3 * kRedWaves < splits; k += 4 * kRedWaves) {
-            int4 v[4];
+    for (int k = wave; k < splits; k += kRedU * kRedWaves) {
+        int4 v[kRedU];
 #pragma unroll
-            for (int u = 0; u < 4; u++) v[u] = *(const int4*)(part + (int64_t)(k + u * kRedWaves) * n + e0);
+        for (int u = 0; u < kRedU; u++) {
+            const int q = k + u * kRedWaves;
+            v[u] = *(const int4*)(part + (int64_t)(q < splits ? q : k) * n + el);
+        }
 #pragma unroll
-            for (int u = 0; u < 4; u++) { s[0] += v[u].x; s[1] += v[u].y; s[2] += v[u].z; s[3] += v[u].w; }
-        }
-        for (; k < splits; k += kRedWaves) {
-            int4 v = *(const int4*)(part + (int64_t)k * n + e0);
-            s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
-        }
+        for (int u = 0; u < kRedU; u++)
+            if (k + u * kRedWaves < splits) { s[0] += v[u].x; s[1] += v[u].y; s[2] += v[u].z; s[3] += v[u].w; }
     }
 #pragma unroll
     for (int u = 0; u < 4; u++) red[wave][lane * 4 + u] = s[u];
@@ -3708,12 +3970,43 @@ int64_t wgrad_taps_splits(int64_t NPQ, int64_t K, int64_t C, int64_t* pps_out)
     return ceil_div64(NPQ, pps);
 }
 
+// the row kernel: 3x3, stride 1, padding = dilation <= 64 (the output has the
+// input's size); splits are ranges of extended pixels
+bool wgrad_rows_shape(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_t R, int64_t S, int sh, int sw,
+                      int ph, int pw, int dh, int dw)
+{
+    return N > 0 && R == 3 && S == 3 && sh == 1 && sw == 1 && ph == dh && pw == dw && dw <= 64 && C % 64 == 0 &&
+           K % 64 == 0 && N * H * (W + dw) < ((int64_t)1 << 31) - 4096;
+}
+
+// Splits of the row kernel.  A block costs about 10 us (launch, first loads, the
+// 295 KB of partial sums it writes) and 0.8 us per 64 pixels.  So the whole chip
+// where every split keeps 32 steps (2048 -> 256 channels on 8 x 32 x 32: 4 splits of
+// 44 steps, 53 + 29 us with the reduction, against 83 + 22 with 2); else half the
+// chip in splits of at least 4 steps (128 -> 128 on 8 x 64 x 64: 52 splits 17.9 +
+// 11 us, 87 splits 17.1 + 14).
+int64_t wgrad_rows_splits(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int dw, int64_t* pps_out)
+{
+    const int64_t total = N * H * (W + dw), tiles = (C / 64) * (K % 128 ? K / 64 : K / 128);
+    const int64_t steps = ceil_div64(total, 64);
+    int64_t splits = std::min(ceil_div64(256, tiles), steps / 32);
+    if (splits * tiles < 128) splits = std::min(ceil_div64(128, tiles), ceil_div64(steps, 4));
+    const int64_t min_splits = ceil_div64(total, kWgradSplit / 128 * 128);
+    if (splits < min_splits) splits = min_splits;
+    if (splits > 65535) splits = 65535;
+    int64_t pps = ceil_div64(ceil_div64(total, splits), 128) * 128;
+    if (pps > kWgradSplit / 128 * 128) pps = kWgradSplit / 128 * 128;
+    *pps_out = pps;
+    return ceil_div64(total, pps);
+}
+
 // chunks of the splits reduced by separate blocks: enough blocks for the chip
 // when the weight tensor alone gives too few, each chunk still >= 8 splits
 int wgrad_reduce_chunks(int64_t n, int64_t splits)
 {
+    // few splits per wave of the one-level kernel, or blocks enough
     const int64_t bx = ceil_div64(n, 1024);
-    if (bx >= 512 || splits < 16) return 1;
+    if (bx >= 128 || splits < 512) return 1;
     int64_t c = ceil_div64(1024, bx);
     const int64_t cmax = splits / 8;
     c = c < cmax ? c : cmax;
@@ -3799,6 +4092,30 @@ int launch_wgrad_taps(WgradArgs a, int32_t* part, uint64_t* pmax, int64_t* npmax
     dim3 grid((unsigned)((a.C / 64) * (a.K / 64)), (unsigned)splits);
     ISEG_TIMED_LAUNCH(ISEG_KID_CONV_WGRAD, s, k_conv_wgrad_taps<9>, grid, dim3(64 * 9), lds, s, a, part);
     int rc = launch_ok();
+    if (rc) return rc;
+    return launch_wgrad_reduce_qg(part, (int64_t)a.K * a.RSC, splits, (long long*)a.acc, pmax, npmax, s, qg);
+}
+
+size_t wgrad_rows_part_bytes(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int dw)
+{
+    int64_t pps;
+    const int64_t splits = wgrad_rows_splits(N, H, W, C, K, dw, &pps), n = K * 9 * C;
+    const int nch = wgrad_reduce_chunks(n, splits);
+    return align256((size_t)(splits * n) * 4) + (nch > 1 ? align256((size_t)(nch * n) * 8) : 0);
+}
+
+int launch_wgrad_rows(WgradArgs a, int64_t N, int32_t* part, uint64_t* pmax, int64_t* npmax, hipStream_t s, int* qg)
+{
+    const int64_t splits = wgrad_rows_splits(N, a.H, a.W, a.C, a.K, a.dw, &a.pix_per_split);
+    auto go = [&](auto kb) -> int {
+        constexpr int KB = decltype(kb)::value;
+        const size_t lds = wgrad_rows_lds<KB>();
+        if (!lds_limit((const void*)k_conv_wgrad_rows<KB>, lds)) return ISEG_ERR_DEVICE;
+        dim3 grid((unsigned)((a.C / 64) * (a.K / KB)), (unsigned)splits);
+        ISEG_TIMED_LAUNCH(ISEG_KID_CONV_WGRAD, s, k_conv_wgrad_rows<KB>, grid, dim3(768), lds, s, a, part);
+        return launch_ok();
+    };
+    const int rc = a.K % 128 == 0 ? go(std::integral_constant<int, 128>()) : go(std::integral_constant<int, 64>());
     if (rc) return rc;
     return launch_wgrad_reduce_qg(part, (int64_t)a.K * a.RSC, splits, (long long*)a.acc, pmax, npmax, s, qg);
 }
@@ -4910,10 +5227,18 @@ extern "C" int iseg_weight_transpose_multi(const iseg_wt_desc* descs, int32_t n_
 
 // workspace: [max word][int64 sums][max partials][padded operands][int32
 // split partials of the taps / split kernels][stem partials]
-static size_t wgrad_part_region(int64_t NPQ, int64_t K, int64_t Cp, int64_t RS)
+static bool wgrad_rows_geom(const iseg_conv_geom* g)
 {
-    const size_t t = wgrad_taps_part_bytes(NPQ, K, Cp, RS), r = wgrad_tr_part_bytes(NPQ, K, Cp, RS);
-    return t > r ? t : r;
+    return wgrad_rows_shape(g->N, g->H, g->W, g->C, g->K, g->R, g->S, g->stride_h, g->stride_w, g->pad_h, g->pad_w,
+                            g->dil_h, g->dil_w);
+}
+
+static size_t wgrad_part_region(const iseg_conv_geom* g, int64_t NPQ, int64_t Cp)
+{
+    const size_t t = wgrad_taps_part_bytes(NPQ, g->K, Cp, g->R * g->S);
+    const size_t r = wgrad_tr_part_bytes(NPQ, g->K, Cp, g->R * g->S);
+    const size_t w = wgrad_rows_geom(g) ? wgrad_rows_part_bytes(g->N, g->H, g->W, g->C, g->K, g->dil_w) : 0;
+    return std::max(w, std::max(t, r));
 }
 
 extern "C" size_t iseg_conv_bwd_weight_ws(const iseg_conv_geom* g, int32_t g_mode)
@@ -4926,7 +5251,7 @@ extern "C" size_t iseg_conv_bwd_weight_ws(const iseg_conv_geom* g, int32_t g_mod
     size_t s = 256 + align256((size_t)(g->K * g->R * g->S * g->C) * 8) + align256((size_t)wgrad_reduce_npmax(nwp) * 8);
     if (Cp != g->C)
         s += align256((size_t)(g->N * g->H * g->W * Cp)) + align256((size_t)nwp * 8);
-    s += wgrad_part_region(g->N * P * Q, g->K, Cp, g->R * g->S);
+    s += wgrad_part_region(g, g->N * P * Q, Cp);
     if (stem_kind(g->C, (int)g->R, (int)g->S, g->stride_h, g->stride_w, g->dil_h, g->dil_w, g->K)) {
         const int64_t nbx = g->N * ceil_div64(P, 16) * ceil_div64(Q, 32), nw = g->K * g->R * g->S * g->C;
         s += align256((size_t)(nbx * nw) * 4);
@@ -4965,7 +5290,7 @@ extern "C" int iseg_conv_bwd_weight(const int8_t* dy, const int32_t* dy_exp, con
     char* pad_region = wp;
     if (Cp != g->C) wp += align256((size_t)(g->N * g->H * g->W * Cp)) + align256((size_t)nwp * 8);
     int32_t* part = (int32_t*)wp;
-    wp += wgrad_part_region(NPQ, g->K, Cp, g->R * g->S);
+    wp += wgrad_part_region(g, NPQ, Cp);
     int rc;
     int64_t npmax = 0;
     int qg = 0;                   // > 0: Q_G re-sums that many int32 splits (no int64 sums)
@@ -5011,6 +5336,13 @@ extern "C" int iseg_conv_bwd_weight(const int8_t* dy, const int32_t* dy_exp, con
     a.RSC = (int32_t)(g->R * g->S * Cp);
     a.sh = g->stride_h; a.sw = g->stride_w; a.ph = g->pad_h; a.pw = g->pad_w;
     a.dh = g->dil_h; a.dw = g->dil_w;
+    if (Cp == g->C && wgrad_rows_geom(g) && (((uintptr_t)x | (uintptr_t)dy) & 15) == 0 &&
+        g->N * g->H * g->W * Cp < ((int64_t)1 << 31) && NPQ * g->K < ((int64_t)1 << 31)) {
+        conv_plan_set("wgrad_rows");
+        if ((rc = launch_wgrad_rows(a, g->N, part, raw ? nullptr : pmax, &npmax, stream, raw ? nullptr : &qg)))
+            return rc;
+        return finish();
+    }
     if (Cp == g->C && wgrad_taps_shape(NPQ, g->K, Cp, g->R * g->S) && (((uintptr_t)x | (uintptr_t)dy) & 15) == 0 &&
         g->N * g->H * g->W * Cp < ((int64_t)1 << 31) && NPQ * g->K < ((int64_t)1 << 31)) {
         conv_plan_set("wgrad_taps");
