@@ -28,6 +28,7 @@
 //           values rounded into the gather table).  Rounding E2 (k_E2 < 15) adds
 //           a second streaming pass before the per-channel kernel, with E2's
 //           scale from the first pass's block maxima of |gamma delta|.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -670,22 +671,23 @@ __device__ __forceinline__ int32_t fwd_xcode_any(int64_t D, int32_t den, int b, 
 // is at most a few thousand): the arrival, reload and arithmetic of a tail in
 // the statistics pass took longer.  Bound by latency: the loads, two exact
 // divisions and three barriers.
-constexpr int kFinCh = kNT / 256;              // channels per block
-__global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat st, FwdWs w, Saved sv, BnCfg cf,
-                                                  const int8_t* gamma_q, const int8_t* beta_q)
+constexpr int kFinCh = kNT / 256;              // channels at a time
+constexpr int kFinGrp = 16;                    // at most so many groups of them per block
+__global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat st, int grp, FwdWs w, Saved sv,
+                                                  BnCfg cf, const int8_t* gamma_q, const int8_t* beta_q)
 {
-    __shared__ int32_t rsh[kWaves], sNs[kFinCh], sDen[kFinCh];
-    __shared__ uint64_t sBal[kWaves][3], sAy[kFinCh][2];
+    __shared__ int32_t rsh[kWaves], sNs[kFinGrp * kFinCh], sDen[kFinGrp * kFinCh];
+    __shared__ uint64_t sBal[2][kWaves][3], sAy[2][kFinCh][2];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lc = t >> 8;
-    const int c = blockIdx.x * kFinCh + lc;
+    const int cfirst = blockIdx.x * grp * kFinCh;          // the block's channels: grp groups of kFinCh
     const int q = (t & 255) - 128;
-    const bool own = c < st.C;
     // every load of the first round goes out before the first wait (no branch on
     // a loaded value in between)
     const int32_t s_in = *x_exp;
-    const int cs = own ? c : 0, k0 = t < st.C ? t : 0;
-    const int32_t nmu = sv.n_mu[cs], qlo = sv.qmin[cs], qhi = sv.qmax[cs];
-    const int gq = gamma_q[cs], bq = beta_q[cs];
+    const int k0 = t < st.C ? t : 0;
+    const int cs0 = cfirst + lc < st.C ? cfirst + lc : 0;
+    int32_t nmu = sv.n_mu[cs0], qlo = sv.qmin[cs0], qhi = sv.qmax[cs0];
+    int gq = gamma_q[cs0], bq = beta_q[cs0];
     int32_t nm = sv.n_mu[k0], lo = sv.qmin[k0], hi = sv.qmax[k0], sumq = w.sumq[k0];
     unsigned long long acc = w.acc[k0];
     const int e_mu = 2 - cf.k_mu, e_sig = 2 - cf.k_sigma;
@@ -695,7 +697,7 @@ __global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat s
         if (k != t) { nm = sv.n_mu[k]; lo = sv.qmin[k]; hi = sv.qmax[k]; sumq = w.sumq[k]; acc = w.acc[k]; }
         const int32_t ns = bnf_sigma(acc, sumq, st, s_x, nm, e_mu, cf);
         const int32_t den = max(ns + cf.eps_code, 1);
-        if (k / kFinCh == (int)blockIdx.x) { sNs[k % kFinCh] = ns; sDen[k % kFinCh] = den; }
+        if (k >= cfirst && k < cfirst + grp * kFinCh) { sNs[k - cfirst] = ns; sDen[k - cfirst] = den; }
         // xhat is linear in q: its largest magnitude is at qmin or qmax
         const int64_t D0 = bn_D(lo, s_x, nm, e_mu), D1 = bn_D(hi, s_x, nm, e_mu);
         const uint64_t m0 = (uint64_t)(D0 < 0 ? -D0 : D0), m1 = (uint64_t)(D1 < 0 ? -D1 : D1);
@@ -709,75 +711,84 @@ __global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat s
 #pragma unroll
     for (int k = 1; k < kWaves; k++) b = max(b, rsh[k]);
     if (b == kSentinelLo) b = 0;
-    const int32_t den = sDen[lc];
     if (blockIdx.x == 0 && t == 0) *w.b_glob = b;
     const FwdExps e = fwd_exps(s_x, b, cf);
-    const int64_t D = bn_D(q, s_x, nmu, e.e_mu);
-    const int32_t nx = own ? fwd_xcode_any(D, den, b, e) : 0;
-    // y on its grid: one of the two shifts is zero; |y| < 2^62 for gaps up to 48
-    const int gx = e.e_g + e.e_xh - e.e_y, gb = e.e_b - e.e_y;
-    const bool wide = gx > 38 || gb > 48;          // uniform over the grid
-    int64_t Yr = 0;
-    bool pos;
-    i128 Yw = 0;
-    if (wide) {
-        Yw = fwd_y(nx, gq, bq, e);
-        pos = Yw > 0;
-        if (cf.relu && Yw < 0) Yw = 0;
-    } else {
-        Yr = (int64_t)(gq * nx) * ((int64_t)1 << gx) + (int64_t)bq * ((int64_t)1 << gb);
-        pos = Yr > 0;
-        if (cf.relu && Yr < 0) Yr = 0;
-    }
-    const int idx = c * 256 + (t & 255);
-    const int sg = (D > 0) - (D < 0);
-    if (own) {
-        sv.xcode[idx] = (int16_t)nx;
-        sv.flags[idx] = (uint8_t)((pos ? 1 : 0) | ((sg + 1) << 1));
-        sv.btab[c * 256 + (q & 255)] = ((uint32_t)(uint16_t)(int16_t)nx << 16) | ((uint32_t)(sg & 3) << 8) |
-                                       ((uint32_t)(sg != 0) << 10) | (pos ? 1u : 0u);
-    }
-    // thresholds (least code with D >= 0, least with D > 0, code range with y >
-    // 0) from the waves' ballots
-    const uint64_t m0 = __ballot(D >= 0), m1 = __ballot(D > 0), m2 = __ballot(pos);
-    if (lane == 0) { sBal[wv][0] = m0; sBal[wv][1] = m1; sBal[wv][2] = m2; }
-    const uint64_t ay = wide ? (uint64_t)abs128(Yw) : (uint64_t)(Yr < 0 ? -Yr : Yr);
-    if (q == qlo) sAy[lc][0] = ay;
-    if (q == qhi) sAy[lc][1] = ay;
-    __syncthreads();
-    const uint64_t mx = sAy[lc][0] > sAy[lc][1] ? sAy[lc][0] : sAy[lc][1];
-    if (own && (t & 255) == 0) {
-        int v[4] = {128, 128, 128, -129};
-#pragma unroll
-        for (int k = 3; k >= 0; k--)
-#pragma unroll
-            for (int j = 0; j < 3; j++) {
-                const uint64_t bm = sBal[wv + k][j];
-                if (bm) v[j] = -128 + 64 * k + __builtin_ctzll(bm);
-            }
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const uint64_t bm = sBal[wv + k][2];
-            if (bm) v[3] = -128 + 64 * k + 63 - __builtin_clzll(bm);
+    for (int g = 0; g < grp; g++) {
+        const int c = cfirst + g * kFinCh + lc;
+        const bool own = c < st.C;
+        if (g) {
+            const int cs = own ? c : 0;
+            nmu = sv.n_mu[cs]; qlo = sv.qmin[cs]; qhi = sv.qmax[cs];
+            gq = gamma_q[cs]; bq = beta_q[cs];
         }
-        sv.t0[c] = v[0]; sv.p0[c] = v[1]; sv.mlo[c] = v[2]; sv.mhi[c] = v[3];
-        sv.n_sigma[c] = sNs[lc];
-        sv.den[c] = den;
-        w.maxYc[c] = mx;
+        const int32_t den = own ? sDen[g * kFinCh + lc] : 1;
+        const int64_t D = bn_D(q, s_x, nmu, e.e_mu);
+        const int32_t nx = own ? fwd_xcode_any(D, den, b, e) : 0;
+        // y on its grid: one of the two shifts is zero; |y| < 2^62 for gaps up to 48
+        const int gx = e.e_g + e.e_xh - e.e_y, gb = e.e_b - e.e_y;
+        const bool wide = gx > 38 || gb > 48;          // uniform over the grid
+        int64_t Yr = 0;
+        bool pos;
+        i128 Yw = 0;
+        if (wide) {
+            Yw = fwd_y(nx, gq, bq, e);
+            pos = Yw > 0;
+            if (cf.relu && Yw < 0) Yw = 0;
+        } else {
+            Yr = (int64_t)(gq * nx) * ((int64_t)1 << gx) + (int64_t)bq * ((int64_t)1 << gb);
+            pos = Yr > 0;
+            if (cf.relu && Yr < 0) Yr = 0;
+        }
+        const int idx = c * 256 + (t & 255);
+        const int sg = (D > 0) - (D < 0);
+        if (own) {
+            sv.xcode[idx] = (int16_t)nx;
+            sv.flags[idx] = (uint8_t)((pos ? 1 : 0) | ((sg + 1) << 1));
+            sv.btab[c * 256 + (q & 255)] = ((uint32_t)(uint16_t)(int16_t)nx << 16) | ((uint32_t)(sg & 3) << 8) |
+                                           ((uint32_t)(sg != 0) << 10) | (pos ? 1u : 0u);
+        }
+        // thresholds (least code with D >= 0, least with D > 0, code range with y >
+        // 0) from the waves' ballots
+        const uint64_t m0 = __ballot(D >= 0), m1 = __ballot(D > 0), m2 = __ballot(pos);
+        if (lane == 0) { sBal[g & 1][wv][0] = m0; sBal[g & 1][wv][1] = m1; sBal[g & 1][wv][2] = m2; }
+        const uint64_t ay = wide ? (uint64_t)abs128(Yw) : (uint64_t)(Yr < 0 ? -Yr : Yr);
+        if (q == qlo) sAy[g & 1][lc][0] = ay;
+        if (q == qhi) sAy[g & 1][lc][1] = ay;
+        __syncthreads();
+        const uint64_t mx = sAy[g & 1][lc][0] > sAy[g & 1][lc][1] ? sAy[g & 1][lc][0] : sAy[g & 1][lc][1];
+        if (own && (t & 255) == 0) {
+            int v[4] = {128, 128, 128, -129};
+#pragma unroll
+            for (int k = 3; k >= 0; k--)
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    const uint64_t bm = sBal[g & 1][wv + k][j];
+                    if (bm) v[j] = -128 + 64 * k + __builtin_ctzll(bm);
+                }
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const uint64_t bm = sBal[g & 1][wv + k][2];
+                if (bm) v[3] = -128 + 64 * k + 63 - __builtin_clzll(bm);
+            }
+            sv.t0[c] = v[0]; sv.p0[c] = v[1]; sv.mlo[c] = v[2]; sv.mhi[c] = v[3];
+            sv.n_sigma[c] = sNs[g * kFinCh + lc];
+            sv.den[c] = den;
+            w.maxYc[c] = mx;
+        }
+        // ReLU(y) floored by 2^t_c, t_c = max(0, r_c - 1) with r_c the Q_A shift
+        // this channel's own maximum would give: below 2^k_A in magnitude for the
+        // occupied codes (clamped elsewhere, where the output pass never looks)
+        const int tc = ystg_shift(mx, cf.k_A);
+        int64_t z;
+        if (wide) {
+            const i128 zw = tc ? (Yw >> tc) : Yw;
+            z = zw > 32767 ? 32767 : (zw < -32767 ? -32767 : (int64_t)zw);
+        } else {
+            z = Yr >> tc;
+            z = z > 32767 ? 32767 : (z < -32767 ? -32767 : z);
+        }
+        if (own) sv.ystg[idx] = (int16_t)z;
     }
-    // ReLU(y) floored by 2^t_c, t_c = max(0, r_c - 1) with r_c the Q_A shift
-    // this channel's own maximum would give: below 2^k_A in magnitude for the
-    // occupied codes (clamped elsewhere, where the output pass never looks)
-    const int tc = ystg_shift(mx, cf.k_A);
-    int64_t z;
-    if (wide) {
-        const i128 zw = tc ? (Yw >> tc) : Yw;
-        z = zw > 32767 ? 32767 : (zw < -32767 ? -32767 : (int64_t)zw);
-    } else {
-        z = Yr >> tc;
-        z = z > 32767 ? 32767 : (z < -32767 ? -32767 : z);
-    }
-    if (own) sv.ystg[idx] = (int16_t)z;
 }
 
 // Output pass.  Every block first takes Q_A's shift r from the channels'
@@ -1625,8 +1636,11 @@ static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t
         ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS1, stream, (k_bnf_stats1<CPL, G>), sg, dim3(kNT), 0, stream, x, st, w);
         ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS2, stream, (k_bnf_stats2<CPL, G>), sg, dim3(kNT), 0, stream, x, x_exp,
                           st, w, sv, cf, dev_status);
-        hipLaunchKernelGGL(k_bnf_fin2, dim3((unsigned)ceil_div64(C, kFinCh)), dim3(kNT), 0, stream, x_exp, st, w, sv,
-                           cf, gamma_q, beta_q);
+        // every block forms all C denominators, so past one block per CU a block
+        // takes more channels (2048 channels: 14.2 us with 512 blocks, 7.2 with 256)
+        const int grp = (int)std::min<int64_t>(kFinGrp, ceil_div64(C, 256 * kFinCh));
+        hipLaunchKernelGGL(k_bnf_fin2, dim3((unsigned)ceil_div64(C, grp * kFinCh)), dim3(kNT), 0, stream, x_exp, st,
+                           grp, w, sv, cf, gamma_q, beta_q);
     };
     const std::integral_constant<int, 16> v16c;
     if (C % 16 == 0 && ((uintptr_t)x & 15) == 0) {

@@ -33,6 +33,8 @@ CASES = [
     (1500, 48, 0, -40, dict(k_mu=2, k_sigma=3), "edge"), (1100, 64, 0, -9, dict(k_mu=8, k_xhat=8, eps_code=32768), "n"),
     # small even codes around zero: many channels whose mean is exactly a code
     (2048, 128, 0, -6, {}, "sym"), (2048, 128, 0, -6, dict(relu=0), "sym"),
+    # several channel groups per finalize block, the last one partly empty
+    (65, 1040, 0, -6, {}, "n"), (33, 2320, 0, -7, dict(k_E2=8), "u"), (9, 6148, 0, -7, {}, "n"),
 ]
 
 
