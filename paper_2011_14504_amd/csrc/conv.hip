@@ -1030,19 +1030,6 @@ __global__ __launch_bounds__(256) void k_gemm_short(IgemmArgs a)
     if (EPI == EPI_MAX) block_store_max_u64(mx, a.pmax);
 }
 
-// ---------------------------------------------------------------------------
-// 3x3, stride-1 convolution from an LDS halo tile (Ci % 64 == 0, Nout % 64 == 0).
-//
-// A block owns TH = 4 output rows x TW output columns of one image and 64
-// output channels; wave w computes output row w.  Per 64-channel chunk the
-// block stages the (TH + 2 dh) x (TW + 2 dw) input halo and the 9 x 64 x 64
-// weight slice once (direct-to-LDS loads, XOR-swizzled 16-byte slots: slot =
-// part ^ ((index >> 2) & 3), so any 16 consecutive pixels or channels are
-// conflict-free for ds_read_b128), then runs all nine taps from LDS: the A
-// operand of tap (r, s) is the halo shifted by (r dh, s dw).  Backward-data
-// with stride 1 is the same convolution over dy with the flipped, transposed
-// filter and padding dil (R - 1) - pad.
-// ---------------------------------------------------------------------------
 struct HaloArgs {
     const int8_t* src;            // [N][Hs][Ws][Ci]
     const int8_t* wmat;           // [Nout][3][3][Ci]
@@ -1060,249 +1047,31 @@ struct HaloArgs {
     int32_t tiles_y, tiles_x;
 };
 
-constexpr int kHaloTH = 4;
-
-size_t halo_lds_bytes(int TW, int dh, int dw)
-{
-    return (size_t)(kHaloTH + 2 * dh) * (TW + 2 * dw) * 64 + 9 * 64 * 64;
-}
-
-template <int TW, int EPI>
-__global__ __launch_bounds__(256) void k_conv3x3_halo(HaloArgs a)
-{
-    constexpr int TH = kHaloTH, TM = TW / 16, TN = 4;
-    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
-    const int HR = TH + 2 * a.dh, HC = TW + 2 * a.dw;
-    const int nhalo = HR * HC * 4;                        // 16-byte pieces
-    int8_t* halo = smem;
-    int8_t* wts = smem + HR * HC * 64;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nbx = gridDim.x;
-    int bx = blockIdx.x;
-    if ((nbx & 7) == 0) bx = (bx & 7) * (nbx >> 3) + (bx >> 3);
-    const int tx = bx % a.tiles_x, t2 = bx / a.tiles_x;
-    const int ty = t2 % a.tiles_y, n = t2 / a.tiles_y;
-    const int oy0 = ty * TH, ox0 = tx * TW, k0 = blockIdx.y * 64;
-    const int iy0 = oy0 - a.ph, ix0 = ox0 - a.pw;
-    const int lrow = lane & 15, lpart = lane >> 4;
-
-    v4i acc[TM][TN];
-
-    // A-operand LDS addresses of fragment 0 for the nine taps: fragment i adds
-    // 16 pixels = 1024 bytes and leaves the swizzle phase unchanged
-    int aaddr[9];
-#pragma unroll
-    for (int r = 0; r < 3; r++)
-#pragma unroll
-        for (int s2 = 0; s2 < 3; s2++) {
-            const int p = (wave + r * a.dh) * HC + lrow + s2 * a.dw;
-            aaddr[r * 3 + s2] = p * 64 + ((lpart ^ ((p >> 2) & 3)) << 4);
-        }
-    int baddr[TN];
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-        const int kk = 16 * j + lrow;
-        baddr[j] = kk * 64 + ((lpart ^ ((kk >> 2) & 3)) << 4);
-    }
-    // halo pieces of this lane: instruction k = wave + 4 u covers pixels
-    // 16 k .. 16 k + 15; pixel (hr, hc) advances by 64 per instruction
-    const int p0 = 16 * wave + (lane >> 2);
-    const int hr0 = p0 / HC, hc0 = p0 - (p0 / HC) * HC;
-    // weight pieces: instruction k = wave + 4 j holds tap j (rows of 16
-    // channels kk = 16 (wave) + lane / 4 ... ), same lane slot in every tap
-    const int wkk = ((wave * 64 + lane) >> 2) & 63;
-    const int wpart = (lane & 3) ^ ((wkk >> 2) & 3);
-    const int wtap0 = (wave * 64 + lane) >> 8;
-    const int8_t* wsrc = a.wmat + ((int64_t)(k0 + wkk) * 9 + wtap0) * a.Ci + wpart * 16;
-
-    const int nchunk = a.Ci / 64;
-    uint64_t gmax = 0;
-    for (int cc = 0; cc < nchunk; cc++) {
-        if (cc) __syncthreads();                          // the previous chunk's reads are done
-        {
-            int hr = hr0, hc = hc0;
-            for (int k = wave; k * 64 < nhalo; k += 4) {
-                const int q = k * 64 + lane;
-                if (q < nhalo) {
-                    const int p = q >> 2;
-                    const int part = (q & 3) ^ ((p >> 2) & 3);
-                    const int iy = iy0 + hr, ix = ix0 + hc;
-                    const bool v = (unsigned)iy < (unsigned)a.Hs && (unsigned)ix < (unsigned)a.Ws;
-                    const void* g = v ? (const void*)(a.src + (((int64_t)n * a.Hs + iy) * a.Ws + ix) * a.Ci +
-                                                      cc * 64 + part * 16)
-                                      : (const void*)g_conv_zero;
-                    dma16(g, halo + k * 1024);
-                }
-                hc += 64;
-                while (hc >= HC) { hc -= HC; ++hr; }
-            }
-        }
-        // instruction wave + 4 j covers pieces (wave + 4 j) * 64 + lane: tap =
-        // wtap0 + j (four instructions per tap), same channel row and slot
-#pragma unroll
-        for (int j = 0; j < 9; j++)
-            dma16(wsrc + (int64_t)j * a.Ci + cc * 64, wts + (wave + 4 * j) * 1024);
-        // second pass: the global max, read while the first chunk is in flight
-        if (EPI == EPI_Q8 && cc == 0) gmax = reduce_partials_u64(a.pmax, a.npmax);
-        wait_vm<0>();
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < 9; t++) {
-            v4i fa[TM], fb[TN];
-#pragma unroll
-            for (int i = 0; i < TM; i++) fa[i] = *(const v4i*)&halo[aaddr[t] + 1024 * i];
-#pragma unroll
-            for (int j = 0; j < TN; j++) fb[j] = *(const v4i*)&wts[t * 4096 + baddr[j]];
-            if (t == 0 && cc == 0) {              // first product: no accumulator to clear
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int j = 0; j < TN; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], (v4i){0, 0, 0, 0}, 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int j = 0; j < TN; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-            }
-        }
-    }
-
-    // acc[i][j][e]: output (row wave, column 16 i + 4 lpart + e), channel k0 + 16 j + lrow
-    const int oy = oy0 + wave;
-    const int64_t rowbase = ((int64_t)n * a.Ho + oy) * a.Wo;
-    if (EPI == EPI_RAW) {
-        if (oy < a.Ho) {
-#pragma unroll
-            for (int i = 0; i < TM; i++)
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int ox = ox0 + 16 * i + 4 * lpart + e;
-                    if (ox < a.Wo) {
-#pragma unroll
-                        for (int j = 0; j < TN; j++)
-                            a.out[(rowbase + ox) * a.Nout + k0 + 16 * j + lrow] = acc[i][j][e];
-                    }
-                }
-        }
-        return;
-    }
-    const int vcols = a.Wo - ox0 < TW ? a.Wo - ox0 : TW;
-    if (EPI == EPI_Q8) {
-        // codes = SQ(acc) with r = bitlen(global max) - 7; rhu(acc, r) = ((acc >> (r - 1)) + 1) >> 1
-        const uint64_t M = gmax;
-        const int r = M ? (64 - __builtin_clzll(M)) - 7 : 0;
-        if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *a.out_exp = *a.exp_a + *a.exp_b + r;
-        constexpr int RB8 = 64 + 16;                  // bytes per LDS row of the code tile
-        int8_t* T = smem + (wave * TW + 4 * lpart) * RB8 + lrow;
-        __syncthreads();                              // every wave is done with the halo
-        const int rs = r > 0 ? r - 1 : 0, ls = r > 0 ? 0 : -r;
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-            for (int e = 0; e < 4; e++)
-#pragma unroll
-                for (int j = 0; j < TN; j++) {
-                    const int32_t v = acc[i][j][e];
-                    int32_t c = r > 0 ? ((v >> rs) + 1) >> 1 : v << ls;
-                    c = c > 127 ? 127 : (c < -127 ? -127 : c);
-                    T[(16 * i + e) * RB8 + 16 * j] = (int8_t)c;
-                }
-        __syncthreads();
-        if (oy < a.Ho) {
-            // wave w stores tile row w: chunk (pixel lane / 4 + 16 u, channels 16 (lane % 4) ..)
-            const int8_t* T0 = smem + (wave * TW + (lane >> 2)) * RB8 + (lane & 3) * 16;
-            int8_t* g = a.out8 + ((rowbase + ox0 + (lane >> 2)) * a.Nout + k0 + (lane & 3) * 16);
-#pragma unroll
-            for (int u = 0; u < TW / 16; u++)
-                if ((lane >> 2) + 16 * u < vcols)
-                    *(int4*)(g + (int64_t)16 * u * a.Nout) = *(const int4*)&T0[16 * u * RB8];
-        }
-        return;
-    }
-    __shared__ uint32_t wmax[4];
-    // tile max |acc| via running max and min (max3/min3 take two values per op)
-    int32_t vmax = 0, vmin = 0;
-    if (oy < a.Ho) {
-        if (vcols == TW) {
-#pragma unroll
-            for (int i = 0; i < TM; i++)
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-#pragma unroll
-                    for (int j = 0; j < TN; j += 2) {
-                        vmax = max(vmax, max(acc[i][j][e], acc[i][j + 1][e]));
-                        vmin = min(vmin, min(acc[i][j][e], acc[i][j + 1][e]));
-                    }
-        } else {
-#pragma unroll
-            for (int i = 0; i < TM; i++)
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-                    if (16 * i + 4 * lpart + e < vcols) {
-#pragma unroll
-                        for (int j = 0; j < TN; j += 2) {
-                            vmax = max(vmax, max(acc[i][j][e], acc[i][j + 1][e]));
-                            vmin = min(vmin, min(acc[i][j][e], acc[i][j + 1][e]));
-                        }
-                    }
-        }
-    }
-    uint32_t mx = (uint32_t)max(vmax, -vmin);
-    mx = wave_max_u32(mx);
-    if (EPI == EPI_MAX) {
-        const uint64_t bm = block_max_u64(mx);
-        if (tid == 0) a.pmax[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = bm;
-        return;
-    }
-    if (lane == 0) wmax[wave] = mx;
-    __syncthreads();                                      // also: all waves are done with the halo
-    uint32_t tmax = wmax[0];
-#pragma unroll
-    for (int w = 1; w < 4; w++) tmax = wmax[w] > tmax ? wmax[w] : tmax;
-    const int tsh = tmax ? max(0, 32 - __builtin_clz(tmax) - 15) : 0;
-    constexpr int RS16 = 64 + 8;
-    int16_t* T = (int16_t*)smem + (wave * TW + 4 * lpart) * RS16 + lrow;
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-#pragma unroll
-            for (int j = 0; j < TN; j++) T[(16 * i + e) * RS16 + 16 * j] = (int16_t)(acc[i][j][e] >> tsh);
-    __syncthreads();
-    // wave w copies tile row w: 16-byte chunk (pixel lane / 8 + 8 u, channels 8 (lane % 8) ..)
-    if (oy < a.Ho) {
-        const int16_t* T0 = (const int16_t*)smem + (wave * TW + (lane >> 3)) * RS16 + (lane & 7) * 8;
-        int16_t* g = a.out16 + ((rowbase + ox0 + (lane >> 3)) * a.Nout + k0 + (lane & 7) * 8);
-#pragma unroll
-        for (int u = 0; u < TW / 8; u++)
-            if ((lane >> 3) + 8 * u < vcols)
-                *(int4*)(g + (int64_t)8 * u * a.Nout) = *(const int4*)&T0[8 * u * RS16];
-    }
-    if (tid == 0) {
-        a.tshift[(int64_t)bx * gridDim.y + blockIdx.y] = (uint8_t)tsh;
-        a.pmax[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = tmax;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // 3x3 stride-1 convolution on v_mfma_i32_32x32x32_i8 (Ci % 64 == 0, Nout % 64
 // == 0, dilation 1 or 2).  The 16x16x64 i8 MFMA issues at half the rate of the
-// 32x32x32 form on gfx950, so this is the main path.
+// 32x32x32 form on gfx950, so this is the main path.  Backward-data with stride
+// 1 is the same convolution over dy with the flipped, transposed filter and
+// padding dil (R - 1) - pad.
 //
-// A block owns a 16 x 32 output tile of one image and 64 output channels.  An
-// A fragment is 32 pixels = 2 rows x 16 columns; wave w computes rows 4w..4w+3
-// (four fragments) for all 64 channels (two B fragments): per tap and
-// 32-channel half, 4 x 2 MFMAs from 6 LDS reads.  The halo (16 + 2 dh rows x
-// 32 + 2 dw columns, one 64-channel chunk) and the 9 x 64 x 64 weight chunk
-// are staged by direct-to-LDS loads.  Halo slots are swizzled by the column
-// (slot = part ^ ((column >> 2) & 3)), which keeps any 16 consecutive pixels
-// of a row conflict-free and leaves the swizzle unchanged by row offsets, so
-// the nine taps need only three per-lane base addresses.
+// A block owns a TH x 32 output tile of one image and 64 output channels.  An
+// A fragment is 32 pixels = 2 rows x 16 columns; wave w computes rows TH/4 w ..
+// TH/4 (w + 1) - 1 (TH/4 fragments) for all 64 channels (two B fragments): per
+// tap and 32-channel half, TH/4 x 2 MFMAs from TH/4 + 2 LDS reads.  The halo (TH
+// + 2 dh rows x 32 + 2 dw columns, one 64-channel chunk) and the 9 x 64 x 64
+// weight chunk are staged by direct-to-LDS loads.  Halo slots are swizzled by
+// the column (slot = part ^ ((column >> 2) & 3)), which keeps any 16 consecutive
+// pixels of a row conflict-free and leaves the swizzle unchanged by row offsets,
+// so the nine taps need only three per-lane base addresses.
+//
+// Eight rows keep every CU busy on small images and tiles of 32 columns fit the
+// 32 x 32 maps: 128 -> 128 channels, 8 x 64 x 64: 13.2 -> 9.3 us a pass (16-row tiles
+// left half the chip idle); 256 -> 256 at 8 x 32 x 32: 22.6 -> 17.0 us, 512 -> 512
+// dilation 2: 45.2 -> 29.9 us (64-column tiles of the 16x16x64 form, half of them
+// outside the image).  Staging two chunks, the second one's loads under the
+// first one's taps, measured the same (28.4 us) for twice the LDS.
 // ---------------------------------------------------------------------------
-constexpr int kM32TH = 16, kM32TW = 32;
+constexpr int kM32TW = 32;
 typedef int v16i_t __attribute__((ext_vector_type(16)));
 
 // The 18 (tap, 32-channel half) steps of one 64-channel chunk.  Fragments of
@@ -1346,11 +1115,16 @@ __device__ __forceinline__ void m32_taps(const int8_t* halo, const int8_t* w, co
 }
 
 
-template <int DH, int DW, int EPI>
+constexpr size_t m32_chunk_bytes(int TH, int dh, int dw)
+{
+    return (size_t)(TH + 2 * dh) * (kM32TW + 2 * dw) * 64 + 9 * 64 * 64;
+}
+
+template <int DH, int DW, int EPI, int TH>
 __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
 {
-    constexpr int TH = kM32TH, TW = kM32TW, HR = TH + 2 * DH, HC = TW + 2 * DW;
-    constexpr int TM = 4, TN = 2;
+    constexpr int TW = kM32TW, HR = TH + 2 * DH, HC = TW + 2 * DW;
+    constexpr int TM = TH / 4, TN = 2;
     constexpr int NHALO = HR * HC * 4;                      // 16-byte pieces
     constexpr int HBYTES = HR * HC * 64;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
@@ -1368,7 +1142,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
     const int l32 = lane & 31, khalf = lane >> 5;          // fragment row, 16-byte half of a 32-byte k slice
     const int lr = l32 >> 4, lc = l32 & 15;                // row in the pair, column in the fragment
 
-    // A base address of fragment (row pair 2 wave, column group 0) for column tap s and k half kh:
+    // A base address of fragment (row pair TM / 2 wave, column group 0) for column tap s and k half kh:
     // fragment (rp, cg), tap (r, s) adds ((2 rp + r DH) HC + 16 cg) * 64 (compile-time)
     int abase[3][2];
 #pragma unroll
@@ -1376,7 +1150,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
 #pragma unroll
         for (int kh = 0; kh < 2; kh++) {
             const int hc = lc + s2 * DW, part = 2 * kh + khalf;
-            abase[s2][kh] = ((4 * wave + lr) * HC + hc) * 64 + ((part ^ ((hc >> 2) & 3)) << 4);
+            abase[s2][kh] = ((TM * wave + lr) * HC + hc) * 64 + ((part ^ ((hc >> 2) & 3)) << 4);
         }
     int bbase[TN][2];
 #pragma unroll
@@ -1425,9 +1199,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
         m32_taps<DH, HC, TM, TN>(halo, wts, abase, bbase, acc, cc == 0);
     }
 
-    // acc[i][j][v]: fragment i (rows 4 wave + 2 (i / 2) + q / 16, columns 16 (i % 2) + q % 16 with
+    // acc[i][j][v]: fragment i (rows TM wave + 2 (i / 2) + q / 16, columns 16 (i % 2) + q % 16 with
     // q = 8 (v / 4) + 4 khalf + v % 4), channel k0 + 32 j + l32
-    auto px_row = [&](int i, int v) { return 4 * wave + 2 * (i >> 1) + ((8 * (v >> 2) + 4 * khalf + (v & 3)) >> 4); };
+    auto px_row = [&](int i, int v) { return TM * wave + 2 * (i >> 1) + ((8 * (v >> 2) + 4 * khalf + (v & 3)) >> 4); };
     auto px_col = [&](int i, int v) { return 16 * (i & 1) + ((8 * (v >> 2) + 4 * khalf + (v & 3)) & 15); };
     const int vrows = a.Ho - oy0 < TH ? a.Ho - oy0 : TH;
     const int vcols = a.Wo - ox0 < TW ? a.Wo - ox0 : TW;
@@ -1445,7 +1219,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
             }
         return;
     }
-    if (EPI == EPI_MAX) {
+    if (EPI == EPI_MAX || EPI == EPI_STAGE16) {
         int32_t vmax = 0, vmin = 0;
         const bool full = vrows == TH && vcols == TW;
 #pragma unroll
@@ -1456,8 +1230,43 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
                     vmax = max(vmax, max(acc[i][0][v], acc[i][1][v]));
                     vmin = min(vmin, min(acc[i][0][v], acc[i][1][v]));
                 }
-        const uint64_t bm = block_max_u64((uint32_t)max(vmax, -vmin));
-        if (tid == 0) a.pmax[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = bm;
+        const uint32_t mx = (uint32_t)max(vmax, -vmin);
+        if (EPI == EPI_MAX) {
+            const uint64_t bm = block_max_u64(mx);
+            if (tid == 0) a.pmax[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = bm;
+            return;
+        }
+        // sums staged as int16 with the tile's shift
+        __shared__ uint32_t wmax[4];
+        const uint32_t wm = wave_max_u32(mx);
+        if (lane == 0) wmax[wave] = wm;
+        __syncthreads();                                    // also: every wave is done with the halo
+        const uint32_t tmax = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+        const int tsh = tmax ? max(0, 32 - __builtin_clz(tmax) - 15) : 0;
+        constexpr int RS16 = 64 + 8;
+        int16_t* T = (int16_t*)smem;
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int v = 0; v < 16; v++)
+#pragma unroll
+                for (int j = 0; j < TN; j++)
+                    T[(px_row(i, v) * TW + px_col(i, v)) * RS16 + 32 * j + l32] = (int16_t)(acc[i][j][v] >> tsh);
+        __syncthreads();
+        // TH x 32 pixels x 8 chunks of 8 sums: thread -> chunk (pixel c / 8, part c % 8)
+#pragma unroll
+        for (int u = 0; u < TH * TW * 8 / 256; u++) {
+            const int c = tid + 256 * u;
+            const int px = c >> 3, part = c & 7;
+            const int ry = px / TW, rx = px % TW;
+            if (ry < vrows && rx < vcols)
+                *(int4*)(a.out16 + ((((int64_t)n * a.Ho + oy0 + ry) * a.Wo + ox0 + rx) * a.Nout + k0 + part * 8)) =
+                    *(const int4*)&T[px * RS16 + part * 8];
+        }
+        if (tid == 0) {
+            a.tshift[(int64_t)bx * gridDim.y + blockIdx.y] = (uint8_t)tsh;
+            a.pmax[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = tmax;
+        }
         return;
     }
     // EPI_Q8: final SQ codes with r = bitlen(global max) - 7, staged per pixel row of 64 codes
@@ -1480,7 +1289,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
             }
         }
     __syncthreads();
-    // 512 pixels x 4 chunks of 16 codes: thread -> chunk (pixel c / 4, part c % 4)
+    // TH x 32 pixels x 4 chunks of 16 codes: thread -> chunk (pixel c / 4, part c % 4)
 #pragma unroll
     for (int u = 0; u < TH * TW * 4 / 256; u++) {
         const int c = tid + 256 * u;
@@ -1490,177 +1299,6 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_m32(HaloArgs a)
             *(int4*)(a.out8 + ((((int64_t)n * a.Ho + oy0 + ry) * a.Wo + ox0 + rx) * a.Nout + k0 + part * 16)) =
                 *(const int4*)&smem[px * RB8 + part * 16];
     }
-}
-
-// Persistent form of the 32x32 kernel (Ci = 64 or 128): weights of all chunks
-// stay in LDS, the next (tile, chunk) halo streams into the second buffer
-// while the current one runs its taps, and a block walks a contiguous run of
-// tiles (neighbours share halo rows and sit on one XCD).  One block per CU.
-template <int DH, int DW, int EPI>
-__global__ __launch_bounds__(256, 1) void k_conv3x3_m32p(HaloArgs a)
-{
-    constexpr int TH = kM32TH, TW = kM32TW, HR = TH + 2 * DH, HC = TW + 2 * DW;
-    constexpr int TM = 4, TN = 2;
-    constexpr int NHALO = HR * HC * 4;
-    constexpr int RB8 = 64 + 16;
-    constexpr int HBUF = (HR * HC * 64 > TH * TW * RB8 ? HR * HC * 64 : TH * TW * RB8);
-    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
-    const int nchunk = a.Ci / 64;
-    int8_t* wts = smem;                                     // [nchunk][9][64][64]
-    int8_t* hb = smem + nchunk * 36864;                     // two halo / staging buffers of HBUF bytes
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = gridDim.x;
-    int b = blockIdx.x;
-    if ((G & 7) == 0) b = (b & 7) * (G >> 3) + (b >> 3);
-    const int ntiles = a.N * a.tiles_y * a.tiles_x;
-    const int t_begin = (int)((int64_t)b * ntiles / G), t_end = (int)((int64_t)(b + 1) * ntiles / G);
-    const int nunits = (t_end - t_begin) * nchunk;
-    const int k0 = blockIdx.y * 64;
-    const int l32 = lane & 31, khalf = lane >> 5;
-    const int lr = l32 >> 4, lc = l32 & 15;
-
-    int abase[3][2];
-#pragma unroll
-    for (int s2 = 0; s2 < 3; s2++)
-#pragma unroll
-        for (int kh = 0; kh < 2; kh++) {
-            const int hc = lc + s2 * DW, part = 2 * kh + khalf;
-            abase[s2][kh] = ((4 * wave + lr) * HC + hc) * 64 + ((part ^ ((hc >> 2) & 3)) << 4);
-        }
-    int bbase[TN][2];
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-        for (int kh = 0; kh < 2; kh++) {
-            const int kk = 32 * j + l32, part = 2 * kh + khalf;
-            bbase[j][kh] = kk * 64 + ((part ^ ((kk >> 2) & 3)) << 4);
-        }
-    const int p0 = 16 * wave + (lane >> 2);
-    const int hr0 = p0 / HC, hc0 = p0 - (p0 / HC) * HC;
-
-    auto tile_origin = [&](int t, int& n, int& oy0, int& ox0) {
-        const int tx = t % a.tiles_x, t2 = t / a.tiles_x;
-        oy0 = (t2 % a.tiles_y) * TH;
-        n = t2 / a.tiles_y;
-        ox0 = tx * TW;
-    };
-    auto issue_halo = [&](int u) {
-        const int t = t_begin + u / nchunk, cc = u - (u / nchunk) * nchunk;
-        int n, oy0, ox0;
-        tile_origin(t, n, oy0, ox0);
-        const int iy0 = oy0 - a.ph, ix0 = ox0 - a.pw;
-        int8_t* dst = hb + (u & 1) * HBUF;
-        int hr = hr0, hc = hc0;
-#pragma unroll
-        for (int k = wave, v = 0; v < (NHALO / 64 + 4) / 4; v++, k += 4) {
-            const int q = k * 64 + lane;
-            if (q < NHALO) {
-                const int part = (q & 3) ^ ((hc >> 2) & 3);
-                const int iy = iy0 + hr, ix = ix0 + hc;
-                const bool ok = (unsigned)iy < (unsigned)a.Hs && (unsigned)ix < (unsigned)a.Ws;
-                const void* g = ok ? (const void*)(a.src + (((int64_t)n * a.Hs + iy) * a.Ws + ix) * a.Ci + cc * 64 +
-                                                   part * 16)
-                                   : (const void*)g_conv_zero;
-                dma16(g, dst + k * 1024);
-            }
-            hc += 64;
-            while (hc >= HC) { hc -= HC; ++hr; }
-        }
-    };
-
-    {
-        const int wkk = 16 * wave + (lane >> 2);
-        const int wpart = (lane & 3) ^ ((wkk >> 2) & 3);
-        const int8_t* wsrc = a.wmat + (int64_t)(k0 + wkk) * 9 * a.Ci + wpart * 16;
-        for (int cc = 0; cc < nchunk; cc++)
-#pragma unroll
-            for (int j = 0; j < 9; j++)
-                dma16(wsrc + (int64_t)j * a.Ci + cc * 64, wts + cc * 36864 + (wave + 4 * j) * 1024);
-    }
-    if (nunits > 0) issue_halo(0);
-    uint64_t gmax = 0;
-    if (EPI == EPI_Q8) gmax = reduce_partials_u64(a.pmax, a.npmax);
-    const int rq = gmax ? (64 - __builtin_clzll(gmax)) - 7 : 0;
-    wait_vm<0>();
-    __syncthreads();
-
-    v16i_t acc[TM][TN];
-    int32_t vmax = 0, vmin = 0;
-    for (int u = 0; u < nunits; u++) {
-        if (u + 1 < nunits) issue_halo(u + 1);
-        const int cc = u - (u / nchunk) * nchunk;
-        const int8_t* halo = hb + (u & 1) * HBUF;
-        const int8_t* w = wts + cc * 36864;
-        m32_taps<DH, HC, TM, TN>(halo, w, abase, bbase, acc, cc == 0);
-        if (cc == nchunk - 1) {
-            int n, oy0, ox0;
-            tile_origin(t_begin + u / nchunk, n, oy0, ox0);
-            const int vrows = a.Ho - oy0 < TH ? a.Ho - oy0 : TH;
-            const int vcols = a.Wo - ox0 < TW ? a.Wo - ox0 : TW;
-            auto px_row = [&](int i, int v) {
-                return 4 * wave + 2 * (i >> 1) + ((8 * (v >> 2) + 4 * khalf + (v & 3)) >> 4);
-            };
-            auto px_col = [&](int i, int v) { return 16 * (i & 1) + ((8 * (v >> 2) + 4 * khalf + (v & 3)) & 15); };
-            if (EPI == EPI_RAW) {
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int v = 0; v < 16; v++) {
-                        const int ry = px_row(i, v), rx = px_col(i, v);
-                        if (ry < vrows && rx < vcols) {
-                            const int64_t pix = ((int64_t)n * a.Ho + oy0 + ry) * a.Wo + ox0 + rx;
-#pragma unroll
-                            for (int j = 0; j < TN; j++) a.out[pix * a.Nout + k0 + 32 * j + l32] = acc[i][j][v];
-                        }
-                    }
-            } else if (EPI == EPI_MAX) {
-                const bool full = vrows == TH && vcols == TW;
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int v = 0; v < 16; v++)
-                        if (full || (px_row(i, v) < vrows && px_col(i, v) < vcols)) {
-                            vmax = max(vmax, max(acc[i][0][v], acc[i][1][v]));
-                            vmin = min(vmin, min(acc[i][0][v], acc[i][1][v]));
-                        }
-            } else {
-                const int rs = rq > 0 ? rq - 1 : 0, ls = rq > 0 ? 0 : -rq;
-                int8_t* T = hb + (u & 1) * HBUF;            // this unit's halo buffer, now free
-                __syncthreads();                            // every wave is done reading it
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int v = 0; v < 16; v++) {
-                        const int px = px_row(i, v) * TW + px_col(i, v);
-#pragma unroll
-                        for (int j = 0; j < TN; j++) {
-                            const int32_t x = acc[i][j][v];
-                            int32_t c = rq > 0 ? ((x >> rs) + 1) >> 1 : x << ls;
-                            c = c > 127 ? 127 : (c < -127 ? -127 : c);
-                            T[px * RB8 + 32 * j + l32] = (int8_t)c;
-                        }
-                    }
-                __syncthreads();
-#pragma unroll
-                for (int v = 0; v < TH * TW * 4 / 256; v++) {
-                    const int c = tid + 256 * v;
-                    const int px = c >> 2, part = c & 3;
-                    const int ry = px / TW, rx = px % TW;
-                    if (ry < vrows && rx < vcols)
-                        *(int4*)(a.out8 + ((((int64_t)n * a.Ho + oy0 + ry) * a.Wo + ox0 + rx) * a.Nout + k0 +
-                                           part * 16)) = *(const int4*)&T[px * RB8 + part * 16];
-                }
-            }
-        }
-        wait_vm<0>();                                       // the next unit's halo has landed
-        __syncthreads();
-    }
-    if (EPI == EPI_MAX) {
-        const uint64_t bm = block_max_u64((uint32_t)max(vmax, -vmin));
-        if (tid == 0) a.pmax[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = bm;
-    }
-    if (EPI == EPI_Q8 && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *a.out_exp = *a.exp_a + *a.exp_b + rq;
 }
 
 // ---------------------------------------------------------------------------
@@ -1844,13 +1482,12 @@ int launch_stem(int kind, HaloArgs a, int epi, int kid, hipStream_t s)
     return launch_stem_t<7, 2, EPI_Q8>(a, kid, s);
 }
 
+// the 3x3 kernel covers stride 1, dilation <= 2, Ci and Nout multiples of 64,
+// 16-byte aligned operands
 struct M32Plan {
     bool ok;
+    int th;                       // tile rows
     int tiles_y, tiles_x;
-    size_t lds;
-    bool persist;                 // weights resident, double-buffered halos
-    int G;                        // persistent blocks per 64-channel group
-    size_t plds;
 };
 
 M32Plan m32_plan(int64_t N, int64_t Ho, int64_t Wo, int64_t Ci, int64_t Nout, int R, int S, int sh, int sw, int dh,
@@ -1858,42 +1495,45 @@ M32Plan m32_plan(int64_t N, int64_t Ho, int64_t Wo, int64_t Ci, int64_t Nout, in
 {
     M32Plan p{};
     p.ok = N > 0 && R == 3 && S == 3 && sh == 1 && sw == 1 && dh >= 1 && dh <= 2 && dw >= 1 && dw <= 2 &&
-           Ci % 64 == 0 && Ci <= 128 && Nout % 64 == 0 && N * Ho * Wo < ((int64_t)1 << 31);
+           Ci % 64 == 0 && Nout % 64 == 0 && N * Ho * Wo < ((int64_t)1 << 31);
     if (!p.ok) return p;
-    p.tiles_y = (int)ceil_div64(Ho, kM32TH);
     p.tiles_x = (int)ceil_div64(Wo, kM32TW);
-    const size_t halo = (size_t)(kM32TH + 2 * dh) * (kM32TW + 2 * dw) * 64;
-    p.lds = halo + 9 * 64 * 64;
-    const size_t stage = (size_t)kM32TH * kM32TW * 80;
-    if (p.lds < stage) p.lds = stage;
+    // 16-row tiles share the weights over twice the pixels, but want two blocks
+    // on every CU: 64 -> 64 at 16 x 224 x 224 (1568 tall tiles) 85.6 us against 90.9,
+    // 128 -> 128 at 8 x 128 x 128 (512) 45.8 against 50.0, yet 21.9 against 18.9 at
+    // 64 -> 64, 8 x 128 x 128 (256).  Dilation 2 in both axes leaves LDS for one
+    // 16-row block only: 116.8 against 96.8 at 128 -> 128, 16 x 128 x 128.
+    const int64_t tall = N * ceil_div64(Ho, 16) * p.tiles_x * (Nout / 64);
+    p.th = tall >= 512 && 2 * m32_chunk_bytes(16, dh, dw) <= 160 * 1024 ? 16 : 8;
+    p.tiles_y = (int)ceil_div64(Ho, p.th);
     p.ok = N * p.tiles_y * p.tiles_x < ((int64_t)1 << 31);
-    const int64_t ntiles = N * p.tiles_y * p.tiles_x, groups = Nout / 64;
-    const size_t hbuf = halo > stage ? halo : stage;
-    p.plds = (size_t)(Ci / 64) * 36864 + 2 * hbuf;
-    int64_t G = 256 / groups;
-    if (G < 8) G = 8;
-    if (G > ntiles) G = ntiles;
-    p.G = (int)G;
-    p.persist = false;   // measured slower than two resident blocks per CU at these sizes
-    (void)ntiles;
     return p;
+}
+
+size_t m32_staged_ws_bytes(const M32Plan& p, int64_t N, int64_t Ho, int64_t Wo, int64_t Nout)
+{
+    return align256((size_t)(N * Ho * Wo * Nout) * 2) +
+           align256((size_t)(N * p.tiles_y * p.tiles_x * (Nout / 64)));
+}
+
+template <int DH, int DW, int EPI, int TH>
+int launch_m32_s(const M32Plan& p, const HaloArgs& a, int kid, hipStream_t s)
+{
+    constexpr size_t chunk = m32_chunk_bytes(TH, DH, DW), stage = (size_t)TH * kM32TW * (EPI == EPI_STAGE16 ? 144 : 80);
+    constexpr size_t lds = chunk > stage ? chunk : stage;
+    dim3 grid((unsigned)(a.N * p.tiles_y * p.tiles_x), (unsigned)(a.Nout / 64));
+    if (!lds_limit((const void*)k_conv3x3_m32<DH, DW, EPI, TH>, lds)) return ISEG_ERR_DEVICE;
+    ISEG_TIMED_LAUNCH(kid, s, (k_conv3x3_m32<DH, DW, EPI, TH>), grid, dim3(256), lds, s, a);
+    return launch_ok();
 }
 
 template <int DH, int DW, int EPI>
 int launch_m32_t(const M32Plan& p, const HaloArgs& a, int kid, hipStream_t s)
 {
-    if (p.persist) {
-        dim3 grid((unsigned)p.G, (unsigned)(a.Nout / 64));
-        if (!lds_limit((const void*)k_conv3x3_m32p<DH, DW, EPI>, (size_t)p.plds))
-            return ISEG_ERR_DEVICE;
-        ISEG_TIMED_LAUNCH(kid, s, (k_conv3x3_m32p<DH, DW, EPI>), grid, dim3(256), p.plds, s, a);
-        return launch_ok();
+    if constexpr (2 * m32_chunk_bytes(16, DH, DW) <= 160 * 1024) {
+        if (p.th == 16) return launch_m32_s<DH, DW, EPI, 16>(p, a, kid, s);
     }
-    dim3 grid((unsigned)(a.N * p.tiles_y * p.tiles_x), (unsigned)(a.Nout / 64));
-    if (!lds_limit((const void*)k_conv3x3_m32<DH, DW, EPI>, (size_t)p.lds))
-        return ISEG_ERR_DEVICE;
-    ISEG_TIMED_LAUNCH(kid, s, (k_conv3x3_m32<DH, DW, EPI>), grid, dim3(256), p.lds, s, a);
-    return launch_ok();
+    return launch_m32_s<DH, DW, EPI, 8>(p, a, kid, s);
 }
 
 template <int EPI>
@@ -1910,366 +1550,32 @@ int launch_m32(const M32Plan& p, HaloArgs a, int epi, int kid, hipStream_t s)
     a.tiles_y = p.tiles_y;
     a.tiles_x = p.tiles_x;
     if (epi == EPI_RAW) return launch_m32_e<EPI_RAW>(p, a, kid, s);
+    if (epi == EPI_STAGE16) return launch_m32_e<EPI_STAGE16>(p, a, kid, s);
     if (epi == EPI_MAX) return launch_m32_e<EPI_MAX>(p, a, kid, s);
     return launch_m32_e<EPI_Q8>(p, a, kid, s);
 }
 
-// Q8 through the 32x32 kernel: max pass, then the final-code pass
+// Q8 output: for short reductions (Ci <= kTwoPassMaxCi) a max-only pass and a
+// recomputing pass that writes final codes, else int16 staging plus a requant
+// pass.  The recompute costs 9 Ci MACs per output while staging moves 4 more
+// bytes per output through HBM.
+constexpr int kTwoPassMaxCi = 128;
+
 int m32_q8(const M32Plan& p, HaloArgs h, int kid, const int32_t* exp_a, const int32_t* exp_b, int8_t* out,
            int32_t* out_exp, uint64_t* pmax, hipStream_t s)
 {
     int rc;
-    h.pmax = pmax;
-    h.npmax = p.persist ? (int64_t)p.G * (h.Nout / 64) : (int64_t)h.N * p.tiles_y * p.tiles_x * (h.Nout / 64);
-    if ((rc = launch_m32(p, h, EPI_MAX, kid, s))) return rc;
-    h.out8 = out; h.exp_a = exp_a; h.exp_b = exp_b; h.out_exp = out_exp;
-    return launch_m32(p, h, EPI_Q8, kid, s);
-}
-
-// ---------------------------------------------------------------------------
-// Persistent variant (Ci = 64 or 128): a block keeps its 64 output channels'
-// weights for all chunks resident in LDS and walks a contiguous run of tiles;
-// the input halo of the next (tile, chunk) streams into the second of two
-// buffers while the current one runs its nine taps, so the loads hide behind
-// the MFMAs.  The final-code epilogue stages a tile's codes in the halo buffer
-// it has just finished with.  Blocks are numbered so that neighbouring tiles
-// (which share halo rows) run on one XCD.
-// ---------------------------------------------------------------------------
-template <int TW, int EPI>
-__global__ __launch_bounds__(256) void k_conv3x3_persist(HaloArgs a)
-{
-    constexpr int TH = kHaloTH, TM = TW / 16, TN = 4;
-    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
-    const int HR = TH + 2 * a.dh, HC = TW + 2 * a.dw;
-    const int nhalo = HR * HC * 4;                        // 16-byte pieces per halo
-    const int nchunk = a.Ci / 64;
-    int8_t* wts = smem;                                   // [nchunk][9][64][64]
-    int8_t* hbuf0 = smem + nchunk * 36864;
-    const int hbytes = HR * HC * 64;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = gridDim.x;
-    int b = blockIdx.x;
-    if ((G & 7) == 0) b = (b & 7) * (G >> 3) + (b >> 3);
-    const int ntiles = a.N * a.tiles_y * a.tiles_x;
-    const int t_begin = (int)((int64_t)b * ntiles / G), t_end = (int)((int64_t)(b + 1) * ntiles / G);
-    const int nunits = (t_end - t_begin) * nchunk;
-    const int k0 = blockIdx.y * 64;
-    const int lrow = lane & 15, lpart = lane >> 4;
-
-    int aaddr[9];
-#pragma unroll
-    for (int r = 0; r < 3; r++)
-#pragma unroll
-        for (int s2 = 0; s2 < 3; s2++) {
-            const int p = (wave + r * a.dh) * HC + lrow + s2 * a.dw;
-            aaddr[r * 3 + s2] = p * 64 + ((lpart ^ ((p >> 2) & 3)) << 4);
-        }
-    int baddr[TN];
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-        const int kk = 16 * j + lrow;
-        baddr[j] = kk * 64 + ((lpart ^ ((kk >> 2) & 3)) << 4);
-    }
-    const int p0 = 16 * wave + (lane >> 2);
-    const int hr0 = p0 / HC, hc0 = p0 - (p0 / HC) * HC;
-
-    // tile t -> (image, tile row, tile column)
-    auto tile_origin = [&](int t, int& n, int& oy0, int& ox0) {
-        const int tx = t % a.tiles_x, t2 = t / a.tiles_x;
-        oy0 = (t2 % a.tiles_y) * TH;
-        n = t2 / a.tiles_y;
-        ox0 = tx * TW;
-    };
-    auto issue_halo = [&](int u) {
-        const int t = t_begin + u / nchunk, cc = u - (u / nchunk) * nchunk;
-        int n, oy0, ox0;
-        tile_origin(t, n, oy0, ox0);
-        const int iy0 = oy0 - a.ph, ix0 = ox0 - a.pw;
-        int8_t* dst = hbuf0 + (u & 1) * hbytes;
-        int hr = hr0, hc = hc0;
-        for (int k = wave; k * 64 < nhalo; k += 4) {
-            const int q = k * 64 + lane;
-            if (q < nhalo) {
-                const int p = q >> 2;
-                const int part = (q & 3) ^ ((p >> 2) & 3);
-                const int iy = iy0 + hr, ix = ix0 + hc;
-                const bool v = (unsigned)iy < (unsigned)a.Hs && (unsigned)ix < (unsigned)a.Ws;
-                const void* g = v ? (const void*)(a.src + (((int64_t)n * a.Hs + iy) * a.Ws + ix) * a.Ci + cc * 64 +
-                                                  part * 16)
-                                  : (const void*)g_conv_zero;
-                dma16(g, dst + k * 1024);
-            }
-            hc += 64;
-            while (hc >= HC) { hc -= HC; ++hr; }
-        }
-    };
-
-    // prologue: every chunk's weights, the first halo, the global max (second pass)
-    {
-        const int wkk = 16 * wave + (lane >> 2);
-        const int wpart = (lane & 3) ^ ((wkk >> 2) & 3);
-        const int8_t* wsrc = a.wmat + (int64_t)(k0 + wkk) * 9 * a.Ci + wpart * 16;
-        for (int cc = 0; cc < nchunk; cc++)
-#pragma unroll
-            for (int j = 0; j < 9; j++)
-                dma16(wsrc + (int64_t)j * a.Ci + cc * 64, wts + cc * 36864 + (wave + 4 * j) * 1024);
-    }
-    if (nunits > 0) issue_halo(0);
-    uint64_t gmax = 0;
-    if (EPI == EPI_Q8) gmax = reduce_partials_u64(a.pmax, a.npmax);
-    wait_vm<0>();
-    __syncthreads();
-
-    int32_t vmax = 0, vmin = 0;                           // max pass: running extremes
-    v4i acc[TM][TN];
-    for (int u = 0; u < nunits; u++) {
-        if (u + 1 < nunits) issue_halo(u + 1);
-        const int cc = u - (u / nchunk) * nchunk;
-        const int8_t* halo = hbuf0 + (u & 1) * hbytes;
-        const int8_t* w = wts + cc * 36864;
-#pragma unroll
-        for (int t = 0; t < 9; t++) {
-            v4i fa[TM], fb[TN];
-#pragma unroll
-            for (int i = 0; i < TM; i++) fa[i] = *(const v4i*)&halo[aaddr[t] + 1024 * i];
-#pragma unroll
-            for (int j = 0; j < TN; j++) fb[j] = *(const v4i*)&w[t * 4096 + baddr[j]];
-            if (t == 0 && cc == 0) {
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int j = 0; j < TN; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], (v4i){0, 0, 0, 0}, 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int j = 0; j < TN; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-            }
-        }
-        if (cc == nchunk - 1) {
-            int n, oy0, ox0;
-            tile_origin(t_begin + u / nchunk, n, oy0, ox0);
-            const int oy = oy0 + wave;
-            const int vcols = a.Wo - ox0 < TW ? a.Wo - ox0 : TW;
-            const int64_t rowbase = ((int64_t)n * a.Ho + oy) * a.Wo;
-            if (EPI == EPI_RAW) {
-                if (oy < a.Ho) {
-#pragma unroll
-                    for (int i = 0; i < TM; i++)
-#pragma unroll
-                        for (int e = 0; e < 4; e++)
-                            if (16 * i + 4 * lpart + e < vcols) {
-#pragma unroll
-                                for (int j = 0; j < TN; j++)
-                                    a.out[(rowbase + ox0 + 16 * i + 4 * lpart + e) * a.Nout + k0 + 16 * j + lrow] =
-                                        acc[i][j][e];
-                            }
-                }
-            } else if (EPI == EPI_MAX) {
-                if (oy < a.Ho) {
-#pragma unroll
-                    for (int i = 0; i < TM; i++)
-#pragma unroll
-                        for (int e = 0; e < 4; e++)
-                            if (16 * i + 4 * lpart + e < vcols) {
-#pragma unroll
-                                for (int j = 0; j < TN; j += 2) {
-                                    vmax = max(vmax, max(acc[i][j][e], acc[i][j + 1][e]));
-                                    vmin = min(vmin, min(acc[i][j][e], acc[i][j + 1][e]));
-                                }
-                            }
-                }
-            } else {                                      // EPI_Q8
-                const int r = gmax ? (64 - __builtin_clzll(gmax)) - 7 : 0;
-                const int rs = r > 0 ? r - 1 : 0, ls = r > 0 ? 0 : -r;
-                constexpr int RB8 = 64 + 16;
-                int8_t* T = (int8_t*)halo + (wave * TW + 4 * lpart) * RB8 + lrow;
-                __syncthreads();                          // every wave is done reading this halo
-#pragma unroll
-                for (int i = 0; i < TM; i++)
-#pragma unroll
-                    for (int e = 0; e < 4; e++)
-#pragma unroll
-                        for (int j = 0; j < TN; j++) {
-                            const int32_t v = acc[i][j][e];
-                            int32_t c = r > 0 ? ((v >> rs) + 1) >> 1 : v << ls;
-                            c = c > 127 ? 127 : (c < -127 ? -127 : c);
-                            T[(16 * i + e) * RB8 + 16 * j] = (int8_t)c;
-                        }
-                __syncthreads();
-                if (oy < a.Ho) {
-                    const int8_t* T0 = halo + (wave * TW + (lane >> 2)) * RB8 + (lane & 3) * 16;
-                    int8_t* g = a.out8 + ((rowbase + ox0 + (lane >> 2)) * a.Nout + k0 + (lane & 3) * 16);
-#pragma unroll
-                    for (int u2 = 0; u2 < TW / 16; u2++)
-                        if ((lane >> 2) + 16 * u2 < vcols)
-                            *(int4*)(g + (int64_t)16 * u2 * a.Nout) = *(const int4*)&T0[16 * u2 * RB8];
-                }
-            }
-        }
-        wait_vm<0>();                                     // the next unit's halo has landed
-        __syncthreads();
-    }
-    if (EPI == EPI_MAX) {
-        const uint64_t bm = block_max_u64((uint32_t)max(vmax, -vmin));
-        if (tid == 0) a.pmax[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = bm;
-    }
-    if (EPI == EPI_Q8 && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
-        const int r = gmax ? (64 - __builtin_clzll(gmax)) - 7 : 0;
-        *a.out_exp = *a.exp_a + *a.exp_b + r;
-    }
-}
-
-struct PersistPlan {
-    bool ok;
-    int TW, tiles_y, tiles_x, G;
-    size_t lds;
-};
-
-PersistPlan persist_plan(int64_t N, int64_t Ho, int64_t Wo, int64_t Ci, int64_t Nout, int R, int S, int sh, int sw,
-                         int dh, int dw)
-{
-    PersistPlan p{};
-    p.ok = N > 0 && R == 3 && S == 3 && sh == 1 && sw == 1 && dh <= 2 && dw <= 2 && (Ci == 64 || Ci == 128) &&
-           Nout % 64 == 0 && N * Ho * Wo < ((int64_t)1 << 31);
-    if (!p.ok) return p;
-    p.TW = (Ci == 64 && Wo % 112 == 0) ? 112 : 64;
-    p.tiles_y = (int)ceil_div64(Ho, kHaloTH);
-    p.tiles_x = (int)ceil_div64(Wo, p.TW);
-    const int64_t ntiles = N * p.tiles_y * p.tiles_x;
-    const int64_t halo = (int64_t)(kHaloTH + 2 * dh) * (p.TW + 2 * dw) * 64;
-    p.lds = (size_t)((Ci / 64) * 36864 + 2 * halo);
-    const int64_t groups = Nout / 64;
-    int64_t G = 256 / groups;
-    if (G < 8) G = 8;
-    if (G > ntiles) G = ntiles;
-    p.G = (int)G;
-    p.ok = ntiles < ((int64_t)1 << 31) && p.lds <= 160 * 1024 &&
-           (int64_t)kHaloTH * p.TW * 80 <= halo;        // code staging fits in a halo buffer
-    return p;
-}
-
-template <int TW, int EPI>
-int launch_persist_t(const PersistPlan& p, const HaloArgs& a, int kid, hipStream_t s)
-{
-    dim3 grid((unsigned)p.G, (unsigned)(a.Nout / 64));
-    if (!lds_limit((const void*)k_conv3x3_persist<TW, EPI>, (size_t)p.lds))
-        return ISEG_ERR_DEVICE;
-    ISEG_TIMED_LAUNCH(kid, s, (k_conv3x3_persist<TW, EPI>), grid, dim3(256), p.lds, s, a);
-    return launch_ok();
-}
-
-int launch_persist(const PersistPlan& p, HaloArgs a, int epi, int kid, hipStream_t s)
-{
-    a.tiles_y = p.tiles_y;
-    a.tiles_x = p.tiles_x;
-    if (p.TW == 112) {
-        if (epi == EPI_RAW) return launch_persist_t<112, EPI_RAW>(p, a, kid, s);
-        if (epi == EPI_MAX) return launch_persist_t<112, EPI_MAX>(p, a, kid, s);
-        return launch_persist_t<112, EPI_Q8>(p, a, kid, s);
-    }
-    if (epi == EPI_RAW) return launch_persist_t<64, EPI_RAW>(p, a, kid, s);
-    if (epi == EPI_MAX) return launch_persist_t<64, EPI_MAX>(p, a, kid, s);
-    return launch_persist_t<64, EPI_Q8>(p, a, kid, s);
-}
-
-// Q8 through the persistent kernel: max pass, then the final-code pass
-int persist_q8(const PersistPlan& p, HaloArgs h, int kid, const int32_t* exp_a, const int32_t* exp_b, int8_t* out,
-               int32_t* out_exp, uint64_t* pmax, hipStream_t s)
-{
-    int rc;
-    h.pmax = pmax;
-    h.npmax = (int64_t)p.G * (h.Nout / 64);
-    if ((rc = launch_persist(p, h, EPI_MAX, kid, s))) return rc;
-    h.out8 = out; h.exp_a = exp_a; h.exp_b = exp_b; h.out_exp = out_exp;
-    return launch_persist(p, h, EPI_Q8, kid, s);
-}
-
-
-// the halo kernel covers 3x3 filters at stride 1, dilation <= 2, Ci and Nout
-// multiples of 64, 16-byte aligned operands
-struct HaloPlan {
-    bool ok;
-    int TW;
-    int tiles_y, tiles_x;
-    size_t lds;
-};
-
-HaloPlan halo_plan(int64_t N, int64_t Ho, int64_t Wo, int64_t Ci, int64_t Nout, int R, int S, int sh, int sw,
-                   int dh, int dw)
-{
-    HaloPlan p{};
-    p.ok = N > 0 && R == 3 && S == 3 && sh == 1 && sw == 1 && dh <= 2 && dw <= 2 && Ci % 64 == 0 &&
-           Nout % 64 == 0 && N * Ho * Wo < ((int64_t)1 << 31);
-    if (!p.ok) return p;
-    // widest tile without a ragged column tile when the width allows it
-    p.TW = (Wo % 112 == 0) ? 112 : 64;
-    p.tiles_y = (int)ceil_div64(Ho, kHaloTH);
-    p.tiles_x = (int)ceil_div64(Wo, p.TW);
-    p.lds = halo_lds_bytes(p.TW, dh, dw);
-    p.ok = N * p.tiles_y * p.tiles_x < ((int64_t)1 << 31);
-    return p;
-}
-
-size_t halo_staged_ws_bytes(const HaloPlan& p, int64_t N, int64_t Ho, int64_t Wo, int64_t Nout)
-{
-    return align256((size_t)(N * Ho * Wo * Nout) * 2) +
-           align256((size_t)(N * p.tiles_y * p.tiles_x * (Nout / 64)));
-}
-
-template <int TW, int EPI>
-int launch_halo_t(const HaloPlan& p, const HaloArgs& a, int kid, hipStream_t s)
-{
-    dim3 grid((unsigned)(a.N * p.tiles_y * p.tiles_x), (unsigned)(a.Nout / 64));
-    if (!lds_limit((const void*)k_conv3x3_halo<TW, EPI>, (size_t)p.lds))
-        return ISEG_ERR_DEVICE;
-    ISEG_TIMED_LAUNCH(kid, s, (k_conv3x3_halo<TW, EPI>), grid, dim3(256), p.lds, s, a);
-    return launch_ok();
-}
-
-int launch_halo(const HaloPlan& p, HaloArgs a, int epi, int kid, hipStream_t s)
-{
-    a.tiles_y = p.tiles_y;
-    a.tiles_x = p.tiles_x;
-    if (p.TW == 112) {
-        switch (epi) {
-        case EPI_RAW: return launch_halo_t<112, EPI_RAW>(p, a, kid, s);
-        case EPI_STAGE16: return launch_halo_t<112, EPI_STAGE16>(p, a, kid, s);
-        case EPI_MAX: return launch_halo_t<112, EPI_MAX>(p, a, kid, s);
-        default: return launch_halo_t<112, EPI_Q8>(p, a, kid, s);
-        }
-    }
-    switch (epi) {
-    case EPI_RAW: return launch_halo_t<64, EPI_RAW>(p, a, kid, s);
-    case EPI_STAGE16: return launch_halo_t<64, EPI_STAGE16>(p, a, kid, s);
-    case EPI_MAX: return launch_halo_t<64, EPI_MAX>(p, a, kid, s);
-    default: return launch_halo_t<64, EPI_Q8>(p, a, kid, s);
-    }
-}
-
-// Q8 output through the halo kernel: for short reductions (Ci <= kTwoPassMaxCi)
-// a max-only pass and a recomputing pass that writes final codes, else int16
-// staging plus a requant pass.  The recompute costs 9 Ci MACs per output while
-// staging moves 4 more bytes per output through HBM.
-constexpr int kTwoPassMaxCi = 128;
-
-int halo_q8(const HaloPlan& p, HaloArgs h, int kid, const int32_t* exp_a, const int32_t* exp_b, int8_t* out,
-            int32_t* out_exp, unsigned long long* maxp, uint64_t* pmax, int64_t rows, hipStream_t s)
-{
-    int rc;
+    const int64_t rows = (int64_t)h.N * h.Ho * h.Wo;
     h.pmax = pmax;
     h.npmax = (int64_t)h.N * p.tiles_y * p.tiles_x * (h.Nout / 64);
     if (h.Ci <= kTwoPassMaxCi) {
-        if ((rc = launch_halo(p, h, EPI_MAX, kid, s))) return rc;
+        if ((rc = launch_m32(p, h, EPI_MAX, kid, s))) return rc;
         h.out8 = out; h.exp_a = exp_a; h.exp_b = exp_b; h.out_exp = out_exp;
-        return launch_halo(p, h, EPI_Q8, kid, s);
+        return launch_m32(p, h, EPI_Q8, kid, s);
     }
-    if ((rc = launch_halo(p, h, EPI_STAGE16, kid, s))) return rc;
-    (void)maxp;
-    StageMap sm{0, 64, h.Ho, h.Wo, kHaloTH, p.TW, p.tiles_y, p.tiles_x};
+    h.tshift = (uint8_t*)h.out16 + align256((size_t)(rows * h.Nout) * 2);
+    if ((rc = launch_m32(p, h, EPI_STAGE16, kid, s))) return rc;
+    StageMap sm{0, 64, h.Ho, h.Wo, p.th, kM32TW, p.tiles_y, p.tiles_x};
     return launch_requant_staged16(h.out16, h.tshift, rows, h.Nout, sm, exp_a, exp_b, 8, out, out_exp, nullptr, s,
                                    pmax, h.npmax);
 }
@@ -4253,16 +3559,11 @@ bool geom_ok(const iseg_conv_geom* g, int64_t* P, int64_t* Q)
 // C ABI
 // ---------------------------------------------------------------------------
 // room for per-block max partials of any path the output of rows x cols can take
-size_t conv_pmax_bytes(int64_t rows, int64_t cols, const HaloPlan& hp, int64_t N, int64_t Ho, int64_t Wo)
+size_t conv_pmax_bytes(int64_t rows, int64_t cols, int64_t N, int64_t Ho, int64_t Wo)
 {
-    int64_t nb = ceil_div64(rows, 128) * ceil_div64(cols, 64);
-    if (hp.ok) {
-        const int64_t nh = N * hp.tiles_y * hp.tiles_x * (cols / 64);
-        nb = nb > nh ? nb : nh;
-    }
-    const int64_t nm = N * ceil_div64(Ho, kM32TH) * ceil_div64(Wo, kM32TW) * ceil_div64(cols, 64);
-    nb = nb > nm ? nb : nm;
-    return align256((size_t)nb * 8);
+    const int64_t nb = ceil_div64(rows, 128) * ceil_div64(cols, 64);
+    const int64_t nm = N * ceil_div64(Ho, 8) * ceil_div64(Wo, kM32TW) * ceil_div64(cols, 64);
+    return align256((size_t)(nb > nm ? nb : nm) * 8);
 }
 
 static size_t conv_fwd_core_ws(const iseg_conv_geom* g, int32_t out_mode)
@@ -4277,13 +3578,10 @@ static size_t conv_fwd_core_ws(const iseg_conv_geom* g, int32_t out_mode)
         const DmaPlan dp = dma_plan(g->N * P * Q, (int32_t)g->K, (int32_t)(padded_c(g->C) * g->R * g->S), true);
         const size_t sk = dma_split_bytes(dp, g->N * P * Q, (int32_t)g->K);
         big = big > sk ? big : sk;
-        const HaloPlan hp = halo_plan(g->N, P, Q, g->C, g->K, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
-                                      g->dil_h, g->dil_w);
-        if (hp.ok) {
-            const size_t sh = halo_staged_ws_bytes(hp, g->N, P, Q, g->K);
-            big = big > sh ? big : sh;
-        }
-        s += big + conv_pmax_bytes(g->N * P * Q, g->K, hp, g->N, P, Q);
+        const M32Plan mp = m32_plan(g->N, P, Q, padded_c(g->C), g->K, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
+                                    g->dil_h, g->dil_w);
+        if (mp.ok) big = std::max(big, m32_staged_ws_bytes(mp, g->N, P, Q, g->K));
+        s += big + conv_pmax_bytes(g->N * P * Q, g->K, g->N, P, Q);
     }
     int64_t Cp = padded_c(g->C);
     if (Cp != g->C)
@@ -4303,16 +3601,15 @@ static int conv_fwd_core(const int8_t* x, const int32_t* x_exp, const int8_t* w,
     if (g->C * g->R * g->S > kMaxKred) return ISEG_ERR_UNSUPPORTED;
     if (!ws || ws_bytes < conv_fwd_core_ws(g, out_mode)) return ISEG_ERR_WORKSPACE;
     // ws: [max][per-block max partials][output staging][padded operands]
-    unsigned long long* maxp = (unsigned long long*)ws;
     const int64_t Cp = padded_c(g->C);
-    const HaloPlan hp = halo_plan(g->N, P, Q, Cp, g->K, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
-                                  g->dil_h, g->dil_w);
+    const M32Plan mp = m32_plan(g->N, P, Q, Cp, g->K, (int)g->R, (int)g->S, g->stride_h, g->stride_w, g->dil_h,
+                                g->dil_w);
     char* wp = (char*)ws + 256;
     uint64_t* pmax = nullptr;
     int32_t* acc = (int32_t*)y;
     if (out_mode == ISEG_OUT_Q8) {
         pmax = (uint64_t*)wp;
-        wp += conv_pmax_bytes(g->N * P * Q, g->K, hp, g->N, P, Q);
+        wp += conv_pmax_bytes(g->N * P * Q, g->K, g->N, P, Q);
         acc = (int32_t*)wp;
         size_t big = align256((size_t)(g->N * P * Q * g->K) * 4);
         const size_t s16 = staged_ws_bytes(g->N * P * Q, g->K);
@@ -4320,10 +3617,7 @@ static int conv_fwd_core(const int8_t* x, const int32_t* x_exp, const int8_t* w,
         const DmaPlan dp = dma_plan(g->N * P * Q, (int32_t)g->K, (int32_t)(Cp * g->R * g->S), true);
         const size_t sk = dma_split_bytes(dp, g->N * P * Q, (int32_t)g->K);
         big = big > sk ? big : sk;
-        if (hp.ok) {
-            const size_t sh = halo_staged_ws_bytes(hp, g->N, P, Q, g->K);
-            big = big > sh ? big : sh;
-        }
+        if (mp.ok) big = std::max(big, m32_staged_ws_bytes(mp, g->N, P, Q, g->K));
         wp += big;
     }
     int rc;
@@ -4367,12 +3661,10 @@ static int conv_fwd_core(const int8_t* x, const int32_t* x_exp, const int8_t* w,
     a.R = (int32_t)g->R; a.S = (int32_t)g->S;
     a.sh = g->stride_h; a.sw = g->stride_w; a.ph = g->pad_h; a.pw = g->pad_w;
     a.dh = g->dil_h; a.dw = g->dil_w;
-    const M32Plan mp = m32_plan(g->N, P, Q, Cp, g->K, (int)g->R, (int)g->S, g->stride_h, g->stride_w, g->dil_h,
-                                g->dil_w);
-    if (mp.ok && (((uintptr_t)xs | (uintptr_t)wsrc | (uintptr_t)y) & 15) == 0) {
+    if (mp.ok && (((uintptr_t)xs | (uintptr_t)wsrc | (uintptr_t)y | (uintptr_t)acc) & 15) == 0) {
         conv_plan_set("m32");
         HaloArgs h{};
-        h.src = xs; h.wmat = wsrc; h.out = (int32_t*)y;
+        h.src = xs; h.wmat = wsrc; h.out = (int32_t*)y; h.out16 = (int16_t*)acc;
         h.N = (int32_t)g->N; h.Hs = (int32_t)g->H; h.Ws = (int32_t)g->W; h.Ci = (int32_t)Cp;
         h.Ho = (int32_t)P; h.Wo = (int32_t)Q; h.Nout = (int32_t)g->K;
         h.ph = g->pad_h; h.pw = g->pad_w; h.dh = g->dil_h; h.dw = g->dil_w;
@@ -4382,38 +3674,6 @@ static int conv_fwd_core(const int8_t* x, const int32_t* x_exp, const int8_t* w,
             return launch_ok();
         }
         return m32_q8(mp, h, ISEG_KID_CONV_FWD, x_exp, w_exp, (int8_t*)y, y_exp, pmax, stream);
-    }
-    const PersistPlan pp = persist_plan(g->N, P, Q, Cp, g->K, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
-                                        g->dil_h, g->dil_w);
-    if (pp.ok && (((uintptr_t)xs | (uintptr_t)wsrc | (uintptr_t)y) & 15) == 0) {
-        conv_plan_set("persist");
-        HaloArgs h{};
-        h.src = xs; h.wmat = wsrc; h.out = (int32_t*)y;
-        h.N = (int32_t)g->N; h.Hs = (int32_t)g->H; h.Ws = (int32_t)g->W; h.Ci = (int32_t)Cp;
-        h.Ho = (int32_t)P; h.Wo = (int32_t)Q; h.Nout = (int32_t)g->K;
-        h.ph = g->pad_h; h.pw = g->pad_w; h.dh = g->dil_h; h.dw = g->dil_w;
-        if (out_mode == ISEG_OUT_RAW) {
-            if ((rc = launch_persist(pp, h, EPI_RAW, ISEG_KID_CONV_FWD, stream))) return rc;
-            hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(1), 0, stream, y_exp, x_exp, w_exp);
-            return launch_ok();
-        }
-        return persist_q8(pp, h, ISEG_KID_CONV_FWD, x_exp, w_exp, (int8_t*)y, y_exp, pmax, stream);
-    }
-    if (hp.ok && (((uintptr_t)xs | (uintptr_t)wsrc | (uintptr_t)y | (uintptr_t)acc) & 15) == 0) {
-        conv_plan_set("halo");
-        HaloArgs h{};
-        h.src = xs; h.wmat = wsrc; h.out = acc;
-        h.out16 = out_mode == ISEG_OUT_Q8 ? (int16_t*)acc : nullptr;
-        h.tshift = (uint8_t*)acc + align256((size_t)(a.Mrows * a.Nout) * 2);
-        h.N = (int32_t)g->N; h.Hs = (int32_t)g->H; h.Ws = (int32_t)g->W; h.Ci = (int32_t)Cp;
-        h.Ho = (int32_t)P; h.Wo = (int32_t)Q; h.Nout = (int32_t)g->K;
-        h.ph = g->pad_h; h.pw = g->pad_w; h.dh = g->dil_h; h.dw = g->dil_w;
-        if (out_mode == ISEG_OUT_RAW) {
-            if ((rc = launch_halo(hp, h, EPI_RAW, ISEG_KID_CONV_FWD, stream))) return rc;
-            hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(1), 0, stream, y_exp, x_exp, w_exp);
-            return launch_ok();
-        }
-        return halo_q8(hp, h, ISEG_KID_CONV_FWD, x_exp, w_exp, (int8_t*)y, y_exp, maxp, pmax, a.Mrows, stream);
     }
     if (igemm_dma_ok(a) && ((uintptr_t)y & 15) == 0)
         return igemm_dma_run<MODE_FWD>(a, out_mode, x_exp, w_exp, y, y_exp, pmax, acc, stream);
@@ -4713,13 +3973,10 @@ static size_t conv_bwd_data_core_ws(const iseg_conv_geom* g, int32_t out_mode)
         const DmaPlan dp = dma_plan(g->N * g->H * g->W, (int32_t)g->C, (int32_t)(g->K * g->R * g->S), true);
         const size_t sk = dma_split_bytes(dp, g->N * g->H * g->W, (int32_t)g->C);
         big = big > sk ? big : sk;
-        const HaloPlan hp = halo_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h,
-                                      g->stride_w, g->dil_h, g->dil_w);
-        if (hp.ok) {
-            const size_t sh = halo_staged_ws_bytes(hp, g->N, g->H, g->W, g->C);
-            big = big > sh ? big : sh;
-        }
-        s += big + conv_pmax_bytes(g->N * g->H * g->W, g->C, hp, g->N, g->H, g->W);
+        const M32Plan mp = m32_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
+                                    g->dil_h, g->dil_w);
+        if (mp.ok) big = std::max(big, m32_staged_ws_bytes(mp, g->N, g->H, g->W, g->C));
+        s += big + conv_pmax_bytes(g->N * g->H * g->W, g->C, g->N, g->H, g->W);
     }
     s += kpad_bytes(g);
     return s > s1 ? s : s1;
@@ -4755,16 +4012,13 @@ static int conv_bwd_data_core(const int8_t* dy, const int32_t* dy_exp, const int
         return launch_ok();
     }
     // ws: [max][transposed weights][per-block max partials][output staging]
-    unsigned long long* maxp = (unsigned long long*)ws;
-    const HaloPlan hp = halo_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
-                                  g->dil_h, g->dil_w);
     int8_t* wt_ws = (int8_t*)ws + 256;
     const size_t wt_bytes = align256((size_t)(g->K * g->R * g->S * g->C));
     uint64_t* pmax = nullptr;
     int32_t* acc = (int32_t*)dx;
     if (out_mode == ISEG_OUT_Q8) {
         pmax = (uint64_t*)((char*)ws + 256 + wt_bytes);
-        acc = (int32_t*)((char*)pmax + conv_pmax_bytes(g->N * g->H * g->W, g->C, hp, g->N, g->H, g->W));
+        acc = (int32_t*)((char*)pmax + conv_pmax_bytes(g->N * g->H * g->W, g->C, g->N, g->H, g->W));
     }
     int rc;
     // the caller's transposed weights when they are in the layout a path needs
@@ -4775,11 +4029,11 @@ static int conv_bwd_data_core(const int8_t* dy, const int32_t* dy_exp, const int
     const M32Plan mp = m32_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
                                 g->dil_h, g->dil_w);
     wt = pick_wt(ISEG_WT_CRSK_FLIP);
-    if (mp.ok && (((uintptr_t)dy | (uintptr_t)wt | (uintptr_t)dx) & 15) == 0) {
+    if (mp.ok && (((uintptr_t)dy | (uintptr_t)wt | (uintptr_t)dx | (uintptr_t)acc) & 15) == 0) {
         conv_plan_set("m32");
         if (wt != wt_in && (rc = launch_w_transpose(w, wt_ws, g->K, g->R * g->S, g->C, true, stream))) return rc;
         HaloArgs h{};
-        h.src = dy; h.wmat = wt; h.out = (int32_t*)dx;
+        h.src = dy; h.wmat = wt; h.out = (int32_t*)dx; h.out16 = (int16_t*)acc;
         h.N = (int32_t)g->N; h.Hs = (int32_t)P; h.Ws = (int32_t)Q; h.Ci = (int32_t)g->K;
         h.Ho = (int32_t)g->H; h.Wo = (int32_t)g->W; h.Nout = (int32_t)g->C;
         h.ph = g->dil_h * (int32_t)(g->R - 1) - g->pad_h; h.pw = g->dil_w * (int32_t)(g->S - 1) - g->pad_w;
@@ -4790,48 +4044,6 @@ static int conv_bwd_data_core(const int8_t* dy, const int32_t* dy_exp, const int
             return launch_ok();
         }
         return m32_q8(mp, h, ISEG_KID_CONV_BWD_DATA, dy_exp, w_exp, (int8_t*)dx, dx_exp, pmax, stream);
-    }
-    const PersistPlan pp = persist_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h,
-                                        g->stride_w, g->dil_h, g->dil_w);
-    wt = pick_wt(ISEG_WT_CRSK_FLIP);
-    if (pp.ok && (((uintptr_t)dy | (uintptr_t)wt | (uintptr_t)dx) & 15) == 0) {
-        conv_plan_set("persist");
-        // stride 1: dx = conv(dy, flipped W^T) with padding dil (R - 1) - pad
-        if (wt != wt_in && (rc = launch_w_transpose(w, wt_ws, g->K, g->R * g->S, g->C, true, stream))) return rc;
-        HaloArgs h{};
-        h.src = dy; h.wmat = wt; h.out = (int32_t*)dx;
-        h.N = (int32_t)g->N; h.Hs = (int32_t)P; h.Ws = (int32_t)Q; h.Ci = (int32_t)g->K;
-        h.Ho = (int32_t)g->H; h.Wo = (int32_t)g->W; h.Nout = (int32_t)g->C;
-        h.ph = g->dil_h * (int32_t)(g->R - 1) - g->pad_h; h.pw = g->dil_w * (int32_t)(g->S - 1) - g->pad_w;
-        h.dh = g->dil_h; h.dw = g->dil_w;
-        if (out_mode == ISEG_OUT_RAW) {
-            if ((rc = launch_persist(pp, h, EPI_RAW, ISEG_KID_CONV_BWD_DATA, stream))) return rc;
-            hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(1), 0, stream, dx_exp, dy_exp, w_exp);
-            return launch_ok();
-        }
-        return persist_q8(pp, h, ISEG_KID_CONV_BWD_DATA, dy_exp, w_exp, (int8_t*)dx, dx_exp, pmax, stream);
-    }
-    wt = pick_wt(ISEG_WT_CRSK_FLIP);
-    if (hp.ok && (((uintptr_t)dy | (uintptr_t)wt | (uintptr_t)dx | (uintptr_t)acc) & 15) == 0) {
-        conv_plan_set("halo");
-        // stride 1: dx = conv(dy, flipped W^T) with padding dil (R - 1) - pad
-        if (wt != wt_in && (rc = launch_w_transpose(w, wt_ws, g->K, g->R * g->S, g->C, true, stream))) return rc;
-        HaloArgs h{};
-        h.src = dy; h.wmat = wt; h.out = acc;
-        const int64_t rows = g->N * g->H * g->W;
-        h.out16 = out_mode == ISEG_OUT_Q8 ? (int16_t*)acc : nullptr;
-        h.tshift = (uint8_t*)acc + align256((size_t)(rows * g->C) * 2);
-        h.N = (int32_t)g->N; h.Hs = (int32_t)P; h.Ws = (int32_t)Q; h.Ci = (int32_t)g->K;
-        h.Ho = (int32_t)g->H; h.Wo = (int32_t)g->W; h.Nout = (int32_t)g->C;
-        h.ph = g->dil_h * (int32_t)(g->R - 1) - g->pad_h; h.pw = g->dil_w * (int32_t)(g->S - 1) - g->pad_w;
-        h.dh = g->dil_h; h.dw = g->dil_w;
-        if (out_mode == ISEG_OUT_RAW) {
-            if ((rc = launch_halo(hp, h, EPI_RAW, ISEG_KID_CONV_BWD_DATA, stream))) return rc;
-            hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(1), 0, stream, dx_exp, dy_exp, w_exp);
-            return launch_ok();
-        }
-        return halo_q8(hp, h, ISEG_KID_CONV_BWD_DATA, dy_exp, w_exp, (int8_t*)dx, dx_exp, maxp, pmax, rows,
-                       stream);
     }
     const TconvPlan tp = tconv_plan(g);
     if (tp.ok)
@@ -5208,11 +4420,7 @@ extern "C" int32_t iseg_conv_bwd_data_wt_kind(const iseg_conv_geom* g)
     if (conv_long_kred(true, g)) return kred_dma_plan(true, g).ok ? ISEG_WT_CRSK : ISEG_WT_NONE;
     const M32Plan mp = m32_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
                                 g->dil_h, g->dil_w);
-    const PersistPlan pp = persist_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h,
-                                        g->stride_w, g->dil_h, g->dil_w);
-    const HaloPlan hp = halo_plan(g->N, g->H, g->W, g->K, g->C, (int)g->R, (int)g->S, g->stride_h, g->stride_w,
-                                  g->dil_h, g->dil_w);
-    return (mp.ok || pp.ok || hp.ok) ? ISEG_WT_CRSK_FLIP : ISEG_WT_CRSK;
+    return mp.ok ? ISEG_WT_CRSK_FLIP : ISEG_WT_CRSK;
 }
 
 extern "C" int iseg_weight_transpose_multi(const iseg_wt_desc* descs, int32_t n_desc, int64_t total_tiles,
