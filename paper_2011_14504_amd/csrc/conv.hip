@@ -224,119 +224,6 @@ __global__ __launch_bounds__(256) void k_conv_igemm(IgemmArgs a)
     if (a.pmax) block_store_max_u64(mx, a.pmax);
 }
 
-// Implicit GEMM for Ci % 64 == 0: the k-loop runs tap-major in 64-channel
-// chunks, so each step is one tap and one contiguous channel chunk.  Source
-// offsets of a thread's rows are recomputed only when the tap changes; LDS
-// is double-buffered (one barrier per step) and the next step's global
-// loads are in flight while the current step's MFMAs run.
-template <int MODE, int BM, int BN>
-__global__ __launch_bounds__(256) void k_conv_igemm_tap(IgemmArgs a)
-{
-    constexpr int PA = BM * 4 / 256;
-    constexpr int PB = BN * 4 / 256;
-    constexpr int WM = BM / 2, WN = BN / 2;
-    constexpr int TM = WM / 16, TN = WN / 16;
-    __shared__ __attribute__((aligned(16))) int8_t As[2][BM * ROW];
-    __shared__ __attribute__((aligned(16))) int8_t Bs[2][BN * ROW];
-
-    const int tid = threadIdx.x;
-    const int part = tid & 3;
-    const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int n0 = blockIdx.y * BN;
-    const int nchunk = a.Ci / BK;
-    const int nk = a.R * a.S * nchunk;
-
-    RowPix rp[PA];
-#pragma unroll
-    for (int j = 0; j < PA; j++) rp[j] = row_pix(a, m0 + ((tid >> 2) + 64 * j));
-    const int8_t* brow[PB];
-#pragma unroll
-    for (int j = 0; j < PB; j++) {
-        int n = n0 + (tid >> 2) + 64 * j;
-        brow[j] = n < a.Nout ? a.wmat + (int64_t)n * a.Kred + part * 16 : nullptr;
-    }
-
-    int64_t soff[PA];
-    auto set_tap = [&](int tap) {
-        int r = tap / a.S, s = tap - (tap / a.S) * a.S;
-#pragma unroll
-        for (int j = 0; j < PA; j++) {
-            int64_t sp = src_pixel<MODE>(a, rp[j], r, s);
-            soff[j] = sp < 0 ? -1 : sp * a.Ci + part * 16;
-        }
-    };
-    int4 ra[PA], rb[PB];
-    auto load = [&](int kb, int cc) {
-#pragma unroll
-        for (int j = 0; j < PA; j++)
-            ra[j] = soff[j] >= 0 ? *(const int4*)(a.src + soff[j] + cc * BK) : make_int4(0, 0, 0, 0);
-#pragma unroll
-        for (int j = 0; j < PB; j++)
-            rb[j] = brow[j] ? *(const int4*)(brow[j] + (int64_t)kb * BK) : make_int4(0, 0, 0, 0);
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int j = 0; j < PA; j++) *(int4*)&As[buf][((tid >> 2) + 64 * j) * ROW + part * 16] = ra[j];
-#pragma unroll
-        for (int j = 0; j < PB; j++) *(int4*)&Bs[buf][((tid >> 2) + 64 * j) * ROW + part * 16] = rb[j];
-    };
-
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int lrow = lane & 15, lk = (lane >> 4) * 16;
-    v4i acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++) acc[i][j] = (v4i){0, 0, 0, 0};
-
-    int tap = 0, cc = 0;
-    set_tap(0);
-    load(0, 0);
-    store(0);
-    __syncthreads();
-    for (int kb = 0; kb < nk; kb++) {
-        const bool more = kb + 1 < nk;
-        if (more) {
-            if (++cc == nchunk) { cc = 0; set_tap(++tap); }
-            load(kb + 1, cc);
-        }
-        const int8_t* A = As[kb & 1];
-        const int8_t* B = Bs[kb & 1];
-        v4i fa[TM], fb[TN];
-#pragma unroll
-        for (int i = 0; i < TM; i++) fa[i] = *(const v4i*)&A[(wm * WM + i * 16 + lrow) * ROW + lk];
-#pragma unroll
-        for (int j = 0; j < TN; j++) fb[j] = *(const v4i*)&B[(wn * WN + j * 16 + lrow) * ROW + lk];
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-            for (int j = 0; j < TN; j++)
-                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        if (more) store((kb + 1) & 1);
-        __syncthreads();
-    }
-
-    uint64_t mx = 0;
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++) {
-            int n = n0 + wn * WN + j * 16 + lrow;
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                int64_t m = m0 + wm * WM + i * 16 + (lane >> 4) * 4 + e;
-                if (m < a.Mrows && n < a.Nout) {
-                    int32_t v = acc[i][j][e];
-                    a.out[m * a.Nout + n] = v;
-                    uint64_t av = v < 0 ? (uint64_t)(-(int64_t)v) : (uint64_t)v;
-                    mx = av > mx ? av : mx;
-                }
-            }
-        }
-    if (a.pmax) block_store_max_u64(mx, a.pmax);
-}
-
 // ---------------------------------------------------------------------------
 // Implicit GEMM with direct-to-LDS loads (Ci % 64 == 0, Nout % BN == 0).
 //
@@ -450,7 +337,16 @@ __device__ __forceinline__ void wait_vm_lgkm0()
 // ahead, so the ds_reads of step kb + 1 run under the MFMAs of step kb; once a
 // step's fragments are in registers its LDS stage is free and receives the
 // DMA of step kb + kStages, which keeps kStages - 1 steps of loads in flight.
-template <int MODE, int BM, int BN, int EPI, bool PIPE>
+//
+// FLAT (raw sums only): Ci and Nout of any multiple of 16 / any count.  Steps are
+// 64 consecutive entries of the flat (tap, channel) reduction; each 16-byte
+// piece lies in one tap, so a lane follows its own tap and channel, and pieces
+// past the reduction or past Nout read the zero page.  The synchronous
+// single-buffered kernel it replaces took 1.4 us per step of 64: 96 -> 160
+// channels, 3 x 97 x 65, stride 2: 25.7 -> 18.1 us forward and 42.7 -> 32.8
+// backward-data with their requantization; 208 -> 336 at 8 x 32 x 32: 44.8 -> 33.5
+// and 73.2 -> 39.9.
+template <int MODE, int BM, int BN, int EPI, bool PIPE, bool FLAT>
 __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
 {
     constexpr int WM = BM / 2, WN = BN / 2;  // 2 x 2 waves
@@ -469,14 +365,14 @@ __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
     if ((nbx & 7) == 0) bx = (bx & 7) * (nbx >> 3) + (bx >> 3);
     const int64_t m0 = (int64_t)bx * BM;
     const int n0 = blockIdx.y * BN;
-    const int nchunk = a.Ci / BK;
+    const int nchunk = FLAT ? 1 : a.Ci / BK;
     // the taps this tile runs (all but those reading only padding).  Steps
     // are (tap, chunk) pairs, tap-major; a split (blockIdx.z of gridDim.z)
     // owns the same step range [kb0, kb1) in every tile, so the blocks of one
     // split read one slice of W (shared in L2), and runs the live steps in it.
     const int RS = a.R * a.S;
     const int64_t vr = a.Mrows - m0;
-    const uint64_t tmask = live_taps<MODE>(a, m0, vr < BM ? (int)vr : BM);
+    const uint64_t tmask = FLAT ? 0ull : live_taps<MODE>(a, m0, vr < BM ? (int)vr : BM);
     // When every tile skips a tap (tap_balance, decided on the host) the live
     // steps themselves are split evenly: the splits of one tile then stay
     // balanced, at the cost of W slices that differ between tiles.
@@ -484,7 +380,9 @@ __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
     const int kb0 = (int)((int64_t)nk_full * blockIdx.z / gridDim.z);
     const int kb1 = (int)((int64_t)nk_full * (blockIdx.z + 1) / gridDim.z);
     int nk = 0;
-    if (a.tap_balance) {
+    if (FLAT) {
+        nk = (a.Kred + BK - 1) / BK;
+    } else if (a.tap_balance) {
         nk = kb1 - kb0;
     } else {
         for (int t = 0; t < RS; t++) {
@@ -511,7 +409,7 @@ __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
 #pragma unroll
         for (int j = 0; j < NA; j++) {
             const int64_t sp = src_pixel<MODE>(a, rp[j], r, s);
-            soff[j] = sp < 0 ? -1 : sp * a.Ci + part * 16;
+            soff[j] = sp < 0 ? -1 : sp * a.Ci + (FLAT ? 0 : part * 16);
         }
     };
     // (tap, chunk) of the step being issued: balanced, the (kb0 / nchunk)-th
@@ -526,8 +424,28 @@ __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
         ltap = rest ? ltap + 1 + __builtin_ctzll(rest) : RS;
         lcc = 0;
     }
+    // FLAT: the tap and channel of this lane's 16 reduction entries
+    int ftap = FLAT ? part * 16 / a.Ci : 0, fc = FLAT ? part * 16 - (part * 16 / a.Ci) * a.Ci : 0;
     auto issue = [&](int kb) {               // kb: step within this split
         int8_t* st = smem + (kb % kStages) * (SA + SB);
+        if constexpr (FLAT) {
+            const bool live = ftap < RS;     // inside the reduction
+#pragma unroll
+            for (int j = 0; j < NA; j++)
+                dma16(live && soff[j] >= 0 ? (const void*)(a.src + soff[j] + fc) : (const void*)g_conv_zero,
+                      st + (wave + 4 * j) * 1024);
+#pragma unroll
+            for (int j = 0; j < NB; j++)
+                dma16(live && n0 + 16 * (wave + 4 * j) + rin < a.Nout ? (const void*)(brow[j] + kb * BK)
+                                                                      : (const void*)g_conv_zero,
+                      st + SA + (wave + 4 * j) * 1024);
+            fc += BK;
+            if (fc >= a.Ci) {
+                do { fc -= a.Ci; ++ftap; } while (fc >= a.Ci);
+                if (ftap < RS) set_tap(ftap);
+            }
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < NA; j++) {
             const void* g = soff[j] >= 0 ? (const void*)(a.src + soff[j] + lcc * BK) : (const void*)g_conv_zero;
@@ -591,7 +509,7 @@ __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
         issue_any(kb + kStages);
     };
 
-    if (nk > 0) set_tap(ltap);
+    if (nk > 0) set_tap(FLAT ? (ftap < RS ? ftap : 0) : ltap);
 #pragma unroll
     for (int p = 0; p < kStages; p++) issue_any(p);
     uint64_t gmax = 0;
@@ -656,7 +574,7 @@ __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
                     const int row = wm * WM + i * 16 + lpart * 4 + e;
-                    if (row < vrows) {
+                    if (row < vrows && (!FLAT || n < a.Nout)) {
                         const int32_t v = acc[i][j][e];
                         a.out[(m0 + row) * a.Nout + n] = v;
                         const uint32_t av = (uint32_t)(v < 0 ? -v : v);
@@ -1738,9 +1656,9 @@ int launch_dma_t(const IgemmArgs& a, int splits, hipStream_t s, int64_t* nblk)
     const size_t epi_lds = EPI == EPI_STAGE16 ? (size_t)BM * (BN + 8) * 2 : EPI == EPI_Q8 ? (size_t)BM * (BN + 16) : 0;
     lds = lds > epi_lds ? lds : epi_lds;
     constexpr bool pipe = ISEG_IGEMM_PIPE != 0;
-    if (lds > 65536 && !lds_limit((const void*)k_conv_igemm_dma<MODE, BM, BN, EPI, pipe>, lds))
+    if (lds > 65536 && !lds_limit((const void*)k_conv_igemm_dma<MODE, BM, BN, EPI, pipe, false>, lds))
         return ISEG_ERR_DEVICE;
-    ISEG_TIMED_LAUNCH(kid, s, (k_conv_igemm_dma<MODE, BM, BN, EPI, pipe>), grid, dim3(256), lds, s, a);
+    ISEG_TIMED_LAUNCH(kid, s, (k_conv_igemm_dma<MODE, BM, BN, EPI, pipe, false>), grid, dim3(256), lds, s, a);
     *nblk = (int64_t)grid.x * grid.y;
     return launch_ok();
 }
@@ -1807,25 +1725,31 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const int32_t* part, int3
     if (pmax) block_store_max_u64(mx, pmax);
 }
 
-// int32 sums (+ per-block max partials) of any shape through the generic or
-// tap kernels (the direct-to-LDS kernel is driven by igemm_dma_run)
+template <int MODE, int BM, int BN>
+int launch_flat(const IgemmArgs& a, hipStream_t s, int64_t* nblk)
+{
+    constexpr size_t lds = (size_t)kStages * (BM + BN) * 64;
+    const int kid = MODE == MODE_FWD ? ISEG_KID_CONV_FWD : ISEG_KID_CONV_BWD_DATA;
+    dim3 grid((unsigned)ceil_div64(a.Mrows, BM), (unsigned)ceil_div64(a.Nout, BN));
+    if (!lds_limit((const void*)k_conv_igemm_dma<MODE, BM, BN, EPI_RAW, true, true>, lds)) return ISEG_ERR_DEVICE;
+    ISEG_TIMED_LAUNCH(kid, s, (k_conv_igemm_dma<MODE, BM, BN, EPI_RAW, true, true>), grid, dim3(256), lds, s, a);
+    *nblk = (int64_t)grid.x * grid.y;
+    return launch_ok();
+}
+
+// int32 sums (+ per-block max partials) of any shape through the flat
+// direct-to-LDS or the generic kernel.  64 x 64 tiles until 128-row tiles fill the chip:
+// 208 -> 336 channels at 8 x 32 x 32 (192 tiles of 128 x 128) 33.6 us against 39.6,
+// 304 -> 256 at 16 x 32 x 32 (256 tiles) 52.0 against 50.3, 96 -> 160 at 8 x 64 x 64
+// (512) 40.1 against 35.7.
 template <int MODE>
 int launch_igemm(const IgemmArgs& a, hipStream_t s, int64_t* nblk)
 {
     *nblk = 0;
-    if (a.Mrows > 0 && a.Nout > 0 && a.Ci % 64 == 0 &&
+    if (a.Mrows > 0 && a.Nout > 0 && a.Ci % 16 == 0 && a.Mrows < ((int64_t)1 << 31) &&
         (((uintptr_t)a.src | (uintptr_t)a.wmat) & 15) == 0) {
-        const int kid = MODE == MODE_FWD ? ISEG_KID_CONV_FWD : ISEG_KID_CONV_BWD_DATA;
-        unsigned gx = (unsigned)ceil_div64(a.Mrows, 128);
-        if (a.Nout > 64) {
-            dim3 grid(gx, (unsigned)ceil_div64(a.Nout, 128));
-            ISEG_TIMED_LAUNCH(kid, s, (k_conv_igemm_tap<MODE, 128, 128>), grid, dim3(256), 0, s, a);
-            *nblk = (int64_t)grid.x * grid.y;
-        } else {
-            ISEG_TIMED_LAUNCH(kid, s, (k_conv_igemm_tap<MODE, 128, 64>), dim3(gx, 1), dim3(256), 0, s, a);
-            *nblk = gx;
-        }
-        return launch_ok();
+        if (ceil_div64(a.Mrows, 128) * ceil_div64(a.Nout, 128) < 256) return launch_flat<MODE, 64, 64>(a, s, nblk);
+        return a.Nout > 64 ? launch_flat<MODE, 128, 128>(a, s, nblk) : launch_flat<MODE, 128, 64>(a, s, nblk);
     }
     return launch_igemm_generic<MODE>(a, s, nblk);
 }
@@ -3561,7 +3485,7 @@ bool geom_ok(const iseg_conv_geom* g, int64_t* P, int64_t* Q)
 // room for per-block max partials of any path the output of rows x cols can take
 size_t conv_pmax_bytes(int64_t rows, int64_t cols, int64_t N, int64_t Ho, int64_t Wo)
 {
-    const int64_t nb = ceil_div64(rows, 128) * ceil_div64(cols, 64);
+    const int64_t nb = ceil_div64(rows, 64) * ceil_div64(cols, 64);
     const int64_t nm = N * ceil_div64(Ho, 8) * ceil_div64(Wo, kM32TW) * ceil_div64(cols, 64);
     return align256((size_t)(nb > nm ? nb : nm) * 8);
 }
