@@ -2281,14 +2281,18 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_tap(WgradArgs a)
         }
 }
 
-// Backward-weight with transposing LDS reads (C % 64 == 0, K % 16 == 0).
+// Backward-weight with transposing LDS reads (C % 16 == 0, K % 16 == 0).
 // Tiles are staged in their natural layout -- [pixel][channel] rows of dy and
 // of the tap-shifted x -- with plain 16-byte copies, and the MFMA operands
 // (16 consecutive pixels of one channel per lane) come out of ds_read_b64_tr_b8:
 // within a 16-lane group, output lane j's byte i is byte (j mod 8) of source
 // lane 2i + j/8, so source lane 2i + h pointing at (pixel i, channels c0 + 8h)
 // hands lane j channel c0 + j of pixels 0..7.  A block owns BM output
-// channels, TAPS filter taps and one 64-channel chunk of C.
+// channels, TAPS filter taps and one 64-channel chunk of C (channels past C and K
+// read as zero and are not stored).
+// Channel counts off 64 took an atomic kernel with a byte transpose in registers,
+// a fill, an absolute-max pass and a requant: 96 -> 160 channels, 3 x 97 x 65,
+// stride 2: 36.6 -> 23.4 us; 208 -> 336 at 8 x 64 x 64: 269 -> 73 us.
 typedef int v2i_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ v4i tr8_frag(const int8_t* lds_rows, int row_bytes, int col0, int lane)
@@ -2319,7 +2323,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_tr(WgradArgs a)
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int nch = a.C / 64;
+    const int nch = (a.C + 63) / 64;
     const int tg = blockIdx.x / nch;
     const int c0 = (blockIdx.x - tg * nch) * 64;
     const int k0 = blockIdx.y * BM;
@@ -2341,6 +2345,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_tr(WgradArgs a)
     }
     // load cursor: coordinates of this thread's pixel, advanced 64 pixels (dp
     // rows and dq columns) per step
+    const bool cok = c0 + part * 16 < a.C;
     int32_t pix = pbeg + prow;
     const int32_t PQ = a.P * a.Q;
     int32_t pn = pix / PQ;
@@ -2353,14 +2358,14 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_tr(WgradArgs a)
     auto load = [&](int4* pa, int4* pb) {
         const bool ok = pix < pend;
 #pragma unroll
-        for (int j = 0; j < PA; j++) {          // k0 + part * 16 + 64 j < K: K % BM == 0
+        for (int j = 0; j < PA; j++) {
             const uint32_t off = (uint32_t)pix * (uint32_t)a.K + (uint32_t)(k0 + part * 16 + 64 * j);
-            pa[j] = ok ? *(const int4*)(a.dy + off) : make_int4(0, 0, 0, 0);
+            pa[j] = ok && k0 + part * 16 + 64 * j < a.K ? *(const int4*)(a.dy + off) : make_int4(0, 0, 0, 0);
         }
 #pragma unroll
         for (int t = 0; t < TAPS; t++) {
             const int ih = pp * a.sh + dr[t], iw = pq * a.sw + ds[t];
-            const bool v = ok && tok[t] && (uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W;
+            const bool v = ok && cok && tok[t] && (uint32_t)ih < (uint32_t)a.H && (uint32_t)iw < (uint32_t)a.W;
             // unsigned (wrapping) arithmetic: an offset out of range is never loaded
             const uint32_t off = (uint32_t)pn * HWC + (uint32_t)ih * WC + (uint32_t)iw * (uint32_t)a.C +
                                  (uint32_t)(c0 + part * 16);
@@ -2426,7 +2431,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_tr(WgradArgs a)
             const int colt = wn * WN + j * 16 + (lane & 15);
             const int t = colt >> 6;
             const int tap = tg * TAPS + t;
-            if (tap >= a.R * a.S) continue;
+            if (tap >= a.R * a.S || c0 + (colt & 63) >= a.C) continue;
             const int64_t col = (int64_t)tap * a.C + c0 + (colt & 63);
 #pragma unroll
             for (int e = 0; e < 4; e++) {
@@ -3351,28 +3356,31 @@ int launch_wgrad_rows(WgradArgs a, int64_t N, int32_t* part, uint64_t* pmax, int
 }
 
 // the transposed-operand kernel over split pixel ranges: int32 partials per
-// split stored into `part`, summed like the all-taps kernel's (C % 64 == 0,
-// K % 64 == 0, 16-byte aligned operands)
+// split stored into `part`, summed like the all-taps kernel's (C % 16 == 0,
+// K % 16 == 0, 16-byte aligned operands)
 bool wgrad_tr_ok(const WgradArgs& a)
 {
     const int64_t nimg = a.P > 0 && a.Q > 0 ? a.NPQ / ((int64_t)a.P * a.Q) : 0;
-    return a.NPQ > 0 && a.C % 64 == 0 && a.K % 64 == 0 && (((uintptr_t)a.x | (uintptr_t)a.dy) & 15) == 0 &&
+    return a.NPQ > 0 && a.C % 16 == 0 && a.K % 16 == 0 && (((uintptr_t)a.x | (uintptr_t)a.dy) & 15) == 0 &&
            nimg * a.H * a.W * a.C < ((int64_t)1 << 31) && a.NPQ * a.K < ((int64_t)1 << 31);
 }
 
+// output channels of a tile: 128 unless the last one would be half empty
+int wgrad_tr_bm(int32_t K) { return K % 128 == 0 || K % 128 > 64 ? 128 : 64; }
+
 int64_t wgrad_tr_splits(const WgradArgs& a, int64_t* pps)
 {
-    const int BMt = a.K % 128 == 0 ? 128 : 64;
+    const int BMt = wgrad_tr_bm(a.K);
     const int RS = a.R * a.S;
     const int TAPS = RS > 1 ? 2 : 1;
     const int ntg = (RS + TAPS - 1) / TAPS;
-    const int64_t tiles = (int64_t)ntg * (a.C / 64) * (a.K / BMt);
+    const int64_t tiles = (int64_t)ntg * ceil_div64(a.C, 64) * ceil_div64(a.K, BMt);
     return wgrad_splits(a.NPQ, tiles, pps);
 }
 
 size_t wgrad_tr_part_bytes(int64_t NPQ, int64_t K, int64_t C, int64_t RS)
 {
-    if (NPQ <= 0 || C % 64 || K % 64) return 0;
+    if (NPQ <= 0 || C % 16 || K % 16) return 0;
     WgradArgs a{};
     a.NPQ = NPQ; a.K = (int32_t)K; a.C = (int32_t)C; a.R = (int32_t)RS; a.S = 1;
     int64_t pps;
@@ -3384,13 +3392,13 @@ size_t wgrad_tr_part_bytes(int64_t NPQ, int64_t K, int64_t C, int64_t RS)
 
 int launch_wgrad_tr_split(WgradArgs a, int32_t* part, uint64_t* pmax, int64_t* npmax, hipStream_t s, int* qg)
 {
-    const int BMt = a.K % 128 == 0 ? 128 : 64;
+    const int BMt = wgrad_tr_bm(a.K);
     const int RS = a.R * a.S;
     const int TAPS = RS > 1 ? 2 : 1;
     const int ntg = (RS + TAPS - 1) / TAPS;
     const int64_t splits = wgrad_tr_splits(a, &a.pix_per_split);
     a.part = part;
-    dim3 grid((unsigned)(ntg * (a.C / 64)), (unsigned)(a.K / BMt), (unsigned)splits);
+    dim3 grid((unsigned)(ntg * ceil_div64(a.C, 64)), (unsigned)ceil_div64(a.K, BMt), (unsigned)splits);
     if (BMt == 128 && TAPS == 2)
         hipLaunchKernelGGL((k_conv_wgrad_tr<128, 2>), grid, dim3(256), 0, s, a);
     else if (BMt == 128)
@@ -3407,13 +3415,13 @@ int launch_wgrad_tr_split(WgradArgs a, int32_t* part, uint64_t* pmax, int64_t* n
 int launch_wgrad(WgradArgs a, hipStream_t s)
 {
     if (wgrad_tr_ok(a)) {
-        const int BMt = a.K % 128 == 0 ? 128 : 64;
+        const int BMt = wgrad_tr_bm(a.K);
         const int RS = a.R * a.S;
         const int TAPS = RS > 1 ? 2 : 1;
         const int ntg = (RS + TAPS - 1) / TAPS;
-        int64_t tiles = (int64_t)ntg * (a.C / 64) * (a.K / BMt);
+        int64_t tiles = (int64_t)ntg * ceil_div64(a.C, 64) * ceil_div64(a.K, BMt);
         int64_t splits = wgrad_splits(a.NPQ, tiles, &a.pix_per_split);
-        dim3 grid((unsigned)(ntg * (a.C / 64)), (unsigned)(a.K / BMt), (unsigned)splits);
+        dim3 grid((unsigned)(ntg * ceil_div64(a.C, 64)), (unsigned)ceil_div64(a.K, BMt), (unsigned)splits);
         if (BMt == 128 && TAPS == 2)
             ISEG_TIMED_LAUNCH(ISEG_KID_CONV_WGRAD, s, (k_conv_wgrad_tr<128, 2>), grid, dim3(256), 0, s, a);
         else if (BMt == 128)

@@ -1,6 +1,7 @@
 """Convs whose channel counts are multiples of 16 but not of the tiles, and any
-number of output channels (the flat direct-to-LDS kernel): steps that straddle taps, several taps per step, ragged reductions,
-rows and columns, strides and dilations, every tile size, both directions
+number of output channels (the flat direct-to-LDS kernel and the split weight
+gradient): steps that straddle taps, several taps per step, ragged reductions,
+rows and columns, strides and dilations, every tile size, all three directions
 and output modes against exact library sums."""
 import numpy as np
 import pytest
@@ -45,7 +46,9 @@ def test_conv_flat(orc, case):
     ref = ref.cpu().numpy().astype(np.int64).reshape(N, P, Q, K)
     dy = torch.from_numpy(synth.int_codes(62, ref.shape, -128, 127)).to(dev)
     dxp = torch.zeros_like(xp)
+    gref = torch.zeros((K, R, R, C), dtype=torch.float64, device=dev)
     for r, s, hs, ws, P, Q in _taps(H, W, R, st, pad, dil):
+        gref[:, r, s] = dy.double().reshape(-1, K).t().contiguous() @ xp[:, hs, ws].reshape(-1, C)
         dxp[:, hs, ws] += (dy.double().reshape(-1, K) @ w[:, r, s].double()).view(N, P, Q, C)
     dref = dxp[:, pad:pad + H, pad:pad + W].cpu().numpy().astype(np.int64)
     for mode in (iseg.ISEG_OUT_RAW, iseg.ISEG_OUT_Q8):
@@ -53,3 +56,10 @@ def test_conv_flat(orc, case):
                               (*iseg.conv_bwd_data(dy, e[0], w, e[1], x.shape, st, pad, dil, mode), dref)):
             r, re = (want, -16) if mode == iseg.ISEG_OUT_RAW else orc.requant(want, -16, 8)
             assert np.array_equal(out.cpu().numpy().astype(np.int64), r) and int(oe.item()) == re
+    g, ge = iseg.conv_bwd_weight(dy, e[0], x, e[1], w.shape, st, pad, dil, iseg.ISEG_G_RAW)
+    gref = gref.cpu().numpy().astype(np.int64)
+    assert K % 16 or iseg.iseg_conv_last_plan() in ("wgrad_tr", "wgrad_rows")
+    assert np.array_equal(g.cpu().numpy(), gref) and int(ge.item()) == -16
+    g, ge = iseg.conv_bwd_weight(dy, e[0], x, e[1], w.shape, st, pad, dil, seed=5, tensor_id=16, step=2)
+    r, re = orc.requant(gref, -16, 8, stochastic=True, keep_scale=True, seed=5, tensor_id=16, step=2)
+    assert np.array_equal(g.cpu().numpy().astype(np.int64), r) and int(ge.item()) == re
