@@ -170,7 +170,8 @@ def _ptr(t):
         return None
     if _REC is not None:
         _REC.keep.append(t)          # a recorded call's buffer stays allocated
-    return C.c_void_p(t.data_ptr())
+        return C.c_void_p(t.data_ptr())
+    return t.data_ptr()              # the declared argument types convert it
 
 
 _raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else None
@@ -189,7 +190,7 @@ def _stream_handle(dev_index=None):
 
 
 def _stream():
-    return C.c_void_p(_stream_handle())
+    return C.c_void_p(_stream_handle()) if _REC is not None else _stream_handle()
 
 
 def _check(rc, name):
@@ -198,7 +199,7 @@ def _check(rc, name):
 
 
 def _ws_tuple(ws):
-    return (_ptr(ws), C.c_size_t(ws.numel() if ws is not None else 0))
+    return (_ptr(ws), ws.numel() if ws is not None else 0)
 
 
 # --------------------------------------------------------------------------
@@ -604,13 +605,20 @@ class Workspace:
         self.device = device
         self.zeroed = zeroed
         self.buf = None
+        self.views = {}              # recent sizes' views of buf (a slice costs 2 us of host time)
 
     def get(self, nbytes):
         nbytes = max(int(nbytes), 256)
-        if self.buf is None or self.buf.numel() < nbytes:
-            alloc = torch.zeros if self.zeroed else torch.empty
-            self.buf = alloc(nbytes, dtype=torch.uint8, device=self.device)
-        return self.buf[:nbytes]
+        v = self.views.get(nbytes)
+        if v is None:
+            if self.buf is None or self.buf.numel() < nbytes:
+                alloc = torch.zeros if self.zeroed else torch.empty
+                self.buf = alloc(nbytes, dtype=torch.uint8, device=self.device)
+                self.views = {}
+            elif len(self.views) >= 64:
+                self.views = {}
+            v = self.views[nbytes] = self.buf[:nbytes]
+        return v
 
 
 _WS = {}
