@@ -16,6 +16,8 @@ CASES = [
     (1, 17, 13, 80, 48, 5, 1, 2, 1), (3, 13, 9, 96, 160, 3, 2, 1, 1), (1, 20, 21, 144, 64, 3, 1, 4, 4),
     (1, 15, 15, 208, 16, 1, 3, 0, 1), (2, 8, 8, 64, 19, 1, 1, 0, 1), (2, 9, 9, 128, 150, 3, 1, 1, 1),
     (1, 65, 63, 32, 48, 3, 1, 1, 1), (1, 7, 7, 256, 21, 1, 1, 0, 1), (1, 11, 6, 336, 80, 2, 1, 0, 2),
+    # input channels padded to 16
+    (2, 9, 11, 20, 32, 3, 2, 1, 1), (1, 10, 12, 36, 48, 3, 1, 1, 1),
     # enough tiles for the large ones, ragged both ways
     (9, 65, 63, 80, 144, 3, 1, 1, 1), (17, 45, 45, 16, 272, 1, 1, 0, 1), (33, 33, 33, 112, 96, 3, 2, 1, 1),
 ]
@@ -58,7 +60,7 @@ def test_conv_flat(orc, case):
             assert np.array_equal(out.cpu().numpy().astype(np.int64), r) and int(oe.item()) == re
     g, ge = iseg.conv_bwd_weight(dy, e[0], x, e[1], w.shape, st, pad, dil, iseg.ISEG_G_RAW)
     gref = gref.cpu().numpy().astype(np.int64)
-    assert K % 16 or iseg.iseg_conv_last_plan() in ("wgrad_tr", "wgrad_rows")
+    assert K % 16 or C % 16 or iseg.iseg_conv_last_plan() in ("wgrad_tr", "wgrad_rows")
     assert np.array_equal(g.cpu().numpy(), gref) and int(ge.item()) == -16
     g, ge = iseg.conv_bwd_weight(dy, e[0], x, e[1], w.shape, st, pad, dil, seed=5, tensor_id=16, step=2)
     r, re = orc.requant(gref, -16, 8, stochastic=True, keep_scale=True, seed=5, tensor_id=16, step=2)
