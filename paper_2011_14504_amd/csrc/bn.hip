@@ -155,8 +155,8 @@ struct OpMax { template <typename T> __device__ T operator()(T a, T b) const { r
 constexpr int kRowB = 256 + 4;      // bytes per row of a byte table in LDS
 constexpr int kRowW = 256 + 1;      // dwords per row of a dword table in LDS
 
-// Both workspaces start with ISEG_BN_WS_ZERO(C) bytes that callers zero at
-// allocation; the kernels need no counters there any more and leave them be.
+// Both workspaces start with ISEG_BN_WS_ZERO(C) reserved bytes that no kernel
+// reads or writes.
 size_t ctr_bytes(int64_t C) { return ISEG_BN_WS_ZERO(C); }
 
 // max over the kNT threads of a block (every thread gets it)
