@@ -2900,32 +2900,38 @@ __global__ __launch_bounds__(768) void k_conv_wgrad_rows(WgradArgs a, int32_t* _
 
 // Sum the per-split int32 partials in int64 (and take their max |.| for the
 // quantizer).  A block owns 256 consecutive elements (one int4 per lane); its
-// 16 waves take every 16th split, eight loads in flight each, then fold in
-// LDS.  One launch also where the weight tensor gives few blocks (64 x 64: 16
-// blocks over 196 splits): a second level over chunks of the splits cost a
-// launch of 4-5 us and saved less (128 x 128 x 9 over 52 splits: 11.8 us for the
-// two, 8.0 here).
-constexpr int kRedWaves = 16, kRedU = 8;
-__global__ __launch_bounds__(64 * kRedWaves) void k_wgrad_reduce(const int32_t* __restrict__ part, int64_t n,
-                                                                 int splits, long long* __restrict__ out,
-                                                                 uint64_t* pmax)
+// NW waves take every NW-th split, eight (the last four: four) loads in flight
+// each, then fold in LDS.  Bound by the partials' bytes
+// where there are many, by latency where there are few.  Four waves unless few
+// blocks share many splits: blocks of sixteen fill the CUs with waves that have
+// one load or none, 26.3 us instead of 8.1 for 589824 weights over 12 splits
+// (1x1, 512 x 512 over 12: 11.8 -> 5.5), yet 7.5 instead of 15.2 for 36864 weights
+// (144 blocks) over 196.
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_wgrad_reduce(const int32_t* __restrict__ part, int64_t n, int splits,
+                                                          long long* __restrict__ out, uint64_t* pmax)
 {
-    __shared__ long long red[kRedWaves][256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ long long red[NW][256];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t e0 = (int64_t)blockIdx.x * 256 + lane * 4;
-    const int64_t el = e0 < n ? e0 : 0;   // n % 4 == 0: K is a multiple of 64
+    const int64_t el = e0 < n ? e0 : 0;   // n % 4 == 0: K is a multiple of 16
     long long s[4] = {0, 0, 0, 0};
-    for (int k = wave; k < splits; k += kRedU * kRedWaves) {
-        int4 v[kRedU];
+    int k = wave;
+    auto step = [&](auto cnt) {           // U splits from k on; past the last one: repeats, not added
+        constexpr int U = decltype(cnt)::value;
+        int4 v[U];
 #pragma unroll
-        for (int u = 0; u < kRedU; u++) {
-            const int q = k + u * kRedWaves;
+        for (int u = 0; u < U; u++) {
+            const int q = k + u * NW;
             v[u] = *(const int4*)(part + (int64_t)(q < splits ? q : k) * n + el);
         }
 #pragma unroll
-        for (int u = 0; u < kRedU; u++)
-            if (k + u * kRedWaves < splits) { s[0] += v[u].x; s[1] += v[u].y; s[2] += v[u].z; s[3] += v[u].w; }
-    }
+        for (int u = 0; u < U; u++)
+            if (k + u * NW < splits) { s[0] += v[u].x; s[1] += v[u].y; s[2] += v[u].z; s[3] += v[u].w; }
+        k += U * NW;
+    };
+    while (k + 4 * NW < splits) step(std::integral_constant<int, 8>());
+    if (k < splits) step(std::integral_constant<int, 4>());
 #pragma unroll
     for (int u = 0; u < 4; u++) red[wave][lane * 4 + u] = s[u];
     __syncthreads();
@@ -2934,7 +2940,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_wgrad_reduce(const int32_t* 
         const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
         long long t = 0;
 #pragma unroll
-        for (int w = 0; w < kRedWaves; w++) t += red[w][threadIdx.x];
+        for (int w = 0; w < NW; w++) t += red[w][threadIdx.x];
         if (e < n) {
             out[e] = t;
             mx = t < 0 ? (uint64_t)(-t) : (uint64_t)t;
@@ -3294,8 +3300,20 @@ int launch_wgrad_reduce(const int32_t* part, int64_t n, int64_t splits, long lon
     }
     if (!out) return ISEG_ERR_ARG;
     if (npmax) *npmax = ceil_div64(n, 256);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)ceil_div64(n, 256)), dim3(64 * kRedWaves), 0, s, part, n,
-                       (int)splits, out, pmax);
+    // at most 256 blocks: more waves per block once four would take more than
+    // six (eight waves: more than ten) splits each (36864 weights: 4.6 us either way
+    // at 24 splits, 4.6 with eight waves against 7.0 at 64, 6.1 with sixteen against
+    // 6.8 at 96); with 576 blocks four win up to 64 splits, as many as such a
+    // tensor is given
+    const int64_t nb = ceil_div64(n, 256);
+    auto go = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        hipLaunchKernelGGL(k_wgrad_reduce<NW>, dim3((unsigned)nb), dim3(64 * NW), 0, s, part, n, (int)splits, out,
+                           pmax);
+    };
+    if (nb > 256 || splits <= 24) go(std::integral_constant<int, 4>());
+    else if (splits <= 80) go(std::integral_constant<int, 8>());
+    else go(std::integral_constant<int, 16>());
     return launch_ok();
 }
 
