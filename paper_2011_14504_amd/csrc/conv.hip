@@ -2682,7 +2682,7 @@ __global__ __launch_bounds__(768) void k_conv_wgrad_rows(WgradArgs a, int32_t* _
     const int nch = a.C / 64;
     const int c0 = (blockIdx.x % nch) * 64, k0 = (blockIdx.x / nch) * KB;
     const int32_t E = a.W + a.dw, EH = E * a.H, N = (int32_t)(a.NPQ / ((int64_t)a.H * a.W));
-    const int32_t total = N * EH;                        // < 2^31 (wgrad_rows_ok)
+    const int32_t total = N * EH;                        // < 2^31 (wgrad_rows_shape)
     const int32_t ebeg = (int32_t)(blockIdx.y * a.pix_per_split);
     const int32_t eend = (int32_t)(ebeg + a.pix_per_split < total ? ebeg + a.pix_per_split : total);
     const int nsteps = (eend - ebeg + 63) / 64;
@@ -3211,15 +3211,6 @@ int64_t wgrad_taps_splits(int64_t NPQ, int64_t K, int64_t C, int64_t* pps_out)
     return ceil_div64(NPQ, pps);
 }
 
-// the row kernel: 3x3, stride 1, padding = dilation <= 64 (the output has the
-// input's size); splits are ranges of extended pixels
-bool wgrad_rows_shape(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_t R, int64_t S, int sh, int sw,
-                      int ph, int pw, int dh, int dw)
-{
-    return N > 0 && R == 3 && S == 3 && sh == 1 && sw == 1 && ph == dh && pw == dw && dw <= 64 && C % 64 == 0 &&
-           K % 64 == 0 && N * H * (W + dw) < ((int64_t)1 << 31) - 4096;
-}
-
 // Splits of the row kernel.  A block costs about 10 us (launch, first loads, the
 // 295 KB of partial sums it writes) and 0.8 us per 64 pixels.  So the whole chip
 // where every split keeps 32 steps (2048 -> 256 channels on 8 x 32 x 32: 4 splits of
@@ -3239,6 +3230,34 @@ int64_t wgrad_rows_splits(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
     if (pps > kWgradSplit / 128 * 128) pps = kWgradSplit / 128 * 128;
     *pps_out = pps;
     return ceil_div64(total, pps);
+}
+
+// The row kernel covers 3x3, stride 1, padding = dilation <= 64 (the output has
+// the input's size); splits are ranges of extended pixels.  It walks W + dil
+// columns a row and never fewer than 128 extended pixels a block, so it is taken
+// where its cost is below the all-taps kernel's.  In us, fitted to both kernels
+// over 950 shapes (1 x 7 x 7 to 16 x 56 x 56, 64 -> 64 to 2048 -> 256, dilations 1
+// to 64): 0.75 a step of 64 extended pixels of 128 output channels (0.5 of 64)
+// against 1.2 a step of 64 pixels, 2 per million partial sums stored and added
+// on either side, and 1.5 for the row kernel's longer start; chosen so, the
+// weight gradients take 0.2 % more than the better kernel's on average, 19 % with the
+// all-taps kernel and 4 % with the row kernel alone: 2048 -> 256 on 8 x 40 x 40,
+// dilation 12: 243 us against 110; 512 -> 256 on 8 x 8 x 8: 24.6 against 27.8 at
+// dilation 1 and 34.2 at 18; 320 -> 192 on 8 x 100 x 16: 45.6 against 40.1 at
+// dilation 2 and 53.9 at 36.
+bool wgrad_rows_shape(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_t R, int64_t S, int sh, int sw,
+                      int ph, int pw, int dh, int dw)
+{
+    if (!(N > 0 && R == 3 && S == 3 && sh == 1 && sw == 1 && ph == dh && pw == dw && dw <= 64 && C % 64 == 0 &&
+          K % 64 == 0 && N * H * (W + dw) < ((int64_t)1 << 31) - 4096))
+        return false;
+    auto cost = [&](int64_t splits, int64_t pps, int64_t blocks, double step) {
+        return (double)(ceil_div64(blocks, 256) * (pps / 64)) * step + (double)(splits * K * 9 * C) * 2e-6;
+    };
+    int64_t rpps, tpps;
+    const int64_t rs = wgrad_rows_splits(N, H, W, C, K, dw, &rpps), ts = wgrad_taps_splits(N * H * W, K, C, &tpps);
+    const int64_t rtiles = (C / 64) * (K % 128 ? K / 64 : K / 128), ttiles = (C / 64) * (K / 64);
+    return 1.5 + cost(rs, rpps, rs * rtiles, K % 128 ? 0.5 : 0.75) < cost(ts, tpps, ts * ttiles, 1.2);
 }
 
 // chunks of the splits reduced by separate blocks: enough blocks for the chip
