@@ -1416,13 +1416,15 @@ M32Plan m32_plan(int64_t N, int64_t Ho, int64_t Wo, int64_t Ci, int64_t Nout, in
            Ci % 64 == 0 && Nout % 64 == 0 && N * Ho * Wo < ((int64_t)1 << 31);
     if (!p.ok) return p;
     p.tiles_x = (int)ceil_div64(Wo, kM32TW);
-    // 16-row tiles share the weights over twice the pixels, but want two blocks
-    // on every CU: 64 -> 64 at 16 x 224 x 224 (1568 tall tiles) 85.6 us against 90.9,
-    // 128 -> 128 at 8 x 128 x 128 (512) 45.8 against 50.0, yet 21.9 against 18.9 at
-    // 64 -> 64, 8 x 128 x 128 (256).  Dilation 2 in both axes leaves LDS for one
+    // 16-row tiles share the weights over twice the pixels, but want most of the
+    // 512 places that two blocks on every CU give: 64 -> 256 at 224 x 224 (392 tall
+    // tiles) 27.7 us against 30.3, 128 -> 128 at 300 x 300 (380) 43.2 against 44.4 and
+    // 64 -> 64 at 16 x 224 x 224 (1568) 85.6 against 90.9, yet 70.4 against 68.5 at
+    // 512 -> 512, 128 x 160 (320) and 21.9 against 18.9 at 64 -> 64, 8 x 128 x 128
+    // (256).  Dilation 2 in both axes leaves LDS for one
     // 16-row block only: 116.8 against 96.8 at 128 -> 128, 16 x 128 x 128.
     const int64_t tall = N * ceil_div64(Ho, 16) * p.tiles_x * (Nout / 64);
-    p.th = tall >= 512 && 2 * m32_chunk_bytes(16, dh, dw) <= 160 * 1024 ? 16 : 8;
+    p.th = tall >= 360 && 2 * m32_chunk_bytes(16, dh, dw) <= 160 * 1024 ? 16 : 8;
     p.tiles_y = (int)ceil_div64(Ho, p.th);
     p.ok = N * p.tiles_y * p.tiles_x < ((int64_t)1 << 31);
     return p;

@@ -16,7 +16,7 @@ CASES = [
     (1, 12, 40, 320, 64, (0, 0), (1, 1)), (2, 11, 20, 64, 64, (3, 0), (2, 2)), (1, 33, 32, 512, 128, (2, 2), (2, 2)),
     # enough tiles for the tall ones (but where both dilations are 2)
     (17, 65, 97, 64, 128, (1, 1), (1, 1)), (16, 17, 33, 192, 512, (1, 1), (1, 1)), (33, 16, 64, 128, 512, (1, 2), (1, 2)),
-    (33, 30, 32, 192, 512, (2, 1), (2, 1)), (33, 16, 32, 192, 1024, (2, 2), (2, 2)),
+    (25, 30, 33, 64, 256, (1, 1), (1, 1)), (33, 30, 32, 192, 512, (2, 1), (2, 1)), (33, 16, 32, 192, 1024, (2, 2), (2, 2)),
 ]
 
 
