@@ -188,6 +188,21 @@ struct FStat {
     int32_t pad;                     // row slots past M in the tiles
 };
 
+// Blocks of a slice: one per tile, or an equal share of kMaxBlocks in a multiple
+// of the eight XCDs.  Consecutive blocks go to the XCDs in turn, so the blocks that
+// read the same rows of different slices then share an L2; rows whose length is
+// no multiple of 128 bytes have most of their lines in two slices, which every
+// XCD otherwise fetches for itself (131072 rows, forward / backward, 85 blocks
+// against 80 at 176 channels: 51.7 / 65.8 -> 36.4 / 51.6 us, 51 against 48 at 272:
+// 73.0 / 95.4 -> 45.1 / 70.3, 21 against 16 at 720, 32768 rows: 52.1 / 71.4 -> 36.0 / 59.5).
+int32_t slice_blocks(int64_t nsl, int64_t ntiles)
+{
+    int64_t n = kMaxBlocks / nsl;
+    if (ntiles <= n) return (int32_t)ntiles;
+    if (nsl > 1 && n >= 8) n &= ~(int64_t)7;
+    return (int32_t)(n < 1 ? 1 : n);
+}
+
 template <int CPL, int G>
 FStat make_fstat(int64_t M, int64_t C)
 {
@@ -197,10 +212,7 @@ FStat make_fstat(int64_t M, int64_t C)
     f.nsl = (int32_t)ceil_div64(C, CS);
     f.ntiles = (int32_t)ceil_div64(M, TR);
     f.pad = (int32_t)((int64_t)f.ntiles * TR - M);
-    int64_t gx = kMaxBlocks / f.nsl;
-    if (gx > f.ntiles) gx = f.ntiles;
-    if (gx < 1) gx = 1;
-    f.gx = (int32_t)gx;
+    f.gx = slice_blocks(f.nsl, f.ntiles);
     return f;
 }
 
@@ -808,9 +820,7 @@ FStat make_fapply(int64_t M, int64_t C)
 {
     FStat f = make_fstat<CPL, G>(M, C);
     f.ntiles = (int32_t)ceil_div64(M, (int64_t)U * kNT / G);
-    int64_t gx = kMaxBlocks / f.nsl;
-    if (gx > f.ntiles) gx = f.ntiles;
-    f.gx = (int32_t)(gx < 1 ? 1 : gx);
+    f.gx = slice_blocks(f.nsl, f.ntiles);
     return f;
 }
 
@@ -998,10 +1008,7 @@ FStat make_bstat(int64_t M, int64_t C)
     f.nsl = (int32_t)ceil_div64(C, CS);
     f.ntiles = (int32_t)ceil_div64(M, TR);
     f.pad = (int32_t)((int64_t)f.ntiles * TR - M);
-    int64_t gx = kMaxBlocks / f.nsl;
-    if (gx > f.ntiles) gx = f.ntiles;
-    if (gx < 1) gx = 1;
-    f.gx = (int32_t)gx;
+    f.gx = slice_blocks(f.nsl, f.ntiles);
     return f;
 }
 

@@ -27,6 +27,12 @@ CASES = [
     (1025, 64, 4, -7, {}, "n"), (1025, 64, 8, -7, dict(k_E2=8), "n"), (4096 * 3 + 5, 16, 0, -4, {}, "n"),
     # more row tiles than blocks
     (1024 * 70 + 3, 256, 0, -6, {}, "n"),
+    # several slices, the last of 16 to 48 channels, with as many tiles as blocks and
+    # one more, and where their blocks are cut to a multiple of eight
+    (256 * 120 + 1, 80, 0, -6, {}, "n"), (1024 * 41, 272, 0, -6, {}, "n"), (1024 * 37 + 700, 160, 0, -6, dict(k_E2=8), "n"),
+    (64 * 1500 + 63, 144, 0, -5, {}, "n"), (512 * 150 + 511, 48, 0, -7, {}, "u"), (40000, 176, 0, -6, dict(k_E2=8), "u"),
+    (64 * 2100 + 1, 100, 0, -6, {}, "n"), (70001, 36, 0, -6, dict(k_E2=8), "n"), (70000, 12, 4, -6, {}, "n"),
+    (50003, 80, 4, -6, {}, "n"), (4 * 64 * 51 * 5 + 64, 336, 8, -6, {}, "n"),
     # constant channels, the extremes of the code range, coarse and fine grids
     (700, 64, 0, -20, {}, "edge"), (700, 64, 0, -14, {}, "edge"), (700, 64, 0, 16, {}, "edge"),
     (700, 64, 0, -40, {}, "edge"), (1500, 48, 0, -4, dict(k_mu=2, k_sigma=2), "edge"),
