@@ -1350,8 +1350,8 @@ __device__ __forceinline__ void bnb_exps_out(const Saved& sv, const BnCfg& cf, c
     *o.dgamma_exp = s_d + sv.hdr[0] - (cf.k_xhat - 1);
 }
 
-// One block per channel, one thread per (sgn class, masked error code): the
-// channel's totals from the streaming blocks' partials (dbeta, dgamma), its
+// One block per channel, one thread per masked error code and one or three of
+// the sgn classes: the channel's totals from the streaming blocks' partials (dbeta, dgamma), its
 // bound on E1's exponent (the largest over its six per-class extremes; E2 is
 // monotone and the bracket linear in the code, so the extremes bound every
 // code the channel's data holds), and its dx values at that bound: Q =
@@ -1363,13 +1363,17 @@ __device__ __forceinline__ void bnb_exps_out(const Saved& sv, const BnCfg& cf, c
 // by 2^g + 1 equals that of x).  Exact E2 (k_E2 >= 15, |gamma delta| <= 127^2 <
 // 2^(k_E2-1)): E2's shift r2 is <= 0 and scales every term of the bracket and
 // the exponent base by inverse powers of two, so dx is that of r2 = 0 with f =
-// gamma_q delta.  Bound by latency (one 128-bit division per thread, in three
-// times as many threads as codes): 7.1 -> 6.4 us at 256 channels.
-constexpr int kChanNT = 768;
-template <bool ROUND>
-__global__ __launch_bounds__(kChanNT) void k_bnb_chan(FStat st, int CS, BwdWs w, Saved sv, BnCfg cf, BnbOut o)
+// gamma_q delta.  Up to kChanWide channels every block is resident and latency
+// bounds it: a thread per class (768) saves two of three 128-bit divisions in a
+// row (backward of 1024 x 256: 20.9 -> 20.5 us).  Past that the blocks queue, and
+// four waves that hold all classes repeat the totals and the bound for a third
+// of the threads: 64 x 1024 26.2 -> 22.6 us, 64 x 2048 35.7 -> 27.9, 64 x 16384 162 -> 86
+// (even at 512).
+constexpr int64_t kChanWide = 512;
+template <bool ROUND, int NT>
+__global__ __launch_bounds__(NT) void k_bnb_chan(FStat st, int CS, BwdWs w, Saved sv, BnCfg cf, BnbOut o)
 {
-    constexpr int NW = kChanNT / 64;
+    constexpr int NW = NT / 64;
     __shared__ int32_t r_sd[NW], r_z[NW], r_lo[NW][3], r_hi[NW][3], r_cand, rsh[NW];
     __shared__ long long r_sdn[NW], r_sf[NW], r_sfn[NW];
     const int c = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6, gx = st.gx;
@@ -1380,7 +1384,7 @@ __global__ __launch_bounds__(kChanNT) void k_bnb_chan(FStat st, int CS, BwdWs w,
     const int sy = c / CS, sc = c - sy * CS;                // slice, channel within it
     const int nw = min(NW, (gx + 63) >> 6);                 // waves that hold partials
     if (wv < nw) {
-        for (int b = t; b < gx; b += kChanNT) {
+        for (int b = t; b < gx; b += NT) {
             const int64_t q = ((int64_t)sy * gx + b) * CS + sc;
             sd += w.p_sd[q];
             sdn += w.p_sdn[q];
@@ -1452,17 +1456,19 @@ __global__ __launch_bounds__(kChanNT) void k_bnb_chan(FStat st, int CS, BwdWs w,
     }
     __syncthreads();
     const int bc = r_cand;
-    const int k = t >> 8, d = (t & 255) - 128;
-    const int lo = k == 0 ? mm[0] : (k == 1 ? mm[2] : mm[4]), hi = k == 0 ? mm[1] : (k == 1 ? mm[3] : mm[5]);
+    const int d = (t & 255) - 128;
     const int S = Ebase + (cf.k_E1 - 1) - bc + 1;
-    int16_t q = 0;
-    if (bc != kSentinelLo && d >= lo && d <= hi && d >= -127) {
-        const i128 B = bnb_bracket(f_of(d), k - 1, M, Sf, T, Z, e_xh);
-        i128 Q = S >= 0 ? floordiv128(B << S, Dd) : floordiv128(B, Dd << -S);
-        Q = Q > 32767 ? 32767 : (Q < -32767 ? -32767 : Q);
-        q = (int16_t)Q;
+    for (int k = t >> 8; k < 3; k += NT / 256) {
+        const int lo = k == 0 ? mm[0] : (k == 1 ? mm[2] : mm[4]), hi = k == 0 ? mm[1] : (k == 1 ? mm[3] : mm[5]);
+        int16_t q = 0;
+        if (bc != kSentinelLo && d >= lo && d <= hi && d >= -127) {
+            const i128 B = bnb_bracket(f_of(d), k - 1, M, Sf, T, Z, e_xh);
+            i128 Q = S >= 0 ? floordiv128(B << S, Dd) : floordiv128(B, Dd << -S);
+            Q = Q > 32767 ? 32767 : (Q < -32767 ? -32767 : Q);
+            q = (int16_t)Q;
+        }
+        w.lutq[(int64_t)c * 768 + k * 256 + (t & 255)] = q;
     }
-    w.lutq[(int64_t)c * 768 + t] = q;
 }
 
 // Output pass: dx code = lut[c][sgn class][masked delta].  Every block first
@@ -1759,19 +1765,26 @@ extern "C" int iseg_bn_bwd(const int8_t* dy, const int32_t* dy_exp, const int8_t
     // E2 = SQ(gamma delta, k_E2) is exact when |gamma delta| <= 127^2 < 2^(k_E2-1)
     const bool exact_e2 = cf.k_E2 >= 15;
     const BnbOut out{dy_exp, gamma_q, dgamma, dbeta, dgamma_exp, dbeta_exp, dx_exp, dev_status};
+    auto chan = [&](auto rnd, const FStat& st, int cs) {
+        constexpr bool R = decltype(rnd)::value;
+        if (C <= kChanWide)
+            hipLaunchKernelGGL((k_bnb_chan<R, 768>), dim3((unsigned)C), dim3(768), 0, stream, st, cs, w, sv, cf, out);
+        else
+            hipLaunchKernelGGL((k_bnb_chan<R, 256>), dim3((unsigned)C), dim3(256), 0, stream, st, cs, w, sv, cf, out);
+    };
     auto run = [&](auto gl) {
         constexpr int G = decltype(gl)::value;
         const FStat st = make_bstat<G, kBndU>(M, C);
-        const dim3 sg((unsigned)st.gx, (unsigned)st.nsl), cg((unsigned)C);
+        const dim3 sg((unsigned)st.gx, (unsigned)st.nsl);
         if (exact_e2) {
             ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 0>), sg, dim3(kNT), 0, stream, dy, x,
                               st, w, sv, cf, out);
-            hipLaunchKernelGGL(k_bnb_chan<false>, cg, dim3(kChanNT), 0, stream, st, 4 * G, w, sv, cf, out);
+            chan(std::false_type(), st, 4 * G);
         } else {
             ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 1>), sg, dim3(kNT), 0, stream, dy, x,
                               st, w, sv, cf, out);
             hipLaunchKernelGGL((k_bnb_stats<G, 2>), sg, dim3(kNT), 0, stream, dy, x, st, w, sv, cf, out);
-            hipLaunchKernelGGL(k_bnb_chan<true>, cg, dim3(kChanNT), 0, stream, st, 4 * G, w, sv, cf, out);
+            chan(std::true_type(), st, 4 * G);
         }
         const FStat sa = make_bstat<G, kBndU>(M, C);
         ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_APPLY, stream, k_bnb_apply<G>, dim3((unsigned)sa.gx, (unsigned)sa.nsl),

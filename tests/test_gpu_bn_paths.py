@@ -40,6 +40,8 @@ CASES = [
     # small even codes around zero: many channels whose mean is exactly a code
     (2048, 128, 0, -6, {}, "sym"), (2048, 128, 0, -6, dict(relu=0), "sym"),
     # several channel groups per finalize block, the last one partly empty
+    # (and, past 512 channels, the backward's per-channel kernel with all classes in one thread)
+    (70, 512, 0, -6, dict(k_E2=8), "n"), (70, 516, 0, -6, {}, "n"), (70, 516, 0, -6, dict(k_E2=8), "n"),
     (65, 1040, 0, -6, {}, "n"), (33, 2320, 0, -7, dict(k_E2=8), "u"), (9, 6148, 0, -7, {}, "n"),
 ]
 
