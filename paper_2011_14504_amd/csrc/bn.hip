@@ -203,6 +203,29 @@ int32_t slice_blocks(int64_t nsl, int64_t ntiles)
     return (int32_t)(n < 1 ? 1 : n);
 }
 
+// The grid of a streaming pass.  Past 2048 channels a slice has fewer blocks than
+// there are XCDs; the two slices of each 128-byte line then take every second
+// eight of one row of blocks, which puts the blocks of the same rows on one XCD
+// again (8192 x 4096 codes: the first and the output pass of the forward 12.8 ->
+// 9.7 and 21.4 -> 18.2 us, those of the backward 33.3 -> 26.2 and 38.3 -> 28.4).
+dim3 slice_grid(const FStat& f)
+{
+    if (kMaxBlocks / f.nsl >= 8) return dim3((unsigned)f.gx, (unsigned)f.nsl);
+    return dim3((unsigned)(ceil_div64(ceil_div64(f.nsl, 2) * f.gx, 8) * 16));
+}
+
+// block bx of slice by; false: none (a block past the last slice)
+__device__ __forceinline__ bool slice_of(const FStat& st, int& bx, int& by)
+{
+    bx = blockIdx.x;
+    by = blockIdx.y;
+    if (kMaxBlocks / st.nsl >= 8) return true;
+    const int q = blockIdx.x, v = (q >> 4) * 8 + (q & 7), pair = v / st.gx;
+    bx = v - pair * st.gx;
+    by = 2 * pair + ((q >> 3) & 1);
+    return by < st.nsl;
+}
+
 template <int CPL, int G>
 FStat make_fstat(int64_t M, int64_t C)
 {
@@ -371,7 +394,7 @@ __device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, u
 // CPL channels; rows past M repeat the last one and are not valid.  The next
 // tile's loads are issued before f runs on the current one.
 template <int CPL, int G, typename F>
-__device__ __forceinline__ void fstat_rows(const FStat& st, const int8_t* __restrict__ x, int c0, F f)
+__device__ __forceinline__ void fstat_rows(const FStat& st, int bx, const int8_t* __restrict__ x, int c0, F f)
 {
     constexpr int RPI = kNT / G;
     const int64_t rsub = threadIdx.x / G, last = st.M - 1;
@@ -384,7 +407,7 @@ __device__ __forceinline__ void fstat_rows(const FStat& st, const int8_t* __rest
             v[u] = vload<CPL>(base + (r < last ? r : last) * st.C);
         }
     };
-    int tile = blockIdx.x;
+    int tile = bx;
     if (tile < st.ntiles) load(tile, cur);
     while (tile < st.ntiles) {
         const int tn = tile + st.gx;
@@ -407,18 +430,20 @@ __device__ __forceinline__ void fstat_rows(const FStat& st, const int8_t* __rest
 template <int CPL, int G>
 __global__ __launch_bounds__(1024) void k_bnf_stats1(const int8_t* __restrict__ x, FStat st, FwdWs w)
 {
+    int bx, by;
+    if (!slice_of(st, bx, by)) return;
     constexpr int CS = CPL * G, DW = CPL / 4;
     __shared__ int32_t sS[kWaves * CS];
     __shared__ int32_t sMm[kWaves * CS];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, g = t % G;
-    const int c0 = blockIdx.y * CS + g * CPL;
+    const int c0 = by * CS + g * CPL;
     int s[CPL];
     short2v mnh[DW], mnl[DW], mxh[DW], mxl[DW];
 #pragma unroll
     for (int i = 0; i < CPL; i++) s[i] = 0;
 #pragma unroll
     for (int j = 0; j < DW; j++) { mnh[j] = mnl[j] = (short)0x7fff; mxh[j] = mxl[j] = (short)-0x8000; }
-    fstat_rows<CPL, G>(st, x, c0 < st.C ? c0 : 0, [&](const Vec<CPL>* v, const bool* ok) {
+    fstat_rows<CPL, G>(st, bx, x, c0 < st.C ? c0 : 0, [&](const Vec<CPL>* v, const bool* ok) {
 #pragma unroll
         for (int u = 0; u < 4; u++)
 #pragma unroll
@@ -456,7 +481,7 @@ __global__ __launch_bounds__(1024) void k_bnf_stats1(const int8_t* __restrict__ 
         }
     }
     __syncthreads();
-    const int c = blockIdx.y * CS + t;
+    const int c = by * CS + t;
     if (t < CS) {
         int bs = 0, lo = 255, hi = 0;
 #pragma unroll
@@ -468,8 +493,8 @@ __global__ __launch_bounds__(1024) void k_bnf_stats1(const int8_t* __restrict__ 
         }
         // one contiguous row of partials per block, reduced by every block of
         // the next pass for its slice; the next pass's accumulators start at zero
-        w.part[((int64_t)blockIdx.y * st.gx + blockIdx.x) * CS + t] = make_int2(bs, lo | (hi << 16));
-        if (blockIdx.x == 0 && c < st.C) w.acc[c] = 0;
+        w.part[((int64_t)by * st.gx + bx) * CS + t] = make_int2(bs, lo | (hi << 16));
+        if (bx == 0 && c < st.C) w.acc[c] = 0;
     }
 }
 
@@ -529,6 +554,8 @@ template <int CPL, int G>
 __global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ x, const int32_t* x_exp,
                                                     FStat st, FwdWs w, Saved sv, BnCfg cf, int32_t* dev_status)
 {
+    int bx, by;
+    if (!slice_of(st, bx, by)) return;
     constexpr int CS = CPL * G, DW = CPL / 4, NG = kNT / CS;
     __shared__ int32_t sS[kNT], sMm[kNT];          // prologue sums; then the wave totals of A0 and A1
     __shared__ int32_t sRef[CS];
@@ -542,7 +569,7 @@ __global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ 
         // block stores them.  All loads of a thread go out together; a row past
         // the last repeats the thread's first one, whose extremes change nothing.
         const int ch = t % CS, grp = t / CS;
-        const int2* ps = w.part + (int64_t)blockIdx.y * st.gx * CS;
+        const int2* ps = w.part + (int64_t)by * st.gx * CS;
         int sum = 0, lo = 255, hi = 0;
         for (int b0 = grp; b0 < st.gx; b0 += 4 * NG) {
             int2 v[4];
@@ -573,8 +600,8 @@ __global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ 
             // code is at most 128, so shifts below -24 give 0 like -24 does
             const int32_t nm = (int32_t)clamp_k(rhu64(sum, max(s_x - 1 + (cf.k_mu - 1), -24), st.M), cf.k_mu);
             sRef[t] = bn_ref(bn_T(bn_off(s_x, nm, e_mu), s_x, e_mu));
-            const int c = blockIdx.y * CS + t;
-            if (blockIdx.x == 0 && c < st.C) {
+            const int c = by * CS + t;
+            if (bx == 0 && c < st.C) {
                 sv.n_mu[c] = nm;
                 sv.qmin[c] = lo - 128;
                 sv.qmax[c] = hi - 128;
@@ -583,14 +610,14 @@ __global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ 
         }
         __syncthreads();
     }
-    const int c0 = blockIdx.y * CS + g * CPL;
+    const int c0 = by * CS + g * CPL;
     uint32_t a0[CPL], a1[CPL], r0[CPL];
 #pragma unroll
     for (int i = 0; i < CPL; i++) {
         a0[i] = a1[i] = 0;
         r0[i] = (uint32_t)sRef[g * CPL + i] * 0x01010101u;
     }
-    fstat_rows<CPL, G>(st, x, c0 < st.C ? c0 : 0, [&](const Vec<CPL>* v, const bool* ok) {
+    fstat_rows<CPL, G>(st, bx, x, c0 < st.C ? c0 : 0, [&](const Vec<CPL>* v, const bool* ok) {
 #pragma unroll
         for (int j = 0; j < DW; j++) {
             uint32_t u[4], o[4];
@@ -617,8 +644,8 @@ __global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ 
         }
     }
     __syncthreads();
-    const int c = blockIdx.y * CS + t;
-    if (!sx_ok(s_in) && blockIdx.x == 0 && blockIdx.y == 0 && t == 0) set_status(dev_status, ISEG_DEV_RANGE);
+    const int c = by * CS + t;
+    if (!sx_ok(s_in) && bx == 0 && by == 0 && t == 0) set_status(dev_status, ISEG_DEV_RANGE);
     if (t < CS && c < st.C) {
         uint32_t b0 = 0, b1 = 0;
 #pragma unroll
@@ -829,11 +856,13 @@ __global__ __launch_bounds__(1024) void k_bnf_apply(const int8_t* __restrict__ x
                                                    FStat st, Saved sv, FwdWs w, BnCfg cf, const int32_t* x_exp,
                                                    const int8_t* gamma_q, const int8_t* beta_q, int32_t* y_exp)
 {
+    int bx, by;
+    if (!slice_of(st, bx, by)) return;
     constexpr int CS = CPL * G, RPI = kNT / G, TV = (CS * 32 + kNT - 1) / kNT;
     __shared__ __attribute__((aligned(16))) int8_t lut[CS * kRowB];
     __shared__ uint64_t rmax[kWaves];
     const int t = threadIdx.x, g = t % G, rsub = t / G;
-    const int c0 = blockIdx.y * CS + g * CPL, cb = blockIdx.y * CS;
+    const int c0 = by * CS + g * CPL, cb = by * CS;
     const int64_t last = st.M - 1;
     const int8_t* xb = x + (c0 < st.C ? c0 : 0);
     Vec<CPL> cur[U], nxt[U];
@@ -857,15 +886,15 @@ __global__ __launch_bounds__(1024) void k_bnf_apply(const int8_t* __restrict__ x
         my[k] = w.maxYc[c];
     }
     // share of the saved A codes, four codes of one channel per step
-    const int64_t nall = (int64_t)st.C * 64, nb = (int64_t)gridDim.x * gridDim.y;
+    const int64_t nall = (int64_t)st.C * 64, nb = (int64_t)st.gx * st.nsl;
     const int64_t per = (nall + nb - 1) / nb;
-    const int64_t i0 = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * per;
+    const int64_t i0 = ((int64_t)by * st.gx + bx) * per;
     const int64_t i1 = i0 + per < nall ? i0 + per : nall;
     int64_t ia = i0 + t;
     const int64_t il = ia < i1 ? ia : 0;
     short4v xq = *(const short4v*)(sv.xcode + il * 4);
     int gq = gamma_q[il >> 6], bq = beta_q[il >> 6];
-    int tile = blockIdx.x;
+    int tile = bx;
     if (tile < st.ntiles) load(tile, cur);
     for (int k = t + kNT; k < st.C; k += kNT) M = w.maxYc[k] > M ? w.maxYc[k] : M;
     M = wave_max_u64(M);
@@ -878,7 +907,7 @@ __global__ __launch_bounds__(1024) void k_bnf_apply(const int8_t* __restrict__ x
     const bool ok = sx_ok(s_in);
     const int32_t s_x = ok ? s_in : -14;          // outputs unspecified; keeps the shifts defined
     const FwdExps e = fwd_exps(s_x, b, cf);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0 && ok) {
+    if (bx == 0 && by == 0 && t == 0 && ok) {
         *y_exp = e.e_y + r;
         sv.hdr[0] = b;
         sv.hdr[1] = e.e_y;
@@ -1091,11 +1120,13 @@ template <int G, int MODE>
 __global__ __launch_bounds__(1024) void k_bnb_stats(const int8_t* __restrict__ dy, const int8_t* __restrict__ x,
                                                    FStat st, BwdWs w, Saved sv, BnCfg cf, BnbOut out)
 {
+    int bx, by;
+    if (!slice_of(st, bx, by)) return;
     constexpr int CS = 4 * G, RPI = kNT / G, U = kBndU, TR = U * RPI, TV = CS * 64 / kNT;
     __shared__ __attribute__((aligned(16))) uint32_t tab[CS * kRowW];
     __shared__ int32_t rsh[kWaves], sZf[CS];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, g = t % G, rsub = t / G;
-    const int cb = blockIdx.y * CS, c0 = cb + g * 4;
+    const int cb = by * CS, c0 = cb + g * 4;
     const int64_t last = st.M - 1;
     const int8_t* xb = x + (c0 < st.C ? c0 : 0);
     const int8_t* db = dy + (c0 < st.C ? c0 : 0);
@@ -1122,7 +1153,7 @@ __global__ __launch_bounds__(1024) void k_bnb_stats(const int8_t* __restrict__ d
             ad[u] = *(const uint32_t*)(db + rr);
         }
     };
-    int tile = blockIdx.x;
+    int tile = bx;
     if (tile < st.ntiles) load(tile, vx, vd);
     int gam[4] = {0, 0, 0, 0};
     int r2 = 0;
@@ -1281,7 +1312,7 @@ __global__ __launch_bounds__(1024) void k_bnb_stats(const int8_t* __restrict__ d
     int F = 0;
     if (t < CS) {
         // [slice][block][channel of the slice]: one contiguous row per block
-        const int64_t o = ((int64_t)blockIdx.y * st.gx + blockIdx.x) * CS + t;
+        const int64_t o = ((int64_t)by * st.gx + bx) * CS + t;
         long long bn = 0, bf = 0;
         int32_t bs = 0;
         uint32_t bz = 0, bx = 0, bm = ~0u, x0 = 0, m0 = 0xffff, bnp = 0;
@@ -1330,7 +1361,7 @@ __global__ __launch_bounds__(1024) void k_bnb_stats(const int8_t* __restrict__ d
     }
     if constexpr (MODE == 1) {
         F = block_max_nt(F, rsh);
-        if (t == 0) w.pF[blockIdx.y * st.gx + blockIdx.x] = F;
+        if (t == 0) w.pF[by * st.gx + bx] = F;
     }
 }
 
@@ -1486,12 +1517,14 @@ __global__ __launch_bounds__(1024) void k_bnb_apply(const int8_t* __restrict__ d
                                                    int8_t* __restrict__ dx, FStat st, BwdWs w, Saved sv,
                                                    BnCfg cf, BnbOut o)
 {
+    int bx, by;
+    if (!slice_of(st, bx, by)) return;
     constexpr int CS = 4 * G, RPI = kNT / G, U = kBndU, TR = U * RPI;
     constexpr int NV = (CS * 96 + kNT - 1) / kNT;
     __shared__ __attribute__((aligned(16))) int8_t lut[CS * 3 * kRowB];
     __shared__ int32_t rb[kWaves];
     const int t = threadIdx.x, g = t % G, rsub = t / G;
-    const int cb = blockIdx.y * CS, c0 = cb + g * 4;
+    const int cb = by * CS, c0 = cb + g * 4;
     const int cl = c0 < st.C ? c0 : 0;
     const int64_t last = st.M - 1;
     // staged values, bounds, thresholds and the first tile all load together
@@ -1519,13 +1552,13 @@ __global__ __launch_bounds__(1024) void k_bnb_apply(const int8_t* __restrict__ d
             ad[u] = *(const uint32_t*)(dy + rr);
         }
     };
-    int tile = blockIdx.x;
+    int tile = bx;
     if (tile < st.ntiles) load(tile, vx, vd);
     int bdx = kSentinelLo;
     for (int i = t; i < st.C; i += kNT) bdx = max(bdx, w.cbnd[i]);
     bdx = block_max_nt(bdx, rb);
     if (bdx == kSentinelLo) bdx = 0;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) {
+    if (bx == 0 && by == 0 && t == 0) {
         *o.dx_exp = bdx - (cf.k_E1 - 1);
         bnb_exps_out(sv, cf, o);
     }
@@ -1645,7 +1678,7 @@ static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t
     auto stats = [&](auto cpl, auto gl) {
         constexpr int CPL = decltype(cpl)::value, G = decltype(gl)::value;
         const FStat st = make_fstat<CPL, G>(M, C);
-        const dim3 sg((unsigned)st.gx, (unsigned)st.nsl);
+        const dim3 sg = slice_grid(st);
         ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS1, stream, (k_bnf_stats1<CPL, G>), sg, dim3(kNT), 0, stream, x, st, w);
         ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS2, stream, (k_bnf_stats2<CPL, G>), sg, dim3(kNT), 0, stream, x, x_exp,
                           st, w, sv, cf, dev_status);
@@ -1672,11 +1705,11 @@ static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t
         const FStat s4 = make_fapply<CPL, G, 4>(M, C), s1 = make_fapply<CPL, G, 1>(M, C);
         if (s4.gx * s4.nsl > kMaxBlocks / 2)
             ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 4>),
-                              dim3((unsigned)s4.gx, (unsigned)s4.nsl), dim3(kNT), 0, stream, x, y_out, s4, sv, w, cf,
+                              slice_grid(s4), dim3(kNT), 0, stream, x, y_out, s4, sv, w, cf,
                               x_exp, gamma_q, beta_q, y_exp);
         else
             ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 1>),
-                              dim3((unsigned)s1.gx, (unsigned)s1.nsl), dim3(kNT), 0, stream, x, y_out, s1, sv, w, cf,
+                              slice_grid(s1), dim3(kNT), 0, stream, x, y_out, s1, sv, w, cf,
                               x_exp, gamma_q, beta_q, y_exp);
     };
     if (v16) {
@@ -1775,7 +1808,7 @@ extern "C" int iseg_bn_bwd(const int8_t* dy, const int32_t* dy_exp, const int8_t
     auto run = [&](auto gl) {
         constexpr int G = decltype(gl)::value;
         const FStat st = make_bstat<G, kBndU>(M, C);
-        const dim3 sg((unsigned)st.gx, (unsigned)st.nsl);
+        const dim3 sg = slice_grid(st);
         if (exact_e2) {
             ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 0>), sg, dim3(kNT), 0, stream, dy, x,
                               st, w, sv, cf, out);
@@ -1787,7 +1820,7 @@ extern "C" int iseg_bn_bwd(const int8_t* dy, const int32_t* dy_exp, const int8_t
             chan(std::true_type(), st, 4 * G);
         }
         const FStat sa = make_bstat<G, kBndU>(M, C);
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_APPLY, stream, k_bnb_apply<G>, dim3((unsigned)sa.gx, (unsigned)sa.nsl),
+        ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_APPLY, stream, k_bnb_apply<G>, slice_grid(sa),
                           dim3(kNT), 0, stream, dy, x, dx_out, sa, w, sv, cf, out);
     };
     if (C <= 16) run(std::integral_constant<int, 4>());

@@ -33,6 +33,8 @@ CASES = [
     (64 * 1500 + 63, 144, 0, -5, {}, "n"), (512 * 150 + 511, 48, 0, -7, {}, "u"), (40000, 176, 0, -6, dict(k_E2=8), "u"),
     (64 * 2100 + 1, 100, 0, -6, {}, "n"), (70001, 36, 0, -6, dict(k_E2=8), "n"), (70000, 12, 4, -6, {}, "n"),
     (50003, 80, 4, -6, {}, "n"), (4 * 64 * 51 * 5 + 64, 336, 8, -6, {}, "n"),
+    # more slices than XCDs have blocks for: paired slices, an odd number of them
+    (3100, 2112, 0, -6, {}, "n"), (1500, 2084, 0, -6, dict(k_E2=8), "u"),
     # constant channels, the extremes of the code range, coarse and fine grids
     (700, 64, 0, -20, {}, "edge"), (700, 64, 0, -14, {}, "edge"), (700, 64, 0, 16, {}, "edge"),
     (700, 64, 0, -40, {}, "edge"), (1500, 48, 0, -4, dict(k_mu=2, k_sigma=2), "edge"),
