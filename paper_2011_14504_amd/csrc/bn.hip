@@ -705,13 +705,48 @@ __device__ __forceinline__ int32_t fwd_xcode_any(int64_t D, int32_t den, int b, 
 
 // Per (channel, code): xhat code, y, flags and the backward's entry; per
 // channel: the sgn and ReLU thresholds and max |ReLU(y)| over the occupied
-// codes (y is monotone in q, so over qmin and qmax).  Every block forms all
-// channels' denominators and bounds on b itself (a few values per thread; C
-// is at most a few thousand): the arrival, reload and arithmetic of a tail in
+// codes (y is monotone in q, so over qmin and qmax).  Up to kDenWide channels
+// every block forms all channels' denominators and bounds on b itself (at most
+// two per thread): the arrival, reload and arithmetic of a tail in
 // the statistics pass took longer.  Bound by latency: the loads, two exact
-// divisions and three barriers.
+// divisions and three barriers.  PRE: k_bnf_den has formed them (forward of 64 x
+// 4096 codes: 39.0 -> 37.1 us, 64 x 65536: 572 -> 256; 64 x 2048: 29.5 against 30.3).
 constexpr int kFinCh = kNT / 256;              // channels at a time
 constexpr int kFinGrp = 16;                    // at most so many groups of them per block
+constexpr int64_t kDenWide = 2048;
+
+// a channel's denominator, and its bound on b (its largest |x-hat|: at qmin or
+// qmax, x-hat is linear in q)
+__device__ __forceinline__ int bnf_bound(int32_t lo, int32_t hi, int32_t nm, int32_t den, int32_t s_x, int e_mu,
+                                         int e_sig)
+{
+    const int64_t D0 = bn_D(lo, s_x, nm, e_mu), D1 = bn_D(hi, s_x, nm, e_mu);
+    const uint64_t m0 = (uint64_t)(D0 < 0 ? -D0 : D0), m1 = (uint64_t)(D1 < 0 ? -D1 : D1);
+    const uint64_t m = m0 > m1 ? m0 : m1;
+    return m ? ceil_pow2_exp64(m, (uint64_t)den) + min(s_x, e_mu) - e_sig : kSentinelLo;
+}
+
+// wide layers: the denominators, and the largest bound of each block's kNT
+// channels (into the statistics' partials, which nothing reads any more)
+__global__ __launch_bounds__(1024) void k_bnf_den(const int32_t* x_exp, FStat st, FwdWs w, Saved sv, BnCfg cf)
+{
+    __shared__ int32_t rsh[kWaves];
+    const int c = blockIdx.x * kNT + threadIdx.x;
+    const int e_mu = 2 - cf.k_mu, e_sig = 2 - cf.k_sigma;
+    const int32_t s_in = *x_exp, s_x = sx_ok(s_in) ? s_in : -14;
+    int best = kSentinelLo;
+    if (c < st.C) {
+        const int32_t nm = sv.n_mu[c], ns = bnf_sigma(w.acc[c], w.sumq[c], st, s_x, nm, e_mu, cf);
+        const int32_t den = max(ns + cf.eps_code, 1);
+        sv.n_sigma[c] = ns;
+        sv.den[c] = den;
+        best = bnf_bound(sv.qmin[c], sv.qmax[c], nm, den, s_x, e_mu, e_sig);
+    }
+    best = block_max_nt(best, rsh);
+    if (threadIdx.x == 0) ((int32_t*)w.part)[blockIdx.x] = best;
+}
+
+template <bool PRE>
 __global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat st, int grp, FwdWs w, Saved sv,
                                                   BnCfg cf, const int8_t* gamma_q, const int8_t* beta_q)
 {
@@ -723,25 +758,27 @@ __global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat s
     // every load of the first round goes out before the first wait (no branch on
     // a loaded value in between)
     const int32_t s_in = *x_exp;
-    const int k0 = t < st.C ? t : 0;
     const int cs0 = cfirst + lc < st.C ? cfirst + lc : 0;
     int32_t nmu = sv.n_mu[cs0], qlo = sv.qmin[cs0], qhi = sv.qmax[cs0];
     int gq = gamma_q[cs0], bq = beta_q[cs0];
-    int32_t nm = sv.n_mu[k0], lo = sv.qmin[k0], hi = sv.qmax[k0], sumq = w.sumq[k0];
-    unsigned long long acc = w.acc[k0];
     const int e_mu = 2 - cf.k_mu, e_sig = 2 - cf.k_sigma;
     const int32_t s_x = sx_ok(s_in) ? s_in : -14;     // outputs unspecified, shifts defined
     int best = kSentinelLo;
-    for (int k = t; k < st.C; k += kNT) {
-        if (k != t) { nm = sv.n_mu[k]; lo = sv.qmin[k]; hi = sv.qmax[k]; sumq = w.sumq[k]; acc = w.acc[k]; }
-        const int32_t ns = bnf_sigma(acc, sumq, st, s_x, nm, e_mu, cf);
-        const int32_t den = max(ns + cf.eps_code, 1);
-        if (k >= cfirst && k < cfirst + grp * kFinCh) { sNs[k - cfirst] = ns; sDen[k - cfirst] = den; }
-        // xhat is linear in q: its largest magnitude is at qmin or qmax
-        const int64_t D0 = bn_D(lo, s_x, nm, e_mu), D1 = bn_D(hi, s_x, nm, e_mu);
-        const uint64_t m0 = (uint64_t)(D0 < 0 ? -D0 : D0), m1 = (uint64_t)(D1 < 0 ? -D1 : D1);
-        const uint64_t m = m0 > m1 ? m0 : m1;
-        if (m) best = max(best, ceil_pow2_exp64(m, (uint64_t)den) + min(s_x, e_mu) - e_sig);
+    if constexpr (PRE) {
+        const int nb = (st.C + kNT - 1) / kNT;        // at most 64
+        best = ((const int32_t*)w.part)[lane < nb ? lane : 0];
+        if (t < grp * kFinCh) sDen[t] = sv.den[cfirst + t < st.C ? cfirst + t : 0];
+    } else {
+        const int k0 = t < st.C ? t : 0;
+        int32_t nm = sv.n_mu[k0], lo = sv.qmin[k0], hi = sv.qmax[k0], sumq = w.sumq[k0];
+        unsigned long long acc = w.acc[k0];
+        for (int k = t; k < st.C; k += kNT) {
+            if (k != t) { nm = sv.n_mu[k]; lo = sv.qmin[k]; hi = sv.qmax[k]; sumq = w.sumq[k]; acc = w.acc[k]; }
+            const int32_t ns = bnf_sigma(acc, sumq, st, s_x, nm, e_mu, cf);
+            const int32_t den = max(ns + cf.eps_code, 1);
+            if (k >= cfirst && k < cfirst + grp * kFinCh) { sNs[k - cfirst] = ns; sDen[k - cfirst] = den; }
+            best = max(best, bnf_bound(lo, hi, nm, den, s_x, e_mu, e_sig));
+        }
     }
     for (int o = 32; o > 0; o >>= 1) best = max(best, __shfl_xor(best, o, 64));
     if (lane == 0) rsh[wv] = best;
@@ -810,8 +847,10 @@ __global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat s
                 if (bm) v[3] = -128 + 64 * k + 63 - __builtin_clzll(bm);
             }
             sv.t0[c] = v[0]; sv.p0[c] = v[1]; sv.mlo[c] = v[2]; sv.mhi[c] = v[3];
-            sv.n_sigma[c] = sNs[g * kFinCh + lc];
-            sv.den[c] = den;
+            if constexpr (!PRE) {
+                sv.n_sigma[c] = sNs[g * kFinCh + lc];
+                sv.den[c] = den;
+            }
             w.maxYc[c] = mx;
         }
         // ReLU(y) floored by 2^t_c, t_c = max(0, r_c - 1) with r_c the Q_A shift
@@ -1685,8 +1724,15 @@ static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t
         // every block forms all C denominators, so past one block per CU a block
         // takes more channels (2048 channels: 14.2 us with 512 blocks, 7.2 with 256)
         const int grp = (int)std::min<int64_t>(kFinGrp, ceil_div64(C, 256 * kFinCh));
-        hipLaunchKernelGGL(k_bnf_fin2, dim3((unsigned)ceil_div64(C, grp * kFinCh)), dim3(kNT), 0, stream, x_exp, st,
-                           grp, w, sv, cf, gamma_q, beta_q);
+        const dim3 fg((unsigned)ceil_div64(C, grp * kFinCh));
+        if (C <= kDenWide) {
+            hipLaunchKernelGGL(k_bnf_fin2<false>, fg, dim3(kNT), 0, stream, x_exp, st, grp, w, sv, cf, gamma_q,
+                               beta_q);
+        } else {
+            hipLaunchKernelGGL(k_bnf_den, dim3((unsigned)ceil_div64(C, kNT)), dim3(kNT), 0, stream, x_exp, st, w, sv,
+                               cf);
+            hipLaunchKernelGGL(k_bnf_fin2<true>, fg, dim3(kNT), 0, stream, x_exp, st, grp, w, sv, cf, gamma_q, beta_q);
+        }
     };
     const std::integral_constant<int, 16> v16c;
     if (C % 16 == 0 && ((uintptr_t)x & 15) == 0) {

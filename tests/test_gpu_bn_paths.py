@@ -45,6 +45,8 @@ CASES = [
     # (and, past 512 channels, the backward's per-channel kernel with all classes in one thread)
     (70, 512, 0, -6, dict(k_E2=8), "n"), (70, 516, 0, -6, {}, "n"), (70, 516, 0, -6, dict(k_E2=8), "n"),
     (65, 1040, 0, -6, {}, "n"), (33, 2320, 0, -7, dict(k_E2=8), "u"), (9, 6148, 0, -7, {}, "n"),
+    # denominators in a kernel of their own
+    (5, 2048, 0, -7, {}, "n"), (5, 2052, 0, -7, {}, "n"), (3, 65536, 0, -6, {}, "u"),
 ]
 
 
