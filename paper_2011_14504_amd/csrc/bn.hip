@@ -247,10 +247,12 @@ int fstat_g16(int64_t C) { return C <= 16 ? 1 : (C <= 32 ? 2 : 4); }
 // ---------------------------------------------------------------------------
 struct FwdWs {
     int32_t* b_glob;                 // exponent of Q_xhat's scale (fin2, block 0)
+    int32_t* bnd;                    // [block] largest bound on it (k_bnf_den; at most 64 blocks)
     int2* part;                      // [slice][gx][CS] sum q; (min q + 128) | (max q + 128) << 16
     unsigned long long* acc;         // [C] sum |q - T| (low half) and sum |q - T - 1| (high half)
     int32_t* sumq;                   // [C] sum q
-    unsigned long long* maxYc;       // [C] max |ReLU(y)| of channel c over its occupied codes (fin2)
+    unsigned long long* maxYc;       // [C] max |ReLU(y)| of channel c over its occupied codes (fin2);
+                                     // in the space of `part`, which no kernel from fin2 on reads
 };
 
 // partial entries of either variant: at most max(kMaxBlocks, slices) blocks of
@@ -264,8 +266,7 @@ size_t fwd_part_entries(int64_t C)
 size_t fwd_ws_bytes(int64_t C)
 {
     const size_t c = (size_t)C;
-    return ctr_bytes(C) + 256 + align256(fwd_part_entries(C) * 8) + align256(c * 8) + align256(c * 4) +
-           align256(c * 8);
+    return ctr_bytes(C) + 512 + align256(fwd_part_entries(C) * 8) + align256(c * 8) + align256(c * 4);
 }
 
 FwdWs fwd_ws_map(void* base, int64_t C)
@@ -275,10 +276,11 @@ FwdWs fwd_ws_map(void* base, int64_t C)
     FwdWs w;
     p += ctr_bytes(C);
     w.b_glob = (int32_t*)p; p += 256;
-    w.part = (int2*)p; p += align256(fwd_part_entries(C) * 8);
+    w.bnd = (int32_t*)p; p += 256;
+    w.part = (int2*)p;
+    w.maxYc = (unsigned long long*)p; p += align256(fwd_part_entries(C) * 8);
     w.acc = (unsigned long long*)p; p += align256(c * 8);
-    w.sumq = (int32_t*)p; p += align256(c * 4);
-    w.maxYc = (unsigned long long*)p;
+    w.sumq = (int32_t*)p;
     return w;
 }
 
@@ -726,8 +728,7 @@ __device__ __forceinline__ int bnf_bound(int32_t lo, int32_t hi, int32_t nm, int
     return m ? ceil_pow2_exp64(m, (uint64_t)den) + min(s_x, e_mu) - e_sig : kSentinelLo;
 }
 
-// wide layers: the denominators, and the largest bound of each block's kNT
-// channels (into the statistics' partials, which nothing reads any more)
+// wide layers: the denominators, and the largest bound of each block's kNT channels
 __global__ __launch_bounds__(1024) void k_bnf_den(const int32_t* x_exp, FStat st, FwdWs w, Saved sv, BnCfg cf)
 {
     __shared__ int32_t rsh[kWaves];
@@ -743,7 +744,7 @@ __global__ __launch_bounds__(1024) void k_bnf_den(const int32_t* x_exp, FStat st
         best = bnf_bound(sv.qmin[c], sv.qmax[c], nm, den, s_x, e_mu, e_sig);
     }
     best = block_max_nt(best, rsh);
-    if (threadIdx.x == 0) ((int32_t*)w.part)[blockIdx.x] = best;
+    if (threadIdx.x == 0) w.bnd[blockIdx.x] = best;
 }
 
 template <bool PRE>
@@ -766,7 +767,7 @@ __global__ __launch_bounds__(1024) void k_bnf_fin2(const int32_t* x_exp, FStat s
     int best = kSentinelLo;
     if constexpr (PRE) {
         const int nb = (st.C + kNT - 1) / kNT;        // at most 64
-        best = ((const int32_t*)w.part)[lane < nb ? lane : 0];
+        best = w.bnd[lane < nb ? lane : 0];
         if (t < grp * kFinCh) sDen[t] = sv.den[cfirst + t < st.C ? cfirst + t : 0];
     } else {
         const int k0 = t < st.C ? t : 0;

@@ -88,6 +88,10 @@ def test_workspace_queries(lib):
     assert lib.iseg_bn_saved_bytes(64) > 64 * 1024
     assert lib.iseg_bn_fwd_ws(401408, 64) > 0 and lib.iseg_bn_bwd_ws(401408, 64) > 0
     assert lib.iseg_bn_fwd_ws(10, 3) == 0
+    # widths that iseg_bn_fwd_noalloc's array has always held
+    for M in (1, 5000, 1 << 22):
+        for Cc in (32768, 36100, 40288):
+            assert lib.iseg_bn_fwd_ws(M, Cc) <= lib.iseg_bn_fwd_noalloc_max_bytes()
 
 
 def test_transposed_weight_host_checks(lib):

@@ -50,6 +50,7 @@ def test_bn_fwd_noalloc_matches_bn_fwd():
     _run_pair(iseg, torch, dev, 8 * 64 * 64, 256, 1, 501)
     _run_pair(iseg, torch, dev, 1000, 64, 0, 502)
     _run_pair(iseg, torch, dev, 8 * 32 * 32, 2048, 1, 503)
+    _run_pair(iseg, torch, dev, 3, 40288, 1, 504)
 
 
 def test_bn_fwd_noalloc_rejects_shapes_beyond_the_array():
