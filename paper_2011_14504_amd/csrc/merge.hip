@@ -428,8 +428,10 @@ __global__ __launch_bounds__(256) void k_sum_max(MergeArgs a)
     bool ok;
     const int gap = sum_shifts<NIN>(a, sh, &e0, &ok);
     uint64_t m = 0;
+    uint32_t m32 = 0;
     short2v mx = (short2v)(short)0, mn = (short2v)(short)0;
-    while (v0 < nv) {                       // a vector past the end repeats the last one
+    // a vector past the end repeats the last one; the wide sums skip it
+    while (v0 < nv) {
 #pragma unroll
         for (int u = 0; u < kU; u++) {
             if (gap <= kPkShift) {
@@ -440,6 +442,13 @@ __global__ __launch_bounds__(256) void k_sum_max(MergeArgs a)
                     mx = __builtin_elementwise_max(mx, s[t]);
                     mn = __builtin_elementwise_min(mn, s[t]);
                 }
+            } else if (v0 + u * stride >= nv) {
+                break;
+            } else if (gap <= kW32Shift) {
+                int32_t s[16];
+                merge_sum16_raw<NIN>(a, sh, raw[u], s);
+#pragma unroll
+                for (int t = 0; t < 16; t++) m32 = max(m32, (uint32_t)abs(s[t]));
             } else {
                 int64_t s[16];
                 merge_sum16_raw<NIN>(a, sh, raw[u], s);
@@ -457,7 +466,8 @@ __global__ __launch_bounds__(256) void k_sum_max(MergeArgs a)
     }
     int p = max((int)mx.x, (int)mx.y);
     if (!a.relu) p = max(p, max(-(int)mn.x, -(int)mn.y));
-    if ((uint64_t)p > m) m = (uint64_t)p;
+    m32 = max(m32, (uint32_t)p);
+    if (m32 > m) m = m32;
     if (!ok && blockIdx.x == 0 && threadIdx.x == 0) set_status(a.status, ISEG_DEV_RANGE);
     block_store_max_u64(m, a.part);
 }
@@ -493,6 +503,7 @@ __global__ __launch_bounds__(256) void k_sum_apply(MergeArgs a, MergeArgs mk, in
 #pragma unroll
         for (int u = 0; u < kU; u++) {
             const int64_t v = v0 + u * stride;
+            if (max(gap, mgap) > kPkShift && v >= nv) break;
             int4 o = sum_codes<NIN>(a, sh, gap, raw[u], r);
             if constexpr (MASK) o = and4(o, sum_pos<NIN>(mk, msh, mgap, mraw[u]));
             if (v < nv) *(int4*)(a.out + v * 16) = o;
@@ -526,6 +537,7 @@ __global__ __launch_bounds__(256) void k_sum_mask(MergeArgs a, const int8_t* dy)
 #pragma unroll
         for (int u = 0; u < kU; u++) {
             const int64_t v = v0 + u * stride;
+            if (gap > kPkShift && v >= nv) break;
             const int4 o = and4(d[u], sum_pos<NIN>(a, sh, gap, raw[u]));
             if (v < nv) *(int4*)(a.out + v * 16) = o;
         }
