@@ -44,3 +44,25 @@ def test_softmax_ce_paths(orc, case):
     # the same bits again: every sum has one order
     loss2, grad2, err2, _ = iseg.softmax_ce(*args, want_grad=True)
     assert torch.equal(loss, loss2) and torch.equal(grad, grad2) and torch.equal(err, err2)
+
+
+@pytest.mark.parametrize("case", [(1, 2, 2, 5, 1200, 400, -1), (1, 3, 3, 150, 900, 120, -2)], ids=str)
+def test_softmax_ce_long_runs(orc, case):
+    """Cells of hundreds of rows and columns: the error of the exps grows with
+    rows times columns, 2.5e-16 each (an exp's and a rounding's error per step)."""
+    import torch
+    from paper_2011_14504_amd import iseg
+    N, h, w, K, H, W, le = case
+    print(f"[loss long runs] {case}", flush=True)
+    logits = synth.int_codes(90 + K, (N, h, w, K))
+    labels = synth.labels(91, (N, H, W), K)
+    dev = "cuda:0"
+    e = torch.tensor([le], dtype=torch.int32, device=dev)
+    loss, grad, err, ee = iseg.softmax_ce(torch.from_numpy(logits).to(dev), e, torch.from_numpy(labels).to(dev),
+                                          want_grad=True)
+    rl, rg = orc.softmax_ce(logits, le, labels)
+    tol = 2.5e-16 * (H / h + 1) * (W / w + 1)
+    assert abs(float(loss.item()) - rl) <= tol * abs(rl)
+    assert np.max(np.abs(grad.cpu().numpy() - rg)) <= tol * np.max(np.abs(rg))
+    rc, re = orc.quantize_f64(rg, 8)
+    assert int(ee.item()) == re and np.array_equal(err.cpu().numpy().astype(np.int64).ravel(), rc.ravel())
