@@ -25,10 +25,8 @@
  * owns all memory.  The library never allocates: scratch space comes from a
  * caller workspace `ws` of at least the size returned by the matching
  * iseg_*_ws() query (256-byte aligned).  Inputs and outputs must not alias.
- * The workspaces of iseg_bn_fwd and iseg_bn_bwd begin with ISEG_BN_WS_ZERO(C)
- * reserved bytes that no call reads or writes; the rest is written before it
- * is read within a call, so nothing needs clearing.  Calls that may run at
- * the same time need buffers of their own.
+ * A workspace is written before it is read within a call, so nothing needs
+ * clearing.  Calls that may run at the same time need buffers of their own.
  *
  * Streams.  Every compute call only enqueues work on `stream` (0 = the null
  * stream) and returns; results are ready when the stream reaches that point.
@@ -90,7 +88,8 @@ enum iseg_out_mode { ISEG_OUT_Q8 = 0, ISEG_OUT_RAW = 1 };
  * returns the exact int64 sums */
 enum iseg_g_mode { ISEG_G_KEEP = 0, ISEG_G_DROP = 1, ISEG_G_RAW = 2 };
 
-/* reserved bytes at the head of an L1BN (iseg_bn_fwd / iseg_bn_bwd) workspace */
+/* kept for programs that clear the head of an L1BN (iseg_bn_fwd / iseg_bn_bwd)
+ * workspace, which is never smaller than this; no call needs it cleared */
 #define ISEG_BN_WS_ZERO(C) ((((size_t)(C) + 511) / 256) * 256)
 
 /* Convolution geometry.  Input NHWC [N,H,W,C]; weights KRSC [K,R,S,C];

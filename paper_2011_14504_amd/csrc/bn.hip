@@ -155,10 +155,6 @@ struct OpMax { template <typename T> __device__ T operator()(T a, T b) const { r
 constexpr int kRowB = 256 + 4;      // bytes per row of a byte table in LDS
 constexpr int kRowW = 256 + 1;      // dwords per row of a dword table in LDS
 
-// Both workspaces start with ISEG_BN_WS_ZERO(C) reserved bytes that no kernel
-// reads or writes.
-size_t ctr_bytes(int64_t C) { return ISEG_BN_WS_ZERO(C); }
-
 // max over the kNT threads of a block (every thread gets it)
 template <typename T>
 __device__ __forceinline__ T block_max_nt(T v, T* sh)
@@ -266,7 +262,7 @@ size_t fwd_part_entries(int64_t C)
 size_t fwd_ws_bytes(int64_t C)
 {
     const size_t c = (size_t)C;
-    return ctr_bytes(C) + 512 + align256(fwd_part_entries(C) * 8) + align256(c * 8) + align256(c * 4);
+    return 512 + align256(fwd_part_entries(C) * 8) + align256(c * 8) + align256(c * 4);
 }
 
 FwdWs fwd_ws_map(void* base, int64_t C)
@@ -274,7 +270,6 @@ FwdWs fwd_ws_map(void* base, int64_t C)
     char* p = (char*)base;
     const size_t c = (size_t)C;
     FwdWs w;
-    p += ctr_bytes(C);
     w.b_glob = (int32_t*)p; p += 256;
     w.bnd = (int32_t*)p; p += 256;
     w.part = (int2*)p;
@@ -1043,7 +1038,7 @@ size_t bwd_blocks(int64_t C)
 size_t bwd_ws_bytes(int64_t C)
 {
     const size_t nb = bwd_blocks(C), pc = nb * 64, c = (size_t)C;
-    return ctr_bytes(C) + align256(nb * 4) + 4 * align256(pc * 4) + 3 * align256(pc * 8) + align256(c * 4) +
+    return align256(nb * 4) + 4 * align256(pc * 4) + 3 * align256(pc * 8) + align256(c * 4) +
            align256(c * 768 * 2);
 }
 
@@ -1052,7 +1047,6 @@ BwdWs bwd_ws_map(void* base, int64_t C)
     char* p = (char*)base;
     const size_t nb = bwd_blocks(C), pc = nb * 64, c = (size_t)C;
     BwdWs w;
-    p += ctr_bytes(C);
     w.pF = (int32_t*)p; p += align256(nb * 4);
     w.p_sd = (int32_t*)p; p += align256(pc * 4);
     w.p_z = (int32_t*)p; p += align256(pc * 4);

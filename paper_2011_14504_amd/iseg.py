@@ -598,12 +598,10 @@ def _maybe_arm(kid, key):
 # --------------------------------------------------------------------------
 class Workspace:
     """A growable device scratch buffer shared by consecutive calls on one
-    stream (stream order keeps the uses apart); each stream has its own.
-    `zeroed` buffers start at zero."""
+    stream (stream order keeps the uses apart); each stream has its own."""
 
-    def __init__(self, device="cuda", zeroed=False):
+    def __init__(self, device="cuda"):
         self.device = device
-        self.zeroed = zeroed
         self.buf = None
         self.views = {}              # recent sizes' views of buf (a slice costs 2 us of host time)
 
@@ -612,8 +610,7 @@ class Workspace:
         v = self.views.get(nbytes)
         if v is None:
             if self.buf is None or self.buf.numel() < nbytes:
-                alloc = torch.zeros if self.zeroed else torch.empty
-                self.buf = alloc(nbytes, dtype=torch.uint8, device=self.device)
+                self.buf = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
                 self.views = {}
             elif len(self.views) >= 64:
                 self.views = {}
@@ -624,17 +621,17 @@ class Workspace:
 _WS = {}
 
 
-def workspace(device, bn=False):
-    """The workspace of the current stream; L1BN (int8 input) has one of its own."""
+def workspace(device):
+    """The workspace of the current stream."""
     d = device if isinstance(device, torch.device) else torch.device(device)
     if d.type == "cuda":
         idx = d.index if d.index is not None else _raw_device()
-        key = (idx, _stream_handle(idx), bn)
+        key = (idx, _stream_handle(idx))
     else:
-        idx, key = None, (str(d), 0, bn)
+        idx, key = None, (str(d), 0)
     ws = _WS.get(key)
     if ws is None:
-        ws = _WS[key] = Workspace(torch.device("cuda", idx) if d.type == "cuda" else d, zeroed=bn)
+        ws = _WS[key] = Workspace(torch.device("cuda", idx) if d.type == "cuda" else d)
     return ws
 
 
@@ -938,7 +935,7 @@ def bn_fwd(x, x_exp, gamma_q, beta_q, cfg=None, saved=None, status=None):
     e = _out_exp(x.device)
     if saved is None:
         saved = torch.empty(lib().iseg_bn_saved_bytes(Cc), dtype=torch.uint8, device=x.device)
-    ws = workspace(x.device, bn=True).get(lib().iseg_bn_fwd_ws(M, Cc))
+    ws = workspace(x.device).get(lib().iseg_bn_fwd_ws(M, Cc))
     for kid in (ISEG_KID_BN_FWD_APPLY, ISEG_KID_BN_FWD_STATS1, ISEG_KID_BN_FWD_STATS2):
         _maybe_arm(kid, (M, Cc))
     iseg_bn_fwd(x, x_exp, M, Cc, gamma_q, beta_q, cfg, y, e, saved, ws, status)
@@ -961,7 +958,7 @@ def bn_bwd(dy, dy_exp, x, gamma_q, saved, cfg=None, status=None, dgb_out=None):
         ws = workspace(x.device).get(lib().iseg_bn_bwd_i32_ws(M, Cc))
         iseg_bn_bwd_i32(dy, dy_exp, x, M, Cc, gamma_q, cfg, saved, dx, e, dg, db, dge, dbe, ws, status)
         return dx, e, dg, db, dge, dbe
-    ws = workspace(x.device, bn=True).get(lib().iseg_bn_bwd_ws(M, Cc))
+    ws = workspace(x.device).get(lib().iseg_bn_bwd_ws(M, Cc))
     for kid in (ISEG_KID_BN_BWD_APPLY, ISEG_KID_BN_BWD_STATS):
         _maybe_arm(kid, (M, Cc))
     iseg_bn_bwd(dy, dy_exp, x, M, Cc, gamma_q, cfg, saved, dx, e, dg, db, dge, dbe, ws, status)

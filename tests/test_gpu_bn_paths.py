@@ -95,3 +95,35 @@ def test_bn_paths(orc, case):
     assert np.array_equal(dg.cpu().numpy(), rb["dgamma"]) and int(dge.item()) == rb["dgamma_exp"]
     assert np.array_equal(db.cpu().numpy(), rb["dbeta"]) and int(dbe.item()) == rb["dbeta_exp"]
     assert np.array_equal(dx.cpu().numpy(), rb["dx"]) and int(dxe.item()) == rb["dx_exp"]
+
+
+@pytest.mark.parametrize("shape", [(700, 80, 16), (700, 80, 8), (65, 2320, 16), (65, 2320, 8), (5000, 12, 8)], ids=str)
+def test_bn_dirty_buffers(orc, shape):
+    """Workspaces and the saved state full of ones before the calls."""
+    import torch
+    from paper_2011_14504_amd import iseg
+    M, C, k_E2 = shape
+    print(f"[bn dirty] {shape}", flush=True)
+    x, dy = synth.int_codes(81, (M, C)), synth.int_codes(82, (M, C))
+    gq, bq = synth.int_codes(83, (C,)), synth.int_codes(84, (C,))
+    cfg = dict(orc.BN_DEFAULT, k_E2=k_E2)
+    c = iseg.bn_cfg(**cfg)
+    dev = "cuda:0"
+
+    def ones(n, dt=torch.uint8):
+        return torch.full((int(n),), 255 if dt == torch.uint8 else -1, dtype=dt, device=dev)
+    xd, dyd, g, b = _dev(x), _dev(dy), _dev(gq), _dev(bq)
+    xe, dye = (torch.tensor([v], dtype=torch.int32, device=dev) for v in (-7, -20))
+    L = iseg.lib()
+    y, dx = (ones(M * C, torch.int8).view(M, C) for _ in range(2))
+    e = [ones(1, torch.int32) for _ in range(4)]
+    dg, db = ones(C, torch.int64), ones(C, torch.int64)
+    saved = ones(L.iseg_bn_saved_bytes(C))
+    iseg.iseg_bn_fwd(xd, xe, M, C, g, b, c, y, e[0], saved, ones(L.iseg_bn_fwd_ws(M, C)))
+    iseg.iseg_bn_bwd(dyd, dye, xd, M, C, g, c, saved, dx, e[1], dg, db, e[2], e[3], ones(L.iseg_bn_bwd_ws(M, C)))
+    r = orc.bn_fwd(x, -7, gq, bq, cfg)
+    assert np.array_equal(y.cpu().numpy(), r["y"]) and int(e[0].item()) == r["y_exp"]
+    rb = orc.bn_bwd(dy, -20, x, -7, gq, bq, cfg)
+    assert np.array_equal(dx.cpu().numpy(), rb["dx"]) and int(e[1].item()) == rb["dx_exp"]
+    assert np.array_equal(dg.cpu().numpy(), rb["dgamma"]) and np.array_equal(db.cpu().numpy(), rb["dbeta"])
+    assert [int(v.item()) for v in e[2:]] == [rb["dgamma_exp"], rb["dbeta_exp"]]

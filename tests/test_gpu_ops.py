@@ -508,8 +508,8 @@ def test_bn_bwd(orc, dev, i):
 
 
 def test_bn_repeated_calls_same_workspace(orc, dev):
-    """Back-to-back calls of different shapes on one workspace: each call
-    must leave the arrival counters at zero for the next."""
+    """Back-to-back calls of different shapes on one workspace: no call may
+    depend on what an earlier one left in it."""
     from paper_2011_14504_amd import iseg
     refs = {}
     for rep in range(2):

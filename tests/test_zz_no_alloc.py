@@ -29,8 +29,8 @@ def _run_pair(iseg, torch, dev, M, Cc, relu, seed):
         if noalloc:
             iseg.iseg_bn_fwd_noalloc(x, xe, M, Cc, g, b, cfg, y, ye, sv, st)
         else:
-            # the workspace starts with arrival counters that must be zero
-            ws = torch.zeros(iseg.lib().iseg_bn_fwd_ws(M, Cc), dtype=torch.uint8, device=dev)
+            # a workspace needs no clearing
+            ws = torch.full((iseg.lib().iseg_bn_fwd_ws(M, Cc),), 255, dtype=torch.uint8, device=dev)
             iseg.iseg_bn_fwd(x, xe, M, Cc, g, b, cfg, y, ye, sv, ws, st)
         torch.cuda.synchronize()
         assert int(st.item()) == 0
