@@ -601,10 +601,11 @@ int iseg_profile_arm(int32_t kernel_id, hipEvent_t start, hipEvent_t stop);
 /* iseg_conv_last_plan -- the kernel path the calling thread's last
  * iseg_conv_fwd / iseg_conv_bwd_data(_t) / iseg_conv_bwd_weight call took:
  * "stem", "m32", "gemm_short", "conv_short", "dma_two_pass", "dma_split",
- * "dma_stage16", "dma" (raw sums), "igemm", "wgrad_stem", "wgrad_rows",
- * "wgrad_taps", "wgrad_tr", "wgrad_atomic", or "none" when it returned before
- * choosing one.  Static storage, per thread.  For tests that
- * must reach a given kernel. */
+ * "dma_stage16", "dma" (raw sums), "flat", "igemm", "phase" and "strided_1x1"
+ * (backward-data), "kred_dma_split" and "kred_split" (reductions above 131071
+ * products), "wgrad_stem", "wgrad_rows", "wgrad_taps", "wgrad_tr",
+ * "wgrad_atomic", or "none" when it returned before choosing one.  Static
+ * storage, per thread.  For tests that must reach a given kernel. */
 const char* iseg_conv_last_plan(void);
 
 /* ------------------------------------------------------------------------ */

@@ -1750,9 +1750,11 @@ int launch_igemm(const IgemmArgs& a, hipStream_t s, int64_t* nblk)
     *nblk = 0;
     if (a.Mrows > 0 && a.Nout > 0 && a.Ci % 16 == 0 && a.Mrows < ((int64_t)1 << 31) &&
         (((uintptr_t)a.src | (uintptr_t)a.wmat) & 15) == 0) {
+        conv_plan_set("flat");
         if (ceil_div64(a.Mrows, 128) * ceil_div64(a.Nout, 128) < 256) return launch_flat<MODE, 64, 64>(a, s, nblk);
         return a.Nout > 64 ? launch_flat<MODE, 128, 128>(a, s, nblk) : launch_flat<MODE, 128, 64>(a, s, nblk);
     }
+    conv_plan_set("igemm");
     return launch_igemm_generic<MODE>(a, s, nblk);
 }
 
@@ -1839,6 +1841,7 @@ int launch_igemm_generic(const IgemmArgs& a, hipStream_t s, int64_t* nblk)
 {
     *nblk = 0;
     if (a.Mrows <= 0 || a.Nout <= 0) return ISEG_OK;
+    // 16-byte loads: left for 2^31 rows and more, which the flat kernel's indices do not hold
     bool vec = (a.Ci % 16) == 0 && (((uintptr_t)a.src | (uintptr_t)a.wmat) & 15) == 0;
     dim3 block(256);
     unsigned gx = (unsigned)ceil_div64(a.Mrows, 128);
@@ -3650,7 +3653,6 @@ static int conv_fwd_core(const int8_t* x, const int32_t* x_exp, const int8_t* w,
     if (igemm_dma_ok(a) && ((uintptr_t)y & 15) == 0)
         return igemm_dma_run<MODE_FWD>(a, out_mode, x_exp, w_exp, y, y_exp, pmax, acc, stream);
     int64_t nblk = 0;
-    conv_plan_set("igemm");
     if ((rc = launch_igemm<MODE_FWD>(a, stream, &nblk))) return rc;
     if (out_mode == ISEG_OUT_RAW) {
         hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(1), 0, stream, y_exp, x_exp, w_exp);
@@ -4052,7 +4054,6 @@ static int conv_bwd_data_core(const int8_t* dy, const int32_t* dy_exp, const int
     if (igemm_dma_ok(a) && ((uintptr_t)dx & 15) == 0)
         return igemm_dma_run<MODE_BWD>(a, out_mode, dy_exp, w_exp, dx, dx_exp, pmax, acc, stream);
     int64_t nblk = 0;
-    conv_plan_set("igemm");
     if ((rc = launch_igemm<MODE_BWD>(a, stream, &nblk))) return rc;
     if (out_mode == ISEG_OUT_RAW) {
         hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(1), 0, stream, dx_exp, dy_exp, w_exp);

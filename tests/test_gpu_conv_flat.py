@@ -54,8 +54,14 @@ def test_conv_flat(orc, case):
         dxp[:, hs, ws] += (dy.double().reshape(-1, K) @ w[:, r, s].double()).view(N, P, Q, C)
     dref = dxp[:, pad:pad + H, pad:pad + W].cpu().numpy().astype(np.int64)
     for mode in (iseg.ISEG_OUT_RAW, iseg.ISEG_OUT_Q8):
-        for out, oe, want in ((*iseg.conv_fwd(x, e[0], w, e[1], st, pad, dil, mode), ref),
-                              (*iseg.conv_bwd_data(dy, e[0], w, e[1], x.shape, st, pad, dil, mode), dref)):
+        fwd = iseg.conv_fwd(x, e[0], w, e[1], st, pad, dil, mode)
+        plans = [iseg.iseg_conv_last_plan()]
+        bwd = iseg.conv_bwd_data(dy, e[0], w, e[1], x.shape, st, pad, dil, mode)
+        plans.append(iseg.iseg_conv_last_plan())
+        # backward-data: strided convs from few channels and strided 1x1 have paths of their own, and
+        # dy of other channel counts takes the generic or (padded) the direct-to-LDS kernel
+        assert plans[0] == "flat" and (plans[1] == "flat") == (K % 16 == 0 and not (st > 1 and (R == 1 or K <= 32)))
+        for out, oe, want in ((*fwd, ref), (*bwd, dref)):
             r, re = (want, -16) if mode == iseg.ISEG_OUT_RAW else orc.requant(want, -16, 8)
             assert np.array_equal(out.cpu().numpy().astype(np.int64), r) and int(oe.item()) == re
     g, ge = iseg.conv_bwd_weight(dy, e[0], x, e[1], w.shape, st, pad, dil, iseg.ISEG_G_RAW)
