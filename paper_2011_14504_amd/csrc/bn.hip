@@ -182,6 +182,7 @@ struct FStat {
     int64_t M;
     int32_t C, nsl, gx, ntiles;
     int32_t pad;                     // row slots past M in the tiles
+    int32_t paired;                  // slice_grid's order of the blocks
 };
 
 // Blocks of a slice: one per tile, or an equal share of kMaxBlocks in a multiple
@@ -206,20 +207,31 @@ int32_t slice_blocks(int64_t nsl, int64_t ntiles)
 // 9.7 and 21.4 -> 18.2 us, those of the backward 33.3 -> 26.2 and 38.3 -> 28.4).
 dim3 slice_grid(const FStat& f)
 {
-    if (kMaxBlocks / f.nsl >= 8) return dim3((unsigned)f.gx, (unsigned)f.nsl);
+    if (!f.paired) return dim3((unsigned)f.gx, (unsigned)f.nsl);
     return dim3((unsigned)(ceil_div64(ceil_div64(f.nsl, 2) * f.gx, 8) * 16));
 }
 
 // block bx of slice by; false: none (a block past the last slice)
+template <bool PAIRED>
 __device__ __forceinline__ bool slice_of(const FStat& st, int& bx, int& by)
 {
     bx = blockIdx.x;
     by = blockIdx.y;
-    if (kMaxBlocks / st.nsl >= 8) return true;
+    if constexpr (!PAIRED) return true;
     const int q = blockIdx.x, v = (q >> 4) * 8 + (q & 7), pair = v / st.gx;
     bx = v - pair * st.gx;
     by = 2 * pair + ((q >> 3) & 1);
     return by < st.nsl;
+}
+
+// f(PAIRED), for the geometries wide enough to have it
+template <int CS, typename F>
+void with_paired(const FStat& st, F f)
+{
+    if constexpr (CS == 64) {
+        if (st.paired) return f(std::true_type());
+    }
+    f(std::false_type());
 }
 
 template <int CPL, int G>
@@ -232,6 +244,7 @@ FStat make_fstat(int64_t M, int64_t C)
     f.ntiles = (int32_t)ceil_div64(M, TR);
     f.pad = (int32_t)((int64_t)f.ntiles * TR - M);
     f.gx = slice_blocks(f.nsl, f.ntiles);
+    f.paired = kMaxBlocks / f.nsl < 8;
     return f;
 }
 
@@ -424,11 +437,11 @@ __device__ __forceinline__ void fstat_rows(const FStat& st, int bx, const int8_t
 // 8.5 us).  Sums by v_dot4 against a
 // selector byte, minima and maxima as packed 16-bit operations on the bytes in
 // the high halves (the low byte below them cannot change which high byte wins).
-template <int CPL, int G>
+template <int CPL, int G, bool PAIRED>
 __global__ __launch_bounds__(1024) void k_bnf_stats1(const int8_t* __restrict__ x, FStat st, FwdWs w)
 {
     int bx, by;
-    if (!slice_of(st, bx, by)) return;
+    if (!slice_of<PAIRED>(st, bx, by)) return;
     constexpr int CS = CPL * G, DW = CPL / 4;
     __shared__ int32_t sS[kWaves * CS];
     __shared__ int32_t sMm[kWaves * CS];
@@ -547,12 +560,12 @@ __device__ __forceinline__ int bn_ref(int T) { return min(max(T + 128, 0), 254);
 // (the pass on 131072 x 256 codes: 23.8 -> 8.5 us, 3.9 TB/s; on 1024 x 16: 12.8 ->
 // 4.5 us, with the slice tail gone; what is left there is the launch and the
 // two round trips of the prologue and the rows).
-template <int CPL, int G>
+template <int CPL, int G, bool PAIRED>
 __global__ __launch_bounds__(1024) void k_bnf_stats2(const int8_t* __restrict__ x, const int32_t* x_exp,
                                                     FStat st, FwdWs w, Saved sv, BnCfg cf, int32_t* dev_status)
 {
     int bx, by;
-    if (!slice_of(st, bx, by)) return;
+    if (!slice_of<PAIRED>(st, bx, by)) return;
     constexpr int CS = CPL * G, DW = CPL / 4, NG = kNT / CS;
     __shared__ int32_t sS[kNT], sMm[kNT];          // prologue sums; then the wave totals of A0 and A1
     __shared__ int32_t sRef[CS];
@@ -883,16 +896,17 @@ FStat make_fapply(int64_t M, int64_t C)
     FStat f = make_fstat<CPL, G>(M, C);
     f.ntiles = (int32_t)ceil_div64(M, (int64_t)U * kNT / G);
     f.gx = slice_blocks(f.nsl, f.ntiles);
+    f.paired = kMaxBlocks / f.nsl < 8;
     return f;
 }
 
-template <int CPL, int G, int U>
+template <int CPL, int G, int U, bool PAIRED>
 __global__ __launch_bounds__(1024) void k_bnf_apply(const int8_t* __restrict__ x, int8_t* __restrict__ y,
                                                    FStat st, Saved sv, FwdWs w, BnCfg cf, const int32_t* x_exp,
                                                    const int8_t* gamma_q, const int8_t* beta_q, int32_t* y_exp)
 {
     int bx, by;
-    if (!slice_of(st, bx, by)) return;
+    if (!slice_of<PAIRED>(st, bx, by)) return;
     constexpr int CS = CPL * G, RPI = kNT / G, TV = (CS * 32 + kNT - 1) / kNT;
     __shared__ __attribute__((aligned(16))) int8_t lut[CS * kRowB];
     __shared__ uint64_t rmax[kWaves];
@@ -1072,6 +1086,7 @@ FStat make_bstat(int64_t M, int64_t C)
     f.ntiles = (int32_t)ceil_div64(M, TR);
     f.pad = (int32_t)((int64_t)f.ntiles * TR - M);
     f.gx = slice_blocks(f.nsl, f.ntiles);
+    f.paired = kMaxBlocks / f.nsl < 8;
     return f;
 }
 
@@ -1150,12 +1165,12 @@ struct OpPkMin {
 // wave that have one (in their occupied range) take six more operations.
 constexpr int kBndU = 4;                 // rows per lane and tile
 
-template <int G, int MODE>
+template <int G, int MODE, bool PAIRED>
 __global__ __launch_bounds__(1024) void k_bnb_stats(const int8_t* __restrict__ dy, const int8_t* __restrict__ x,
                                                    FStat st, BwdWs w, Saved sv, BnCfg cf, BnbOut out)
 {
     int bx, by;
-    if (!slice_of(st, bx, by)) return;
+    if (!slice_of<PAIRED>(st, bx, by)) return;
     constexpr int CS = 4 * G, RPI = kNT / G, U = kBndU, TR = U * RPI, TV = CS * 64 / kNT;
     __shared__ __attribute__((aligned(16))) uint32_t tab[CS * kRowW];
     __shared__ int32_t rsh[kWaves], sZf[CS];
@@ -1521,10 +1536,11 @@ __global__ __launch_bounds__(NT) void k_bnb_chan(FStat st, int CS, BwdWs w, Save
     }
     __syncthreads();
     const int bc = r_cand;
+    int k = t >> 8;
     const int d = (t & 255) - 128;
-    const int S = Ebase + (cf.k_E1 - 1) - bc + 1;
-    for (int k = t >> 8; k < 3; k += NT / 256) {
+    do {
         const int lo = k == 0 ? mm[0] : (k == 1 ? mm[2] : mm[4]), hi = k == 0 ? mm[1] : (k == 1 ? mm[3] : mm[5]);
+        const int S = Ebase + (cf.k_E1 - 1) - bc + 1;
         int16_t q = 0;
         if (bc != kSentinelLo && d >= lo && d <= hi && d >= -127) {
             const i128 B = bnb_bracket(f_of(d), k - 1, M, Sf, T, Z, e_xh);
@@ -1533,7 +1549,8 @@ __global__ __launch_bounds__(NT) void k_bnb_chan(FStat st, int CS, BwdWs w, Save
             q = (int16_t)Q;
         }
         w.lutq[(int64_t)c * 768 + k * 256 + (t & 255)] = q;
-    }
+        k += NT / 256;
+    } while (NT < 768 && k < 3);
 }
 
 // Output pass: dx code = lut[c][sgn class][masked delta].  Every block first
@@ -1546,13 +1563,13 @@ __global__ __launch_bounds__(NT) void k_bnb_chan(FStat st, int CS, BwdWs w, Save
 // 50 KB of tables per block instead of two and 115 KB.  Bound by memory on the
 // large tensors (131072 x 256 codes: 24.0 -> 23.1 us; its row loop runs at 6.1
 // TB/s after 4 us of prologue), by the prologue on the small ones.
-template <int G>
+template <int G, bool PAIRED>
 __global__ __launch_bounds__(1024) void k_bnb_apply(const int8_t* __restrict__ dy, const int8_t* __restrict__ x,
                                                    int8_t* __restrict__ dx, FStat st, BwdWs w, Saved sv,
                                                    BnCfg cf, BnbOut o)
 {
     int bx, by;
-    if (!slice_of(st, bx, by)) return;
+    if (!slice_of<PAIRED>(st, bx, by)) return;
     constexpr int CS = 4 * G, RPI = kNT / G, U = kBndU, TR = U * RPI;
     constexpr int NV = (CS * 96 + kNT - 1) / kNT;
     __shared__ __attribute__((aligned(16))) int8_t lut[CS * 3 * kRowB];
@@ -1713,9 +1730,13 @@ static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t
         constexpr int CPL = decltype(cpl)::value, G = decltype(gl)::value;
         const FStat st = make_fstat<CPL, G>(M, C);
         const dim3 sg = slice_grid(st);
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS1, stream, (k_bnf_stats1<CPL, G>), sg, dim3(kNT), 0, stream, x, st, w);
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS2, stream, (k_bnf_stats2<CPL, G>), sg, dim3(kNT), 0, stream, x, x_exp,
-                          st, w, sv, cf, dev_status);
+        with_paired<CPL * G>(st, [&](auto pc) {
+            constexpr bool P = decltype(pc)::value;
+            ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS1, stream, (k_bnf_stats1<CPL, G, P>), sg, dim3(kNT), 0, stream, x,
+                              st, w);
+            ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_STATS2, stream, (k_bnf_stats2<CPL, G, P>), sg, dim3(kNT), 0, stream, x,
+                              x_exp, st, w, sv, cf, dev_status);
+        });
         // every block forms all C denominators, so past one block per CU a block
         // takes more channels (2048 channels: 14.2 us with 512 blocks, 7.2 with 256)
         const int grp = (int)std::min<int64_t>(kFinGrp, ceil_div64(C, 256 * kFinCh));
@@ -1744,14 +1765,15 @@ static int bn_fwd_impl(const int8_t* x, const int32_t* x_exp, int64_t M, int64_t
         // four rows per lane keep the most loads in flight; one where that
         // would use less than half the CUs
         const FStat s4 = make_fapply<CPL, G, 4>(M, C), s1 = make_fapply<CPL, G, 1>(M, C);
-        if (s4.gx * s4.nsl > kMaxBlocks / 2)
-            ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 4>),
-                              slice_grid(s4), dim3(kNT), 0, stream, x, y_out, s4, sv, w, cf,
-                              x_exp, gamma_q, beta_q, y_exp);
-        else
-            ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 1>),
-                              slice_grid(s1), dim3(kNT), 0, stream, x, y_out, s1, sv, w, cf,
-                              x_exp, gamma_q, beta_q, y_exp);
+        with_paired<CPL * G>(s4, [&](auto pc) {
+            constexpr bool P = decltype(pc)::value;
+            if (s4.gx * s4.nsl > kMaxBlocks / 2)
+                ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 4, P>), slice_grid(s4),
+                                  dim3(kNT), 0, stream, x, y_out, s4, sv, w, cf, x_exp, gamma_q, beta_q, y_exp);
+            else
+                ISEG_TIMED_LAUNCH(ISEG_KID_BN_FWD_APPLY, stream, (k_bnf_apply<CPL, G, 1, P>), slice_grid(s1),
+                                  dim3(kNT), 0, stream, x, y_out, s1, sv, w, cf, x_exp, gamma_q, beta_q, y_exp);
+        });
     };
     if (v16) {
         switch (fstat_g16(C)) {
@@ -1850,19 +1872,21 @@ extern "C" int iseg_bn_bwd(const int8_t* dy, const int32_t* dy_exp, const int8_t
         constexpr int G = decltype(gl)::value;
         const FStat st = make_bstat<G, kBndU>(M, C);
         const dim3 sg = slice_grid(st);
-        if (exact_e2) {
-            ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 0>), sg, dim3(kNT), 0, stream, dy, x,
-                              st, w, sv, cf, out);
-            chan(std::false_type(), st, 4 * G);
-        } else {
-            ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 1>), sg, dim3(kNT), 0, stream, dy, x,
-                              st, w, sv, cf, out);
-            hipLaunchKernelGGL((k_bnb_stats<G, 2>), sg, dim3(kNT), 0, stream, dy, x, st, w, sv, cf, out);
-            chan(std::true_type(), st, 4 * G);
-        }
-        const FStat sa = make_bstat<G, kBndU>(M, C);
-        ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_APPLY, stream, k_bnb_apply<G>, slice_grid(sa),
-                          dim3(kNT), 0, stream, dy, x, dx_out, sa, w, sv, cf, out);
+        with_paired<4 * G>(st, [&](auto pc) {
+            constexpr bool P = decltype(pc)::value;
+            if (exact_e2) {
+                ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 0, P>), sg, dim3(kNT), 0, stream, dy,
+                                  x, st, w, sv, cf, out);
+                chan(std::false_type(), st, 4 * G);
+            } else {
+                ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_STATS, stream, (k_bnb_stats<G, 1, P>), sg, dim3(kNT), 0, stream, dy,
+                                  x, st, w, sv, cf, out);
+                hipLaunchKernelGGL((k_bnb_stats<G, 2, P>), sg, dim3(kNT), 0, stream, dy, x, st, w, sv, cf, out);
+                chan(std::true_type(), st, 4 * G);
+            }
+            ISEG_TIMED_LAUNCH(ISEG_KID_BN_BWD_APPLY, stream, (k_bnb_apply<G, P>), sg, dim3(kNT), 0, stream, dy, x,
+                              dx_out, st, w, sv, cf, out);
+        });
     };
     if (C <= 16) run(std::integral_constant<int, 4>());
     else if (C <= 32) run(std::integral_constant<int, 8>());
