@@ -5,10 +5,11 @@
 // is a function of (channel, input code) only, and the backward's dx code is
 // a function of (channel, sgn class, masked error code).  The work therefore
 // splits into
-//   * streaming passes over [M, C]: coalesced dword loads (four channels per
-//     lane), four rows in flight per lane, per-channel sums reduced in LDS and
-//     written as one partial per block and channel (no global atomics, so no
-//     same-address serialization across blocks);
+//   * streaming passes over [M, C]: 16 channels per lane in the forward where the
+//     rows allow 16-byte loads, else four, four rows in flight per lane,
+//     per-channel sums reduced in LDS and written as one partial per block and
+//     channel (stats2 instead adds its two sums to the channel's word by one
+//     64-bit atomic per block: whole numbers, so in any order the same);
 //   * finalize steps that reduce the partials and do the exact rational
 //     arithmetic once per channel or per table entry, in kernels of their own.
 // sgn(x - mu_q) and the ReLU mask are monotone in the input code, so the
