@@ -343,9 +343,9 @@ __device__ __forceinline__ void wait_vm_lgkm0()
 // piece lies in one tap, so a lane follows its own tap and channel, and pieces
 // past the reduction or past Nout read the zero page.  The synchronous
 // single-buffered kernel it replaces took 1.4 us per step of 64: 96 -> 160
-// channels, 3 x 97 x 65, stride 2: 25.7 -> 18.1 us forward and 42.7 -> 32.8
-// backward-data with their requantization; 208 -> 336 at 8 x 32 x 32: 44.8 -> 33.5
-// and 73.2 -> 39.9.
+// channels, 3 x 97 x 65, stride 2: 24.9 -> 17.0 us forward and 39.6 -> 29.0
+// backward-data with their requantization; 208 -> 336 at 8 x 32 x 32: 42.7 -> 32.2
+// and 66.7 -> 35.4.
 template <int MODE, int BM, int BN, int EPI, bool PIPE, bool FLAT>
 __global__ __launch_bounds__(256) void k_conv_igemm_dma(IgemmArgs a)
 {
@@ -2297,7 +2297,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_tap(WgradArgs a)
 // read as zero and are not stored).
 // Channel counts off 64 took an atomic kernel with a byte transpose in registers,
 // a fill, an absolute-max pass and a requant: 96 -> 160 channels, 3 x 97 x 65,
-// stride 2: 36.6 -> 23.4 us; 208 -> 336 at 8 x 64 x 64: 269 -> 73 us.
+// stride 2: 36.2 -> 19.5 us a call; 208 -> 336 at 8 x 32 x 32: 90.2 -> 36.2.
 typedef int v2i_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ v4i tr8_frag(const int8_t* lds_rows, int row_bytes, int col0, int lane)
