@@ -435,7 +435,8 @@ __device__ __forceinline__ void fstat_rows(const FStat& st, int bx, const int8_t
 
 // Bound by memory on the large tensors and by latency on the small ones; a
 // lane's 16-byte loads keep 64 KB per CU in flight (131072 x 256 codes: 10.2 ->
-// 8.5 us).  Sums by v_dot4 against a
+// 8.5 us; on 8192 x 256 the 64-channel slices cost this pass 4.7 -> 5.5 us and
+// save the next one, which reads their partials, 13.2 -> 5.4).  Sums by v_dot4 against a
 // selector byte, minima and maxima as packed 16-bit operations on the bytes in
 // the high halves (the low byte below them cannot change which high byte wins).
 template <int CPL, int G, bool PAIRED>
