@@ -385,7 +385,8 @@ __device__ __forceinline__ int4 sum_pos_wide(const MergeArgs& a, const int* sh, 
 }
 
 template <int NIN>
-__device__ __forceinline__ int4 sum_codes(const MergeArgs& a, const int* sh, int gap, const int4* raw, int r)
+__device__ __forceinline__ int4 sum_codes(const MergeArgs& a, const int* sh, int gap, const int4* raw, int r,
+                                          bool live)                // live: a vector inside the tensor
 {
     if (gap <= kPkShift) {
         short2v s[8];
@@ -396,17 +397,19 @@ __device__ __forceinline__ int4 sum_codes(const MergeArgs& a, const int* sh, int
         }
         return sum_codes_pk(s, r, a.bits);
     }
+    if (!live) return make_int4(0, 0, 0, 0);
     return gap <= kW32Shift ? sum_codes_wide<NIN, int32_t>(a, sh, raw, r) : sum_codes_wide<NIN, int64_t>(a, sh, raw, r);
 }
 
 template <int NIN>
-__device__ __forceinline__ int4 sum_pos(const MergeArgs& a, const int* sh, int gap, const int4* raw)
+__device__ __forceinline__ int4 sum_pos(const MergeArgs& a, const int* sh, int gap, const int4* raw, bool live)
 {
     if (gap <= kPkShift) {
         short2v s[8];
         sum_pk<NIN>(raw, sh, s);
         return sum_pos_pk(s);
     }
+    if (!live) return make_int4(0, 0, 0, 0);
     return gap <= kW32Shift ? sum_pos_wide<NIN, int32_t>(a, sh, raw) : sum_pos_wide<NIN, int64_t>(a, sh, raw);
 }
 
@@ -503,9 +506,8 @@ __global__ __launch_bounds__(256) void k_sum_apply(MergeArgs a, MergeArgs mk, in
 #pragma unroll
         for (int u = 0; u < kU; u++) {
             const int64_t v = v0 + u * stride;
-            if (max(gap, mgap) > kPkShift && v >= nv) break;
-            int4 o = sum_codes<NIN>(a, sh, gap, raw[u], r);
-            if constexpr (MASK) o = and4(o, sum_pos<NIN>(mk, msh, mgap, mraw[u]));
+            int4 o = sum_codes<NIN>(a, sh, gap, raw[u], r, v < nv);
+            if constexpr (MASK) o = and4(o, sum_pos<NIN>(mk, msh, mgap, mraw[u], v < nv));
             if (v < nv) *(int4*)(a.out + v * 16) = o;
         }
         v0 += stride * kU;
@@ -537,8 +539,7 @@ __global__ __launch_bounds__(256) void k_sum_mask(MergeArgs a, const int8_t* dy)
 #pragma unroll
         for (int u = 0; u < kU; u++) {
             const int64_t v = v0 + u * stride;
-            if (gap > kPkShift && v >= nv) break;
-            const int4 o = and4(d[u], sum_pos<NIN>(a, sh, gap, raw[u]));
+            const int4 o = and4(d[u], sum_pos<NIN>(a, sh, gap, raw[u], v < nv));
             if (v < nv) *(int4*)(a.out + v * 16) = o;
         }
         v0 += stride * kU;
